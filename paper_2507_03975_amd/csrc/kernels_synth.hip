@@ -1187,8 +1187,13 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *d
         if (own[k][m].ok) r0[own[k][m].c] = own[k][m].b;
     __syncthreads();
   } else {
-    // ---- down: top level, red from zero, black, red residuals, restrict
+    // ---- down: top level, red from zero, black, red residuals, restrict.
+    // The black cells start at 0: a missing neighbour reads the cell itself
+    // (times a zero coupling), which must not find what the LDS held before
     top_half(0, true);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      if (own[1][m].ok) x0[own[1][m].c] = 0.0;
     __syncthreads();
     top_half(1, false);
     __syncthreads();
