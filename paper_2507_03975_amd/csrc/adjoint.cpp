@@ -117,8 +117,10 @@ gsis_status gsis_plan_adjoint(gsis_plan *pl, const double *g_phi, const double *
   HIPCHK(ctx, hipMemsetAsync(B.s_old, 0, N * sizeof(double), s));
   HIPCHK(ctx, hipMemsetAsync(B.bb, 0, N * sizeof(double), s));
   HIPCHK(ctx, hipMemsetAsync(B.state, 0, 4 * sizeof(int32_t), s));
-  // lambda^{n+1} = G^T lambda^n + M^T g from lambda = 0; the first pass
-  // gives M^T g, Err compares successive ordinate sums
+  HIPCHK(ctx, hipMemsetAsync(B.part, 0, 8 * N * sizeof(double), s));
+  // lambda^{n+1} = G^T lambda^n + M^T g from lambda = 0; Err compares
+  // successive ordinate sums. The first pass gives M^T g: in the split form
+  // of lambda that is the zero arrays above, so it launches nothing
   int m = 0, status = 1;
   double err = INFINITY;
   std::vector<double> h(max_iter + 1);
@@ -126,7 +128,8 @@ gsis_status gsis_plan_adjoint(gsis_plan *pl, const double *g_phi, const double *
   while (m < max_iter) {
     const int todo = std::min(check, max_iter - m);
     for (int t = 0; t < todo; ++t, ++m)
-      adj_launch_pass(P, B, B.args.data(), ihalf, B.S, B.hist, m, (int32_t *)pl->host_scal + 4, s);
+      if (m > 0)
+        adj_launch_pass(P, B, B.args.data(), ihalf, B.S, B.hist, m, (int32_t *)pl->host_scal + 4, s);
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipMemcpyAsync(h.data(), B.hist, m * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));

@@ -39,6 +39,7 @@ constexpr double kInv4Pi = 1.0 / kFourPi;
 struct AArgs {
   int nx, ny, N, K, nbf, order, alsm, method;
   double dx, dy, V;
+  double sw, swm, swe;                                        // sums of w, w mu, w eta
   int qoff[5];
   const double *w, *wmu, *weta, *amu, *aeta;                  // internal ordinates
   const double *sig_t, *sig_s, *cE, *cW, *cN, *cS;            // caller's cell order
@@ -48,7 +49,7 @@ struct AArgs {
   const double *Ih;                                           // I^{m+1/2} [K][N]
   const double *delta, *phi, *phih;
   const double *gphi, *gFx, *gFy;                             // cotangents or null
-  double *lam, *ihb, *rb;                                     // [K][N]
+  double *lam, *ihb, *rb;                                     // [K][N] (lam: m, see lam_cell)
   double *s, *s_old, *bb, *hxb, *hyb, *phb, *Sb, *bfb;
   double *part;                                               // [4][5][N]
   double *dbar;                                               // [4][N]
@@ -103,29 +104,35 @@ __device__ inline int face_n(const AArgs &a, int q, int x) {
   return (q & 2) ? 2 * a.ny + i : 2 * a.ny + a.nx + i;
 }
 
-// Per quadrant, one thread per stored cell: unweighted sum of src over the
-// quadrant's ordinates into part[q][c] (c in the caller's order).
-__global__ void k_a_qsum(AArgs a, const double *src) {
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const int q = blockIdx.y;
-  if (t >= a.N) return;
-  int x, y;
-  dg_cell(t, a.nx, a.ny, x, y);
-  double v = 0.0;
-  for (int kk = a.qoff[q]; kk < a.qoff[q + 1]; ++kk) v += src[(size_t)kk * a.N + t];
-  a.part[(size_t)q * a.N + gcell(a, q, x, y)] = v;
+// What lambda holds beside the stored m (lam): lambda_k = m_k + w_k A +
+// w_k mu_k B + w_k eta_k C with A = sigma_s Sb / (4 pi) + g_phi, B = g_Fx,
+// C = g_Fy per cell. These terms need the sum of rb over all ordinates, so
+// they are not added where m is formed (k_a_out sums rb and m in the same
+// pass over the ordinates) but where lambda is next used.
+__device__ inline void lam_cell(const AArgs &a, int c, double Sb, double &A, double &B, double &C) {
+  A = a.sig_s[c] * Sb * kInv4Pi + (a.gphi ? a.gphi[c] : 0.0);
+  B = a.gFx ? a.gFx[c] : 0.0;
+  C = a.gFy ? a.gFy[c] : 0.0;
 }
 
-// out = scale * sum_q part[q]; with err, the Err partials of out against
-// s_old (which then takes out).
-__global__ void k_a_combine(AArgs a, double *out, double scale, int err) {
+// Sb = sum_k rb and s = sum_k lambda / (4 pi) from the quadrant sums that
+// k_a_out left in part; with err, the Err partials of s against s_old (which
+// then takes s).
+__global__ void k_a_combine(AArgs a, int err) {
   __shared__ double sh[kB];
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   double num = 0.0, den = 0.0;
   if (c < a.N) {
-    const double v = scale * (((a.part[c] + a.part[(size_t)a.N + c]) + a.part[2 * (size_t)a.N + c]) +
-                              a.part[3 * (size_t)a.N + c]);
-    out[c] = v;
+    double p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = a.part[(size_t)k * a.N + c];
+    const double Sb = ((p[4] + p[5]) + p[6]) + p[7];
+    double A, B, C;
+    lam_cell(a, c, Sb, A, B, C);
+    const double m = ((p[0] + p[1]) + p[2]) + p[3];
+    const double v = kInv4Pi * (m + (a.sw * A + a.swm * B + a.swe * C));
+    a.Sb[c] = Sb;
+    a.s[c] = v;
     if (err) {
       const double d = v - a.s_old[c];
       num = a.V * d * d;
@@ -197,7 +204,8 @@ __global__ void k_a_phbar(AArgs a, const double *kappa) {
 }
 
 // Ih_bar = lambda + w (phb + mu hbx + eta hby) + the outflow-wall
-// reconstruction transposed (GSIS); lambda alone (SI).
+// reconstruction transposed (GSIS); lambda alone (SI). lambda from the stored
+// m and lam_cell.
 __global__ void __launch_bounds__(kB) k_a_ihalf(AArgs a) {
   // one thread per stored cell of quadrant blockIdx.y, looping over the
   // quadrant's ordinates: the cell's cotangents, boundary terms and record
@@ -211,11 +219,12 @@ __global__ void __launch_bounds__(kB) k_a_ihalf(AArgs a) {
   bool xe = false, xe2 = false, yn = false, yn2 = false;
   const double hx = 0.5 * a.dx, hy = 0.5 * a.dy;
   const int so = a.order >= 2;
+  int x, y;
+  dg_cell(t, a.nx, a.ny, x, y);
+  const int c = gcell(a, q, x, y);
+  lam_cell(a, c, a.Sb[c], phb, hxb, hyb);
   if (gsis) {
-    int x, y;
-    dg_cell(t, a.nx, a.ny, x, y);
-    const int c = gcell(a, q, x, y);
-    phb = a.phb[c]; hxb = a.hxb[c]; hyb = a.hyb[c];
+    phb += a.phb[c]; hxb += a.hxb[c]; hyb += a.hyb[c];
     const double *Cq = a.cellq + (size_t)q * a.N * 6;
     // local east face of the last column: value u_c + hx (cW (u_c - u_w))
     xe = x == a.nx - 1;
@@ -230,8 +239,8 @@ __global__ void __launch_bounds__(kB) k_a_ihalf(AArgs a) {
   typedef const __attribute__((address_space(4))) double cdouble;
   cdouble *W = (cdouble *)a.w, *WM = (cdouble *)a.wmu, *WE = (cdouble *)a.weta;
   auto one = [&](int kk, double v) {
+    v += W[kk] * phb + WM[kk] * hxb + WE[kk] * hyb;
     if (gsis) {
-      v += W[kk] * phb + WM[kk] * hxb + WE[kk] * hyb;
       const double wmx = fabs(WM[kk]), wmy = fabs(WE[kk]);
       if (xe) {
         const double vb = be * wmx;
@@ -407,16 +416,24 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
   }
 }
 
-// lambda' = ihb - sigma_t rb - Div2^T rb + w sigma_s Sb / (4 pi) + M^T g.
+// m' = ihb - sigma_t rb - Div2^T rb, the part of lambda' that belongs to one
+// ordinate (lam_cell has the rest), with the quadrant's sums of m' and rb in
+// the same pass (part[q], part[4 + q], caller's cell order).
 // In the ordinate's frame r_c = ... - ax (E_c - E_w) - ay (N_c - N_s) with
 // E_c = u_c + hx (cE (u_e - u_c) - cW (u_w - u_c)) the east face value; so
 // Ebar_c = -ax (rb_c - rb_e) and ubar_d collects Ebar of d, d-1, d+1.
-__global__ void __launch_bounds__(kB) k_a_out(AArgs a) {
-  // one thread per stored cell of quadrant blockIdx.y, looping over the
-  // quadrant's ordinates: the cell's record entries, neighbour positions and
-  // cotangents are loaded once for all of them
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const int q = blockIdx.y;
+//
+// One thread per stored cell of a quadrant, looping over the quadrant's
+// ordinates: the cell's record entries and neighbour positions are found once
+// for all of them. Bound by HBM: rb and ihb are read and m' written, 24 B per
+// cell-ordinate. The neighbours of a block of 256 cells lie one or two
+// diagonals away, in other blocks, so the blocks of a quadrant fall into eight
+// contiguous runs, one per XCD (block b runs on XCD b % 8; ts blocks a run):
+// dealt round-robin, every XCD's L2 fetched rb of three diagonals for itself
+// (OUT_FIGS).
+__global__ void __launch_bounds__(kB) k_a_out(AArgs a, int ts) {
+  const int bi = blockIdx.x >> 3, q = bi / ts;
+  const long long t = ((long long)(blockIdx.x & 7) * ts + (bi - q * ts)) * kB + threadIdx.x;
   if (t >= a.N) return;
   const int nx = a.nx, ny = a.ny;
   int x, y;
@@ -433,13 +450,10 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a) {
   const double c0 = Cq[6 * t + 0], c1 = Cq[6 * t + 1], c2 = Cq[6 * t + 2], c3 = Cq[6 * t + 3];
   const double c4 = Cq[6 * t + 4];
   const double cW0 = Cq[6 * tW + 0], cE1 = Cq[6 * tE + 1], cS2 = Cq[6 * tS + 2], cN3 = Cq[6 * tN + 3];
-  const double sgs = a.sig_s[c], sbc = a.Sb[c];
-  const double gp = a.gphi ? a.gphi[c] : 0.0, gx = a.gFx ? a.gFx[c] : 0.0;
-  const double gy = a.gFy ? a.gFy[c] : 0.0;
   // ordinate weights through the constant address space (scalar loads)
   typedef const __attribute__((address_space(4))) double cdouble;
-  cdouble *W = (cdouble *)a.w, *WM = (cdouble *)a.wmu, *WE = (cdouble *)a.weta;
   cdouble *AM = (cdouble *)a.amu, *AE = (cdouble *)a.aeta;
+  double sm = 0.0, sr = 0.0;
   // ordinate kk from its loaded values (rb at the cell and its neighbours,
   // ihb at the cell)
   auto one = [&](int kk, double r0, double rE, double rE2, double rW, double rN, double rN2,
@@ -467,12 +481,9 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a) {
       }
     }
     v += ub;
-    v += W[kk] * sgs * sbc * kInv4Pi;
-    double g = 0.0;
-    if (a.gphi) g += W[kk] * gp;
-    if (a.gFx) g += WM[kk] * gx;
-    if (a.gFy) g += WE[kk] * gy;
-    a.lam[(size_t)kk * a.N + t] = v + g;
+    a.lam[(size_t)kk * a.N + t] = v;
+    sm += v;
+    sr += r0;
   };
   // four ordinates at a time: every load before any store (the arrays do
   // not overlap, which the compiler cannot see)
@@ -495,6 +506,8 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a) {
     const double *R = a.rb + (size_t)kk * a.N;
     one(kk, R[t], R[tE], R[tE2], R[tW], R[tN], R[tN2], R[tS], a.ihb[(size_t)kk * a.N + t]);
   }
+  a.part[(size_t)q * a.N + c] = sm;
+  a.part[(size_t)(4 + q) * a.N + c] = sr;
 }
 
 // Gradient pass, per quadrant and stored cell, summed over the quadrant's
@@ -667,6 +680,7 @@ void adj_fill_args(const PlanDev &P, const AdjointBuffers &B, const double *gphi
   a.nx = P.nx; a.ny = P.ny; a.N = P.N; a.K = P.K; a.nbf = P.nbf;
   a.order = P.order; a.alsm = P.alsm; a.method = P.method;
   a.dx = P.dx; a.dy = P.dy; a.V = P.V;
+  a.sw = P.sw; a.swm = P.swm; a.swe = P.swe;
   for (int t = 0; t < 5; ++t) a.qoff[t] = P.qoff[t];
   a.w = P.w; a.wmu = P.wmu; a.weta = P.weta; a.amu = P.amu; a.aeta = P.aeta;
   a.sig_t = P.sig_t; a.sig_s = P.sig_s;
@@ -684,16 +698,16 @@ void adj_fill_args(const PlanDev &P, const AdjointBuffers &B, const double *gphi
   memcpy(dst, &a, sizeof a);
 }
 
-// lambda <- G^T lambda + M^T g (ihalf_src: the stored I^{m+1/2} buffer).
-// With hist, Err of s against the previous s goes to hist[m].
+// lambda <- G^T lambda + M^T g (ihalf_src: the stored I^{m+1/2} buffer), in
+// the split form of lam_cell. With hist, Err of s against the previous s goes
+// to hist[m].
 void adj_launch_pass(const PlanDev &P, const AdjointBuffers &B, const void *args,
                      const double *ihalf, const SynthSet &S, double *hist, int m,
                      int32_t *host_flag, hipStream_t s) {
   AArgs a = *reinterpret_cast<const AArgs *>(args);
   a.Ih = ihalf;
   const int N = P.N, nb = nb_(N);
-  hipLaunchKernelGGL(k_a_qsum, dim3(nb, 4), dim3(kB), 0, s, a, (const double *)a.lam);
-  hipLaunchKernelGGL(k_a_combine, dim3(nb), dim3(kB), 0, s, a, a.s, kInv4Pi, hist ? 1 : 0);
+  hipLaunchKernelGGL(k_a_combine, dim3(nb), dim3(kB), 0, s, a, hist ? 1 : 0);
   if (hist) hipLaunchKernelGGL(k_a_err, dim3(1), dim3(kB), 0, s, a, nb, hist, m);
   if (P.method == GSIS_GSIS) {
     launch_synth_solve(S, s, host_flag, 0);
@@ -709,18 +723,19 @@ void adj_launch_pass(const PlanDev &P, const AdjointBuffers &B, const void *args
   else if (P.ny <= kAMaxW * 64)
     hipLaunchKernelGGL(k_a_chain<false>, dim3(P.K), dim3(rows), 0, s, a, 1);
   else hipLaunchKernelGGL(k_a_sweep, dim3(P.K), dim3(rows), 0, s, a);
-  hipLaunchKernelGGL(k_a_qsum, dim3(nb, 4), dim3(kB), 0, s, a, (const double *)a.rb);
-  hipLaunchKernelGGL(k_a_combine, dim3(nb), dim3(kB), 0, s, a, a.Sb, 1.0, 0);
-  hipLaunchKernelGGL(k_a_out, dim3(nb, 4), dim3(kB), 0, s, a);
+  const int ts = (nb + 7) / 8;
+  hipLaunchKernelGGL(k_a_out, dim3(4 * 8 * ts), dim3(kB), 0, s, a, ts);
   (void)B;
 }
 
-// dJ/dp from the quantities the last pass left (bb, hb, phb, bfb, rb, Sb).
+// dJ/dp from the quantities the last pass left (bb, hb, phb, bfb, rb, and the
+// sums of rb that give Sb).
 void adj_launch_gradient(const PlanDev &P, const void *args, const double *ihalf,
                          double *g_sa, double *g_ss, double *g_q, hipStream_t s) {
   AArgs a = *reinterpret_cast<const AArgs *>(args);
   a.Ih = ihalf;
   const int N = P.N, nb = nb_(N);
+  hipLaunchKernelGGL(k_a_combine, dim3(nb), dim3(kB), 0, s, a, 0);
   hipLaunchKernelGGL(k_a_coef_q, dim3(nb, 4), dim3(kB), 0, s, a);
   hipLaunchKernelGGL(k_a_grad1, dim3(nb), dim3(kB), 0, s, a);
   hipLaunchKernelGGL(k_a_grad2, dim3(nb), dim3(kB), 0, s, a, g_sa, g_ss, g_q);
