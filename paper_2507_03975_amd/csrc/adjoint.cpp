@@ -20,14 +20,14 @@ gsis_status adjoint_setup(gsis_plan *pl) {
   pl->adj = B;
   const size_t N = P.N, NK = (size_t)P.N * P.K;
   gsis_status st;
-  if ((st = dalloc(pl, &B->lam, NK)) || (st = dalloc(pl, &B->ihb, NK)) ||
-      (st = dalloc(pl, &B->rb, NK)) || (st = dalloc(pl, &B->s, N)) ||
+  if ((st = dalloc(pl, &B->lam, NK)) || (st = dalloc(pl, &B->rb, NK)) ||
+      (st = dalloc(pl, &B->pl, 12 * N)) || (st = dalloc(pl, &B->s, N)) ||
       (st = dalloc(pl, &B->s_old, N)) || (st = dalloc(pl, &B->bb, N)) ||
       (st = dalloc(pl, &B->hxb, N)) || (st = dalloc(pl, &B->hyb, N)) ||
       (st = dalloc(pl, &B->phb, N)) || (st = dalloc(pl, &B->Sb, N)) ||
       (st = dalloc(pl, &B->bfb, P.nbf)) || (st = dalloc(pl, &B->part, 20 * N)) ||
       (st = dalloc(pl, &B->dbar, 4 * N)) || (st = dalloc(pl, &B->stp, N)) ||
-      (st = dalloc(pl, &B->errp, 2 * ((N + 255) / 256) + 2)) ||
+      (st = dalloc(pl, &B->errp, 2 * (size_t)((P.nx + 15) / 16) * ((P.ny + 15) / 16) + 2)) ||
       (st = dalloc(pl, &B->gphi, N)) || (st = dalloc(pl, &B->gFx, N)) ||
       (st = dalloc(pl, &B->gFy, N)) || (st = dalloc(pl, &B->g_sa, N)) ||
       (st = dalloc(pl, &B->g_ss, N)) || (st = dalloc(pl, &B->g_q, N)) ||

@@ -55,6 +55,28 @@ __host__ __device__ inline int dg_row0(int d, int nx, int ny) {
   return o - (d - nx + 1 > 0 ? d - nx + 1 : 0);
 }
 
+// The cell (x, y) of stored index t: the inverse of dg_idx, for grids of
+// fewer than 2^28 cells. In the two corners a diagonal of index e starts at
+// e (e + 1) / 2; the square root finds e to within one, the comparisons fix
+// it (a search over the diagonals cost 80 us for the 2^20 cells of four
+// quadrants of 512 x 512, more than what the threads then did).
+__device__ inline int dg_corner(int t) {
+  int e = (int)((__builtin_sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+  if (e * (e + 1) / 2 > t) --e;
+  else if ((e + 1) * (e + 2) / 2 <= t) ++e;
+  return e;
+}
+__device__ inline void dg_cell(int t, int nx, int ny, int &x, int &y) {
+  const int A = nx < ny ? nx : ny, B = nx < ny ? ny : nx;
+  const int oA = A * (A + 1) / 2, oB = oA + (B - A) * A;
+  int d;
+  if (t < oA) d = dg_corner(t);
+  else if (t < oB) d = A + (t - oA) / A;
+  else d = nx + ny - 2 - dg_corner(nx * ny - 1 - t);
+  y = t - dg_row0(d, nx, ny);
+  x = d - y;
+}
+
 // One multigrid level of the synthetic operator D1 (5-point, SPD):
 //   (D x)_c = diag_c x_c - ax_c x_{c+1} - ax_{c-1} x_{c-1}
 //             - ay_c x_{c+nx} - ay_{c-nx} x_{c-nx}
@@ -353,7 +375,8 @@ double *synth_vcycle_total(const PlanDev &P);
 
 // ---- adjoint (kernels_adjoint.hip)
 struct AdjointBuffers {
-  double *lam = nullptr, *ihb = nullptr, *rb = nullptr;          // [K][N]
+  double *lam = nullptr, *rb = nullptr;                          // [K][N]
+  double *pl = nullptr;        // [4][3][N]
   double *s = nullptr, *s_old = nullptr, *bb = nullptr, *hxb = nullptr, *hyb = nullptr;
   double *phb = nullptr, *Sb = nullptr, *bfb = nullptr;
   double *part = nullptr;      // [4][5][N]

@@ -29,6 +29,7 @@
 #include "wave_ops.h"
 
 #include <cstring>
+#include <type_traits>
 
 namespace gsis {
 namespace {
@@ -49,7 +50,8 @@ struct AArgs {
   const double *Ih;                                           // I^{m+1/2} [K][N]
   const double *delta, *phi, *phih;
   const double *gphi, *gFx, *gFy;                             // cotangents or null
-  double *lam, *ihb, *rb;                                     // [K][N] (lam: m, see lam_cell)
+  double *lam, *rb;                                           // [K][N] (lam: m, see lam_cell)
+  double *pl;                                                 // [4][3][N], see k_a_planes
   double *s, *s_old, *bb, *hxb, *hyb, *phb, *Sb, *bfb;
   double *part;                                               // [4][5][N]
   double *dbar;                                               // [4][N]
@@ -66,15 +68,6 @@ __device__ inline int gcell(const AArgs &a, int q, int xl, int yl) {
   const int i = (q & 1) ? a.nx - 1 - xl : xl;
   const int j = (q & 2) ? a.ny - 1 - yl : yl;
   return j * a.nx + i;
-}
-__device__ inline void dg_cell(long long t, int nx, int ny, int &x, int &y) {
-  int lo = 0, hi = nx + ny - 2;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (dg_off(mid, nx, ny) <= t) lo = mid; else hi = mid - 1;
-  }
-  y = dg_ylo(lo, nx) + (int)(t - dg_off(lo, nx, ny));
-  x = lo - y;
 }
 __device__ inline void cell_ij(int c, int nx, int &i, int &j) {
   int q = (int)((double)c * __builtin_amdgcn_rcp((double)nx));
@@ -115,21 +108,67 @@ __device__ inline void lam_cell(const AArgs &a, int c, double Sb, double &A, dou
   C = a.gFy ? a.gFy[c] : 0.0;
 }
 
+// 16 x 16 tiles of the caller's grid, for the kernels that pass per-cell
+// fields between the caller's order and the quadrants' stored order. In a
+// quadrant's mirrored frame the tile is a square whose anti-diagonals are
+// runs of up to 16 stored cells; thread t takes the square's cell t in
+// anti-diagonal order for the stored arrays and cell t by rows for the
+// caller's, and LDS carries the values across. (One thread doing both reads
+// or writes one of the two sides 64 cache lines at a time: k_a_planes 90 ->
+// PLANES_US us at 512x512x128.)
+constexpr int kTS = 16;
+struct TileCell {
+  int i0, j0;        // the tile's first column and row
+  int u, w;          // the thread's cell of the square, from the quadrant's corner
+};
+__device__ inline TileCell tile_cell(const AArgs &a) {
+  TileCell T;
+  const int tw = (a.nx + kTS - 1) / kTS;
+  T.i0 = (int)(blockIdx.x % tw) * kTS;
+  T.j0 = (int)(blockIdx.x / tw) * kTS;
+  // diagonal e of the square: corners as in dg_corner, the square's middle
+  // is its longest diagonal
+  const int t = threadIdx.x, n = kTS * kTS;
+  const int e = t < n / 2 + kTS / 2 ? dg_corner(t) : 2 * kTS - 2 - dg_corner(n - 1 - t);
+  const int before = e < kTS ? e * (e + 1) / 2 : n - (2 * kTS - 1 - e) * (2 * kTS - e) / 2;
+  T.w = (e < kTS ? 0 : e - kTS + 1) + (t - before);
+  T.u = e - T.w;
+  return T;
+}
+// stored cell (x, y) of the thread in quadrant q, its index t and its place l
+// in the tile by rows; false: outside the grid
+__device__ inline bool tile_stored(const AArgs &a, const TileCell &T, int q, int &x, int &y, int &t,
+                                   int &l) {
+  x = (q & 1) ? a.nx - T.i0 - kTS + T.u : T.i0 + T.u;
+  y = (q & 2) ? a.ny - T.j0 - kTS + T.w : T.j0 + T.w;
+  l = ((q & 2) ? kTS - 1 - T.w : T.w) * kTS + ((q & 1) ? kTS - 1 - T.u : T.u);
+  const bool in = x >= 0 && x < a.nx && y >= 0 && y < a.ny;
+  t = in ? dg_row0(x + y, a.nx, a.ny) + y : 0;
+  return in;
+}
+
 // Sb = sum_k rb and s = sum_k lambda / (4 pi) from the quadrant sums that
-// k_a_out left in part; with err, the Err partials of s against s_old (which
-// then takes s).
-__global__ void k_a_combine(AArgs a, int err) {
-  __shared__ double sh[kB];
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  double num = 0.0, den = 0.0;
-  if (c < a.N) {
-    double p[8];
+// k_a_out left in part (stored order); with err, the Err partials of s
+// against s_old (which then takes s).
+__global__ void __launch_bounds__(kB) k_a_combine(AArgs a, int err) {
+  __shared__ double sh[kB], sm[8][kTS * kTS];
+  const TileCell T = tile_cell(a);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = a.part[(size_t)k * a.N + c];
-    const double Sb = ((p[4] + p[5]) + p[6]) + p[7];
+  for (int q = 0; q < 4; ++q) {
+    int x, y, t, l;
+    const bool in = tile_stored(a, T, q, x, y, t, l);
+    sm[q][l] = in ? a.part[(size_t)q * a.N + t] : 0.0;
+    sm[4 + q][l] = in ? a.part[(size_t)(4 + q) * a.N + t] : 0.0;
+  }
+  __syncthreads();
+  const int l = threadIdx.x, i = T.i0 + l % kTS, j = T.j0 + l / kTS;
+  double num = 0.0, den = 0.0;
+  if (i < a.nx && j < a.ny) {
+    const int c = j * a.nx + i;
+    const double Sb = ((sm[4][l] + sm[5][l]) + sm[6][l]) + sm[7][l];
     double A, B, C;
     lam_cell(a, c, Sb, A, B, C);
-    const double m = ((p[0] + p[1]) + p[2]) + p[3];
+    const double m = ((sm[0][l] + sm[1][l]) + sm[2][l]) + sm[3][l];
     const double v = kInv4Pi * (m + (a.sw * A + a.swm * B + a.swe * C));
     a.Sb[c] = Sb;
     a.s[c] = v;
@@ -203,73 +242,61 @@ __global__ void k_a_phbar(AArgs a, const double *kappa) {
   a.phb[d] = v;
 }
 
-// Ih_bar = lambda + w (phb + mu hbx + eta hby) + the outflow-wall
-// reconstruction transposed (GSIS); lambda alone (SI). lambda from the stored
-// m and lam_cell.
-__global__ void __launch_bounds__(kB) k_a_ihalf(AArgs a) {
-  // one thread per stored cell of quadrant blockIdx.y, looping over the
-  // quadrant's ordinates: the cell's cotangents, boundary terms and record
-  // entries are loaded once for all of them
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const int q = blockIdx.y;
-  if (t >= a.N) return;
+// Ih_bar_k = m_k + w_k P + w_k mu_k X + w_k eta_k Y (m_k: lam_cell): per
+// quadrant and stored cell the three fields that do not depend on the
+// ordinate, pl[q][3][N]. They hold lam_cell's terms and (GSIS) the cotangents
+// phb, hbx, hby and the outflow-wall reconstruction transposed, which takes
+// |w_k mu_k| = +-w_k mu_k, one sign per quadrant. The sweep and k_a_out form
+// Ih_bar from them where they need it: as an array of its own it cost a write
+// and two reads per cell-ordinate (k_a_ihalf, 173 us at 512x512x128).
+__global__ void __launch_bounds__(kB) k_a_planes(AArgs a) {
+  __shared__ double sm[3][kTS * kTS];
+  const TileCell T = tile_cell(a);
   const bool gsis = a.method == 1;
-  double phb = 0.0, hxb = 0.0, hyb = 0.0;
-  double be = 0.0, be2 = 0.0, bn = 0.0, bn2 = 0.0, ce = 0.0, ce2 = 0.0, cn = 0.0, cn2 = 0.0;
-  bool xe = false, xe2 = false, yn = false, yn2 = false;
-  const double hx = 0.5 * a.dx, hy = 0.5 * a.dy;
-  const int so = a.order >= 2;
-  int x, y;
-  dg_cell(t, a.nx, a.ny, x, y);
-  const int c = gcell(a, q, x, y);
-  lam_cell(a, c, a.Sb[c], phb, hxb, hyb);
-  if (gsis) {
-    phb += a.phb[c]; hxb += a.hxb[c]; hyb += a.hyb[c];
-    const double *Cq = a.cellq + (size_t)q * a.N * 6;
-    // local east face of the last column: value u_c + hx (cW (u_c - u_w))
-    xe = x == a.nx - 1;
-    xe2 = so && x == a.nx - 2;
-    yn = y == a.ny - 1;
-    yn2 = so && y == a.ny - 2;
-    if (xe) { be = a.bfb[face_e(a, q, y)]; ce = so && x > 0 ? hx * Cq[6 * t + 1] : 0.0; }
-    if (xe2) { be2 = a.bfb[face_e(a, q, y)]; ce2 = Cq[6 * dg_idx(x + 1, y, a.nx, a.ny) + 1]; }
-    if (yn) { bn = a.bfb[face_n(a, q, x)]; cn = so && y > 0 ? hy * Cq[6 * t + 3] : 0.0; }
-    if (yn2) { bn2 = a.bfb[face_n(a, q, x)]; cn2 = Cq[6 * dg_idx(x, y + 1, a.nx, a.ny) + 3]; }
-  }
-  typedef const __attribute__((address_space(4))) double cdouble;
-  cdouble *W = (cdouble *)a.w, *WM = (cdouble *)a.wmu, *WE = (cdouble *)a.weta;
-  auto one = [&](int kk, double v) {
-    v += W[kk] * phb + WM[kk] * hxb + WE[kk] * hyb;
-    if (gsis) {
-      const double wmx = fabs(WM[kk]), wmy = fabs(WE[kk]);
-      if (xe) {
-        const double vb = be * wmx;
-        v += vb * (1.0 + ce);
-      }
-      if (xe2) v -= be2 * wmx * hx * ce2;
-      if (yn) {
-        const double vb = bn * wmy;
-        v += vb * (1.0 + cn);
-      }
-      if (yn2) v -= bn2 * wmy * hy * cn2;
+  {
+    const int l = threadIdx.x, i = T.i0 + l % kTS, j = T.j0 + l / kTS;
+    double P = 0.0, X = 0.0, Y = 0.0;
+    if (i < a.nx && j < a.ny) {
+      const int c = j * a.nx + i;
+      lam_cell(a, c, a.Sb[c], P, X, Y);
+      if (gsis) { P += a.phb[c]; X += a.hxb[c]; Y += a.hyb[c]; }
     }
-    a.ihb[(size_t)kk * a.N + t] = v;
-  };
-  // eight ordinates' lambda loaded before any ihb is stored
-  constexpr int U = 8;
-  int kk = a.qoff[q];
-  const int ke = a.qoff[q + 1];
-  for (; kk + U <= ke; kk += U) {
-    double l[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) l[u] = a.lam[(size_t)(kk + u) * a.N + t];
-#pragma unroll
-    for (int u = 0; u < U; ++u) one(kk + u, l[u]);
+    sm[0][l] = P; sm[1][l] = X; sm[2][l] = Y;
   }
-  for (; kk < ke; ++kk) one(kk, a.lam[(size_t)kk * a.N + t]);
+  __syncthreads();
+  const double hx = 0.5 * a.dx, hy = 0.5 * a.dy;
+  const bool so = a.order >= 2;
+  for (int q = 0; q < 4; ++q) {
+    int x, y, t, l;
+    if (!tile_stored(a, T, q, x, y, t, l)) continue;
+    double X = sm[1][l], Y = sm[2][l];
+    if (gsis) {
+      const double *Cq = a.cellq + (size_t)q * a.N * 6;
+      // local east face of the last column: value u_c + hx (cW (u_c - u_w))
+      double vx = 0.0, vy = 0.0;
+      if (x == a.nx - 1)
+        vx = a.bfb[face_e(a, q, y)] * (1.0 + (so && x > 0 ? hx * Cq[6 * (size_t)t + 1] : 0.0));
+      else if (so && x == a.nx - 2)
+        vx = -a.bfb[face_e(a, q, y)] * hx * Cq[6 * dg_idx(x + 1, y, a.nx, a.ny) + 1];
+      if (y == a.ny - 1)
+        vy = a.bfb[face_n(a, q, x)] * (1.0 + (so && y > 0 ? hy * Cq[6 * (size_t)t + 3] : 0.0));
+      else if (so && y == a.ny - 2)
+        vy = -a.bfb[face_n(a, q, x)] * hy * Cq[6 * dg_idx(x, y + 1, a.nx, a.ny) + 3];
+      X += (q & 1) ? -vx : vx;
+      Y += (q & 2) ? -vy : vy;
+    }
+    double *p = a.pl + (size_t)q * 3 * a.N + t;
+    p[0] = sm[0][l];
+    p[a.N] = X;
+    p[2 * (size_t)a.N] = Y;
+  }
+}
+__device__ inline double ihalf(double m, double P, double X, double Y, double w, double wm,
+                               double we) {
+  return fma(we, Y, fma(wm, X, fma(w, P, m)));
 }
 
-// rb = H^-T ihb per ordinate: rb_c = (ihb_c + ax rb_east + ay rb_north) / d_c,
+// rb = H^-T ihb per ordinate (ihb = Ih_bar): rb_c = (ihb_c + ax rb_east + ay rb_north) / d_c,
 // d_c = sigma_t + ax + ay, downstream cells first. Thread t of a pass owns
 // reversed row y' = y0 + t (local row ny-1-y'); at step s it is at reversed
 // column s - t, so each step is one anti-diagonal and both dependencies are
@@ -282,7 +309,9 @@ __global__ void k_a_sweep(AArgs a) {
   const int nx = a.nx, ny = a.ny;
   const double ax = a.amu[kk], ay = a.aeta[kk];
   const double *Cq = a.cellq + (size_t)q * a.N * 6;
-  const double *src = a.ihb + (size_t)kk * a.N;
+  const double *src = a.lam + (size_t)kk * a.N;
+  const double *pl = a.pl + (size_t)q * 3 * a.N;
+  const double w = a.w[kk], wm = a.wmu[kk], we = a.weta[kk];
   double *out = a.rb + (size_t)kk * a.N;
   __shared__ double edge[2][16];
   for (int y0 = 0; y0 < ny; y0 += rows_pp) {
@@ -307,7 +336,8 @@ __global__ void k_a_sweep(AArgs a) {
         const double east = xr > 0 ? prev : 0.0;
         const double north = yr > 0 ? below : 0.0;
         const double d = Cq[6 * o + 5] + ax + ay;
-        const double v = (src[o] + ax * east + ay * north) / d;
+        const double ih = ihalf(src[o], pl[o], pl[a.N + o], pl[2 * (long long)a.N + o], w, wm, we);
+        const double v = (ih + ax * east + ay * north) / d;
         out[o] = v;
         prev = v;
       }
@@ -324,7 +354,8 @@ __global__ void k_a_sweep(AArgs a) {
 // entry plus the lane's row), rb_north is lane t-1's previous value (a DPP
 // shift), waves run kAL steps apart and meet at a barrier every kAL steps
 // (the top lane's values through an LDS ring), and the operands of a step
-// (ihb, sigma_t + shift) are loaded kAL steps ahead. Out-of-range indices
+// (m and the fields that make Ih_bar of it, sigma_t + shift) are loaded kAL
+// steps ahead. Out-of-range indices
 // fall outside the buffer resources: their loads read 0, their stores are
 // dropped. rb = ihb / d + (ax / d) rb_east + (ay / d) rb_north.
 // SPLIT: as the forward recurrence, the reversed rows spread over np
@@ -341,7 +372,12 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double ax = a.amu[kk], ay = a.aeta[kk], axy = ax + ay;
-  const __amdgpu_buffer_rsrc_t Sr = buf_rsrc(a.ihb + (size_t)kk * N, (size_t)N * 8);
+  const double w = a.w[kk], wm = a.wmu[kk], we = a.weta[kk];
+  const __amdgpu_buffer_rsrc_t Sr = buf_rsrc(a.lam + (size_t)kk * N, (size_t)N * 8);
+  const double *pl = a.pl + (size_t)q * 3 * N;
+  const __amdgpu_buffer_rsrc_t Pr = buf_rsrc(pl, (size_t)N * 8);
+  const __amdgpu_buffer_rsrc_t Xr = buf_rsrc(pl + N, (size_t)N * 8);
+  const __amdgpu_buffer_rsrc_t Yr = buf_rsrc(pl + 2 * (size_t)N, (size_t)N * 8);
   const __amdgpu_buffer_rsrc_t Dr = buf_rsrc(a.sdq + (size_t)q * N, (size_t)N * 8);
   const __amdgpu_buffer_rsrc_t Or = buf_rsrc(a.rb + (size_t)kk * N, (size_t)N * 8);
   const __attribute__((address_space(4))) int *DS =
@@ -367,13 +403,16 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
   const int nsteps = nx + rows - 1;
   const int tend = ((nsteps + (nw - 1) * kAL + kAL - 1) / kAL) * kAL;
   const int s0 = -wave * kAL;               // this wave's step at time 0
-  double rb_s[kAL] = {}, rb_d[kAL] = {};
+  double rb_s[kAL] = {}, rb_d[kAL] = {}, rb_p[kAL] = {}, rb_x[kAL] = {}, rb_y[kAL] = {};
   unsigned rb_i[kAL] = {};
   auto load = [&](int t, int so) {          // row-0 storage index so of the step's diagonal
     const unsigned i = (unsigned)(so + yl);
     rb_i[t] = i;
     rb_s[t] = buf_ld64(Sr, i * 8u);
     rb_d[t] = buf_ld64(Dr, i * 8u);
+    rb_p[t] = buf_ld64(Pr, i * 8u);
+    rb_x[t] = buf_ld64(Xr, i * 8u);
+    rb_y[t] = buf_ld64(Yr, i * 8u);
   };
   double vp = 0.0;
   for (int tb = -kAL; tb < tend; tb += kAL) {
@@ -399,7 +438,8 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
       const bool act = (unsigned)xr < (unsigned)nx;
       const double vN = shr1_fill(vp, bl[t2]);
       const double inv = rcp64(rb_d[t2] + axy);
-      const double vn = fma(ax * inv, vp, fma(ay * inv, vN, rb_s[t2] * inv));
+      const double ih = ihalf(rb_s[t2], rb_p[t2], rb_x[t2], rb_y[t2], w, wm, we);
+      const double vn = fma(ax * inv, vp, fma(ay * inv, vN, ih * inv));
       const double v = act ? vn : vp;
       buf_store(v, Or, act ? rb_i[t2] * 8u : kNoCell);
       if (SPLIT && wave == nw - 1 && part + 1 < np)
@@ -418,14 +458,14 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
 
 // m' = ihb - sigma_t rb - Div2^T rb, the part of lambda' that belongs to one
 // ordinate (lam_cell has the rest), with the quadrant's sums of m' and rb in
-// the same pass (part[q], part[4 + q], caller's cell order).
+// the same pass (part[q], part[4 + q], stored order).
 // In the ordinate's frame r_c = ... - ax (E_c - E_w) - ay (N_c - N_s) with
 // E_c = u_c + hx (cE (u_e - u_c) - cW (u_w - u_c)) the east face value; so
 // Ebar_c = -ax (rb_c - rb_e) and ubar_d collects Ebar of d, d-1, d+1.
 //
 // One thread per stored cell of a quadrant, looping over the quadrant's
 // ordinates: the cell's record entries and neighbour positions are found once
-// for all of them. Bound by HBM: rb and ihb are read and m' written, 24 B per
+// for all of them. Bound by HBM: rb and m are read and m' written, 24 B per
 // cell-ordinate. The neighbours of a block of 256 cells lie one or two
 // diagonals away, in other blocks, so the blocks of a quadrant fall into eight
 // contiguous runs, one per XCD (block b runs on XCD b % 8; ts blocks a run):
@@ -437,29 +477,38 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a, int ts) {
   if (t >= a.N) return;
   const int nx = a.nx, ny = a.ny;
   int x, y;
-  dg_cell(t, nx, ny, x, y);
-  const int c = gcell(a, q, x, y);
+  dg_cell((int)t, nx, ny, x, y);
   const double *Cq = a.cellq + (size_t)q * a.N * 6;
   const double hx = 0.5 * a.dx, hy = 0.5 * a.dy;
-  auto I = [&](int xx, int yy) { return dg_idx(xx, yy, nx, ny); };
   const bool hE = x + 1 < nx, hE2 = x + 2 < nx, hW = x > 0;
   const bool hN = y + 1 < ny, hN2 = y + 2 < ny, hS = y > 0;
-  const long long tE = hE ? I(x + 1, y) : t, tE2 = hE2 ? I(x + 2, y) : t, tW = hW ? I(x - 1, y) : t;
-  const long long tN = hN ? I(x, y + 1) : t, tN2 = hN2 ? I(x, y + 2) : t, tS = hS ? I(x, y - 1) : t;
+  // byte offsets in an ordinate's array, the same for every ordinate: the
+  // loads take a scalar base per ordinate and these
+  auto I = [&](bool has, int xx, int yy) {
+    return has ? (unsigned)(dg_row0(xx + yy, nx, ny) + yy) * 8u : (unsigned)t * 8u;
+  };
+  const unsigned t0 = (unsigned)t * 8u;
+  const unsigned tE = I(hE, x + 1, y), tE2 = I(hE2, x + 2, y), tW = I(hW, x - 1, y);
+  const unsigned tN = I(hN, x, y + 1), tN2 = I(hN2, x, y + 2), tS = I(hS, x, y - 1);
   const bool so = a.order >= 2;
   const double c0 = Cq[6 * t + 0], c1 = Cq[6 * t + 1], c2 = Cq[6 * t + 2], c3 = Cq[6 * t + 3];
   const double c4 = Cq[6 * t + 4];
-  const double cW0 = Cq[6 * tW + 0], cE1 = Cq[6 * tE + 1], cS2 = Cq[6 * tS + 2], cN3 = Cq[6 * tN + 3];
+  const __amdgpu_buffer_rsrc_t Cr = buf_rsrc(Cq, (size_t)a.N * 48);
+  const double cW0 = buf_ld64(Cr, 6 * tW), cE1 = buf_ld64(Cr, 6 * tE + 8u);
+  const double cS2 = buf_ld64(Cr, 6 * tS + 16u), cN3 = buf_ld64(Cr, 6 * tN + 24u);
   // ordinate weights through the constant address space (scalar loads)
   typedef const __attribute__((address_space(4))) double cdouble;
+  cdouble *W = (cdouble *)a.w, *WM = (cdouble *)a.wmu, *WE = (cdouble *)a.weta;
   cdouble *AM = (cdouble *)a.amu, *AE = (cdouble *)a.aeta;
+  const double *pl = a.pl + (size_t)q * 3 * a.N + t;
+  const double P = pl[0], X = pl[a.N], Y = pl[2 * (size_t)a.N];
   double sm = 0.0, sr = 0.0;
-  // ordinate kk from its loaded values (rb at the cell and its neighbours,
-  // ihb at the cell)
+  // ordinate kk from its loaded values (rb at the cell and its neighbours, m
+  // at the cell)
   auto one = [&](int kk, double r0, double rE, double rE2, double rW, double rN, double rN2,
-                 double rS, double ih) {
+                 double rS, double m) {
     const double ax = AM[kk], ay = AE[kk];
-    double v = ih - c4 * r0;
+    double v = ihalf(m, P, X, Y, W[kk], WM[kk], WE[kk]) - c4 * r0;
     double ub = 0.0;
     {
       // Ebar at columns x, x - 1, x + 1 of row y; Nbar likewise
@@ -481,33 +530,37 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a, int ts) {
       }
     }
     v += ub;
-    a.lam[(size_t)kk * a.N + t] = v;
     sm += v;
     sr += r0;
+    return v;
   };
-  // four ordinates at a time: every load before any store (the arrays do
-  // not overlap, which the compiler cannot see)
-  constexpr int U = 4;
-  int kk = a.qoff[q];
-  const int ke = a.qoff[q + 1];
-  for (; kk + U <= ke; kk += U) {
-    double r0[U], rE[U], rE2[U], rW[U], rN[U], rN2[U], rS[U], ih[U];
+  auto base = [&](const double *p, int kk) {
+    return buf_rsrc(p + (size_t)kk * a.N, (size_t)a.N * 8);
+  };
+  // U ordinates at a time: every load before any store (the arrays do not
+  // overlap, which the compiler cannot see)
+  auto group = [&](auto n, int kk) {
+    constexpr int U = decltype(n)::value;
+    double r0[U], rE[U], rE2[U], rW[U], rN[U], rN2[U], rS[U], m[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const double *R = a.rb + (size_t)(kk + u) * a.N;
-      r0[u] = R[t]; rE[u] = R[tE]; rE2[u] = R[tE2]; rW[u] = R[tW];
-      rN[u] = R[tN]; rN2[u] = R[tN2]; rS[u] = R[tS];
-      ih[u] = a.ihb[(size_t)(kk + u) * a.N + t];
+      const __amdgpu_buffer_rsrc_t R = base(a.rb, kk + u);
+      r0[u] = buf_ld64(R, t0); rE[u] = buf_ld64(R, tE); rE2[u] = buf_ld64(R, tE2);
+      rW[u] = buf_ld64(R, tW); rN[u] = buf_ld64(R, tN); rN2[u] = buf_ld64(R, tN2);
+      rS[u] = buf_ld64(R, tS);
+      m[u] = buf_ld64(base(a.lam, kk + u), t0);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) one(kk + u, r0[u], rE[u], rE2[u], rW[u], rN[u], rN2[u], rS[u], ih[u]);
-  }
-  for (; kk < ke; ++kk) {
-    const double *R = a.rb + (size_t)kk * a.N;
-    one(kk, R[t], R[tE], R[tE2], R[tW], R[tN], R[tN2], R[tS], a.ihb[(size_t)kk * a.N + t]);
-  }
-  a.part[(size_t)q * a.N + c] = sm;
-  a.part[(size_t)(4 + q) * a.N + c] = sr;
+    for (int u = 0; u < U; ++u)
+      buf_store(one(kk + u, r0[u], rE[u], rE2[u], rW[u], rN[u], rN2[u], rS[u], m[u]),
+                base(a.lam, kk + u), t0);
+  };
+  int kk = a.qoff[q];
+  const int ke = a.qoff[q + 1];
+  for (; kk + 4 <= ke; kk += 4) group(std::integral_constant<int, 4>(), kk);
+  for (; kk < ke; ++kk) group(std::integral_constant<int, 1>(), kk);
+  a.part[(size_t)q * a.N + t] = sm;
+  a.part[(size_t)(4 + q) * a.N + t] = sr;
 }
 
 // Gradient pass, per quadrant and stored cell, summed over the quadrant's
@@ -521,7 +574,7 @@ __global__ void k_a_coef_q(AArgs a) {
   if (t >= a.N) return;
   const int nx = a.nx, ny = a.ny;
   int x, y;
-  dg_cell(t, nx, ny, x, y);
+  dg_cell((int)t, nx, ny, x, y);
   const int c = gcell(a, q, x, y);
   const double *Cq = a.cellq + (size_t)q * a.N * 6;
   (void)Cq;
@@ -690,7 +743,7 @@ void adj_fill_args(const PlanDev &P, const AdjointBuffers &B, const double *gphi
   a.dso = P.dso;
   a.delta = P.delta; a.phi = P.phi; a.phih = P.phih;
   a.gphi = gphi; a.gFx = gFx; a.gFy = gFy;
-  a.lam = B.lam; a.ihb = B.ihb; a.rb = B.rb;
+  a.lam = B.lam; a.rb = B.rb; a.pl = B.pl;
   a.s = B.s; a.s_old = B.s_old; a.bb = B.bb; a.hxb = B.hxb; a.hyb = B.hyb; a.phb = B.phb;
   a.Sb = B.Sb; a.bfb = B.bfb; a.part = B.part; a.dbar = B.dbar; a.stp = B.stp; a.errp = B.errp;
   a.hand = P.hand;
@@ -707,14 +760,15 @@ void adj_launch_pass(const PlanDev &P, const AdjointBuffers &B, const void *args
   AArgs a = *reinterpret_cast<const AArgs *>(args);
   a.Ih = ihalf;
   const int N = P.N, nb = nb_(N);
-  hipLaunchKernelGGL(k_a_combine, dim3(nb), dim3(kB), 0, s, a, hist ? 1 : 0);
-  if (hist) hipLaunchKernelGGL(k_a_err, dim3(1), dim3(kB), 0, s, a, nb, hist, m);
+  const int nt = ((P.nx + kTS - 1) / kTS) * ((P.ny + kTS - 1) / kTS);
+  hipLaunchKernelGGL(k_a_combine, dim3(nt), dim3(kB), 0, s, a, hist ? 1 : 0);
+  if (hist) hipLaunchKernelGGL(k_a_err, dim3(1), dim3(kB), 0, s, a, nt, hist, m);
   if (P.method == GSIS_GSIS) {
     launch_synth_solve(S, s, host_flag, 0);
     hipLaunchKernelGGL(k_a_hbar, dim3(nb), dim3(kB), 0, s, a);
     hipLaunchKernelGGL(k_a_phbar, dim3(nb), dim3(kB), 0, s, a, (const double *)P.kappa);
   }
-  hipLaunchKernelGGL(k_a_ihalf, dim3(nb, 4), dim3(kB), 0, s, a);
+  hipLaunchKernelGGL(k_a_planes, dim3(nt), dim3(kB), 0, s, a);
   int rows = ((P.ny + 63) / 64) * 64;
   if (rows > 1024) rows = 1024;
   if (P.chain_parts > 1)
@@ -735,7 +789,8 @@ void adj_launch_gradient(const PlanDev &P, const void *args, const double *ihalf
   AArgs a = *reinterpret_cast<const AArgs *>(args);
   a.Ih = ihalf;
   const int N = P.N, nb = nb_(N);
-  hipLaunchKernelGGL(k_a_combine, dim3(nb), dim3(kB), 0, s, a, 0);
+  const int nt = ((P.nx + kTS - 1) / kTS) * ((P.ny + kTS - 1) / kTS);
+  hipLaunchKernelGGL(k_a_combine, dim3(nt), dim3(kB), 0, s, a, 0);
   hipLaunchKernelGGL(k_a_coef_q, dim3(nb, 4), dim3(kB), 0, s, a);
   hipLaunchKernelGGL(k_a_grad1, dim3(nb), dim3(kB), 0, s, a);
   hipLaunchKernelGGL(k_a_grad2, dim3(nb), dim3(kB), 0, s, a, g_sa, g_ss, g_q);

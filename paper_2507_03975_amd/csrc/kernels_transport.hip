@@ -1421,17 +1421,7 @@ __global__ void k_zero_int(int *p) { *p = 0; }
 
 // phi, F of I^{m+1/2} in two passes: per quadrant and tile, sums over the
 // quadrant's ordinates into partials at the caller's cell index (below);
-// then the four partials are added in a fixed order. dg_cell: the cell (x,
-// y) of stored index t.
-__device__ inline void dg_cell(long long t, int nx, int ny, int &x, int &y) {
-  int lo = 0, hi = nx + ny - 2;               // find d with off(d) <= t < off(d+1)
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (dg_off(mid, nx, ny) <= t) lo = mid; else hi = mid - 1;
-  }
-  y = dg_ylo(lo, nx) + (int)(t - dg_off(lo, nx, ny));
-  x = lo - y;
-}
+// then the four partials are added in a fixed order.
 
 // Sum of src^2 = ((sigma_s phi^m + q)/(4 pi))^2 over the cells of one block
 // of 256 (natural cell order), for the relative transport residual; every
@@ -1632,7 +1622,7 @@ __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, cons
   if (t >= a.N) return;
   const int nx = a.nx, ny = a.ny, N = a.N;
   int x, y;
-  dg_cell(t, nx, ny, x, y);
+  dg_cell((int)t, nx, ny, x, y);
   const int c = gcell(a, q, x, y);
   const bool he = x + 1 < nx, hw = x > 0, hn = y + 1 < ny, hs = y > 0;
   if (!he && !hn) return;                     // both outgoing faces are walls
