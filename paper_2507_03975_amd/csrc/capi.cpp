@@ -594,17 +594,24 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       cus = 0;
     int parts = std::min((ny + 255) / 256, 4);
     while (parts < 4 && 2 * K * parts < cus) parts *= 2;
+    // the adjoint's sweep loads five values a step where the recurrence loads
+    // two: parts of about 128 rows, two waves (256 rows 85 us in 2 parts
+    // against 112 in 1; 512 rows 307 us in 4 against 349 in 2)
+    int aparts = std::max(parts, std::min((ny + 127) / 128, 4));
     const char *e = getenv("GSIS_CHAIN_PARTS");
-    if (e && e[0] >= '1' && e[0] <= '4' && e[1] == 0) parts = e[0] - '0';
-    parts = std::max(1, std::min(parts, 4));
-    int rows = 0;
-    for (; parts > 1; --parts) {
-      rows = ((ny + parts - 1) / parts + 63) / 64 * 64;
-      if (rows <= 1024 && (parts - 1) * rows < ny) break;
-    }
+    if (e && e[0] >= '1' && e[0] <= '4' && e[1] == 0) parts = aparts = e[0] - '0';
+    auto split = [&](int n, int &np, int &rows) {
+      np = std::max(1, std::min(n, 4));
+      rows = 0;
+      for (; np > 1; --np) {
+        rows = ((ny + np - 1) / np + 63) / 64 * 64;
+        if (rows <= 1024 && (np - 1) * rows < ny) break;
+      }
+      if (np <= 1) rows = 0;
+    };
+    split(aparts, P.adj_parts, P.adj_rows);
     if (P.sweep_impl == 1 || P.sweep_impl == 2) parts = 1;
-    P.chain_parts = parts;
-    P.chain_rows = parts > 1 ? rows : 0;
+    split(parts, P.chain_parts, P.chain_rows);
   }
   // residual tiles (GSIS_RESID_DIAGONALS=31 or 47 sets their length)
   P.resid_rd = residual_tile_diagonals((long long)N * K);
@@ -688,8 +695,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       (st = dalloc(pl, &P.src2_part, (size_t)(N + 255) / 256)) ||
       (st = dalloc(pl, &P.state, 5)) || (st = dalloc(pl, &P.last_err, 2)))
     return bail(st);
-  if (std::max(P.chain_parts, P.pipe_parts) > 1 &&
-      (st = dalloc(pl, &P.hand, (size_t)K * (std::max(P.chain_parts, P.pipe_parts) - 1) * nx)))
+  if (hand_parts(P) > 1 && (st = dalloc(pl, &P.hand, (size_t)K * (hand_parts(P) - 1) * nx)))
     return bail(st);
   if (f32) {
     std::vector<float> sdqf(sdq.begin(), sdq.end());

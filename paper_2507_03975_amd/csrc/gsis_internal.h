@@ -194,10 +194,12 @@ struct PlanDev {
   double *cellq = nullptr, *dynq = nullptr;
   double *rowbuf = nullptr;    // [K][3][nx] hand-off between sweep passes
   unsigned long long *hand = nullptr;  // [K][parts - 1][nx] row hand-over between
-                               // the workgroups of one ordinate (split recurrence
-                               // or pipelined step; sized for the larger)
+                               // the workgroups of one ordinate (split recurrence,
+                               // pipelined step or adjoint sweep; sized for the
+                               // one with the most parts)
   int chain_parts = 1;         // workgroups per ordinate in the recurrence
   int chain_rows = 0;          // rows per part (a multiple of 64, <= 1024)
+  int adj_parts = 1, adj_rows = 0;   // the same for the adjoint's sweep
   int pipe_bands = 0;          // pipelined step: bands of 64 rows per workgroup (1, 2, 4)
   int pipe_parts = 1;          // pipelined step: workgroups per ordinate
   int n_tres = 0;              // partial sums of w r^2 the transport step writes
@@ -271,6 +273,10 @@ struct PlanDev {
 // increment solve (for the fused kernel the residual launch is empty).
 void launch_residual(const PlanDev &P, hipStream_t s);
 void launch_sweep(const PlanDev &P, hipStream_t s);
+inline int hand_parts(const PlanDev &P) {
+  const int p = P.chain_parts > P.pipe_parts ? P.chain_parts : P.pipe_parts;
+  return p > P.adj_parts ? p : P.adj_parts;
+}
 // Puts every entry of the split recurrence's hand-over buffer in its empty
 // state (plan set-up and reset; the recurrence keeps it so between launches).
 void launch_hand_reset(const PlanDev &P, hipStream_t s);

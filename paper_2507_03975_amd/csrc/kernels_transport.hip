@@ -1967,7 +1967,7 @@ std::vector<int2> residual_tiles(int nx, int ny, int rd) {
 size_t targs_bytes() { return sizeof(TArgs); }
 
 void launch_hand_reset(const PlanDev &P, hipStream_t s) {
-  const int hp = std::max(P.chain_parts, P.pipe_parts);
+  const int hp = hand_parts(P);
   if (hp <= 1) return;
   const size_t n = (size_t)P.K * (hp - 1) * P.nx;
   hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, P.hand, n,
