@@ -613,6 +613,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     if (P.sweep_impl == 1 || P.sweep_impl == 2) parts = 1;
     split(parts, P.chain_parts, P.chain_rows);
   }
+  P.mom_split = moment_split(P);
   // residual tiles (GSIS_RESID_DIAGONALS=31 or 47 sets their length)
   P.resid_rd = residual_tile_diagonals((long long)N * K);
   {
@@ -684,7 +685,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       (st = upload(pl, &P.cN, cN)) || (st = upload(pl, &P.cS, cS)) ||
       (st = dalloc(pl, &P.src, N)) || (st = dalloc(pl, &P.phi, N)) ||
       (st = dalloc(pl, &P.phih, N)) || (st = dalloc(pl, &P.Fx, N)) ||
-      (st = dalloc(pl, &P.mom_part, (size_t)12 * N)) ||
+      (st = dalloc(pl, &P.mom_part, (size_t)12 * P.mom_split * N)) ||
       (st = dalloc(pl, &P.Fy, N)) || (st = dalloc(pl, &P.delta, N)) ||
       (st = dalloc(pl, &P.hx, N)) || (st = dalloc(pl, &P.hy, N)) ||
       (st = dalloc(pl, &P.rhs, N)) || (st = upload(pl, &P.bnd, bnd_int)) ||
@@ -845,7 +846,7 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
     launch_moments(P, s, P.method == GSIS_GSIS);
     if ((st = record(pl, 3))) return st;
     if (P.method == GSIS_GSIS) {
-      launch_hot(P.S, s, true);
+      launch_hot(P.S, s, P.mom_split == 1);
     }
     if ((st = record(pl, 4))) return st;
     // the synthetic solve copies the device flags to the host once while it

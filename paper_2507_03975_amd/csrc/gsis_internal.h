@@ -220,7 +220,8 @@ struct PlanDev {
   double *src = nullptr;       // (sigma_s phi^m + q)/(4 pi)
   double *phi = nullptr;       // phi^m
   double *phih = nullptr, *Fx = nullptr, *Fy = nullptr;  // moments of I^{m+1/2}
-  double *mom_part = nullptr;  // [4][3][N] per-quadrant partial moments
+  double *mom_part = nullptr;  // [mom_split][4][3][N] per-quadrant partial moments
+  int mom_split = 1;           // parts of a quadrant's ordinates (moment_split)
   double *ftp = nullptr;       // transport-face HoT: [4][2][N] per-quadrant
                                // sum_k w_k (Omega_k . n) I_f,k on the east / north
                                // face of each cell (reconstructed upwind values)
@@ -323,9 +324,9 @@ void launch_moments_batch(const void *targs, const int2 *bt_cell, int nb_cell,
                           const int2 *bt_tile, int nb_tile, bool fp32, hipStream_t s);
 void launch_boundary_flux_batch(const void *targs, const int2 *bt_face, int nb_face,
                                 hipStream_t s);
-// phi, F of the swept intensity; with bflux (GSIS) only the per-quadrant
-// partials, which launch_hot(.., true) combines, and the boundary faces'
-// F_T . n in the same launch
+// phi, F of the swept intensity; with bflux (GSIS) the boundary faces'
+// F_T . n in the same launch and, for undivided quadrants (mom_split 1), only
+// the per-quadrant partials, which launch_hot(.., true) combines
 void launch_moments(const PlanDev &P, hipStream_t s, bool bflux);
 
 // ---- synthetic / update kernels (kernels_synth.hip)
@@ -340,6 +341,15 @@ int source_tiles_of(int nx, int ny);   // 16 x 16 tiles of the source kernel
 // plan, moment_tile_size_batch for batches)
 int moment_tile_size(int nx, int ny);
 int moment_tile_size_batch();
+// Parts a quadrant's ordinates are summed in. Where the tiles of the four
+// quadrants make fewer than 128 blocks, half the CUs idle while each block
+// walks all of a quadrant's ordinates: parts of at least 24 ordinates then,
+// until about 1024 blocks run (40x40x1728: 36 blocks of 432 ordinates 54 us,
+// 576 of 27 19 us). From 128 blocks on it does not pay (100x100x1728: 196
+// blocks 72 us, 1568 blocks 79 us and a launch to add them). 1 in FP32-mixed
+// form (its sums are rounded in groups of eight ordinates, in order) and with
+// transport-face HoT (its face sums are formed in the same blocks).
+int moment_split(const PlanDev &P);
 int moment_tiles_of(int nx, int ny, int mt);
 void prepare_synth(size_t coarse_lds);      // kernel attribute for the LDS size
 void launch_source(const SynthSet &S, hipStream_t s);          // src from phi

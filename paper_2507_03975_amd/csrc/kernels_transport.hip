@@ -52,6 +52,7 @@ struct TArgs {
   const double *bnd;
   double *phih, *Fx, *Fy, *bflux;
   double *mom_part;
+  int mom_split;     // partials per quadrant (moment_split)
   const double *cellq, *dynq;
   double *rowbuf;
   const double *sdq;
@@ -82,6 +83,7 @@ TArgs make_args(const PlanDev &P) {
   a.cE = P.cE; a.cW = P.cW; a.cN = P.cN; a.cS = P.cS;
   a.bnd = P.bnd; a.phih = P.phih; a.Fx = P.Fx; a.Fy = P.Fy; a.bflux = P.bflux;
   a.mom_part = P.mom_part;
+  a.mom_split = P.mom_split;
   a.cellq = P.cellq; a.dynq = P.dynq; a.rowbuf = P.rowbuf;
   a.sdq = P.sdq; a.sdq_f = P.sdq_f; a.w_f = P.w_f; a.rtiles = P.rtiles; a.n_rtiles = P.n_rtiles;
   a.dso = P.dso;
@@ -1468,7 +1470,8 @@ __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, cons
 
 template <typename T, int kMT>
 __device__ __forceinline__ void moments_tile(const TArgs &a, double *part, double *ftp,
-                                             const int tile, const int q) {
+                                             const int tile, const int q, const int z = 0,
+                                             const int ns = 1) {
   constexpr int kMC = kMT * kMT / 256;
   static_assert(kMC * 256 == kMT * kMT, "whole cells per thread");
   __shared__ double sm[3][kMT * kMT];
@@ -1497,7 +1500,11 @@ __device__ __forceinline__ void moments_tile(const TArgs &a, double *part, doubl
   typedef const __attribute__((address_space(4))) double cdouble;
   cdouble *W = (cdouble *)a.w, *WM = (cdouble *)a.wmu, *WE = (cdouble *)a.weta;
   double s0[kMC], sx[kMC], sy[kMC];
-  const int kb = a.qoff[q], ke = a.qoff[q + 1];
+  // ordinates of part z of the quadrant, whole groups of eight but the last
+  const int per = ns == 1 ? a.qoff[q + 1] - a.qoff[q]
+                          : ((a.qoff[q + 1] - a.qoff[q] + ns - 1) / ns + 7) / 8 * 8;
+  const int kb = min(a.qoff[q] + z * per, a.qoff[q + 1]), ke = min(kb + per, a.qoff[q + 1]);
+  part += (size_t)(12 * z) * N;
   if constexpr (sizeof(T) == 4) {
     // FP32-mixed form: the stored deviations are summed in FP32, each group
     // of eight ordinates as a balanced tree and the groups in order (the
@@ -1659,14 +1666,15 @@ __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, cons
 // on XCD b % 8 and takes tile (b % 8) ts + b / 8, none past the grid.
 __device__ inline int xcd_tile(int b, int ts) { return (b & 7) * ts + (b >> 3); }
 
-// Moment partials: block (tile slot, quadrant); the quadrant-0 blocks also
-// sum src^2 over the tile's blocks of 256 cells (src2_tile).
+// Moment partials: block (tile slot, quadrant, part of its ordinates); the
+// first blocks of quadrant 0 also sum src^2 over the tile's blocks of 256
+// cells (src2_tile).
 template <typename T, int MT>
 __global__ void k_moments_q(TArgs a, double *part, int ntile, int ts) {
   const int tile = xcd_tile(blockIdx.x, ts);
   if (tile >= ntile || (blockIdx.x >> 3) >= ts) return;
-  if (blockIdx.y == 0) src2_tile<MT>(a, tile);
-  moments_tile<T, MT>(a, part, nullptr, tile, blockIdx.y);
+  if (blockIdx.y == 0 && blockIdx.z == 0) src2_tile<MT>(a, tile);
+  moments_tile<T, MT>(a, part, nullptr, tile, blockIdx.y, blockIdx.z, a.mom_split);
 }
 
 // Batched launches: bt maps block -> (problem, tile of that problem, or -1:
@@ -1682,35 +1690,48 @@ __global__ void k_moments_q_b(const TArgs *tas, const int2 *bt) {
   moments_tile<T, kBatchMT>(a, a.mom_part, nullptr, v.y, blockIdx.y);
 }
 
-__device__ __forceinline__ void moments_combine(const TArgs &a, const double *part, const int c) {
+// One of the three moments (f: phi, Fx, Fy) of cell c from its partials: per
+// quadrant the parts in order, then the quadrants in order, the parts' loads
+// four at a time.
+__device__ __forceinline__ void moments_combine(const TArgs &a, const double *part, const int c,
+                                                const int f, const int ns) {
   const int f1 = a.state[1];   // tested after the loads
   if (c >= a.N) return;
-  double v[12];
+  const size_t N = a.N;
+  const double *p = part + f * N + c;
+  double v[4] = {};
+  int z = 0;
+  for (; z + 4 <= ns; z += 4) {
+    double u[4][4];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) v[k] = part[(size_t)k * a.N + c];
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) u[m][q] = p[(12 * (size_t)(z + m) + 3 * q) * N];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += u[m][q];
+  }
+  for (; z < ns; ++z)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] += p[(12 * (size_t)z + 3 * q) * N];
   const double ph = a.fp32 ? a.phi[c] : 0.0;
   if (f1 != 0) return;
-  double s0 = 0, sx = 0, sy = 0;
-  for (int q = 0; q < 4; ++q) {
-    s0 += v[3 * q];
-    sx += v[3 * q + 1];
-    sy += v[3 * q + 2];
-  }
-  if (a.fp32) {                               // I^{m+1/2} = Itilde + phi^m/(4 pi)
-    const double sub = ph / kFourPi;
-    s0 += sub * a.sw; sx += sub * a.swm; sy += sub * a.swe;
-  }
-  a.phih[c] = s0; a.Fx[c] = sx; a.Fy[c] = sy;
+  double s = 0;
+  for (int q = 0; q < 4; ++q) s += v[q];
+  if (a.fp32)                                 // I^{m+1/2} = Itilde + phi^m/(4 pi)
+    s += ph / kFourPi * (f == 0 ? a.sw : f == 1 ? a.swm : a.swe);
+  (f == 0 ? a.phih : f == 1 ? a.Fx : a.Fy)[c] = s;
 }
 
 __global__ void k_moments_combine(TArgs a, const double *part) {
-  moments_combine(a, part, blockIdx.x * blockDim.x + threadIdx.x);
+  moments_combine(a, part, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, a.mom_split);
 }
 
 __global__ void k_moments_combine_b(const TArgs *tas, const int2 *bt) {
   const int2 v = bt[blockIdx.x];
   const TArgs &a = tas[v.x];
-  moments_combine(a, a.mom_part, v.y * blockDim.x + threadIdx.x);
+  moments_combine(a, a.mom_part, v.y * blockDim.x + threadIdx.x, blockIdx.y, 1);
 }
 
 // Wall face f: its side (0 W, 1 E, 2 S, 3 N) and position along it, and
@@ -1740,7 +1761,7 @@ __device__ __forceinline__ double face_term(const TArgs &a, const int f, const i
     const long long base = (long long)kk * a.N;
     const double *SUB = a.dynq + ((size_t)q * 3 + 2) * a.N;
     auto ld = [&](int x, int y) {
-      const long long o = dg_idx(x, y, a.nx, a.ny);
+      const int o = dg_row0(x + y, a.nx, a.ny) + y;
       if (a.fp32) return (double)Iout_of<float>(a)[base + o] + SUB[o];
       return Iout_of<double>(a)[base + o];
     };
@@ -1780,11 +1801,11 @@ __global__ void k_moments_q_bflux(TArgs a, double *part, int nbf8, int ntile, in
     if (f < a.nbf) boundary_flux_wave(a, f);
     return;
   }
-  const int q = b / (8 * ts), r = b - q * 8 * ts;
+  const int qz = b / (8 * ts), r = b - qz * 8 * ts;
   const int tile = xcd_tile(r, ts);
   if (tile >= ntile || (r >> 3) >= ts) return;
-  if (q == 0) src2_tile<MT>(a, tile);
-  moments_tile<T, MT>(a, part, ftp, tile, q);
+  if (qz == 0) src2_tile<MT>(a, tile);
+  moments_tile<T, MT>(a, part, ftp, tile, qz & 3, qz >> 2, a.mom_split);
 }
 
 // Batched wall faces: four (problem, face) entries per workgroup, a wave each.
@@ -1946,6 +1967,15 @@ int residual_pairs(const PlanDev &P) {
 
 int moment_tile_size(int nx, int ny) { return (long long)nx * ny >= (1 << 18) ? 32 : 16; }
 int moment_tile_size_batch() { return kBatchMT; }
+int moment_split(const PlanDev &P) {
+  if (P.precision == GSIS_FP32_MIXED || P.hot_face) return 1;
+  const int mt = moment_tile_size(P.nx, P.ny);
+  const long long blocks = 4LL * moment_tiles_of(P.nx, P.ny, mt);
+  int ns = 1;
+  if (blocks < 128)
+    while (blocks * ns < 1024 && P.K / 4 / (2 * ns) >= 24) ns *= 2;
+  return ns;
+}
 int moment_tiles_of(int nx, int ny, int mt) {
   return ((nx + mt - 1) / mt) * ((ny + mt - 1) / mt);
 }
@@ -2068,15 +2098,17 @@ template <typename T, int MT>
 void launch_moments_t(const TArgs &a, const PlanDev &P, hipStream_t s, bool bflux) {
   const int ntile = moment_tiles_of(P.nx, P.ny, MT);
   const int ts = (ntile + 7) / 8;   // tiles per XCD
-  if (bflux) {   // the combine follows in the HoT kernel
+  if (bflux) {   // the combine follows in the HoT kernel (undivided quadrants)
     const int nbf8 = ((P.nbf + 3) / 4 + 7) / 8 * 8;
-    hipLaunchKernelGGL((k_moments_q_bflux<T, MT>), dim3(nbf8 + 4 * 8 * ts), dim3(256), 0, s, a,
+    hipLaunchKernelGGL((k_moments_q_bflux<T, MT>), dim3(nbf8 + 4 * 8 * ts * P.mom_split), dim3(256), 0,
+                       s, a,
                        P.mom_part, nbf8, ntile, ts, P.hot_face ? P.ftp : nullptr);
-    return;
+    if (P.mom_split == 1) return;
+  } else {
+    hipLaunchKernelGGL((k_moments_q<T, MT>), dim3(8 * ts, 4, P.mom_split), dim3(256), 0, s, a,
+                       P.mom_part, ntile, ts);
   }
-  hipLaunchKernelGGL((k_moments_q<T, MT>), dim3(8 * ts, 4), dim3(256), 0, s, a, P.mom_part, ntile,
-                     ts);
-  hipLaunchKernelGGL(k_moments_combine, dim3((P.N + 255) / 256), dim3(256), 0, s, a,
+  hipLaunchKernelGGL(k_moments_combine, dim3((P.N + 255) / 256, 3), dim3(256), 0, s, a,
                      (const double *)P.mom_part);
 }
 
@@ -2099,7 +2131,7 @@ void launch_moments_batch(const void *targs, const int2 *bt_cell, int nb_cell,
     hipLaunchKernelGGL(k_moments_q_b<float>, dim3(nb_tile, 4), dim3(256), 0, s, ta, bt_tile);
   else
     hipLaunchKernelGGL(k_moments_q_b<double>, dim3(nb_tile, 4), dim3(256), 0, s, ta, bt_tile);
-  hipLaunchKernelGGL(k_moments_combine_b, dim3(nb_cell), dim3(256), 0, s, ta, bt_cell);
+  hipLaunchKernelGGL(k_moments_combine_b, dim3(nb_cell, 3), dim3(256), 0, s, ta, bt_cell);
 }
 
 void launch_boundary_flux_batch(const void *targs, const int2 *bt_face, int nb_face,
