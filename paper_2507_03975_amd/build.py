@@ -29,7 +29,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
           "-I" + os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function"]
 
 SOURCES = ["capi.cpp", "batch.cpp", "adjoint.cpp", "kernels_transport.hip",
-           "kernels_synth.hip", "kernels_adjoint.hip"]
+           "kernels_synth.hip", "kernels_adjoint.hip", "kernels_setup.hip"]
 
 
 def _compile(src):

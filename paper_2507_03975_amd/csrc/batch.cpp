@@ -327,7 +327,8 @@ void enqueue_iteration(gsis_batch *b, bool capture) {
 gsis_status reset_all(gsis_batch *b) {
   gsis_status st;
   for (gsis_plan *pl : b->subs)
-    if ((st = gsis_plan_reset(pl))) return st;
+    if ((st = plan_reset_enqueue(pl))) return st;
+  HIPCHK(b->ctx, hipStreamSynchronize(b->stream));
   if (b->cg_iters0 > 0) {
     b->cg_iters = b->cg_iters0;
     b->S.synth_max_iter = b->cg_iters0;

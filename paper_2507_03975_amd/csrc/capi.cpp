@@ -89,11 +89,11 @@ gsis_status fetch(gsis_ctx *ctx, const double *src, size_t n, int dev, std::vect
   return GSIS_OK;
 }
 
+// Everything about the problem but its cell and boundary fields, which are
+// checked on the device (check_fields).
 gsis_status check_problem(gsis_ctx *ctx, const gsis_problem *p, const gsis_options *o,
                           std::vector<double> &mu, std::vector<double> &eta,
-                          std::vector<double> &w, std::vector<double> &sa,
-                          std::vector<double> &ss, std::vector<double> &q,
-                          std::vector<double> &bnd) {
+                          std::vector<double> &w) {
   if (!p) return fail(ctx, GSIS_E_INVALID_ARG, "problem is NULL");
   if (!o) return fail(ctx, GSIS_E_INVALID_ARG, "options is NULL");
   if (p->nx < 1 || p->ny < 1)
@@ -127,14 +127,14 @@ gsis_status check_problem(gsis_ctx *ctx, const gsis_problem *p, const gsis_optio
   if (o->synth_form == 1 && o->synth_sub < 1)
     return fail(ctx, GSIS_E_INVALID_ARG, "options.synth_sub must be >= 1");
   const int dev = o->device_ptrs;
-  const size_t N = (size_t)p->nx * p->ny, K = p->K;
+  const size_t K = p->K;
   gsis_status st;
   if ((st = fetch(ctx, p->mu, K, dev, mu, "mu")) || (st = fetch(ctx, p->eta, K, dev, eta, "eta")) ||
-      (st = fetch(ctx, p->w, K, dev, w, "w")) ||
-      (st = fetch(ctx, p->sigma_a, N, dev, sa, "sigma_a")) ||
-      (st = fetch(ctx, p->sigma_s, N, dev, ss, "sigma_s")) ||
-      (st = fetch(ctx, p->q, N, dev, q, "q")))
+      (st = fetch(ctx, p->w, K, dev, w, "w")))
     return st;
+  if (!p->sigma_a) return fail(ctx, GSIS_E_INVALID_ARG, "sigma_a is NULL");
+  if (!p->sigma_s) return fail(ctx, GSIS_E_INVALID_ARG, "sigma_s is NULL");
+  if (!p->q) return fail(ctx, GSIS_E_INVALID_ARG, "q is NULL");
   double wsum = 0;
   for (size_t k = 0; k < K; ++k) {
     if (!std::isfinite(mu[k]) || !std::isfinite(eta[k]) || !std::isfinite(w[k]))
@@ -146,24 +146,16 @@ gsis_status check_problem(gsis_ctx *ctx, const gsis_problem *p, const gsis_optio
   }
   if (std::fabs(wsum - kFourPi) > 1e-12 * kFourPi)
     return fail(ctx, GSIS_E_INVALID_ARG, "sum(w) = %.17g, expected 4*pi", wsum);
-  for (size_t c = 0; c < N; ++c) {
-    if (!std::isfinite(sa[c]) || sa[c] < 0)
-      return fail(ctx, GSIS_E_INVALID_ARG, "sigma_a[%zu] must be finite and >= 0", c);
-    if (!std::isfinite(ss[c]) || ss[c] < 0)
-      return fail(ctx, GSIS_E_INVALID_ARG, "sigma_s[%zu] must be finite and >= 0", c);
-    if (!(sa[c] + ss[c] > 0))
-      return fail(ctx, GSIS_E_INVALID_ARG, "sigma_a[%zu] + sigma_s[%zu] must be > 0", c, c);
-    if (!std::isfinite(q[c])) return fail(ctx, GSIS_E_INVALID_ARG, "q[%zu] is not finite", c);
-  }
-  const size_t nbf = 2 * ((size_t)p->nx + p->ny);
-  if (p->bnd_in) {
-    if ((st = fetch(ctx, p->bnd_in, nbf * K, dev, bnd, "bnd_in"))) return st;
-    for (size_t t = 0; t < nbf * K; ++t)
-      if (!std::isfinite(bnd[t]))
-        return fail(ctx, GSIS_E_INVALID_ARG, "bnd_in[%zu][%zu] is not finite", t / K, t % K);
-  } else {
-    bnd.assign(nbf * K, 0.0);
-  }
+  return GSIS_OK;
+}
+
+// Copies n doubles of the caller (host or device) to the device on s.
+gsis_status fetch_dev(gsis_plan *pl, const double *src, double *dst, size_t n, const char *name) {
+  const hipError_t e =
+      hipMemcpyAsync(dst, src, n * sizeof(double),
+                     pl->device_ptrs ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, pl->stream);
+  if (e != hipSuccess)
+    return fail(pl->ctx, GSIS_E_DEVICE, "reading %s: %s", name, hipGetErrorString(e));
   return GSIS_OK;
 }
 
@@ -197,20 +189,25 @@ bool dense_spd_inverse(int n, std::vector<double> &A) {
       L[(size_t)i * n + j] = t / d;
     }
   }
-  // columns of A^{-1}: solve L L^T x = e_c
-  std::vector<double> x(n);
-  for (int c = 0; c < n; ++c) {
-    for (int i = 0; i < n; ++i) {
-      double t = (i == c) ? 1.0 : 0.0;
-      for (int k = 0; k < i; ++k) t -= L[(size_t)i * n + k] * x[k];
-      x[i] = t / L[(size_t)i * n + i];
+  // A^{-1}: solve L L^T X = 1, all columns side by side
+  for (int i = 0; i < n; ++i) {
+    double *x = &A[(size_t)i * n];
+    for (int c = 0; c < n; ++c) x[c] = i == c ? 1.0 : 0.0;
+    for (int k = 0; k < i; ++k) {
+      const double l = L[(size_t)i * n + k], *y = &A[(size_t)k * n];
+      for (int c = 0; c < n; ++c) x[c] -= l * y[c];
     }
-    for (int i = n - 1; i >= 0; --i) {
-      double t = x[i];
-      for (int k = i + 1; k < n; ++k) t -= L[(size_t)k * n + i] * x[k];
-      x[i] = t / L[(size_t)i * n + i];
+    const double d = L[(size_t)i * n + i];
+    for (int c = 0; c < n; ++c) x[c] /= d;
+  }
+  for (int i = n - 1; i >= 0; --i) {
+    double *x = &A[(size_t)i * n];
+    for (int k = i + 1; k < n; ++k) {
+      const double l = L[(size_t)k * n + i], *y = &A[(size_t)k * n];
+      for (int c = 0; c < n; ++c) x[c] -= l * y[c];
     }
-    for (int i = 0; i < n; ++i) A[(size_t)i * n + c] = x[i];
+    const double d = L[(size_t)i * n + i];
+    for (int c = 0; c < n; ++c) x[c] /= d;
   }
   return true;
 }
@@ -218,73 +215,104 @@ bool dense_spd_inverse(int n, std::vector<double> &A) {
 
 }  // namespace
 
-// Multigrid hierarchy of the level-0 synthetic operator hl[0] (Galerkin
+namespace {
+
+gsis_status alloc_level(gsis_plan *pl, MGLevel &L) {
+  const size_t n = (size_t)L.nx * L.ny;
+  gsis_status st;
+  if ((st = dalloc(pl, &L.diag, 3 * n))) return st;   // the operator in one piece
+  L.ax = L.diag + n;
+  L.ay = L.diag + 2 * n;
+  if ((st = dalloc(pl, &L.x, n)) || (st = dalloc(pl, &L.b, n)) || (st = dalloc(pl, &L.r, n)))
+    return st;
+  return GSIS_OK;
+}
+
+// Aggregates of level F: 2x2, or 2x1 / 1x2 when the couplings in one
+// direction are much weaker than in the other (then merging across the weak
+// direction would leave error the point smoother cannot reach), by the
+// geometric means of the couplings. The device's sums of logarithms decide
+// unless they are so close to the threshold that their rounding could; then
+// the sums are formed on the host, cell by cell (a uniform medium on cells of
+// aspect ratio 2 sits on the threshold).
+gsis_status choose_aggregates(gsis_plan *pl, MGLevel &F, double *part) {
+  gsis_ctx *ctx = pl->ctx;
+  const long mx = (long)(F.nx - 1) * F.ny, my = (long)F.nx * (F.ny - 1);
+  const int nb = launch_log_sums(F, part, pl->stream);
+  std::vector<double> h(2 * (size_t)nb);
+  HIPCHK(ctx, hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost,
+                             pl->stream));
+  HIPCHK(ctx, hipStreamSynchronize(pl->stream));
+  double lx = 0, ly = 0;
+  for (int b = 0; b < nb; ++b) { lx += h[2 * b]; ly += h[2 * b + 1]; }
+  if (mx && my) {
+    const double r = lx / mx - ly / my, thr = std::log(0.25);
+    if (!(std::fabs(r - thr) > 1e-9 && std::fabs(-r - thr) > 1e-9)) {
+      const size_t n = (size_t)F.nx * F.ny;
+      std::vector<double> a(2 * n);
+      HIPCHK(ctx, hipMemcpyAsync(a.data(), F.ax, 2 * n * sizeof(double), hipMemcpyDeviceToHost,
+                                 pl->stream));
+      HIPCHK(ctx, hipStreamSynchronize(pl->stream));
+      lx = ly = 0;
+      for (int j = 0; j < F.ny; ++j)
+        for (int i = 0; i < F.nx; ++i) {
+          const size_t c = (size_t)j * F.nx + i;
+          if (i + 1 < F.nx) lx += std::log(a[c]);
+          if (j + 1 < F.ny) ly += std::log(a[n + c]);
+        }
+    }
+  }
+  const double gx = mx ? std::exp(lx / mx) : 0.0, gy = my ? std::exp(ly / my) : 0.0;
+  F.fx = (F.nx > 1 && gx >= 0.25 * gy) ? 2 : 1;
+  F.fy = (F.ny > 1 && gy >= 0.25 * gx) ? 2 : 1;
+  return GSIS_OK;
+}
+
+// Multigrid hierarchy of the level-0 synthetic operator P.mg[0] (Galerkin
 // coarsening) and the device state of a synthetic solve on P: levels, dense
 // coarsest inverse, CG vectors, block partials and scalars. P.N must be set.
-gsis_status setup_synth(gsis_plan *pl, PlanDev &P, std::vector<HostLevel> &hl) {
-  // Galerkin coarsening. Aggregates are 2x2, or 2x1 / 1x2 when the
-  // couplings in one direction are much weaker than in the other (then
-  // merging across the weak direction would leave error the point smoother
-  // cannot reach).
+gsis_status setup_synth(gsis_plan *pl, PlanDev &P) {
+  gsis_ctx *ctx = pl->ctx;
+  gsis_status st;
   const int kCoarseMax = 64;   // dense inverse of the coarsest level: at most 64 x 64
-  while ((long)hl.back().nx * hl.back().ny > kCoarseMax && (hl.back().nx > 1 || hl.back().ny > 1)) {
-    HostLevel &F = hl.back();
-    double lx = 0, ly = 0;
-    long mx = 0, my = 0;
-    for (int j = 0; j < F.ny; ++j)
-      for (int i = 0; i < F.nx; ++i) {
-        const int c = j * F.nx + i;
-        if (i + 1 < F.nx) { lx += std::log(F.ax[c]); ++mx; }
-        if (j + 1 < F.ny) { ly += std::log(F.ay[c]); ++my; }
-      }
-    const double gx = mx ? std::exp(lx / mx) : 0.0, gy = my ? std::exp(ly / my) : 0.0;
-    F.fx = (F.nx > 1 && gx >= 0.25 * gy) ? 2 : 1;
-    F.fy = (F.ny > 1 && gy >= 0.25 * gx) ? 2 : 1;
-    HostLevel C;
+  double *part = nullptr;
+  if ((st = dalloc(pl, &part, 2 * (size_t)kLogBlocks))) return st;
+  while ((long)P.mg.back().nx * P.mg.back().ny > kCoarseMax &&
+         (P.mg.back().nx > 1 || P.mg.back().ny > 1)) {
+    if ((st = choose_aggregates(pl, P.mg.back(), part))) return st;
+    const MGLevel F = P.mg.back();
+    MGLevel C;
     C.nx = (F.nx + F.fx - 1) / F.fx;
     C.ny = (F.ny + F.fy - 1) / F.fy;
-    const int Nc = C.nx * C.ny;
-    C.diag.assign(Nc, 0.0); C.ax.assign(Nc, 0.0); C.ay.assign(Nc, 0.0);
-    for (int j = 0; j < F.ny; ++j)
-      for (int i = 0; i < F.nx; ++i) {
-        const int c = j * F.nx + i;
-        const int Ci = i / F.fx, Cj = j / F.fy;
-        const int Cc = Cj * C.nx + Ci;
-        C.diag[Cc] += F.diag[c];
-        if (i + 1 < F.nx) {
-          const int Ci2 = (i + 1) / F.fx;
-          if (Ci2 == Ci) C.diag[Cc] -= 2.0 * F.ax[c];
-          else C.ax[Cc] += F.ax[c];
-        }
-        if (j + 1 < F.ny) {
-          const int Cj2 = (j + 1) / F.fy;
-          if (Cj2 == Cj) C.diag[Cc] -= 2.0 * F.ay[c];
-          else C.ay[Cc] += F.ay[c];
-        }
-      }
-    hl.push_back(std::move(C));
+    if ((st = alloc_level(pl, C))) return st;
+    launch_coarsen(F, C, pl->stream);
+    P.mg.push_back(C);
+    if (P.mg.size() > (size_t)kMaxLevels)
+      return fail(ctx, GSIS_E_INVALID_ARG, "multigrid hierarchy deeper than %d levels", kMaxLevels);
   }
   // dense inverse of the coarsest level
-  const HostLevel &Lc = hl.back();
+  const MGLevel &Lc = P.mg.back();
   const int nc = Lc.nx * Lc.ny;
-  std::vector<double> dense((size_t)nc * nc, 0.0);
+  std::vector<double> op(3 * (size_t)nc), dense((size_t)nc * nc, 0.0);
+  HIPCHK(ctx, hipMemcpyAsync(op.data(), Lc.diag, op.size() * sizeof(double), hipMemcpyDeviceToHost,
+                             pl->stream));
+  HIPCHK(ctx, hipStreamSynchronize(pl->stream));
   for (int j = 0; j < Lc.ny; ++j)
     for (int i = 0; i < Lc.nx; ++i) {
       const int c = j * Lc.nx + i;
-      dense[(size_t)c * nc + c] = Lc.diag[c];
+      dense[(size_t)c * nc + c] = op[c];
       if (i + 1 < Lc.nx) {
-        dense[(size_t)c * nc + c + 1] = -Lc.ax[c];
-        dense[(size_t)(c + 1) * nc + c] = -Lc.ax[c];
+        dense[(size_t)c * nc + c + 1] = -op[nc + c];
+        dense[(size_t)(c + 1) * nc + c] = -op[nc + c];
       }
       if (j + 1 < Lc.ny) {
-        dense[(size_t)c * nc + c + Lc.nx] = -Lc.ay[c];
-        dense[(size_t)(c + Lc.nx) * nc + c] = -Lc.ay[c];
+        dense[(size_t)c * nc + c + Lc.nx] = -op[2 * nc + c];
+        dense[(size_t)(c + Lc.nx) * nc + c] = -op[2 * nc + c];
       }
     }
   if (!dense_spd_inverse(nc, dense))
-    return fail(pl->ctx, GSIS_E_INVALID_ARG, "synthetic operator is not positive definite");
+    return fail(ctx, GSIS_E_INVALID_ARG, "synthetic operator is not positive definite");
 
-  gsis_status st;
   const int N = P.N;
   if ((st = dalloc(pl, &P.cg_r, N)) || (st = dalloc(pl, &P.cg_r2, N)) ||
       (st = dalloc(pl, &P.cg_z, N)) ||
@@ -301,20 +329,11 @@ gsis_status setup_synth(gsis_plan *pl, PlanDev &P, std::vector<HostLevel> &hl) {
   P.red_blocks = (N + 255) / 256;
   const size_t ntp = std::max<size_t>(tiles_of(P.nx, P.ny), P.red_blocks);
   if ((st = dalloc(pl, &P.red, 2 * (size_t)P.red_blocks + 3 * ntp + 2))) return st;
-  P.mg.resize(hl.size());
-  for (size_t l = 0; l < hl.size(); ++l) {
-    MGLevel &L = P.mg[l];
-    L.nx = hl[l].nx; L.ny = hl[l].ny; L.fx = hl[l].fx; L.fy = hl[l].fy;
-    const size_t n = (size_t)L.nx * L.ny;
-    if ((st = upload(pl, &L.diag, hl[l].diag)) || (st = upload(pl, &L.ax, hl[l].ax)) ||
-        (st = upload(pl, &L.ay, hl[l].ay)) || (st = dalloc(pl, &L.x, n)) ||
-        (st = dalloc(pl, &L.b, n)) || (st = dalloc(pl, &L.r, n)))
-      return st;
-  }
   P.coarse_n = nc;
-  if ((st = upload(pl, &P.coarse_inv, dense))) return st;
-  return GSIS_OK;
+  return upload(pl, &P.coarse_inv, dense);
 }
+
+}  // namespace
 
 // Launch set of a single plan: its synthetic-step descriptor on the device
 // and block counts per level (no block tables). Needs every array of P.
@@ -366,10 +385,9 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
   if (!ctx) return fail(nullptr, GSIS_E_INVALID_ARG, "ctx is NULL");
   if (!out) return fail(ctx, GSIS_E_INVALID_ARG, "out is NULL");
   *out = nullptr;
-  std::vector<double> mu, eta, w, sa, ss, q, bnd;
-  gsis_status st = check_problem(ctx, p, o, mu, eta, w, sa, ss, q, bnd);
+  std::vector<double> mu, eta, w;
+  gsis_status st = check_problem(ctx, p, o, mu, eta, w);
   if (st) return st;
-  std::vector<double> cvh, T0h;
   if (mt) {
     if (!(mt->c > 0) || !std::isfinite(mt->c))
       return fail(ctx, GSIS_E_INVALID_ARG, "material.c must be finite and > 0");
@@ -382,16 +400,8 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       return fail(ctx, GSIS_E_UNSUPPORTED, "the time-dependent form runs in FP64 only");
     if (o->synth_form != 0)
       return fail(ctx, GSIS_E_UNSUPPORTED, "the time-dependent form needs options.synth_form 0");
-    const size_t N = (size_t)p->nx * p->ny;
-    if ((st = fetch(ctx, mt->cv, N, o->device_ptrs, cvh, "material.cv")) ||
-        (st = fetch(ctx, mt->T0, N, o->device_ptrs, T0h, "material.T0")))
-      return st;
-    for (size_t c = 0; c < N; ++c) {
-      if (!(cvh[c] > 0) || !std::isfinite(cvh[c]))
-        return fail(ctx, GSIS_E_INVALID_ARG, "material.cv[%zu] must be finite and > 0", c);
-      if (!(T0h[c] >= 0) || !std::isfinite(T0h[c]))
-        return fail(ctx, GSIS_E_INVALID_ARG, "material.T0[%zu] must be finite and >= 0", c);
-    }
+    if (!mt->cv) return fail(ctx, GSIS_E_INVALID_ARG, "material.cv is NULL");
+    if (!mt->T0) return fail(ctx, GSIS_E_INVALID_ARG, "material.T0 is NULL");
   }
   if (o->method == GSIS_GSIS && o->hot_face == GSIS_HOT_TRANSPORT && o->synth_form != 0)
     return fail(ctx, GSIS_E_UNSUPPORTED,
@@ -422,7 +432,6 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     P.tdiag = 1.0 / (mt->c * mt->dt);
     P.ca = mt->a * mt->c;
     P.dt = mt->dt;
-    pl->T0_host = T0h;
   }
   auto bail = [&](gsis_status s) {
     gsis_plan_destroy(pl);
@@ -457,103 +466,6 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
   P.swe = pl->sweta;
   const bool f32 = P.precision == GSIS_FP32_MIXED;
 
-  // -- per-cell coefficients
-  std::vector<double> st_(N), cE(N), cW(N), cN(N), cS(N);
-  for (int c = 0; c < N; ++c) st_[c] = sa[c] + ss[c];
-  for (int j = 0; j < ny; ++j)
-    for (int i = 0; i < nx; ++i) {
-      const int c = j * nx + i;
-      // distance from x_c to the (shifted) neighbour point along the normal
-      // (Eq. shifted_j): half a cell to the face, then sigma_nb/sigma_c times
-      // the half cell beyond it; plain least squares uses the centre.
-      auto dist = [&](int nb, double h) {
-        if (nb < 0) return 0.0;
-        return P.alsm ? 0.5 * h + (st_[nb] / st_[c]) * (0.5 * h) : h;
-      };
-      const double dE = dist(i + 1 < nx ? c + 1 : -1, p->dx);
-      const double dW = dist(i > 0 ? c - 1 : -1, p->dx);
-      const double dN = dist(j + 1 < ny ? c + nx : -1, p->dy);
-      const double dS = dist(j > 0 ? c - nx : -1, p->dy);
-      const double mx = dE * dE + dW * dW, my = dN * dN + dS * dS;
-      cE[c] = mx > 0 ? dE / mx : 0.0;
-      cW[c] = mx > 0 ? dW / mx : 0.0;
-      cN[c] = my > 0 ? dN / my : 0.0;
-      cS[c] = my > 0 ? dS / my : 0.0;
-    }
-  // kappa per boundary face (Eqs. macro_bc_delta_flux, macro_bc_delta_flux2)
-  std::vector<double> kap(P.nbf);
-  for (int j = 0; j < ny; ++j) {
-    kap[j] = 2.0 / (3.0 * st_[j * nx] * p->dx) + 0.25;
-    kap[ny + j] = 2.0 / (3.0 * st_[j * nx + nx - 1] * p->dx) + 0.25;
-  }
-  for (int i = 0; i < nx; ++i) {
-    kap[2 * ny + i] = 2.0 / (3.0 * st_[i] * p->dy) + 0.25;
-    kap[2 * ny + nx + i] = 2.0 / (3.0 * st_[(ny - 1) * nx + i] * p->dy) + 0.25;
-  }
-  // D1 (Eqs. MSE_d_mtx1, elem_mtx_M, Gamma_ij_com2), multiplied by V
-  std::vector<HostLevel> hl(1);
-  hl[0].nx = nx; hl[0].ny = ny;
-  hl[0].diag.assign(N, 0.0); hl[0].ax.assign(N, 0.0); hl[0].ay.assign(N, 0.0);
-  for (int j = 0; j < ny; ++j)
-    for (int i = 0; i < nx; ++i) {
-      const int c = j * nx + i;
-      double d = P.V * sa[c];
-      if (i + 1 < nx) {
-        const double a = p->dy * 2.0 / (3.0 * (st_[c] * p->dx + st_[c + 1] * p->dx));
-        hl[0].ax[c] = a;
-      }
-      if (j + 1 < ny) {
-        const double a = p->dx * 2.0 / (3.0 * (st_[c] * p->dy + st_[c + nx] * p->dy));
-        hl[0].ay[c] = a;
-      }
-      if (i + 1 < nx) d += hl[0].ax[c]; else d += p->dy * kap[ny + j];
-      if (i > 0) d += hl[0].ax[c - 1]; else d += p->dy * kap[j];
-      if (j + 1 < ny) d += hl[0].ay[c]; else d += p->dx * kap[2 * ny + nx + i];
-      if (j > 0) d += hl[0].ay[c - nx]; else d += p->dx * kap[2 * ny + i];
-      hl[0].diag[c] = d + P.V * P.tdiag;   // 1/(c dt) of Eq. elem_mtx_M (td form)
-    }
-  // -- pseudo-time shift of the increment-solve diagonal (Eqs. cfl_pse,
-  // tau_pse, elem_main_shifted); |sigma_i r^L - sigma_j r^R| is
-  // (sigma_i h + sigma_j h) / 2 for the face-normal width h
-  std::vector<double> shift(N, 0.0);
-  {
-    const double dref = std::min(p->dx, p->dy);
-    for (int j = 0; j < ny; ++j)
-      for (int i = 0; i < nx; ++i) {
-        const int c = j * nx + i;
-        double sh = o->cfl_p > 0 ? 1.0 / (o->cfl_p * dref) : 0.0;
-        if (o->beta > 0) {
-          double m = 0.0;
-          if (i > 0) m = std::max(m, 0.5 * (st_[c] + st_[c - 1]) * p->dx);
-          if (i + 1 < nx) m = std::max(m, 0.5 * (st_[c] + st_[c + 1]) * p->dx);
-          if (j > 0) m = std::max(m, 0.5 * (st_[c] + st_[c - nx]) * p->dy);
-          if (j + 1 < ny) m = std::max(m, 0.5 * (st_[c] + st_[c + nx]) * p->dy);
-          sh += m / (o->beta * dref);
-        }
-        shift[c] = sh;
-      }
-  }
-
-  // -- per-quadrant coefficient records in each quadrant's mirrored frame
-  //    (cE, cW, cN, cS, sigma_t, sigma_t + pseudo-time shift)
-  std::vector<double> cellq((size_t)4 * N * 6, 0.0), sdq((size_t)4 * N, 0.0);
-  for (int qd = 0; qd < 4; ++qd)
-    for (int yl = 0; yl < ny; ++yl)
-      for (int xl = 0; xl < nx; ++xl) {
-        const int i = (qd & 1) ? nx - 1 - xl : xl, j = (qd & 2) ? ny - 1 - yl : yl;
-        const int c = j * nx + i;
-        double *r = &cellq[((size_t)qd * N + dg_idx(xl, yl, nx, ny)) * 6];
-        r[0] = (qd & 1) ? cW[c] : cE[c];
-        r[1] = (qd & 1) ? cE[c] : cW[c];
-        r[2] = (qd & 2) ? cS[c] : cN[c];
-        r[3] = (qd & 2) ? cN[c] : cS[c];
-        // the time-dependent form's 1/(c dt) joins sigma_t in the residual's
-        // -sigma_t I term and in the increment solve's diagonal (Eqs.
-        // RTE_d_res, elem_mtx)
-        r[4] = st_[c] + P.tdiag;
-        r[5] = st_[c] + P.tdiag + shift[c];
-        sdq[(size_t)qd * N + dg_idx(xl, yl, nx, ny)] = r[5];
-      }
   {
     // transport step: 0 residual kernel + recurrence, 3 pipelined (one
     // launch); 1 two-kernel reference and 2 fused wavefront sweep (tests
@@ -626,14 +538,144 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
   P.n_tres = P.sweep_impl == 3 ? K * P.pipe_parts * P.pipe_bands
                                : P.n_rtiles * residual_pairs(P);
 
-  // -- boundary intensities in the internal ordinate order
-  std::vector<double> bnd_int((size_t)P.nbf * K);
-  for (int f = 0; f < P.nbf; ++f)
-    for (int kk = 0; kk < K; ++kk) bnd_int[(size_t)f * K + kk] = bnd[(size_t)f * K + pl->perm[kk]];
+  // -- device arrays
+  Pack pack;
+  pack.add(&P.amu, amu);
+  pack.add(&P.aeta, aeta);
+  pack.add(&P.w, wv);
+  pack.add(&P.wmu, wmu);
+  pack.add(&P.weta, weta);
+  pack.add(&P.rtiles, rtiles);
+  pack.add(&P.dso, diag_row0_table(nx, ny));
+  if (f32) {
+    // w, w mu, w eta in FP32 for the moment sums of the deviations
+    std::vector<float> wf(3 * (size_t)K);
+    for (int kk = 0; kk < K; ++kk) {
+      wf[kk] = (float)wv[kk];
+      wf[K + kk] = (float)wmu[kk];
+      wf[2 * K + kk] = (float)weta[kk];
+    }
+    pack.add(&P.w_f, wf);
+  }
+  int *perm = nullptr;
+  unsigned long long *bad = nullptr;
+  pack.add(&perm, pl->perm);
+  pack.add(&bad, std::vector<unsigned long long>(3, ~0ull));
+  MGLevel L0;
+  L0.nx = nx;
+  L0.ny = ny;
+  const size_t nbk = (size_t)P.nbf * K;
+  if ((st = alloc_intensity(pl, 0, (size_t)N * K, f32)) ||
+      (st = alloc_intensity(pl, 1, (size_t)N * K, f32)) ||
+      (st = dalloc(pl, &P.R, P.sweep_impl == 1 ? (size_t)N * K : 1)) ||
+      (st = dalloc(pl, &P.cellq, (size_t)4 * N * 6)) || (st = dalloc(pl, &P.dynq, (size_t)4 * N * 3)) ||
+      (st = dalloc(pl, &P.rowbuf, (size_t)K * 3 * nx)) || (st = dalloc(pl, &P.sdq, (size_t)4 * N)) ||
+      (st = dalloc(pl, &P.sig_t, N)) || (st = dalloc(pl, &P.sig_a, N)) ||
+      (st = dalloc(pl, &P.sig_s, N)) || (st = dalloc(pl, &P.q, N)) ||
+      (st = dalloc(pl, &P.cE, N)) || (st = dalloc(pl, &P.cW, N)) ||
+      (st = dalloc(pl, &P.cN, N)) || (st = dalloc(pl, &P.cS, N)) ||
+      (st = dalloc(pl, &P.src, N)) || (st = dalloc(pl, &P.phi, N)) ||
+      (st = dalloc(pl, &P.phih, N)) || (st = dalloc(pl, &P.Fx, N)) ||
+      (st = dalloc(pl, &P.mom_part, (size_t)12 * P.mom_split * N)) ||
+      (st = dalloc(pl, &P.Fy, N)) || (st = dalloc(pl, &P.delta, N)) ||
+      (st = dalloc(pl, &P.hx, N)) || (st = dalloc(pl, &P.hy, N)) ||
+      (st = dalloc(pl, &P.rhs, N)) || (st = dalloc(pl, &P.bnd, nbk)) ||
+      (st = dalloc(pl, &P.bflux, P.nbf)) || (st = dalloc(pl, &P.kappa, P.nbf)) ||
+      (st = dalloc(pl, &P.err_hist, o->max_iter)) ||
+      (st = dalloc(pl, &P.tres_hist, o->max_iter)) ||
+      (st = dalloc(pl, &P.tres_part, tres_slots(P))) ||
+      (st = dalloc(pl, &P.src2_part, (size_t)(N + 255) / 256)) ||
+      (st = dalloc(pl, &P.state, 5)) || (st = dalloc(pl, &P.last_err, 2)) ||
+      (st = dalloc(pl, &P.err_parts, 2 * (size_t)((N + 255) / 256) + 2)) ||
+      (st = alloc_level(pl, L0)))
+    return bail(st);
+  if (hand_parts(P) > 1 && (st = dalloc(pl, &P.hand, (size_t)K * (hand_parts(P) - 1) * nx)))
+    return bail(st);
+  if (f32 && ((st = dalloc(pl, &P.sdq_f, (size_t)4 * N)) || (st = dalloc(pl, &P.base, N))))
+    return bail(st);
+  if (!f32) P.base = P.delta;
+  if (P.method == GSIS_GSIS && P.hot_face == GSIS_HOT_TRANSPORT &&
+      (st = dalloc(pl, &P.ftp, (size_t)8 * N)))
+    return bail(st);
+  if (P.td &&
+      ((st = dalloc(pl, &P.cv, N)) || (st = dalloc(pl, &P.T0, N)) || (st = dalloc(pl, &P.Tm, N)) ||
+       (st = dalloc(pl, &P.Tn, N)) || (st = dalloc(pl, &P.Tsub0, N)) ||
+       (st = dalloc(pl, &P.Tsub1, N)) || (st = dalloc(pl, &P.rho_n, N)) ||
+       (st = dalloc(pl, &P.err_parts_T, 2 * (size_t)((N + 255) / 256) + 2)) ||
+       (st = dalloc(pl, &P.In, (size_t)N * K))))
+    return bail(st);
+  P.mg.assign(1, L0);
 
+  // -- the caller's fields, checked on the device. Work the caller has on the
+  // default stream comes first, as it would for a blocking copy
+  hipStream_t s = pl->stream;
+  if (hipStreamSynchronize(nullptr) != hipSuccess)
+    return bail(fail(ctx, GSIS_E_DEVICE, "hipStreamSynchronize failed"));
+  if ((st = pack.commit(pl)) || (st = fetch_dev(pl, p->sigma_a, P.sig_a, N, "sigma_a")) ||
+      (st = fetch_dev(pl, p->sigma_s, P.sig_s, N, "sigma_s")) ||
+      (st = fetch_dev(pl, p->q, P.q, N, "q")))
+    return bail(st);
+  if (P.td && ((st = fetch_dev(pl, mt->cv, P.cv, N, "material.cv")) ||
+               (st = fetch_dev(pl, mt->T0, P.T0, N, "material.T0"))))
+    return bail(st);
+  launch_check_cells(N, P.sig_a, P.sig_s, P.q, P.cv, P.T0, P.sig_t, bad, s);
+  if (!p->bnd_in) {
+    if (hipMemsetAsync(P.bnd, 0, nbk * sizeof(double), s) != hipSuccess)
+      return bail(fail(ctx, GSIS_E_DEVICE, "hipMemsetAsync failed"));
+  } else if (o->device_ptrs) {
+    launch_setup_bnd(nbk, K, p->bnd_in, perm, P.bnd, bad, s);
+  } else {
+    std::vector<double> bnd(nbk);
+    for (size_t t = 0; t < nbk; ++t) {
+      const size_t fc = t / K;
+      bnd[t] = p->bnd_in[fc * K + pl->perm[t - fc * K]];
+    }
+    // (checked below with the caller's index, after the cells)
+    if (hipMemcpyAsync(P.bnd, bnd.data(), nbk * sizeof(double), hipMemcpyHostToDevice, s) !=
+            hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+      return bail(fail(ctx, GSIS_E_DEVICE, "copying bnd_in failed"));
+  }
+  {
+    unsigned long long hb[3];
+    if (hipMemcpyAsync(hb, bad, sizeof hb, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+      return bail(fail(ctx, GSIS_E_DEVICE, "reading the problem's fields: %s",
+                       hipGetErrorString(hipGetLastError())));
+    if (p->bnd_in && !o->device_ptrs)
+      for (size_t t = 0; t < nbk && hb[1] == ~0ull; ++t)
+        if (!std::isfinite(p->bnd_in[t])) hb[1] = t;
+    for (int k = 0; k < 3; k += 2) {
+      if (hb[k] == ~0ull) continue;
+      const size_t c = hb[k] >> 3;
+      const char *const what[] = {"sigma_a[%zu] must be finite and >= 0",
+                                  "sigma_s[%zu] must be finite and >= 0",
+                                  "sigma_a[%zu] + sigma_s[%zu] must be > 0", "q[%zu] is not finite",
+                                  "material.cv[%zu] must be finite and > 0",
+                                  "material.T0[%zu] must be finite and >= 0"};
+      if (k == 2 && hb[1] != ~0ull) break;
+      return bail(fail(ctx, GSIS_E_INVALID_ARG, what[hb[k] & 7], c, c));
+    }
+    if (hb[1] != ~0ull)
+      return bail(fail(ctx, GSIS_E_INVALID_ARG, "bnd_in[%zu][%zu] is not finite",
+                       (size_t)hb[1] / K, (size_t)hb[1] % K));
+  }
+
+  // -- coefficients, records and the level-0 operator
+  {
+    SetupArgs a;
+    a.nx = nx; a.ny = ny; a.alsm = P.alsm;
+    a.dx = P.dx; a.dy = P.dy; a.V = P.V; a.tdiag = P.tdiag;
+    a.cfl_p = o->cfl_p; a.beta = o->beta; a.dref = std::min(p->dx, p->dy);
+    a.st = P.sig_t; a.sa = P.sig_a;
+    a.cE = P.cE; a.cW = P.cW; a.cN = P.cN; a.cS = P.cS; a.kappa = P.kappa;
+    a.diag = L0.diag; a.ax = L0.ax; a.ay = L0.ay;
+    a.cellq = P.cellq; a.sdq = P.sdq; a.sdq_f = P.sdq_f;
+    launch_setup_cells(a, s);
+  }
   // -- warm start
-  std::vector<double> phi0(N, 0.0);
   if (o->I0) {
+    std::vector<double> phi0(N, 0.0);
     std::vector<double> I0;
     if ((st = fetch(ctx, o->I0, (size_t)N * K, o->device_ptrs, I0, "I0"))) return bail(st);
     pl->I0_host.assign((size_t)N * K, 0.0);
@@ -667,70 +709,9 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       }
       pl->I0_host.clear();
     }
+    if ((st = upload(pl, &P.phi0, phi0))) return bail(st);
   }
-  pl->phi0_host = phi0;
-
-  // -- device allocations and uploads
-  if ((st = upload(pl, &P.amu, amu)) || (st = upload(pl, &P.aeta, aeta)) ||
-      (st = upload(pl, &P.w, wv)) || (st = upload(pl, &P.wmu, wmu)) ||
-      (st = upload(pl, &P.weta, weta)) || (st = alloc_intensity(pl, 0, (size_t)N * K, f32)) ||
-      (st = alloc_intensity(pl, 1, (size_t)N * K, f32)) ||
-      (st = dalloc(pl, &P.R, P.sweep_impl == 1 ? (size_t)N * K : 1)) ||
-      (st = upload(pl, &P.cellq, cellq)) || (st = dalloc(pl, &P.dynq, (size_t)4 * N * 3)) ||
-      (st = dalloc(pl, &P.rowbuf, (size_t)K * 3 * nx)) || (st = upload(pl, &P.sdq, sdq)) ||
-      (st = upload(pl, &P.rtiles, rtiles)) || (st = upload(pl, &P.dso, diag_row0_table(nx, ny))) ||
-      (st = upload(pl, &P.sig_t, st_)) || (st = upload(pl, &P.sig_a, sa)) ||
-      (st = upload(pl, &P.sig_s, ss)) || (st = upload(pl, &P.q, q)) ||
-      (st = upload(pl, &P.cE, cE)) || (st = upload(pl, &P.cW, cW)) ||
-      (st = upload(pl, &P.cN, cN)) || (st = upload(pl, &P.cS, cS)) ||
-      (st = dalloc(pl, &P.src, N)) || (st = dalloc(pl, &P.phi, N)) ||
-      (st = dalloc(pl, &P.phih, N)) || (st = dalloc(pl, &P.Fx, N)) ||
-      (st = dalloc(pl, &P.mom_part, (size_t)12 * P.mom_split * N)) ||
-      (st = dalloc(pl, &P.Fy, N)) || (st = dalloc(pl, &P.delta, N)) ||
-      (st = dalloc(pl, &P.hx, N)) || (st = dalloc(pl, &P.hy, N)) ||
-      (st = dalloc(pl, &P.rhs, N)) || (st = upload(pl, &P.bnd, bnd_int)) ||
-      (st = dalloc(pl, &P.bflux, P.nbf)) || (st = upload(pl, &P.kappa, kap)) ||
-      (st = dalloc(pl, &P.err_hist, o->max_iter)) ||
-      (st = dalloc(pl, &P.tres_hist, o->max_iter)) ||
-      (st = dalloc(pl, &P.tres_part, tres_slots(P))) ||
-      (st = dalloc(pl, &P.src2_part, (size_t)(N + 255) / 256)) ||
-      (st = dalloc(pl, &P.state, 5)) || (st = dalloc(pl, &P.last_err, 2)))
-    return bail(st);
-  if (hand_parts(P) > 1 && (st = dalloc(pl, &P.hand, (size_t)K * (hand_parts(P) - 1) * nx)))
-    return bail(st);
-  if (f32) {
-    std::vector<float> sdqf(sdq.begin(), sdq.end());
-    if ((st = upload(pl, &P.sdq_f, sdqf))) return bail(st);
-    // w, w mu, w eta in FP32 for the moment sums of the deviations
-    std::vector<float> wf(3 * (size_t)K);
-    for (int kk = 0; kk < K; ++kk) {
-      wf[kk] = (float)wv[kk];
-      wf[K + kk] = (float)wmu[kk];
-      wf[2 * K + kk] = (float)weta[kk];
-    }
-    if ((st = upload(pl, &P.w_f, wf))) return bail(st);
-  }
-  if (P.method == GSIS_GSIS && P.hot_face == GSIS_HOT_TRANSPORT &&
-      (st = dalloc(pl, &P.ftp, (size_t)8 * N)))
-    return bail(st);
-  if (P.td &&
-      ((st = upload(pl, &P.cv, cvh)) || (st = dalloc(pl, &P.Tm, N)) || (st = dalloc(pl, &P.Tn, N)) ||
-       (st = dalloc(pl, &P.Tsub0, N)) || (st = dalloc(pl, &P.Tsub1, N)) ||
-       (st = dalloc(pl, &P.rho_n, N)) ||
-       (st = dalloc(pl, &P.err_parts_T, 2 * (size_t)((N + 255) / 256) + 2)) ||
-       (st = dalloc(pl, &P.In, (size_t)N * K))))
-    return bail(st);
-  if (f32) {
-    if ((st = dalloc(pl, &P.base, N))) return bail(st);
-  } else {
-    P.base = P.delta;
-  }
-  if ((st = dalloc(pl, &P.err_parts, 2 * (size_t)((N + 255) / 256) + 2)) ||
-      (st = setup_synth(pl, P, hl)))
-    return bail(st);
-  if (P.mg.size() > (size_t)kMaxLevels)
-    return bail(fail(ctx, GSIS_E_INVALID_ARG, "multigrid hierarchy deeper than %d levels",
-                     kMaxLevels));
+  if ((st = setup_synth(pl, P))) return bail(st);
   if ((st = make_single_set(pl))) return bail(st);
   if (arena) {
     // pageable host flags: the synthetic solve's copies of them are followed
@@ -741,9 +722,9 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     // count of the last forward solve; [4, 7) and [12] the same for the
     // adjoint's solves
     void *h = nullptr;
-    hipError_t e = hipHostMalloc(&h, 64, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc(&h, kHostScal * sizeof(double), hipHostMallocDefault);
     if (e != hipSuccess) return bail(fail(ctx, GSIS_E_OOM, "hipHostMalloc: %s", hipGetErrorString(e)));
-    memset(h, 0, 64);
+    memset(h, 0, kHostScal * sizeof(double));
     pl->host_scal = (double *)h;
     if ((e = hipEventCreateWithFlags(&pl->spec_ev, hipEventDisableTiming)) != hipSuccess) {
       pl->spec_ev = nullptr;
@@ -772,8 +753,7 @@ extern "C" void gsis_plan_destroy(gsis_plan *pl) {
   delete pl;
 }
 
-extern "C" gsis_status gsis_plan_reset(gsis_plan *pl) {
-  if (!pl) return GSIS_E_INVALID_ARG;
+gsis_status plan_reset_enqueue(gsis_plan *pl) {
   gsis_ctx *ctx = pl->ctx;
   PlanDev &P = pl->P;
   const size_t NK = (size_t)P.N * P.K;
@@ -788,31 +768,18 @@ extern "C" gsis_status gsis_plan_reset(gsis_plan *pl) {
                                hipMemcpyHostToDevice, s));
   else
     HIPCHK(ctx, hipMemsetAsync(P.I[0], 0, NK * (f32 ? sizeof(float) : sizeof(double)), s));
-  HIPCHK(ctx, hipMemcpyAsync(P.phi, pl->phi0_host.data(), P.N * sizeof(double),
-                             hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemsetAsync(P.delta, 0, P.N * sizeof(double), s));
-  if (f32)   // I^0 = Itilde + phi0/(4 pi)
-    HIPCHK(ctx, hipMemcpyAsync(P.base, pl->phi0_host.data(), P.N * sizeof(double),
-                               hipMemcpyHostToDevice, s));
-  if (P.td)   // T^0 (the source kernel below takes the emission of T^m)
-    HIPCHK(ctx, hipMemcpyAsync(P.Tm, pl->T0_host.data(), P.N * sizeof(double),
-                               hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemsetAsync(P.state, 0, 5 * sizeof(int32_t), s));
-  launch_hand_reset(P, s);
-  HIPCHK(ctx, hipMemsetAsync(P.err_hist, 0, P.max_iter * sizeof(double), s));
-  HIPCHK(ctx, hipMemsetAsync(P.tres_hist, 0, P.max_iter * sizeof(double), s));
-  HIPCHK(ctx, hipMemsetAsync(P.tres_part, 0, tres_slots(P) * sizeof(double), s));
-  HIPCHK(ctx, hipMemsetAsync(synth_vcycle_total(P), 0, sizeof(double), s));
-  {
-    // Err of the last iteration and the smallest ||phi^{m+1} - phi^m||_V so
-    // far (divergence test)
-    static const double init[2] = {0.0, INFINITY};
-    HIPCHK(ctx, hipMemcpyAsync(P.last_err, init, sizeof init, hipMemcpyHostToDevice, s));
-  }
+  launch_plan_reset(P, tres_slots(P), s);
   launch_source(P.S, s);
   HIPCHK(ctx, hipGetLastError());
-  HIPCHK(ctx, hipStreamSynchronize(s));
   pl->prof_iters = 0;
+  return GSIS_OK;
+}
+
+extern "C" gsis_status gsis_plan_reset(gsis_plan *pl) {
+  if (!pl) return GSIS_E_INVALID_ARG;
+  gsis_status st = plan_reset_enqueue(pl);
+  if (st) return st;
+  HIPCHK(pl->ctx, hipStreamSynchronize(pl->stream));
   return GSIS_OK;
 }
 
@@ -888,24 +855,40 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
   return GSIS_OK;
 }
 
+// Enqueues the copies of the flags and Err to the host (status_get reads them
+// after a wait for the stream).
+static gsis_status status_enqueue(gsis_plan *pl) {
+  double *h = pl->host_scal + kStatusSlot;
+  HIPCHK(pl->ctx, hipMemcpyAsync(h, pl->P.last_err, sizeof(double), hipMemcpyDeviceToHost,
+                                 pl->stream));
+  HIPCHK(pl->ctx, hipMemcpyAsync(h + 1, pl->P.state, 5 * sizeof(int32_t), hipMemcpyDeviceToHost,
+                                 pl->stream));
+  return GSIS_OK;
+}
+static gsis_status status_get(gsis_plan *pl, int32_t *n_iter, int32_t *converged,
+                              double *last_err) {
+  const double *h = pl->host_scal + kStatusSlot;
+  int32_t stv[5];
+  memcpy(stv, h + 1, sizeof stv);
+  if (stv[4] != 0)
+    return fail(pl->ctx, GSIS_E_DEVICE,
+                "the recurrence's workgroups of one ordinate stopped waiting for each other; "
+                "reset the plan");
+  if (n_iter) *n_iter = stv[0];
+  if (converged) *converged = stv[1] == 1 ? 1 : (stv[1] == -1 ? -1 : 0);
+  if (last_err) *last_err = h[0];
+  return GSIS_OK;
+}
+
 extern "C" gsis_status gsis_plan_status(gsis_plan *pl, int32_t *n_iter, int32_t *converged,
                                         double *last_err) {
   if (!pl) return GSIS_E_INVALID_ARG;
   gsis_ctx *ctx = pl->ctx;
   HIPCHK(ctx, hipSetDevice(ctx->device));
-  int32_t stv[5];
-  double le = 0;
-  HIPCHK(ctx, hipMemcpyAsync(stv, pl->P.state, sizeof stv, hipMemcpyDeviceToHost, pl->stream));
-  HIPCHK(ctx, hipMemcpyAsync(&le, pl->P.last_err, sizeof le, hipMemcpyDeviceToHost, pl->stream));
+  gsis_status st = status_enqueue(pl);
+  if (st) return st;
   HIPCHK(ctx, hipStreamSynchronize(pl->stream));
-  if (stv[4] != 0)
-    return fail(ctx, GSIS_E_DEVICE,
-                "the recurrence's workgroups of one ordinate stopped waiting for each other; "
-                "reset the plan");
-  if (n_iter) *n_iter = stv[0];
-  if (converged) *converged = stv[1] == 1 ? 1 : (stv[1] == -1 ? -1 : 0);
-  if (last_err) *last_err = le;
-  return GSIS_OK;
+  return status_get(pl, n_iter, converged, last_err);
 }
 
 extern "C" gsis_status gsis_plan_read(gsis_plan *pl, gsis_result *r) {
@@ -918,22 +901,29 @@ extern "C" gsis_status gsis_plan_read(gsis_plan *pl, gsis_result *r) {
   hipStream_t s = pl->stream;
   int32_t n_iter = 0, conv = 0;
   double le = 0;
-  gsis_status st = gsis_plan_status(pl, &n_iter, &conv, &le);
+  gsis_status st = status_enqueue(pl);
   if (st) return st;
-  const size_t bytes = P.N * sizeof(double);
-  // F of the final iterate: F_half plus the pending correction's flux (hx, hy
-  // are free here and serve as staging).
-  launch_apply_delta_final(P, s, pl->swmu, pl->sweta, P.hx, P.hy);
+  // F of the final iterate: F_half plus the pending correction's flux; for
+  // host memory staged in hx, hy, which are free here
+  if (pl->device_ptrs)
+    launch_plan_read(P, pl->swmu, pl->sweta, r->phi, r->Fx, r->Fy, r->err_hist, r->tres_hist, s);
+  else
+    launch_plan_read(P, pl->swmu, pl->sweta, nullptr, P.hx, P.hy, nullptr, nullptr, s);
   HIPCHK(ctx, hipGetLastError());
-  const hipMemcpyKind k = pl->device_ptrs ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  HIPCHK(ctx, hipMemcpyAsync(r->phi, P.phi, bytes, k, s));
-  HIPCHK(ctx, hipMemcpyAsync(r->Fx, P.hx, bytes, k, s));
-  HIPCHK(ctx, hipMemcpyAsync(r->Fy, P.hy, bytes, k, s));
-  if (r->err_hist && n_iter > 0)
-    HIPCHK(ctx, hipMemcpyAsync(r->err_hist, P.err_hist, n_iter * sizeof(double), k, s));
-  if (r->tres_hist && n_iter > 0)
-    HIPCHK(ctx, hipMemcpyAsync(r->tres_hist, P.tres_hist, n_iter * sizeof(double), k, s));
   HIPCHK(ctx, hipStreamSynchronize(s));
+  if ((st = status_get(pl, &n_iter, &conv, &le))) return st;
+  if (!pl->device_ptrs) {
+    const size_t bytes = P.N * sizeof(double);
+    const hipMemcpyKind k = hipMemcpyDeviceToHost;
+    HIPCHK(ctx, hipMemcpyAsync(r->phi, P.phi, bytes, k, s));
+    HIPCHK(ctx, hipMemcpyAsync(r->Fx, P.hx, bytes, k, s));
+    HIPCHK(ctx, hipMemcpyAsync(r->Fy, P.hy, bytes, k, s));
+    if (r->err_hist && n_iter > 0)
+      HIPCHK(ctx, hipMemcpyAsync(r->err_hist, P.err_hist, n_iter * sizeof(double), k, s));
+    if (r->tres_hist && n_iter > 0)
+      HIPCHK(ctx, hipMemcpyAsync(r->tres_hist, P.tres_hist, n_iter * sizeof(double), k, s));
+    HIPCHK(ctx, hipStreamSynchronize(s));
+  }
   r->n_iter = n_iter;
   r->final_err = n_iter > 0 ? le : INFINITY;
   return GSIS_OK;

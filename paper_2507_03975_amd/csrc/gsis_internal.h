@@ -219,6 +219,8 @@ struct PlanDev {
   double *cE = nullptr, *cW = nullptr, *cN = nullptr, *cS = nullptr;  // ALSM
   double *src = nullptr;       // (sigma_s phi^m + q)/(4 pi)
   double *phi = nullptr;       // phi^m
+  double *phi0 = nullptr;      // phi of the warm start (NULL: zero)
+  double *T0 = nullptr;        // time-dependent form: initial temperature
   double *phih = nullptr, *Fx = nullptr, *Fy = nullptr;  // moments of I^{m+1/2}
   double *mom_part = nullptr;  // [mom_split][4][3][N] per-quadrant partial moments
   int mom_split = 1;           // parts of a quadrant's ordinates (moment_split)
@@ -269,6 +271,50 @@ struct PlanDev {
   int lc = 0;                  // first level of the one-workgroup cycle
 };
 
+// ---- set-up, restart and read-out (kernels_setup.hip)
+// Kinds of a bad cell, in the order they are reported for one cell.
+enum { kBadSigA = 0, kBadSigS = 1, kBadSigT = 2, kBadQ = 3, kBadCv = 4, kBadT0 = 5 };
+// st = sa + ss; bad[0] (bad[2]: cv, T0) receives the smallest 8 * cell + kind
+// of an inadmissible cell, bad[1] the smallest inadmissible index of bnd_in
+// (all ~0 before). cv and T0 may be NULL.
+void launch_check_cells(int N, const double *sa, const double *ss, const double *q,
+                        const double *cv, const double *T0, double *st, unsigned long long *bad,
+                        hipStream_t s);
+// dst[f][kk] = src[f][perm[kk]], n = faces * K entries
+void launch_setup_bnd(long long n, int K, const double *src, const int *perm, double *dst,
+                      unsigned long long *bad, hipStream_t s);
+struct SetupArgs {
+  int nx, ny, alsm;
+  double dx, dy, V, tdiag, cfl_p, beta, dref;
+  const double *st, *sa;
+  double *cE, *cW, *cN, *cS, *kappa, *diag, *ax, *ay, *cellq, *sdq;
+  float *sdq_f;                // FP32-mixed only
+};
+void launch_setup_cells(const SetupArgs &a, hipStream_t s);
+constexpr int kLogBlocks = 128;
+// partial sums of log ax, log ay over the level's interior faces; the pairs'
+// count
+int launch_log_sums(const struct MGLevel &L, double *part, hipStream_t s);
+void launch_coarsen(const struct MGLevel &F, const struct MGLevel &C, hipStream_t s);
+struct ResetArgs {
+  int N, max_iter;
+  size_t n_tres, n_hand;
+  const double *phi0, *T0;
+  double *phi, *delta, *base, *Tm, *err_hist, *tres_hist, *tres_part, *vcycles, *last_err;
+  unsigned long long *hand;
+  int32_t *state;
+};
+struct ReadArgs {
+  int N;
+  const int32_t *state;
+  const double *phi, *Fx, *Fy, *delta, *err_hist, *tres_hist;
+  double swm, swe;
+  double *ophi, *oFx, *oFy, *oerr, *otres;
+};
+void launch_plan_reset(const struct PlanDev &P, size_t n_tres, hipStream_t s);
+void launch_plan_read(const struct PlanDev &P, double swm, double swe, double *phi, double *Fx,
+                      double *Fy, double *err, double *tres, hipStream_t s);
+
 // ---- transport kernels (kernels_transport.hip)
 // Transport step: residual of every cell-ordinate, then the wavefront
 // increment solve (for the fused kernel the residual launch is empty).
@@ -278,9 +324,6 @@ inline int hand_parts(const PlanDev &P) {
   const int p = P.chain_parts > P.pipe_parts ? P.chain_parts : P.pipe_parts;
   return p > P.adj_parts ? p : P.adj_parts;
 }
-// Puts every entry of the split recurrence's hand-over buffer in its empty
-// state (plan set-up and reset; the recurrence keeps it so between launches).
-void launch_hand_reset(const PlanDev &P, hipStream_t s);
 // Tiles of the residual kernel for an nx x ny grid: (first diagonal, first
 // row) of each band of rows x run of diagonals that holds a cell.
 // Residual-kernel tiles of rd diagonals (residual_tile_diagonals: 31, or 47
@@ -382,8 +425,6 @@ void launch_update(const SynthSet &S, hipStream_t s, int cond = 0);
 // Time-dependent form, start of a time step: I^n = the current iterate (with
 // its pending correction), rho^n, T^n; the step's counters and flags cleared
 void launch_td_begin(const PlanDev &P, hipStream_t s);
-void launch_apply_delta_final(const PlanDev &P, hipStream_t s, double swmu, double sweta,
-                              double *Fx_out, double *Fy_out);
 // CG iterations of P's last synthetic solve (one device double)
 double *synth_iteration_counter(const PlanDev &P);
 // V-cycles of all synthetic solves since the last reset (one device double)

@@ -1539,16 +1539,6 @@ __global__ void __launch_bounds__(kRedBlock) k_err_source(const SynthDesc *ds, c
   source_tile(D, B, s_sc, s_dq, s_pq);
 }
 
-// Final F with the pending correction: F = F_half + delta/(4 pi) sum_k w Omega_k
-__global__ void k_final_flux(int n, const double *Fx, const double *Fy, const double *delta,
-                             double swmu, double sweta, double *ox, double *oy) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  const double d = delta[c] / kFourPi;
-  ox[c] = Fx[c] + d * swmu;
-  oy[c] = Fy[c] + d * sweta;
-}
-
 // z = M^{-1} r_v (one V(1,1) cycle with scaled coarse corrections) for
 // every problem of the set, with the partials of r.z. V-cycle v > 0 follows
 // CG iteration v - 1, whose update its level-0 tile kernel makes. part 1
@@ -1778,12 +1768,6 @@ void launch_update(const SynthSet &S, hipStream_t s, int cond) {
   const int nb = S.bt_src ? S.nb_src : 8 * ts;
   hipLaunchKernelGGL(k_err_source, dim3(n8 + nb), dim3(kRedBlock), 0, s, S.desc, S.bt_src, S.n,
                      n8, S.nb_src, ts, cond);
-}
-
-void launch_apply_delta_final(const PlanDev &P, hipStream_t s, double swmu, double sweta,
-                              double *Fx_out, double *Fy_out) {
-  hipLaunchKernelGGL(k_final_flux, dim3(nblk(P.N)), dim3(kRedBlock), 0, s, P.N, P.Fx, P.Fy,
-                     P.delta, swmu, sweta, Fx_out, Fy_out);
 }
 
 double *synth_iteration_counter(const PlanDev &P) { return P.scal + S_NIT; }

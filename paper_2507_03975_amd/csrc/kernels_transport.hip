@@ -1393,11 +1393,6 @@ __global__ void __launch_bounds__(2 * NB * 64) k_pipe(TArgs a, int np) {
   pipe_ordinate<T, TD, NB, PF>(a, xcd_ordinate(blockIdx.x - part * a.K, a.K), part, np);
 }
 
-__global__ void k_fill_u64(unsigned long long *p, size_t n, unsigned long long v) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
 // Batched recurrence: a persistent launch whose workgroups take work items
 // (problem, ordinate) from a shared counter in the order of the item table
 // (longest first) and run the recurrence with that problem's arguments, in
@@ -1996,13 +1991,6 @@ std::vector<int2> residual_tiles(int nx, int ny, int rd) {
 // ---- batched sweep
 size_t targs_bytes() { return sizeof(TArgs); }
 
-void launch_hand_reset(const PlanDev &P, hipStream_t s) {
-  const int hp = hand_parts(P);
-  if (hp <= 1) return;
-  const size_t n = (size_t)P.K * (hp - 1) * P.nx;
-  hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, P.hand, n,
-                     kHandEmpty);
-}
 void fill_targs(const PlanDev &P, void *dst) {
   const TArgs a = make_args(P);
   memcpy(dst, &a, sizeof a);

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -19,6 +20,8 @@ struct gsis_ctx {
   std::string err;
 };
 
+constexpr int kHostScal = 16, kStatusSlot = 8;   // doubles
+
 struct gsis_plan {
   gsis_ctx *ctx = nullptr;
   PlanDev P;
@@ -29,10 +32,11 @@ struct gsis_plan {
   double swmu = 0, sweta = 0;     // sum_k w_k mu_k, sum_k w_k eta_k
   std::vector<double> I0_host;    // warm start in the internal layout (may be empty)
   std::vector<float> I0_host_f;   // FP32-mixed: I0 - phi0/(4 pi) in the internal layout
-  std::vector<double> phi0_host;  // phi of the warm start
-  std::vector<double> T0_host;    // time-dependent form: initial temperature
   std::vector<void *> allocs;
-  double *host_scal = nullptr;    // pinned
+  char *slab = nullptr;           // the allocation small arrays are carved from
+  size_t slab_used = 0, slab_cap = 0;
+  double *host_scal = nullptr;    // pinned: the synthetic solves' flags, then
+                                  // (kStatusSlot) the status read-out
   hipEvent_t spec_ev = nullptr;   // marks the synthetic solve's flag copy (see
                                   // launch_synth_solve); not in the allocation-free solve
   // profiling: per iteration GSIS_NUM_PHASES + 1 events bracketing the phases
@@ -45,7 +49,7 @@ struct gsis_plan {
   // live in host_flag_store instead of pinned memory
   char *arena = nullptr;
   size_t arena_used = 0, arena_cap = 0;
-  double host_flag_store[8] = {};
+  double host_flag_store[kHostScal] = {};
 };
 
 extern thread_local std::string g_create_err;
@@ -70,6 +74,8 @@ inline gsis_status fail_impl(gsis_ctx *ctx, gsis_status st, const char *fmt, ...
   } while (0)
 
 
+constexpr size_t kSlabShare = 1 << 20, kSlabBytes = 4 << 20;
+
 template <typename T>
 gsis_status dalloc(gsis_plan *pl, T **p, size_t n) {
   void *v = nullptr;
@@ -85,11 +91,26 @@ gsis_status dalloc(gsis_plan *pl, T **p, size_t n) {
     pl->arena_used += bytes;
     return GSIS_OK;
   }
-  hipError_t e = hipMalloc(&v, std::max<size_t>(n, 1) * sizeof(T));
+  // arrays below 1 MiB share allocations of 4 MiB: a plan has some fifty of
+  // them, and an allocation costs 1 to 10 us and its release as much again
+  size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~(size_t)255;
+  const bool small = bytes < kSlabShare;
+  if (small && bytes <= pl->slab_cap - pl->slab_used) {
+    *p = (T *)(pl->slab + pl->slab_used);
+    pl->slab_used += bytes;
+    return GSIS_OK;
+  }
+  const size_t used = bytes;
+  if (small) bytes = kSlabBytes;
+  hipError_t e = hipMalloc(&v, bytes);
   if (e != hipSuccess)
-    return fail(pl->ctx, GSIS_E_OOM, "hipMalloc(%zu bytes): %s", n * sizeof(T),
-                hipGetErrorString(e));
+    return fail(pl->ctx, GSIS_E_OOM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
   pl->allocs.push_back(v);
+  if (small) {
+    pl->slab = (char *)v;
+    pl->slab_used = used;
+    pl->slab_cap = bytes;
+  }
   *p = (T *)v;
   return GSIS_OK;
 }
@@ -102,15 +123,29 @@ gsis_status upload(gsis_plan *pl, T **p, const std::vector<T> &h) {
   return GSIS_OK;
 }
 
-struct HostLevel {
-  int nx, ny, fx = 1, fy = 1;
-  std::vector<double> diag, ax, ay;
+// Small host arrays that go to the device in one copy.
+struct Pack {
+  std::vector<char> h;
+  std::vector<std::pair<void **, size_t>> at;
+  template <typename T>
+  void add(T **p, const std::vector<T> &v) {
+    at.push_back({(void **)p, h.size()});
+    h.resize((h.size() + v.size() * sizeof(T) + 255) & ~(size_t)255);
+    if (!v.empty()) memcpy(h.data() + at.back().second, v.data(), v.size() * sizeof(T));
+  }
+  gsis_status commit(gsis_plan *pl) {
+    char *d = nullptr;
+    gsis_status st = dalloc(pl, &d, h.size());
+    if (st) return st;
+    if (!h.empty()) HIPCHK(pl->ctx, hipMemcpy(d, h.data(), h.size(), hipMemcpyHostToDevice));
+    for (auto &e : at) *e.first = d + e.second;
+    return GSIS_OK;
+  }
 };
 
-// Multigrid hierarchy of hl[0] and the device state of a synthetic solve on
-// P (defined in capi.cpp).
-gsis_status setup_synth(gsis_plan *pl, PlanDev &P, std::vector<HostLevel> &hl);
 // P.S for the plan alone (descriptor upload, block counts).
 gsis_status make_single_set(gsis_plan *pl);
 // Frees the adjoint's host-side state (device memory goes with the plan).
 void adjoint_release(gsis_plan *pl);
+// gsis_plan_reset without the wait at its end.
+gsis_status plan_reset_enqueue(gsis_plan *pl);
