@@ -309,7 +309,7 @@ void enqueue_iteration(gsis_batch *b, bool capture) {
   (void)capture;
   if (b->active.empty()) return;
   if (b->split) {
-    launch_resid_batch(b->targs, b->ritems, b->n_ritems, b->fp32, s);
+    launch_resid_batch(b->subs[0]->P, b->targs, b->ritems, b->n_ritems, b->fp32, s);
     launch_chain_batch(b->targs, b->items, b->n_items, b->counter, b->cfg, b->fp32, b->grid, s);
   } else {
     launch_sweep_batch(b->targs, b->items, b->n_items, b->counter, b->cfg, b->fp32, b->grid, s);
@@ -401,7 +401,7 @@ gsis_status gsis_batch_create(gsis_ctx *ctx, int32_t n, const gsis_problem *p,
   so.profile = 0;
   for (int i = 0; i < n; ++i) {
     gsis_plan *pl = nullptr;
-    if ((st = gsis_plan_create(ctx, &p[i], &so, &pl))) {
+    if ((st = plan_create_shared(ctx, &p[i], &so, n, &pl))) {
       std::string msg = ctx->err;
       destroy(b);
       return fail(ctx, st, "problem %d: %s", i, msg.c_str());
@@ -458,7 +458,7 @@ gsis_status gsis_batch_create(gsis_ctx *ctx, int32_t n, const gsis_problem *p,
     // timed run starts from a fresh residual launch (outside the events)
     float ms = 0;
     for (int r = 0; r < 3; ++r) {
-      if (b->split) launch_resid_batch(b->targs, b->ritems, b->n_ritems, b->fp32, b->stream);
+      if (b->split) launch_resid_batch(b->subs[0]->P, b->targs, b->ritems, b->n_ritems, b->fp32, b->stream);
       HIPCHK(ctx, hipEventRecord(e0, b->stream));
       run(c, grid);
       HIPCHK(ctx, hipEventRecord(e1, b->stream));

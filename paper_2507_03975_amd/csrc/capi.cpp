@@ -373,6 +373,7 @@ gsis_status make_single_set(gsis_plan *pl) {
 // from the arena_cap bytes at arena (no device or pinned allocation at all;
 // profiling off).
 // With mt, the time-dependent form (backward-Euler steps of size mt->dt).
+// share: plans that run together (a batch).
 // room for the partial sums of w r^2 of either residual kernel (a batch
 // runs its own on a plan made for the pipelined step)
 static size_t tres_slots(const PlanDev &P) {
@@ -381,7 +382,7 @@ static size_t tres_slots(const PlanDev &P) {
 
 static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_options *o,
                                gsis_plan **out, char *arena, size_t arena_cap,
-                               const gsis_material *mt = nullptr) {
+                               const gsis_material *mt = nullptr, int share = 1) {
   if (!ctx) return fail(nullptr, GSIS_E_INVALID_ARG, "ctx is NULL");
   if (!out) return fail(ctx, GSIS_E_INVALID_ARG, "out is NULL");
   *out = nullptr;
@@ -493,6 +494,9 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     P.pipe_bands = nb;
     P.pipe_parts = P.sweep_impl == 3 ? (ny + 64 * nb - 1) / (64 * nb) : 1;
   }
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
+    cus = 0;
   {
     // workgroups per ordinate in the recurrence (GSIS_CHAIN_PARTS=1..4 sets
     // it): a step costs a wave about the same whatever the rest of the chip
@@ -500,10 +504,6 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     // (one wave per SIMD); more parts while the ordinates fill fewer than
     // half the CUs; at most 4, each a multiple of 64 rows and at most 1024,
     // the top part not empty
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) !=
-        hipSuccess)
-      cus = 0;
     int parts = std::min((ny + 255) / 256, 4);
     while (parts < 4 && 2 * K * parts < cus) parts *= 2;
     // the adjoint's sweep loads five values a step where the recurrence loads
@@ -527,7 +527,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
   }
   P.mom_split = moment_split(P);
   // residual tiles (GSIS_RESID_DIAGONALS=31 or 47 sets their length)
-  P.resid_rd = residual_tile_diagonals((long long)N * K);
+  P.resid_rd = residual_tile_diagonals(nx, ny, residual_pairs(P), share, cus);
   {
     const char *e = getenv("GSIS_RESID_DIAGONALS");
     if (e && (!strcmp(e, "31") || !strcmp(e, "47"))) P.resid_rd = atoi(e);
@@ -739,6 +739,11 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
 extern "C" gsis_status gsis_plan_create(gsis_ctx *ctx, const gsis_problem *p,
                                         const gsis_options *o, gsis_plan **out) {
   return plan_create(ctx, p, o, out, nullptr, 0);
+}
+
+gsis_status plan_create_shared(gsis_ctx *ctx, const gsis_problem *p, const gsis_options *o,
+                               int share, gsis_plan **out) {
+  return plan_create(ctx, p, o, out, nullptr, 0, nullptr, share);
 }
 
 extern "C" void gsis_plan_destroy(gsis_plan *pl) {

@@ -324,11 +324,17 @@ inline int hand_parts(const PlanDev &P) {
   const int p = P.chain_parts > P.pipe_parts ? P.chain_parts : P.pipe_parts;
   return p > P.adj_parts ? p : P.adj_parts;
 }
+// Diagonals of a residual tile. A tile of rd diagonals costs its wave rd + 1
+// steps and about six more for its halo; the chip holds 8 waves per CU (two to
+// a SIMD), and a step takes half a full chip's time with few waves, so the
+// length that makes the fewest, fullest rounds wins: few waves, short
+// tiles (32x32 S4: 3 diagonals 10.2 us, 31 23.1; 64x64x32: 13 against 24);
+// 256x256x128: 2048 waves of 43, one round, 49.3 us (31: 2816 waves, 54.6; 39:
+// 2304, 61.6); many rounds, long tiles (512x512x128: 59 230 us, 31 246).
+// share: problems that run together (a batch). From 2^26 cell-ordinates on 47.
+int residual_tile_diagonals(int nx, int ny, int pairs, int share, int cus);
 // Tiles of the residual kernel for an nx x ny grid: (first diagonal, first
-// row) of each band of rows x run of diagonals that holds a cell.
-// Residual-kernel tiles of rd diagonals (residual_tile_diagonals: 31, or 47
-// from 2^26 cell-ordinates on)
-int residual_tile_diagonals(long long cell_ordinates);
+// row) of each band of rows x run of rd diagonals that holds a cell.
 std::vector<int2> residual_tiles(int nx, int ny, int rd);
 // Ordinate pairs of one quadrant the residual kernel takes per wave (the
 // residual-norm partials are indexed tile * pairs + pair).
@@ -351,8 +357,8 @@ constexpr int kNumBatchChainConfigs = 4;
 extern const BatchSweepConfig kBatchChainConfigs[kNumBatchChainConfigs];
 int chain_batch_blocks_per_cu(int cfg, bool fp32);
 constexpr int kResidWaves = 4;     // ordinate pairs (of one quadrant) per residual item
-void launch_resid_batch(const void *targs, const int4 *items, int n_items, bool fp32,
-                        hipStream_t s);
+void launch_resid_batch(const PlanDev &P /* one of the batch: its options */, const void *targs,
+                        const int4 *items, int n_items, bool fp32, hipStream_t s);
 void launch_chain_batch(const void *targs, const int2 *items, int n_items, int *counter, int cfg,
                         bool fp32, int grid, hipStream_t s);
 size_t targs_bytes();

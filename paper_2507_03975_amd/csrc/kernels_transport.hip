@@ -28,7 +28,9 @@
 #include "wave_ops.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
+#include <type_traits>
 
 namespace gsis {
 namespace {
@@ -69,7 +71,7 @@ struct TArgs {
   double *src2_part;          // [ceil(N / 256)] sum of src^2 per block of cells
   const double *In;           // time-dependent form: I^n, [K][N] like the intensity
   double tdiag;               // 1/(c dt) (the records' sigma_t already include it)
-  int resid_rd;               // diagonals per residual tile (kRDSmall or kRDLarge)
+  int resid_rd;               // diagonals per residual tile (residual_tile_diagonals)
 };
 
 TArgs make_args(const PlanDev &P) {
@@ -559,23 +561,36 @@ __global__ void __launch_bounds__(MAXW * 64)
 // Shifts across the whole 64-lane wave (DPP wave_shr:1 / wave_shl:1): lane i
 // gets lane i-1's (i+1's) value; lane 0 (63) keeps its own.
 
+// Face values of a plan (its order and limiter options): first order, second
+// order, second order limited. A template parameter of the kernels that form
+// them on their critical path: branches on the options cut every step into
+// short runs of instructions that wait for each other.
+constexpr int kFaceFirst = 0, kFaceSecond = 1, kFaceLimited = 2;
+template <class A>
+__device__ __host__ inline int face_order(const A &a) {
+  return a.order < 2 ? kFaceFirst : a.limiter ? kFaceLimited : kFaceSecond;
+}
+
 // Second-order values on a cell's local east and north faces, u + psi h with
 // the ALSM gradient (Eqs. shifted_j, LSF_mdf) and the Barth-Jespersen
-// limiter; a missing neighbour is passed as u.
-__device__ __forceinline__ void face_pair(double u, double UE, double UW, double UN, double US,
+// limiter; dE..dS: the neighbours' values less u, 0 for a missing neighbour.
+// umax - u and u - umin of the limiter are the largest and the negated
+// smallest of those differences and 0, to the bit (rounding is monotonic).
+template <int FO>
+__device__ __forceinline__ void face_diff(double u, double dE, double dW, double dN, double dS,
                                           double2 c0, double2 c1, double hdx, double hdy,
-                                          bool second, bool lim, double &Fe, double &Fn) {
+                                          double &Fe, double &Fn) {
   Fe = u;
   Fn = u;
-  if (!second) return;
-  const double gx = c0.x * (UE - u) - c0.y * (UW - u);
-  const double gy = c1.x * (UN - u) - c1.y * (US - u);
+  if constexpr (FO == kFaceFirst) return;
+  const double gx = c0.x * dE - c0.y * dW;
+  const double gy = c1.x * dN - c1.y * dS;
   const double hx = gx * hdx, hy = gy * hdy;
   double psi = 1.0;
-  if (lim) {
-    const double umax = fmax(fmax(fmax(u, UE), fmax(UW, UN)), US);
-    const double umin = fmin(fmin(fmin(u, UE), fmin(UW, UN)), US);
-    const double m = fmin(umax - u, u - umin);
+  if constexpr (FO == kFaceLimited) {
+    const double up = fmax(fmax(fmax(0.0, dE), fmax(dW, dN)), dS);
+    const double dn = fmin(fmin(fmin(0.0, dE), fmin(dW, dN)), dS);
+    const double m = fmin(up, -dn);
     const double M = fmax(fabs(hx), fabs(hy));
     const double pl = m * rcp64(M);           // discarded unless M > m
     psi = M > m ? pl : 1.0;
@@ -583,16 +598,21 @@ __device__ __forceinline__ void face_pair(double u, double UE, double UW, double
   Fe = fma(psi, hx, u);
   Fn = fma(psi, hy, u);
 }
+// the same from the neighbours' values, a missing neighbour's passed as u
+template <int FO>
+__device__ __forceinline__ void face_pair(double u, double UE, double UW, double UN, double US,
+                                          double2 c0, double2 c1, double hdx, double hdy,
+                                          double &Fe, double &Fn) {
+  face_diff<FO>(u, UE - u, UW - u, UN - u, US - u, c0, c1, hdx, hdy, Fe, Fn);
+}
 
 
-// Residual tiles: a band of 64 rows (one per lane) x RD diagonals, walked a
-// diagonal per step after one warm-up step on the diagonal before the tile:
-// 31 diagonals, or 47 on grids of 2^26 cell-ordinates and more, where
-// fewer, longer tiles re-read fewer halo cells (0.85 -> 0.80 ms at
-// 1024x1024x128 FP32-mixed) and there are tiles enough for the chip.
-constexpr int kRDSmall = 31, kRDLarge = 47;
+// Residual tiles: a band of 64 rows (one per lane) x resid_rd diagonals,
+// walked a diagonal per step after one warm-up step on the diagonal before the
+// tile (residual_tile_diagonals chooses the length).
 constexpr int kRWaves = 4;           // waves per workgroup, one ordinate each
 constexpr int kRPF = 4;              // steps of loads in flight
+constexpr int kRMaxRD = 59;          // longest tile (its halo in the lanes of one wave)
 
 
 template <typename T>
@@ -642,14 +662,13 @@ __device__ inline int ordinate_pairs(A &a) {
 // kB < 0: no second ordinate (its loads repeat kA's, its stores are dropped).
 // TD: the time-dependent form's residual (Eq. RTE_d_res) also takes
 // + I^n / (c dt); the -(1/(c dt)) I^m term rides in the records' sigma_t.
-template <typename T, bool TD = false, int RD = kRDSmall, class A>
+template <typename T, int FO, bool TD = false, class A>
 __device__ __forceinline__ void resid_tile(A &a, const int tile, const int kA, const int kB,
                                            const int wave, const int slot) {
-  constexpr int kRD = RD, kRSteps = RD + 1;
+  const int kRD = a.resid_rd, kRSteps = kRD + 1;   // whole turns of the load ring
   constexpr bool kF32 = sizeof(T) == 4;
   constexpr int PF = kRPF;
-  static_assert(kRSteps % PF == 0, "whole turns of the load ring");
-  static_assert(kRSteps + PF + 2 <= kDiagPad, "diagonal table padding");
+  static_assert(kRMaxRD + 1 + PF + 2 <= kDiagPad && (kRMaxRD + 1) % PF == 0, "diagonal table padding");
   const int lane = threadIdx.x & 63;
   const int2 tl = a.rtiles[tile];
   const int d0 = tl.x, y0 = tl.y;
@@ -669,7 +688,6 @@ __device__ __forceinline__ void resid_tile(A &a, const int tile, const int kA, c
     if constexpr (TD) Nb[o] = buf_rsrc(a.In + (size_t)kk[o] * N, (size_t)N * 8);
   }
   const double hdx = 0.5 * a.dx, hdy = 0.5 * a.dy;
-  const bool second = a.order >= 2, lim = a.limiter != 0;
   const __amdgpu_buffer_rsrc_t Cb = buf_rsrc(a.cellq + (size_t)q * N * 6, (size_t)N * 48);
   const double *SRC = a.dynq + (size_t)q * 3 * N;
   const __amdgpu_buffer_rsrc_t Sb = buf_rsrc(SRC, (size_t)N * 8);
@@ -680,7 +698,7 @@ __device__ __forceinline__ void resid_tile(A &a, const int tile, const int kA, c
   const int y = y0 + lane;
   const bool rowok = y < ny, hn = y + 1 < ny, hs = y > 0;
   // ---- halo (see above) into LDS: lane j's values at [wave][ordinate][slot][j]
-  __shared__ double hal[kRWaves][2][4][kRSteps + 1];
+  __shared__ double hal[kRWaves][2][4][kRMaxRD + 2];
   {
     auto cidx = [&](int x, int yy) {       // storage index, clamped into the grid
       x = min(max(x, 0), nx - 1);
@@ -708,8 +726,8 @@ __device__ __forceinline__ void resid_tile(A &a, const int tile, const int kA, c
       const double vN = (double)buf_ldT<T>(Ib[o], iN) + qN;
       const double vin = a.bnd[fs + kk[o]];
       double Fe, Fn;
-      face_pair(vf, xf + 1 < nx ? ve : vf, xf > 0 ? vw : vf, vn, ys > 0 ? vs : vf, f0, f1, hdx,
-                hdy, second, lim, Fe, Fn);
+      face_pair<FO>(vf, xf + 1 < nx ? ve : vf, xf > 0 ? vw : vf, vn, ys > 0 ? vs : vf, f0, f1, hdx,
+                    hdy, Fe, Fn);
       double hu = 0.0, hsb = 0.0, hf = 0.0, hnv = 0.0;
       if (y0 > 0) {
         if (lane <= kRD && xu >= 0 && xu < nx) { hu = vu; hsb = su; }
@@ -768,53 +786,67 @@ __device__ __forceinline__ void resid_tile(A &a, const int tile, const int kA, c
   for (int t = 0; t < PF; ++t) load(ring[t], d0 - 1 + t);
   double uw[2] = {0.0, 0.0}, Fe_p[2] = {0.0, 0.0}, Fn_p[2] = {0.0, 0.0}, subw = 0.0;
   double rr = 0.0;                            // sum of w r^2 over the lane's cells
-  for (int sb = 0; sb < kRSteps; sb += PF) {
+  // XI: no lane of the tile meets the walls x = 0 and x = nx - 1, so no value
+  // is chosen by its column
+  auto steps = [&](auto xi) {
+    constexpr bool XI = decltype(xi)::value;
+    for (int sb = 0; sb < kRSteps; sb += PF) {
 #pragma unroll
-    for (int t = 0; t < PF; ++t) {
-      const int dd = sb + t - 1;              // diagonal d0 + dd
-      RSlot<T> &sl = ring[t];
-      if constexpr (kF32) { subw = subc; subc = sube; sube = sl.sube; }
-      double sS = 0.0;
-      if constexpr (kF32) sS = shr1_fill(subw, hal[wave][0][3][dd + 1]);
-      const int x = d0 + dd - y;
-      const bool ok = dd >= 0 && rowok && x >= 0 && x < nx;
-      const double inv0 = sl.st.y;
+      for (int t = 0; t < PF; ++t) {
+        const int dd = sb + t - 1;            // diagonal d0 + dd
+        RSlot<T> &sl = ring[t];
+        if constexpr (kF32) { subw = subc; subc = sube; sube = sl.sube; }
+        double sS = 0.0;
+        if constexpr (kF32) sS = shr1_fill(subw, hal[wave][0][3][dd + 1]);
+        const int x = d0 + dd - y;
+        const bool hE = XI || x + 1 < nx, hW = XI || x > 0;
+        const bool ok = dd >= 0 && rowok && (XI || (x >= 0 && x < nx));
+        const double inv0 = sl.st.y;
 #pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        uw[o] = uc[o]; uc[o] = ue[o]; ue[o] = (double)sl.ib[o] + sl.dq;
-        // row below lane 0 / above lane 63 from the halo (LDS broadcasts)
-        const double uS = shr1_fill(uw[o], hal[wave][o][0][dd + 1]);
-        const double FnS = shr1_fill(Fn_p[o], hal[wave][o][1][dd < 0 ? 0 : dd]);
-        const double uN = shl1_fill(ue[o], hal[wave][o][2][dd + 1]);
-        const double u = uc[o];
-        const double UE = x + 1 < nx ? ue[o] : u, UW = x > 0 ? uw[o] : u;
-        const double UN = hn ? uN : u, US = hs ? uS : u;
-        double Fe, Fn;
-        face_pair(u, UE, UW, UN, US, sl.c0, sl.c1, hdx, hdy, second, lim, Fe, Fn);
-        const double FeW = x > 0 ? Fe_p[o] : inW[o];
-        double r = sl.src - sl.st.x * u - ax[o] * (Fe - FeW) - ay[o] * (Fn - FnS);
-        if constexpr (TD) r += a.tdiag * sl.in[o];
-        const double inv = rcp64(inv0 + (ax[o] + ay[o]));   // as in the recurrence
-        double t0 = kF32 ? u - subc : u;
-        const double tw = fma(-(ax[o] * inv), kF32 ? uw[o] - subw : uw[o], t0);
-        t0 = x > 0 ? tw : t0;
-        const double ts = fma(-(ay[o] * inv), kF32 ? uS - sS : uS, t0);
-        t0 = hs ? ts : t0;
-        buf_store((T)(t0 + r * inv), Ob[o], ok ? sl.ic * (unsigned)sizeof(T) : kNoCell);
-        rr = ok ? fma(wr[o] * r, r, rr) : rr;
-        Fe_p[o] = Fe;
-        Fn_p[o] = Fn;
+        for (int o = 0; o < 2; ++o) {
+          uw[o] = uc[o]; uc[o] = ue[o]; ue[o] = (double)sl.ib[o] + sl.dq;
+          // row below lane 0 / above lane 63 from the halo (LDS broadcasts)
+          const double uS = shr1_fill(uw[o], hal[wave][o][0][dd + 1]);
+          const double FnS = shr1_fill(Fn_p[o], hal[wave][o][1][dd < 0 ? 0 : dd]);
+          const double uN = shl1_fill(ue[o], hal[wave][o][2][dd + 1]);
+          const double u = uc[o];
+          double Fe, Fn;
+          face_diff<FO>(u, hE ? ue[o] - u : 0.0, hW ? uw[o] - u : 0.0, hn ? uN - u : 0.0,
+                        hs ? uS - u : 0.0, sl.c0, sl.c1, hdx, hdy, Fe, Fn);
+          const double FeW = hW ? Fe_p[o] : inW[o];
+          double r = sl.src - sl.st.x * u - ax[o] * (Fe - FeW) - ay[o] * (Fn - FnS);
+          if constexpr (TD) r += a.tdiag * sl.in[o];
+          const double inv = rcp64(inv0 + (ax[o] + ay[o]));   // as in the recurrence
+          double t0 = kF32 ? u - subc : u;
+          const double tw = fma(-(ax[o] * inv), kF32 ? uw[o] - subw : uw[o], t0);
+          t0 = hW ? tw : t0;
+          const double ts = fma(-(ay[o] * inv), kF32 ? uS - sS : uS, t0);
+          t0 = hs ? ts : t0;
+          buf_store((T)(t0 + r * inv), Ob[o], ok ? sl.ic * (unsigned)sizeof(T) : kNoCell);
+          rr = ok ? fma(wr[o] * r, r, rr) : rr;
+          Fe_p[o] = Fe;
+          Fn_p[o] = Fn;
+        }
+        load(sl, d0 + dd + PF);               // past the tile: unused
       }
-      load(sl, d0 + dd + PF);                 // past the tile: unused
     }
-  }
+  };
+  if (d0 - 1 - (y0 + 63) >= 1 && d0 + kRD - 1 - y0 <= nx - 2) steps(std::true_type());
+  else steps(std::false_type());
   // the wave's sum (fixed order), one partial per (tile, ordinate pair)
   rr = wave_sum64(rr);
   if (lane == 0) a.tres_part[slot] = rr;
 }
 
-template <typename T, bool TD = false, int RD = kRDSmall>
-__global__ void __launch_bounds__(kRWaves * 64) k_resid(TArgs a) {
+// Bound by the issue of a wave's step (two ordinates, about 170 FP64
+// instructions) and its latencies: two waves to a SIMD with the registers for
+// a whole step in flight beat three with 170 (256x256x128: 57.7 against 79.9
+// us at tiles of 31). Face options as template parameters, no value chosen by
+// column in tiles off the x walls and the tile length by
+// residual_tile_diagonals took it from 61.5 to 49.3 us there, from 272 to 230
+// at 512x512x128 and from 26.8 to 10.2 at 32x32 S4.
+template <typename T, int FO, bool TD = false>
+__global__ void __launch_bounds__(kRWaves * 64, 2) k_resid(TArgs a) {
   if (a.state[1] != 0) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform per wave
   // workgroup b runs on XCD b % 8; each XCD takes a contiguous run of
@@ -831,13 +863,13 @@ __global__ void __launch_bounds__(kRWaves * 64) k_resid(TArgs a) {
   if (pi >= ordinate_pairs(a)) return;
   int kA, kB;
   ordinate_pair(a, pi, kA, kB);
-  resid_tile<T, TD, RD>(a, tile, kA, kB, wave, tile * ordinate_pairs(a) + pi);
+  resid_tile<T, FO, TD>(a, tile, kA, kB, wave, tile * ordinate_pairs(a) + pi);
 }
 
 // Batched residual: one workgroup per item (problem, tile, group of four
 // ordinate pairs) of every problem that has not finished.
-template <typename T>
-__global__ void __launch_bounds__(kRWaves * 64) k_resid_batch(const TArgs *targs,
+template <typename T, int FO>
+__global__ void __launch_bounds__(kRWaves * 64, 2) k_resid_batch(const TArgs *targs,
                                                              const int4 *items) {
   const __attribute__((address_space(4))) int *it =
       (const __attribute__((address_space(4))) int *)items + 4 * blockIdx.x;
@@ -848,11 +880,7 @@ __global__ void __launch_bounds__(kRWaves * 64) k_resid_batch(const TArgs *targs
   if (pi >= ordinate_pairs(a)) return;
   int kA, kB;
   ordinate_pair(a, pi, kA, kB);
-  // the problem's own tile length
-  if (a.resid_rd == kRDLarge)
-    resid_tile<T, false, kRDLarge>(a, it[1], kA, kB, wave, it[1] * ordinate_pairs(a) + pi);
-  else
-    resid_tile<T, false, kRDSmall>(a, it[1], kA, kB, wave, it[1] * ordinate_pairs(a) + pi);
+  resid_tile<T, FO>(a, it[1], kA, kB, wave, it[1] * ordinate_pairs(a) + pi);
 }
 
 // Recurrence v = bv + cx v_W + cy v_S for one ordinate per workgroup; lane t
@@ -1107,7 +1135,7 @@ struct PHalo {
 // have time to spare, also load and form the residual waves' neighbour
 // values of the row above the band and of the row below band 0 a block
 // ahead and pass them through LDS.
-template <typename T, bool TD, int NB, int PF>
+template <typename T, int FO, bool TD, int NB, int PF>
 __device__ __forceinline__ void pipe_ordinate(const TArgs &a, const int kk, const int part,
                                               const int np) {
   constexpr bool kF32 = sizeof(T) == 4;
@@ -1139,7 +1167,6 @@ __device__ __forceinline__ void pipe_ordinate(const TArgs &a, const int kk, cons
   const __amdgpu_buffer_rsrc_t Qb = buf_rsrc(SRC + N, (size_t)N * 8);
   const __amdgpu_buffer_rsrc_t Ub = buf_rsrc(SRC + 2 * N, (size_t)N * 8);
   const double hdx = 0.5 * a.dx, hdy = 0.5 * a.dy;
-  const bool second = a.order >= 2, lim = a.limiter != 0;
 
   __shared__ PPair<T> pbuf[2][NB][LAG][64];
   __shared__ double pedge[NB][3][R];            // residual waves: u, F_n, sub of the top row
@@ -1222,10 +1249,9 @@ __device__ __forceinline__ void pipe_ordinate(const TArgs &a, const int kk, cons
           const int x = s - t;
           const bool ok = rowok && x >= 0 && x < nx;
           const double u = uc;
-          const double UE = x + 1 < nx ? ue : u, UW = x > 0 ? uw : u;
-          const double UN = hn ? uN : u, US = hs ? uS : u;
           double Fe, Fn;
-          face_pair(u, UE, UW, UN, US, sl.c0, sl.c1, hdx, hdy, second, lim, Fe, Fn);
+          face_diff<FO>(u, x + 1 < nx ? ue - u : 0.0, x > 0 ? uw - u : 0.0, hn ? uN - u : 0.0,
+                        hs ? uS - u : 0.0, sl.c0, sl.c1, hdx, hdy, Fe, Fn);
           const double FeW = x > 0 ? Fe_p : inW;
           double r = sl.src - sl.st.x * u - axd * (Fe - FeW) - ayd * (Fn - FnS);
           if constexpr (TD) r += a.tdiag * sl.in;
@@ -1314,8 +1340,8 @@ __device__ __forceinline__ void pipe_ordinate(const TArgs &a, const int kk, cons
       const double u = h.fI + h.fq, ve = h.eI + h.eq, vw = h.wI + h.wq;
       const double vn = h.uI + h.uq, vs = h.sI + h.sq;
       double Fe, Fn;
-      face_pair(u, x + 1 < nx ? ve : u, x > 0 ? vw : u, vn, yh > 0 ? vs : u, h.f0, h.f1, hdx, hdy,
-                second, lim, Fe, Fn);
+      face_pair<FO>(u, x + 1 < nx ? ve : u, x > 0 ? vw : u, vn, yh > 0 ? vs : u, h.f0, h.f1, hdx,
+                    hdy, Fe, Fn);
       const bool below = band == 0 && part > 0;
       if (lane < LAG) {
         hal[slot][band][0][lane] = below ? u : 0.0;
@@ -1386,11 +1412,11 @@ __device__ __forceinline__ void pipe_ordinate(const TArgs &a, const int kk, cons
   }
 }
 
-template <typename T, bool TD, int NB, int PF>
+template <typename T, int FO, bool TD, int NB, int PF>
 __global__ void __launch_bounds__(2 * NB * 64) k_pipe(TArgs a, int np) {
   if (a.state[1] != 0) return;
   const int part = blockIdx.x / a.K;
-  pipe_ordinate<T, TD, NB, PF>(a, xcd_ordinate(blockIdx.x - part * a.K, a.K), part, np);
+  pipe_ordinate<T, FO, TD, NB, PF>(a, xcd_ordinate(blockIdx.x - part * a.K, a.K), part, np);
 }
 
 // Batched recurrence: a persistent launch whose workgroups take work items
@@ -1638,7 +1664,7 @@ __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, cons
   const double ss = a.fp32 ? SUB[iS] : 0.0;
   const T *O = Iout_of<T>(a);
   const double hdx = 0.5 * a.dx, hdy = 0.5 * a.dy;
-  const bool second = a.order >= 2, lim = a.limiter != 0;
+  const int fo = face_order(a);
   double pe = 0.0, pn = 0.0;
   for (int kk = a.qoff[q]; kk < a.qoff[q + 1]; ++kk) {
     const T *Ok = O + (size_t)kk * N;
@@ -1646,7 +1672,9 @@ __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, cons
     const double UE = he ? (double)Ok[iE] + se : u, UW = hw ? (double)Ok[iW] + sw : u;
     const double UN = hn ? (double)Ok[iN] + sn : u, US = hs ? (double)Ok[iS] + ss : u;
     double Fe, Fn;
-    face_pair(u, UE, UW, UN, US, c0, c1, hdx, hdy, second, lim, Fe, Fn);
+    if (fo == kFaceLimited) face_pair<kFaceLimited>(u, UE, UW, UN, US, c0, c1, hdx, hdy, Fe, Fn);
+    else if (fo == kFaceSecond) face_pair<kFaceSecond>(u, UE, UW, UN, US, c0, c1, hdx, hdy, Fe, Fn);
+    else face_pair<kFaceFirst>(u, UE, UW, UN, US, c0, c1, hdx, hdy, Fe, Fn);
     pe += a.wmu[kk] * Fe;
     pn += a.weta[kk] * Fn;
   }
@@ -1834,6 +1862,13 @@ int sweep_rows(const PlanDev &P) {
 }
 }  // namespace
 
+template <int FO>
+static void launch_resid_fo(const TArgs &a, const PlanDev &P, dim3 g, dim3 b, hipStream_t s) {
+  if (P.td) hipLaunchKernelGGL((k_resid<double, FO, true>), g, b, 0, s, a);
+  else if (a.fp32) hipLaunchKernelGGL((k_resid<float, FO>), g, b, 0, s, a);
+  else hipLaunchKernelGGL((k_resid<double, FO>), g, b, 0, s, a);
+}
+
 // sweep_impl 0: residual kernel, then the recurrence in place; 1: plain
 // two-kernel reference (FP64 only; FP32 falls back to the fused kernel);
 // 2: fused wavefront sweep; 3: pipelined residual + recurrence (2 and 3 put
@@ -1849,14 +1884,10 @@ void launch_residual(const PlanDev &P, hipStream_t s) {
   for (int q = 0; q < 4; ++q) pairs += (P.qoff[q + 1] - P.qoff[q] + 1) / 2;
   const int G = (pairs + kRWaves - 1) / kRWaves;
   const dim3 g(8 * ((G + 7) / 8) * P.n_rtiles), b(kRWaves * 64);
-  if (P.resid_rd == kRDLarge) {
-    if (P.td) hipLaunchKernelGGL((k_resid<double, true, kRDLarge>), g, b, 0, s, a);
-    else if (a.fp32) hipLaunchKernelGGL((k_resid<float, false, kRDLarge>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_resid<double, false, kRDLarge>), g, b, 0, s, a);
-  } else {
-    if (P.td) hipLaunchKernelGGL((k_resid<double, true>), g, b, 0, s, a);
-    else if (a.fp32) hipLaunchKernelGGL(k_resid<float>, g, b, 0, s, a);
-    else hipLaunchKernelGGL(k_resid<double>, g, b, 0, s, a);
+  switch (face_order(a)) {
+    case kFaceFirst: launch_resid_fo<kFaceFirst>(a, P, g, b, s); break;
+    case kFaceSecond: launch_resid_fo<kFaceSecond>(a, P, g, b, s); break;
+    default: launch_resid_fo<kFaceLimited>(a, P, g, b, s);
   }
 }
 
@@ -1896,16 +1927,24 @@ void launch_td_begin(const PlanDev &P, hipStream_t s) {
 }
 
 namespace {
-template <typename T, bool TD>
-void launch_pipe_t(const TArgs &a, const PlanDev &P, hipStream_t s) {
+template <typename T, int FO, bool TD>
+void launch_pipe_fo(const TArgs &a, const PlanDev &P, hipStream_t s) {
   constexpr int PF = 8;
   const dim3 g(P.pipe_parts * P.K);
   if (P.pipe_bands == 1)
-    hipLaunchKernelGGL((k_pipe<T, TD, 1, PF>), g, dim3(128), 0, s, a, P.pipe_parts);
+    hipLaunchKernelGGL((k_pipe<T, FO, TD, 1, PF>), g, dim3(128), 0, s, a, P.pipe_parts);
   else if (P.pipe_bands == 2)
-    hipLaunchKernelGGL((k_pipe<T, TD, 2, PF>), g, dim3(256), 0, s, a, P.pipe_parts);
+    hipLaunchKernelGGL((k_pipe<T, FO, TD, 2, PF>), g, dim3(256), 0, s, a, P.pipe_parts);
   else
-    hipLaunchKernelGGL((k_pipe<T, TD, 4, PF>), g, dim3(512), 0, s, a, P.pipe_parts);
+    hipLaunchKernelGGL((k_pipe<T, FO, TD, 4, PF>), g, dim3(512), 0, s, a, P.pipe_parts);
+}
+template <typename T, bool TD>
+void launch_pipe_t(const TArgs &a, const PlanDev &P, hipStream_t s) {
+  switch (face_order(a)) {
+    case kFaceFirst: launch_pipe_fo<T, kFaceFirst, TD>(a, P, s); break;
+    case kFaceSecond: launch_pipe_fo<T, kFaceSecond, TD>(a, P, s); break;
+    default: launch_pipe_fo<T, kFaceLimited, TD>(a, P, s);
+  }
 }
 }  // namespace
 
@@ -1975,8 +2014,25 @@ int moment_tiles_of(int nx, int ny, int mt) {
   return ((nx + mt - 1) / mt) * ((ny + mt - 1) / mt);
 }
 
-int residual_tile_diagonals(long long cell_ordinates) {
-  return cell_ordinates >= (1LL << 26) ? kRDLarge : kRDSmall;
+int residual_tile_diagonals(int nx, int ny, int pairs, int share, int cus) {
+  if ((long long)nx * ny * pairs * 2 >= (1LL << 26)) return 47;
+  const double slots = 8.0 * std::max(cus, 1);
+  // a step's time in units of a full chip's, with the fraction f of its waves
+  // on it: alone, and (measured on the last round) behind full rounds
+  auto alone = [](double f) { return f <= 0.5 ? 0.5 + 0.28 * f : 0.64 + 0.36 * std::sqrt(2 * f - 1); };
+  auto behind = [](double f) { return std::min(1.0, 0.28 + f * f); };
+  int best = 31;
+  double least = 1e300;
+  for (int rd = 3; rd <= kRMaxRD; rd += kRPF) {
+    long long tiles = 0;
+    for (int y0 = 0; y0 < ny; y0 += 64)
+      tiles += (std::min(64, ny - y0) + nx - 1 + rd - 1) / rd;
+    const double w = (double)tiles * pairs * share;
+    const double full = std::floor(w / slots), f = w / slots - full;
+    const double t = (rd + 7) * (full + (f == 0 ? 0.0 : full > 0 ? behind(f) : alone(f)));
+    if (t < least) { least = t; best = rd; }
+  }
+  return best;
 }
 
 std::vector<int2> residual_tiles(int nx, int ny, int rd) {
@@ -2032,11 +2088,22 @@ int chain_batch_blocks_per_cu(int cfg, bool fp32) {
   return nb;
 }
 
-void launch_resid_batch(const void *targs, const int4 *items, int n_items, bool fp32,
-                        hipStream_t s) {
+void launch_resid_batch(const PlanDev &P, const void *targs, const int4 *items, int n_items,
+                        bool fp32, hipStream_t s) {
   const TArgs *ta = reinterpret_cast<const TArgs *>(targs);
-  if (fp32) hipLaunchKernelGGL(k_resid_batch<float>, dim3(n_items), dim3(kRWaves * 64), 0, s, ta, items);
-  else hipLaunchKernelGGL(k_resid_batch<double>, dim3(n_items), dim3(kRWaves * 64), 0, s, ta, items);
+  auto go = [&](auto fo) {
+    constexpr int FO = decltype(fo)::value;
+    if (fp32)
+      hipLaunchKernelGGL((k_resid_batch<float, FO>), dim3(n_items), dim3(kRWaves * 64), 0, s, ta, items);
+    else
+      hipLaunchKernelGGL((k_resid_batch<double, FO>), dim3(n_items), dim3(kRWaves * 64), 0, s, ta, items);
+  };
+  // a batch shares its options
+  switch (face_order(P)) {
+    case kFaceFirst: go(std::integral_constant<int, kFaceFirst>()); break;
+    case kFaceSecond: go(std::integral_constant<int, kFaceSecond>()); break;
+    default: go(std::integral_constant<int, kFaceLimited>());
+  }
 }
 
 void launch_chain_batch(const void *targs, const int2 *items, int n_items, int *counter, int cfg,

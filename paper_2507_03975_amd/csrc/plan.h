@@ -147,5 +147,8 @@ struct Pack {
 gsis_status make_single_set(gsis_plan *pl);
 // Frees the adjoint's host-side state (device memory goes with the plan).
 void adjoint_release(gsis_plan *pl);
+// gsis_plan_create for one of `share` plans that run together.
+gsis_status plan_create_shared(gsis_ctx *ctx, const gsis_problem *p, const gsis_options *o,
+                               int share, gsis_plan **out);
 // gsis_plan_reset without the wait at its end.
 gsis_status plan_reset_enqueue(gsis_plan *pl);
