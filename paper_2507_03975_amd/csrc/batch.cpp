@@ -175,6 +175,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
   int max_lc = 0, min_lc = 1 << 30;
   bool any_sep = false;
   size_t lds = 0;
+  int cells = 0;
   for (int a = 0; a < n; ++a) {
     const PlanDev &P = b->subs[act[a]]->P;
     D[a] = make_synth_desc(P);
@@ -183,6 +184,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
     min_lc = std::min(min_lc, D[a].lc);
     any_sep = any_sep || D[a].coef_sep != 0;
     lds = std::max(lds, P.S.coarse_lds);
+    cells = std::max(cells, P.S.coarse_cells);
   }
   {
     std::vector<char> dh(sizeof(SynthDesc) * std::max(n, 1));
@@ -195,6 +197,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
   S.max_lc = max_lc;
   S.min_lc = n ? min_lc : 0;
   S.coarse_lds = lds;
+  S.coarse_cells = cells;
   S.any_coef_sep = any_sep;
   S.state0 = nullptr;
   auto nb = [](long long m) { return (int)((m + 255) / 256); };

@@ -95,14 +95,19 @@ struct MGLevel {
 // problems (NULL table: a single problem, block = blockIdx.x).
 constexpr int kMaxLevels = 40;
 constexpr int kMaxCoarseLevels = 10;
-struct CoarseLevels {
-  int nlev;
-  int nx[kMaxCoarseLevels], ny[kMaxCoarseLevels], fx[kMaxCoarseLevels], fy[kMaxCoarseLevels];
-  const double *dg[kMaxCoarseLevels], *ax[kMaxCoarseLevels], *ay[kMaxCoarseLevels];
-  // LDS offsets (doubles): level 0 holds x, r; a level t >= 1 holds x, b,
-  // r and its operator (1/diag, ax, ay, diag at aoff + 0, n, 2n, 3n)
-  int xoff[kMaxCoarseLevels], boff[kMaxCoarseLevels], roff[kMaxCoarseLevels];
-  int aoff[kMaxCoarseLevels];
+// What the one-workgroup kernels need of a problem, one word per lane of a
+// wave: scalars, addresses (two words each), then four words per level from
+// the first coarse one: nx | ny << 16; LDS offset (doubles) of x | log2 of the
+// aggregates in bits 20 (x) and 21 (y); address of the operator (diag, ax, ay
+// one behind the other). LDS holds x and r of the top level, x, b, r and the
+// operator (4 n) of a lower one, in this order.
+// What a caller puts in place of the plan's own in a SynthDesc (state, rhs,
+// phi, level 0's x) is not in it.
+enum { kCwLast, kCwLc, kCwNb, kCwTile, kCwRrt, kCwRed, kCwScal = 7, kCwB0 = 9, kCwB1 = 11,
+       kCwX = 13, kCwInv = 15, kCwRtol = 17, kCwLev = 20 };
+static_assert(kCwLev + 4 * kMaxCoarseLevels <= 64, "a wave's lanes");
+struct CoarseRec {
+  int32_t w[64];
 };
 struct LevelDev {
   int nx, ny, fx, fy;
@@ -148,8 +153,7 @@ struct SynthDesc {
   int ntp;                      // slots of each tile-partial region: max(ntile0, cell blocks)
   int coef_sep;                 // 1: the CG coefficients come from k_cg_coef (many partials)
   LevelDev lev[kMaxLevels];
-  CoarseLevels cl;
-  const double *coarse_inv;
+  CoarseRec cl;
 };
 // Host-side description of one launch set (a plan, or a batch of plans).
 struct SynthSet {
@@ -158,6 +162,7 @@ struct SynthSet {
   int max_lc = 0;                     // deepest first coarse level
   int min_lc = 0;                     // shallowest first coarse level
   size_t coarse_lds = 0;              // dynamic LDS of the coarse kernel
+  int coarse_cells = 0;               // most cells of a first coarse level
   int synth_max_iter = 50;
   // block tables (nullptr for a single problem) and their block counts
   int2 *bt_cell = nullptr;            // level-0 cells of every problem
@@ -384,6 +389,7 @@ void launch_moments(const PlanDev &P, hipStream_t s, bool bflux);
 SynthDesc make_synth_desc(const PlanDev &P);
 int coarse_start(const PlanDev &P);
 size_t coarse_lds_bytes(const PlanDev &P);
+int coarse_cells(const PlanDev &P);   // of the first level of the one-workgroup cycle
 int tiles_of(int nx, int ny);   // multigrid tiles covering an nx x ny level
 int source_tiles_of(int nx, int ny);   // 16 x 16 tiles of the source kernel
 // tiles of the moment kernels: edge mt (16 or 32; moment_tile_size for a

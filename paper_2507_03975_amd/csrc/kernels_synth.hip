@@ -22,6 +22,7 @@
 // All reductions are two-stage with a fixed order, so results repeat bit for
 // bit, and a problem gets the same numbers alone or in a batch.
 #include "gsis_internal.h"
+#include "wave_ops.h"
 
 #include <algorithm>
 #include <cstring>
@@ -253,11 +254,10 @@ __device__ inline int n_rz(CDesc &D) { return D.lc == 0 ? nblk_d(D.N) : D.ntile0
 // flags), and the sum of all n partials: thread t adds p[t], p[t + blockDim],
 // ... in that order, then block_sum.
 __device__ inline double first_partial(const double *p, int n) {
-  return (int)threadIdx.x < n ? p[threadIdx.x] : 0.0;
+  return p[(int)threadIdx.x < n ? threadIdx.x : 0];   // sum_partials drops what is past n
 }
 __device__ inline double sum_partials(const double *p, int n, double *sh, double first) {
-  double v = 0.0;
-  v += first;
+  double v = (int)threadIdx.x < n ? first : 0.0;
   // sixteen loads in flight at a time, added in order (terms past n add 0)
   constexpr int U = 16;
   for (int t0 = threadIdx.x + blockDim.x; t0 < n; t0 += U * (int)blockDim.x) {
@@ -280,43 +280,63 @@ __device__ inline double sum_partials(const double *p, int n, double *sh, double
 // the block returns the same decision; thread 0 stores the scalars and the
 // flag. Its operands can be loaded early (rr_prefetch), before the caller
 // waits for its flags.
+struct RRTest {
+  const double *rr, *bb;       // partials
+  int nrr, nb;
+  bool first;
+  double *scal;
+  int32_t *state;
+  double rtol;
+};
 struct RRPre {
   double rr, bb, stop;
 };
-__device__ inline RRPre rr_prefetch(CDesc &D, bool first, bool tiles) {
-  const int nb = nblk_d(D.N);
+__device__ inline RRTest rr_test(CDesc &D, bool first, bool tiles) {
+  RRTest T;
+  T.nb = nblk_d(D.N);
+  T.rr = tiles ? red_rrt(D) : red_rr(D);
+  T.nrr = tiles ? D.ntile0 : T.nb;
+  T.bb = red_bb(D);
+  T.first = first;
+  T.scal = D.scal;
+  T.state = D.state;
+  T.rtol = D.rtol;
+  return T;
+}
+__device__ inline RRPre rr_prefetch(const RRTest &T) {
   RRPre q;
-  q.rr = tiles ? first_partial(red_rrt(D), D.ntile0) : first_partial(red_rr(D), nb);
-  q.bb = first ? first_partial(red_bb(D), nb) : 0.0;
-  q.stop = D.scal[S_STOP];
+  q.rr = first_partial(T.rr, T.nrr);
+  q.bb = T.first ? first_partial(T.bb, T.nb) : 0.0;
+  q.stop = T.scal[S_STOP];
   return q;
 }
-__device__ inline bool finish_rr(CDesc &D, bool first, bool tiles, double *sh, const RRPre &q) {
-  const int nb = nblk_d(D.N);
-  const double rr = tiles ? sum_partials(red_rrt(D), D.ntile0, sh, q.rr)
-                          : sum_partials(red_rr(D), nb, sh, q.rr);
-  double stop;
-  double bb = 0.0;
-  if (first) {
-    bb = sum_partials(red_bb(D), nb, sh, q.bb);
-    stop = fmax(D.rtol * D.rtol * rr, 1e-28 * bb);
-  } else {
-    stop = q.stop;
+__device__ inline RRPre rr_prefetch(CDesc &D, bool first, bool tiles) {
+  return rr_prefetch(rr_test(D, first, tiles));
+}
+__device__ inline bool finish_rr(const RRTest &T, double *sh, const RRPre &q) {
+  const double rr = sum_partials(T.rr, T.nrr, sh, q.rr);
+  double stop = q.stop, bb = 0.0;
+  if (T.first) {
+    bb = sum_partials(T.bb, T.nb, sh, q.bb);
+    stop = fmax(T.rtol * T.rtol * rr, 1e-28 * bb);
   }
   const bool conv = !(rr > stop);
   if (threadIdx.x == 0) {
-    double *scal = D.scal;
+    double *scal = T.scal;
     scal[S_RR] = rr;
-    if (first) {
+    if (T.first) {
       scal[S_BB] = bb;
       scal[S_STOP] = stop;
     }
-    const double nit = first ? 0.0 : scal[S_NIT] + 1.0;
+    const double nit = T.first ? 0.0 : scal[S_NIT] + 1.0;
     scal[S_NIT] = nit;
     // converged: 1 + the CG iterations it took (the host's next check point)
-    if (conv) D.state[3] = 1 + (int32_t)nit;
+    if (conv) T.state[3] = 1 + (int32_t)nit;
   }
   return conv;
+}
+__device__ inline bool finish_rr(CDesc &D, bool first, bool tiles, double *sh, const RRPre &q) {
+  return finish_rr(rr_test(D, first, tiles), sh, q);
 }
 
 // The r.r test of the last CG iteration when the iteration cap ends the
@@ -949,28 +969,44 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up0(const SynthDesc *ds, const
 }
 
 // The coarse end of the V-cycle (every level from the first with at most
-// kCoarseWG cells down to the dense solve) in one workgroup of 1024 threads
-// per problem, so the half sweeps are separated by workgroup barriers
-// instead of kernel launches.
-//  * Each half sweep runs over the cells of one colour only: thread t takes
-//    the colour's cells number t, t + 1024 (colour_cell), so no lane idles
-//    on a cell of the other colour. Diagonals are applied as precomputed
-//    reciprocals.
-//  * The top coarse level keeps its cells' operator rows and right-hand
-//    side in registers (at most 2 cells of each colour per thread); lower
-//    levels keep theirs in LDS. Vectors live in LDS.
-//  * After the second (black) half sweep from zero the black residuals
-//    vanish, so only red cells form a residual for the restriction.
+// kCoarseCells cells down to the dense solve) in one workgroup per problem,
+// so the half sweeps are separated by workgroup barriers instead of kernel
+// launches. Bound by latency: loads and index arithmetic until the first half
+// sweep (12,000 of 25,000 cycles), then some twenty phases of 400 to 1100.
+// 64 x 64 below 128 x 128: 16.7 us before, 10.7 us; 50 x 50: 16.5 to 10.1 us.
+// On the way there: 13.1 us with 512 threads and pairs alone, 12.0 with the
+// planes, 10.7 with the shared offsets; with 1024 threads and as much owned the
+// registers spill (20 us).
+//  * 512 threads with 256 registers each rather than 1024 with 128: half the
+//    waves meet at a barrier, and what a thread holds once (places, the
+//    dense inverse's part, the owned lower levels) it holds for twice the
+//    cells.
+//  * Thread t owns the top level's pairs of cells (2 p, 2 p + 1), p = t + 512
+//    m: one of each colour, so no lane idles in a half sweep, and two
+//    neighbouring values per load. It owns pair t of the next two levels
+//    (those of at most 512 pairs). Owned operators and right-hand sides stay
+//    in registers and a phase is the reads of four neighbours from LDS.
+//    Levels below keep theirs in LDS. Vectors live in LDS.
+//  * The top level's x lies in two planes, one per colour, cell c at c / 2.
+//    The neighbours of a cell are in the other plane, at the same place, one
+//    to the side and half a row up and down: neighbouring lanes read
+//    neighbouring words, and with zeros around the planes no edge is a case
+//    of its own.
+//  * After the second (black) half sweep from zero the black residuals vanish
+//    and a red one is the sum of its couplings times the black values (what
+//    it was from zero, b - d (b / d), is 0). The black cells start at 0: a
+//    missing neighbour reads the cell itself, times a zero coupling, which
+//    must not find what the LDS held before.
 //  * Going up, the black half sweep reads its red neighbours with the
 //    scaled coarse correction added (x + omega e, formed where it is read:
 //    the corrected values of black cells are never read), then the red half
 //    sweep recomputes the red cells, as in the tile kernels.
 //  * The restriction of a level's residuals also makes the next level's
-//    first (red, from zero) half sweep, and below the top level it forms the
-//    red residuals where it reads them, so each level costs two barriers
-//    going down and two going up.
-constexpr int kCoarseWG = 4096;
-constexpr int kCoarseThreads = 1024;
+//    first (red, from zero) half sweep.
+//  * Two waves share a SIMD, so 500 instructions of index arithmetic are 4000
+//    cycles: addresses are 32-bit offsets shared by the arrays of a level.
+constexpr int kCoarseThreads = 512;
+constexpr int kCoarseCells = 8 * kCoarseThreads;
 
 // Cell number e of colour k ((i + j) & 1 == k) of an nx x ny grid, cells of
 // a colour numbered row by row. Rows come in pairs holding nx cells of each
@@ -984,150 +1020,470 @@ __device__ inline bool colour_cell(int e, int k, int nx, int ny, int &i, int &j)
   return j < ny;
 }
 
-// One cell of the top coarse level held by a thread.
-struct OwnCell {
-  int c, cE, cW, cN, cS;       // index; neighbour indices (itself when missing)
-  int pE, pW, pN, pS;          // the neighbours' parents on the next level
-  bool ok;
-  double d, id, aE, aW, aN, aS, b;
+// Two consecutive cells of a level below the top that a thread owns, by
+// colour (0 red, 1 black; in this order of cells colours alternate, also from
+// one row to the next when nx is odd), and the LDS places of them and of their
+// neighbours. The other cell of the pair is the neighbour in the row on one
+// side (not across a row's end: zero coupling), o the one on the other side. A
+// neighbour that does not exist is given the cell's own place, with a zero
+// coupling; so has a last cell without its other one (right-hand side 0).
+struct Pair {
+  int c[2], o[2], n[2], s[2];
+  int pc;                      // parent of the black cell on the next level
+  int f;                       // flags below
+  double id[2], aP, aO[2], aN[2], aS[2];
+};
+// kOk: the pair exists; kLB: its first (left) cell is black; kTwo: the right
+// cell exists. Parents of the black cell's neighbours that differ from its
+// own: kPP the other cell's, kPO the outer one's, kPN, kPS north and south.
+// kWrap: the pair across the first row's end
+enum { kOk = 1, kLB = 2, kTwo = 4, kPP = 8, kPO = 16, kPN = 32, kPS = 64, kWrap = 128 };
+typedef double dbl2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// The problem's record for these kernels (CoarseRec in lane k's word k): read
+// by one vector load instead of a chain of scalar ones.
+typedef const __attribute__((address_space(1))) double *gdbl;
+typedef const __attribute__((address_space(1))) dbl2 *gdbl2;
+typedef const __attribute__((address_space(1))) char *gchr;
+// one or two values at a byte offset (an address register pair for the base,
+// one 32-bit register for the offset)
+__device__ __forceinline__ double ld1(gdbl b, unsigned o) { return *(gdbl)((gchr)b + o); }
+__device__ __forceinline__ dbl2 ld2(gdbl b, unsigned o) { return *(gdbl2)((gchr)b + o); }
+__device__ __forceinline__ int coarse_words(const SynthDesc *ds) {
+  const int *w = (const int *)&ds[blockIdx.x].cl;
+  return w[threadIdx.x & 63];
+}
+// margin around the top level's planes: half a row, and one
+__host__ __device__ inline int coarse_margin(int nx, int ny) {
+  return 1 + (ny > 1 ? (nx + 1) / 2 : 0);
+}
+// LDS of the top level: three margins, the planes, r
+inline int coarse_top_words(int nx, int ny, bool only) {
+  const int n = nx * ny, h = (n + 1) / 2;
+  return 3 * coarse_margin(nx, ny) + 2 * h + (only ? n : h);
+}
+// A level: sizes, log2 of the aggregates, LDS offsets (doubles) of x, b, r
+// and the operator (1/diag, ax, ay, diag). The top level has x, r and, between
+// three margins of zeros, planes of h places, s apart,
+// black after red; its r is the red plane's (in order and of both colours when
+// there is no other level).
+struct Lev {
+  int nx, ny, n, sx, sy, x, b, r, a, h, pad, s;
 };
 
-__global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *ds, double omega,
-                                                              int vc, int rr_ext) {
-  extern __shared__ double sm[];
-  __shared__ double red[kCoarseThreads];
-  CDesc &D = cdesc(ds, blockIdx.x);
-  // a problem whose V-cycle starts here or on level 1 makes the r.r test of
-  // the CG step before it here (level 1: the level-0 tile kernel made the
-  // update)
-  const bool fin = D.lc == 0 || (D.lc == 1 && !rr_ext);   // rr_ext: k_rr_test made it
-  RRPre q = {0.0, 0.0, 0.0};
-  if (fin) q = rr_prefetch(D, vc == 0, vc > 0 && D.lc == 1);
-  if (cg_off(D.state)) return;
-  if (fin && finish_rr(D, vc == 0, vc > 0 && D.lc == 1, red, q)) return;
-  __attribute__((address_space(4))) const CoarseLevels &L = D.cl;
-  const double *bin = D.lc == 0 ? cg_rv(D, vc) : D.lev[D.lc].b;
-  double *xout = D.lc == 0 ? D.cg_z : D.lev[D.lc].x;
-  const double *Ainv = D.coarse_inv;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int last = L.nlev - 1;
-  const int nx0 = L.nx[0], ny0 = L.ny[0];
-  auto X = [&](int t) { return sm + L.xoff[t]; };
-  auto Bv = [&](int t) { return sm + L.boff[t]; };
-  auto Rv = [&](int t) { return sm + L.roff[t]; };
-  // ---- top level: own cells (colour k, slot m) with their operator rows
-  OwnCell own[2][2];
+// M: top pairs per thread; OM: owned levels below the top at most
+template <int M, int OM>
+struct CoarseWG {
+  double *sm;
+  const int hdr, tid;          // word tid & 63 of the record; thread
+  const int last;              // the coarsest level
+  int ol;                      // levels 1 .. ol are owned by threads
+  const double omega;
+  // the top level's pairs, by colour; places of the neighbours in the other
+  // plane, relative to the pair's: outer at to (red), -to (black), north at tg
+  // (red), th (black), south at -th (red), -tg (black)
+  double ti[2][M], tP[M], tO[2][M], tN[2][M], tS[2][M];   // 1 / diagonal, couplings
+  double tb[2][M];             // right-hand side
+  double td[2][M];             // diagonal
+  int to[M], tg[M], th[M];
+  int tij[M];                  // the left cell's i | j << 16
+  Pair lo[OM];
+  double lb[2][OM];
+  int lch[2][OM];              // red children (two 16-bit indices, kNone)
+  int dch;                     // of cell tid of level ol + 1
+  double ainv[8];
+  double ay0[OM + 1];          // the owned levels' first ay
+  int nd;
+  int lw[OM + 2][2];           // records of the top, the owned levels and the next
+  gdbl ldg[OM + 1];
+  Lev low, end;                // the first level not owned, the coarsest
+  static constexpr int kNone = 0xffff;
+
+  __device__ __forceinline__ CoarseWG(int h, double *s, double om)
+      : sm(s), hdr(h), tid(threadIdx.x), last(word(kCwLast)), omega(om) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      OwnCell &o = own[k][m];
-      int i = 0, j = 0;
-      o.ok = colour_cell(tid + m * nt, k, nx0, ny0, i, j);
-      if (!o.ok) { i = 0; j = 0; }
-      const int c = j * nx0 + i;
-      const bool hE = o.ok && i + 1 < nx0, hW = o.ok && i > 0;
-      const bool hN = o.ok && j + 1 < ny0, hS = o.ok && j > 0;
-      o.c = c;
-      o.cE = hE ? c + 1 : c; o.cW = hW ? c - 1 : c;
-      o.cN = hN ? c + nx0 : c; o.cS = hS ? c - nx0 : c;
-      if (last > 0) {
-        const int sx = L.fx[0] >> 1, sy = L.fy[0] >> 1, cnx = L.nx[1];
-        const int iE = hE ? i + 1 : i, iW = hW ? i - 1 : i, jN = hN ? j + 1 : j, jS = hS ? j - 1 : j;
-        o.pE = (j >> sy) * cnx + (iE >> sx); o.pW = (j >> sy) * cnx + (iW >> sx);
-        o.pN = (jN >> sy) * cnx + (i >> sx); o.pS = (jS >> sy) * cnx + (i >> sx);
-      } else {
-        o.pE = o.pW = o.pN = o.pS = 0;
-      }
-      o.d = o.ok ? L.dg[0][c] : 1.0;
-      o.aE = hE ? L.ax[0][c] : 0.0; o.aW = hW ? L.ax[0][c - 1] : 0.0;
-      o.aN = hN ? L.ay[0][c] : 0.0; o.aS = hS ? L.ay[0][c - nx0] : 0.0;
-      o.b = o.ok ? bin[c] : 0.0;
+    for (int t = 0; t < OM + 2; ++t) {
+      lw[t][0] = word(kCwLev + 4 * t);
+      lw[t][1] = word(kCwLev + 4 * t + 1);
+      if (t <= OM) ldg[t] = (gdbl)ptr(kCwLev + 4 * t + 2);
     }
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) own[k][m].id = 1.0 / own[k][m].d;
-  // the coarsest level's dense inverse (n <= 64) in registers
-  const int nd = L.nx[last] * L.ny[last];
-  double ainv[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int row = tid >> 4, col = (tid & 15) + 16 * q;
-    ainv[q] = (row < nd && col < nd) ? Ainv[(size_t)row * nd + col] : 0.0;
+    const int n1 = lev(1).n, n2 = lev(2).n;
+    ol = 0;
+    if (OM >= 1 && last > 1 && n1 <= 2 * kCoarseThreads) ol = 1;
+    if (OM >= 2 && ol == 1 && last > 2 && n2 <= 2 * kCoarseThreads) ol = 2;
+    low = lev_at(ol + 1);
+    end = lev_at(last);
+    nd = end.n;
   }
-  // lower levels' operators into LDS (reciprocal diagonal, ax, ay, diagonal)
-  for (int t = 1; t < L.nlev; ++t) {
-    const int n = L.nx[t] * L.ny[t];
-    double *a = sm + L.aoff[t];
-    for (int c = tid; c < n; c += nt) {
-      const double d = L.dg[t][c];
-      a[c] = 1.0 / d; a[n + c] = L.ax[t][c]; a[2 * n + c] = L.ay[t][c]; a[3 * n + c] = d;
+  // The record's words come from one lane each, not from memory: read where
+  // all lanes are active.
+  __device__ __forceinline__ int word(int k) const { return __builtin_amdgcn_readlane(hdr, k); }
+  __device__ __forceinline__ unsigned long long ptr(int k) const {
+    return (unsigned long long)(unsigned)word(k) | (unsigned long long)(unsigned)word(k + 1) << 32;
+  }
+  static __device__ __forceinline__ Lev decode(int w0, int w1, bool first) {
+    Lev l;
+    l.nx = w0 & 0xffff;
+    l.ny = (unsigned)w0 >> 16;
+    l.n = l.nx * l.ny;
+    l.sx = (w1 >> 20) & 1;
+    l.sy = (w1 >> 21) & 1;
+    l.x = w1 & 0xfffff;
+    l.b = l.x + l.n;
+    l.r = l.b + l.n;
+    l.a = l.r + l.n;
+    l.h = l.pad = l.s = 0;
+    if (first) {
+      l.h = (l.n + 1) >> 1;
+      l.pad = coarse_margin(l.nx, l.ny);
+      l.s = l.h + l.pad;
+      l.r = l.x + 2 * l.s + l.pad;
+      l.x += l.pad;
+    }
+    return l;
+  }
+  __device__ __forceinline__ Lev lev(int t) const {   // t known at compile time, <= OM + 1
+    if (t > OM + 1) return lev_at(t);
+    return decode(lw[t][0], lw[t][1], t == 0);
+  }
+  __device__ __forceinline__ Lev lev_at(int t) const {
+    return decode(word(kCwLev + 4 * t), word(kCwLev + 4 * t + 1), t == 0);
+  }
+
+  __device__ __forceinline__ RRTest rr_test(bool first, bool tiles, int32_t *state) const {
+    const int nb = word(kCwNb);
+    const double *red = (const double *)(gdbl)ptr(kCwRed);
+    RRTest T;
+    T.rr = tiles ? red + word(kCwRrt) : red;
+    T.nrr = tiles ? word(kCwTile) : nb;
+    T.bb = red + nb;
+    T.nb = nb;
+    T.first = first;
+    T.scal = (double *)(__attribute__((address_space(1))) double *)ptr(kCwScal);
+    T.state = state;
+    T.rtol = __longlong_as_double((long long)ptr(kCwRtol));
+    return T;
+  }
+
+  // Pair p of level t > 0, its left cell at (i, j): loads of the operator, by
+  // place (left 0, right 1; the left cell's west coupling in aO[0], the right
+  // cell's east one in aO[1]) until sort() orders them by colour, and the
+  // places meanwhile. Couplings across a grid's edge are stored as zeros (ax
+  // at the end of each row, ay on the last row): those of the west and south
+  // edges are read there. A last cell on its own loads one value past the
+  // level's arrays: they lie one behind the other, and the device pieces they
+  // lie in end on 256 bytes.
+  __device__ __forceinline__ void own(Pair &q, int t, int p, int i, int j) {
+    const Lev v = lev(t);
+    const int nx = v.nx, ny = v.ny, n = v.n, l = 2 * p;
+    const gdbl dg = ldg[t], ax = dg + n, ay = ax + n;
+    const bool W = i > 0, SL = j > 0;
+    const unsigned o = 8u * l;
+    const dbl2 d = ld2(dg, o), x = ld2(ax, o), y = ld2(ay, o);
+    const dbl2 u = ld2(ay, o + 8u * (SL ? -nx : n - nx));
+    q.aO[0] = ld1(ax, o + 8u * (W ? -1 : nx - 1));
+    q.id[0] = d.x; q.id[1] = d.y;
+    q.aP = x.x; q.aO[1] = x.y;
+    q.aN[0] = y.x; q.aN[1] = y.y;
+    q.aS[0] = u.x; q.aS[1] = u.y;
+    const bool in = i + 1 < nx, two = l + 1 < n;   // in: both in one row
+    const int ir = in ? i + 1 : 0, jr = in ? j : j + 1;
+    const bool E = two && ir + 1 < nx, SR = two && jr > 0;
+    const bool NL = j + 1 < ny, NR = two && jr + 1 < ny, lbk = (i + j) & 1;
+    const int oL = W ? -1 : 0, oR = E ? 1 : 0;
+    const int r = two ? l + 1 : l;
+    const int nL = NL ? nx : 0, nR = NR ? nx : 0, sL = SL ? nx : 0, sR = SR ? nx : 0;
+    q.c[0] = lbk ? r : l; q.c[1] = lbk ? l : r;
+    q.o[0] = q.c[0] + (lbk ? oR : oL); q.o[1] = q.c[1] + (lbk ? oL : oR);
+    q.n[0] = q.c[0] + (lbk ? nR : nL); q.n[1] = q.c[1] + (lbk ? nL : nR);
+    q.s[0] = q.c[0] - (lbk ? sR : sL); q.s[1] = q.c[1] - (lbk ? sL : sR);
+    q.f = kOk | (lbk ? kLB : 0) | (two ? kTwo : 0) | (!in && !SL ? kWrap : 0);
+    // with aggregates of two, the odd cell's next and the even cell's
+    // previous neighbour have another parent; of one, every neighbour
+    const int sx = v.sx, sy = v.sy, cnx = lev(t + 1).nx;
+    const int ib = lbk ? i : ir, jb = lbk ? j : jr;
+    const bool N = lbk ? NL : NR, S = lbk ? SL : SR;
+    q.pc = lbk || two ? (jb >> sy) * cnx + (ib >> sx) : 0;
+    const bool xo = !sx || (ib & 1), xe = !sx || !(ib & 1);
+    const bool yo = !sy || (jb & 1), ye = !sy || !(jb & 1);
+    q.f |= (two && in && (lbk ? xo : xe) ? kPP : 0) | ((lbk ? W && xe : E && xo) ? kPO : 0) |
+           (N && yo ? kPN : 0) | (S && ye ? kPS : 0);
+  }
+  // the loaded operator by colour, the diagonal inverted
+  __device__ __forceinline__ void sort(Pair &q, int t) {
+    const bool lbk = q.f & kLB, two = q.f & kTwo;
+    const double e = two ? q.aO[1] : 0.0, w = q.aO[0], nl = q.aN[0], sl = q.aS[0];
+    const double nr = two ? q.aN[1] : 0.0;
+    const double sr = !two ? 0.0 : q.f & kWrap ? ay0[t] : q.aS[1];
+    const double dl = q.id[0], dr = two ? q.id[1] : 1.0;
+    q.aO[0] = lbk ? e : w; q.aO[1] = lbk ? w : e;
+    q.aN[0] = lbk ? nr : nl; q.aN[1] = lbk ? nl : nr;
+    q.aS[0] = lbk ? sr : sl; q.aS[1] = lbk ? sl : sr;
+    q.id[0] = rcp64(lbk ? dr : dl);
+    q.id[1] = rcp64(lbk ? dl : dr);
+  }
+  // The top level's pairs: loads as for own() and, where b is not NULL, of
+  // the right-hand side (a thread without an m-th pair loads pair 0).
+  __device__ __forceinline__ void own_top(gdbl b) {
+    const Lev v = lev(0);
+    const int nx = v.nx, n = v.n;
+    const gdbl dg = ldg[0], ax = dg + n, ay = ax + n;
+    // the left cell of pair tid, and the step to that of pair tid + 512: in
+    // pairs of an even row, in cells of an odd one
+    const int odd = nx & 1, u = odd ? nx : nx >> 1, ha = v.ny > 1 ? nx >> 1 : 0;
+    const int hb = v.ny > 1 ? nx - ha : 0;
+    int r, j, dr, dj;
+    cell_ij(tid << odd, u, r, j);
+    cell_ij(kCoarseThreads << odd, u, dr, dj);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int p = tid + m * kCoarseThreads;
+      const int i = odd ? r : 2 * r;
+      const unsigned o = p < v.h ? 16u * p : 0u;
+      const int ii = p < v.h ? i : 0, jj = p < v.h ? j : 0;
+      const dbl2 d = ld2(dg, o), x = ld2(ax, o), y = ld2(ay, o);
+      const dbl2 w = ld2(ay, o + 8u * (jj > 0 ? -nx : n - nx));
+      tO[0][m] = ld1(ax, o + 8u * (ii > 0 ? -1 : nx - 1));
+      dbl2 bb = {0.0, 0.0};
+      if (b) bb = ld2(b, o);
+      ti[0][m] = d.x; ti[1][m] = d.y;
+      tP[m] = x.x; tO[1][m] = x.y;
+      tN[0][m] = y.x; tN[1][m] = y.y;
+      tS[0][m] = w.x; tS[1][m] = w.y;
+      tb[0][m] = bb.x; tb[1][m] = bb.y;
+      const bool lbk = (i + j) & 1;
+      tij[m] = i | j << 16;
+      to[m] = lbk ? 1 : -1;
+      tg[m] = lbk ? hb : ha;
+      th[m] = lbk ? ha : hb;
+      r += dr;
+      j += dj;
+      if (r >= u) { r -= u; ++j; }
+    }
+    ay0[0] = ld1(ay, 0);
+  }
+  __device__ __forceinline__ void sort_top() {
+    const Lev v = lev(0);
+    if (v.nx & 1) {
+      // a last cell without its other one; the pair across the first row's
+      // end, whose right cell's south coupling is the first of ay
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int p = tid + m * kCoarseThreads;
+        if (2 * p == v.nx - 1) tS[1][m] = ay0[0];
+        if (2 * p + 1 >= v.n) {
+          tO[1][m] = tN[1][m] = tS[1][m] = tb[1][m] = 0.0;
+          ti[1][m] = 1.0;
+        }
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const bool lbk = to[m] > 0;
+      auto by_colour = [&](double (&a)[2][M]) {
+        const double l = a[0][m], r = a[1][m];
+        a[0][m] = lbk ? r : l;
+        a[1][m] = lbk ? l : r;
+      };
+      by_colour(tO);
+      by_colour(tN);
+      by_colour(tS);
+      by_colour(tb);
+      by_colour(ti);
+      td[0][m] = ti[0][m];
+      td[1][m] = ti[1][m];
+      ti[0][m] = rcp64(ti[0][m]);
+      ti[1][m] = rcp64(ti[1][m]);
     }
   }
-  // ---- top-level pieces
-  double *x0 = X(0), *r0 = Rv(0);
-  auto top_half = [&](int k, bool zero) {
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const OwnCell &o = own[k][m];
-      if (!o.ok) continue;
-      double s = o.b;
-      if (!zero) {
-        s = fma(o.aE, x0[o.cE], s);
-        s = fma(o.aW, x0[o.cW], s);
-        s = fma(o.aN, x0[o.cN], s);
-        s = fma(o.aS, x0[o.cS], s);
-      }
-      x0[o.c] = s * o.id;
+  __device__ __forceinline__ bool has(int m) const {
+    return tid + m * kCoarseThreads < lev(0).h;
+  }
+  // the place of the pair's cell of colour k
+  __device__ __forceinline__ double *at(int k, int m) const {
+    const Lev v = lev(0);
+    return sm + v.x + (k ? v.s : 0) + tid + m * kCoarseThreads;
+  }
+  // s + sum of the couplings of the top pair's cell of colour k times x
+  __device__ __forceinline__ double add_top(int k, int m, double s) const {
+    const double *x = at(1 - k, m);
+    const double a = x[0], b = x[k ? -to[m] : to[m]];
+    const double n = x[k ? th[m] : tg[m]], u = x[-(k ? tg[m] : th[m])];
+    s = fma(tP[m], a, s);
+    s = fma(tO[k][m], b, s);
+    s = fma(tN[k][m], n, s);
+    return fma(tS[k][m], u, s);
+  }
+  // the same for the black cell with the scaled correction of the parents
+  // (e, on the next level) added to x
+  __device__ __forceinline__ double add_top_corr(int m, const double *e, double s) const {
+    const Lev v = lev(0), w = lev(1);
+    const double *x = at(0, m);
+    const double xp = x[0], xo = x[-to[m]], xn = x[th[m]], xs = x[-tg[m]];
+    const bool lbk = to[m] > 0;
+    int i = tij[m] & 0xffff, j = tij[m] >> 16;
+    if (!lbk) ++i;
+    if (i >= v.nx) { i = 0; j = min(j + 1, v.ny - 1); }
+    // parents of the neighbours (of one within the grid where there is none)
+    const int I = i >> v.sx, row = (j >> v.sy) * w.nx;
+    const int ie = min((i + 1) >> v.sx, w.nx - 1), iw = max(i - 1, 0) >> v.sx;
+    const int jn = min((j + 1) >> v.sy, w.ny - 1), js = max(j - 1, 0) >> v.sy;
+    const double ep = e[row + (lbk ? ie : iw)], eo = e[row + (lbk ? iw : ie)];
+    const double en = e[jn * w.nx + I], es = e[js * w.nx + I];
+    s = fma(tP[m], fma(omega, ep, xp), s);
+    s = fma(tO[1][m], fma(omega, eo, xo), s);
+    s = fma(tN[1][m], fma(omega, en, xn), s);
+    return fma(tS[1][m], fma(omega, es, xs), s);
+  }
+  // x of the pair's cell k on an owned level below the top (not of a missing
+  // cell: it has the other one's place)
+  __device__ __forceinline__ void put(double *x, const Pair &q, int k, double v) {
+    if ((q.f & kTwo) || k == (q.f & kLB ? 1 : 0)) x[q.c[k]] = v;
+  }
+  // s + sum of the couplings of the pair's cell k times x of its neighbours
+  __device__ __forceinline__ double add_nb(const Pair &q, int k, const double *x, double s) {
+    const double a = x[q.c[1 - k]], b = x[q.o[k]], n = x[q.n[k]], u = x[q.s[k]];
+    s = fma(q.aP, a, s);
+    s = fma(q.aO[k], b, s);
+    s = fma(q.aN[k], n, s);
+    return fma(q.aS[k], u, s);
+  }
+  // the same for the black cell with the scaled correction e of the parents
+  // added to x
+  __device__ __forceinline__ double add_nb_corr(const Pair &q, int cnx, const double *x,
+                                                const double *e, double s) {
+    const double xp = x[q.c[0]], xo = x[q.o[1]], xn = x[q.n[1]], xs = x[q.s[1]];
+    const int dir = q.f & kLB ? 1 : -1;      // to the other cell
+    const double ep = e[q.pc + (q.f & kPP ? dir : 0)], eo = e[q.pc - (q.f & kPO ? dir : 0)];
+    const double en = e[q.pc + (q.f & kPN ? cnx : 0)], es = e[q.pc - (q.f & kPS ? cnx : 0)];
+    s = fma(q.aP, fma(omega, ep, xp), s);
+    s = fma(q.aO[1], fma(omega, eo, xo), s);
+    s = fma(q.aN[1], fma(omega, en, xn), s);
+    return fma(q.aS[1], fma(omega, es, xs), s);
+  }
+  // the red children on level v (first: the top) of cell (I, J) of the next
+  static __device__ __forceinline__ int red_children(const Lev &v, bool first, int I, int J) {
+    const int nx = v.nx, ny = v.ny, fx = 1 + v.sx, fy = 1 + v.sy;
+    const int i = fx * I, j = fy * J;
+    int a = kNone, b = kNone;
+    if (!((i + j) & 1)) {
+      a = j * nx + i;
+      if (fx > 1 && fy > 1 && i + 1 < nx && j + 1 < ny) b = a + nx + 1;
+    } else {                   // fx or fy is 1: the other child is red
+      if (fx > 1 && i + 1 < nx) a = j * nx + i + 1;
+      if (fy > 1 && j + 1 < ny) a = (j + 1) * nx + i;
     }
-  };
-  // level t >= 1: half sweep of colour k over the colour's cells
-  auto low_half = [&](int t, int k, bool zero) {
-    const int nx = L.nx[t], ny = L.ny[t], n = nx * ny;
-    double *x = X(t);
-    const double *b = Bv(t), *id = sm + L.aoff[t], *ax = id + n, *ay = id + 2 * n;
-    for (int e = tid; 2 * e < n + 1; e += nt) {
+    if (first) {               // the residuals of the red plane only
+      if (a != kNone) a >>= 1;
+      if (b != kNone) b >>= 1;
+    }
+    return a | b << 16;
+  }
+  __device__ __forceinline__ double child_sum(int ch, const double *r) {
+    const unsigned a = ch & 0xffff, b = (unsigned)ch >> 16;
+    const double u = r[a != kNone ? a : 0], v = r[b != kNone ? b : 0];
+    const double s = a != kNone ? u : 0.0;
+    return b != kNone ? s + v : s;
+  }
+
+  // Loads of the owned levels (of the top right-hand side where b is not
+  // NULL) and of the dense inverse, and the places while they are under way.
+  __device__ __forceinline__ void begin(gdbl b) {
+    own_top(b);
+#pragma unroll
+    for (int t = 1; t <= OM; ++t) {
+      if (t > ol) break;
+      const Lev v = lev(t), u = lev(t - 1);
+      Pair &q = lo[t - 1];
+      q.f = 0;
+      ay0[t] = ld1(ldg[t], 16u * v.n);
+      if (2 * tid < v.n) {
+        int i, j;
+        cell_ij(2 * tid, v.nx, i, j);
+        own(q, t, tid, i, j);
+        const bool in = i + 1 < v.nx, lbk = q.f & kLB;
+        const int cl = red_children(u, t == 1, i, j);
+        const int cr = q.f & kTwo
+                           ? red_children(u, t == 1, in ? i + 1 : 0, in ? j : j + 1) : -1;
+        lch[0][t - 1] = lbk ? cr : cl;
+        lch[1][t - 1] = lbk ? cl : cr;
+      }
+    }
+    // the coarsest level's dense inverse (n <= 64): 8 threads per row (terms
+    // past the row's end are dropped where they are used)
+    const gdbl Ainv = (gdbl)ptr(kCwInv);
+    {
+      const int a = (tid >> 3) * nd + (tid & 7), e = nd * nd - 1;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) ainv[q] = ld1(Ainv, 8u * min(a + 8 * q, e));
+    }
+    dch = -1;
+    if (last > 0) {
+      const Lev u = lev_at(ol);
+      const bool first = ol == 0;
+      if (tid < low.n) {
+        int i, j;
+        cell_ij(tid, low.nx, i, j);
+        dch = red_children(u, first, i, j);
+      }
+    }
+  }
+  // What was loaded put in place (a barrier before others' LDS).
+  __device__ __forceinline__ void settle() {
+    // deeper levels' operators into LDS (reciprocal diagonal, ax, ay, diagonal)
+    for (int t = ol + 1; t < last; ++t) {
+      const Lev v = lev_at(t);
+      const int n = v.n;
+      const gdbl dg = (gdbl)ptr(kCwLev + 4 * t + 2);
+      double *a = sm + v.a;
+      for (int c = tid; c < n; c += kCoarseThreads) {
+        const double d = dg[c], x = dg[n + c], y = dg[2 * n + c];
+        a[c] = rcp64(d); a[n + c] = x; a[2 * n + c] = y; a[3 * n + c] = d;
+      }
+    }
+    // the margins of the top level's planes
+    const Lev v = lev(0);
+    for (int c = tid; c < v.pad; c += kCoarseThreads) {
+      double *x = sm + v.x - v.pad + c;
+      x[0] = x[v.s] = x[2 * v.s] = 0.0;
+    }
+    sort_top();
+#pragma unroll
+    for (int t = 1; t <= OM; ++t) {
+      if (t > ol) break;
+      sort(lo[t - 1], t);
+    }
+  }
+
+  // level t > ol: half sweep of colour k over the colour's cells
+  __device__ __forceinline__ void low_half(int t, int k) {
+    const Lev v = lev_at(t);
+    const int nx = v.nx, ny = v.ny, n = v.n;
+    double *x = sm + v.x;
+    const double *b = sm + v.b, *id = sm + v.a, *ax = id + n, *ay = id + 2 * n;
+    for (int e = tid; 2 * e < n + 1; e += kCoarseThreads) {
       int i, j;
       if (!colour_cell(e, k, nx, ny, i, j)) break;
       const int c = j * nx + i;
       double s = b[c];
-      if (!zero) {
-        if (i + 1 < nx) s = fma(ax[c], x[c + 1], s);
-        if (i > 0) s = fma(ax[c - 1], x[c - 1], s);
-        if (j + 1 < ny) s = fma(ay[c], x[c + nx], s);
-        if (j > 0) s = fma(ay[c - nx], x[c - nx], s);
-      }
+      if (i + 1 < nx) s = fma(ax[c], x[c + 1], s);
+      if (i > 0) s = fma(ax[c - 1], x[c - 1], s);
+      if (j + 1 < ny) s = fma(ay[c], x[c + nx], s);
+      if (j > 0) s = fma(ay[c - nx], x[c - nx], s);
       x[c] = s * id[c];
     }
-  };
-  // black half sweep of the top level with the coarse correction of its red
-  // neighbours formed where they are read
-  auto top_black_corr = [&]() {
-    const double *e = X(1);
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const OwnCell &o = own[1][m];
-      if (!o.ok) continue;
-      double s = o.b;
-      s = fma(o.aE, fma(omega, e[o.pE], x0[o.cE]), s);
-      s = fma(o.aW, fma(omega, e[o.pW], x0[o.cW]), s);
-      s = fma(o.aN, fma(omega, e[o.pN], x0[o.cN]), s);
-      s = fma(o.aS, fma(omega, e[o.pS], x0[o.cS]), s);
-      x0[o.c] = s * o.id;
-    }
-  };
-  // the same on level t >= 1
-  auto low_black_corr = [&](int t) {
-    const int nx = L.nx[t], ny = L.ny[t], n = nx * ny, sx = L.fx[t] >> 1, sy = L.fy[t] >> 1;
-    const int cnx = L.nx[t + 1];
-    double *x = X(t);
-    const double *e = X(t + 1);
-    const double *b = Bv(t), *id = sm + L.aoff[t], *ax = id + n, *ay = id + 2 * n;
+  }
+  // level t > ol: black half sweep with the correction of its red neighbours
+  __device__ __forceinline__ void low_black_corr(int t) {
+    const Lev v = lev_at(t), w = lev_at(t + 1);
+    const int nx = v.nx, ny = v.ny, n = v.n, sx = v.sx, sy = v.sy, cnx = w.nx;
+    double *x = sm + v.x;
+    const double *e = sm + w.x;
+    const double *b = sm + v.b, *id = sm + v.a, *ax = id + n, *ay = id + 2 * n;
     auto xc = [&](int i, int j) {
       return fma(omega, e[(j >> sy) * cnx + (i >> sx)], x[j * nx + i]);
     };
-    for (int q = tid; 2 * q < n + 1; q += nt) {
+    for (int q = tid; 2 * q < n + 1; q += kCoarseThreads) {
       int i, j;
       if (!colour_cell(q, 1, nx, ny, i, j)) break;
       const int c = j * nx + i;
@@ -1138,128 +1494,207 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *d
       if (j > 0) s = fma(ay[c - nx], xc(i, j - 1), s);
       x[c] = s * id[c];
     }
-  };
-  // restriction of level t's residuals into b_{t+1} (level 0: the owners'
-  // residuals in r_0; below: the red residuals b - A x formed here, black
-  // ones being zero), and on a level t + 1 above the coarsest its red half
-  // sweep from zero, x = b / d
-  auto restrict_red = [&](int t) {
-    const int nx = L.nx[t], ny = L.ny[t], n = nx * ny, fx = L.fx[t], fy = L.fy[t];
-    const int cnx = L.nx[t + 1], cn = cnx * L.ny[t + 1];
-    const double *x = X(t), *b = Bv(t), *id = sm + L.aoff[t], *ax = id + n, *ay = id + 2 * n;
-    const double *dg = id + 3 * n, *r = Rv(t);
-    double *cb = Bv(t + 1), *cx = X(t + 1);
-    const double *cid = sm + L.aoff[t + 1];
-    const bool red_next = t + 1 < last;
-    for (int C = tid; C < cn; C += nt) {
-      int I, J;
-      cell_ij(C, cnx, I, J);
-      double v = 0.0;
-      for (int dj = 0; dj < fy; ++dj)
-        for (int di = 0; di < fx; ++di) {
-          const int i = fx * I + di, j = fy * J + dj;
-          if (i >= nx || j >= ny) continue;
-          const int c = j * nx + i;
-          double rv = 0.0;
-          if (t == 0) {
-            rv = r[c];
-          } else if (((i + j) & 1) == 0) {
-            double q = b[c];
-            if (i + 1 < nx) q = fma(ax[c], x[c + 1], q);
-            if (i > 0) q = fma(ax[c - 1], x[c - 1], q);
-            if (j + 1 < ny) q = fma(ay[c], x[c + nx], q);
-            if (j > 0) q = fma(ay[c - nx], x[c - nx], q);
-            rv = fma(-dg[c], x[c], q);
-          }
-          v += rv;
-        }
+  }
+  // level v below the owned ones: residual of cell c
+  __device__ __forceinline__ double low_resid(const Lev &v, int c) {
+    const int nx = v.nx, ny = v.ny, n = v.n;
+    const double *x = sm + v.x, *b = sm + v.b, *id = sm + v.a, *ax = id + n, *ay = id + 2 * n;
+    const double *dg = id + 3 * n;
+    int i, j;
+    cell_ij(c, nx, i, j);
+    double q = b[c];
+    if (i + 1 < nx) q = fma(ax[c], x[c + 1], q);
+    if (i > 0) q = fma(ax[c - 1], x[c - 1], q);
+    if (j + 1 < ny) q = fma(ay[c], x[c + nx], q);
+    if (j > 0) q = fma(ay[c - nx], x[c - nx], q);
+    return fma(-dg[c], x[c], q);
+  }
+  // restriction of a level's residuals (the red ones: black residuals vanish;
+  // r) to level t and, above the coarsest, its red half sweep from zero. To
+  // an owned level:
+  __device__ __forceinline__ void restrict_to_own(const double *r, int t, const Pair &q,
+                                                  const int (&ch)[2], double &b0, double &b1) {
+    double *x = sm + lev(t).x;
+    if (!(q.f & kOk)) return;
+    b0 = child_sum(ch[0], r);
+    b1 = child_sum(ch[1], r);
+    put(x, q, 0, b0 * q.id[0]);
+    put(x, q, 1, 0.0);
+  }
+  // from the last owned level (or the top) to the next
+  __device__ __forceinline__ void restrict_to_lds() {
+    const Lev u = lev_at(ol);
+    double *cb = sm + low.b, *cx = sm + low.x;
+    const double *cid = sm + low.a, *r = sm + u.r;
+    const bool sweep = ol + 1 < last, first = ol == 0;
+    for (int C = tid; C < low.n; C += kCoarseThreads) {
+      int I, J, ch = dch;
+      cell_ij(C, low.nx, I, J);
+      if (C != tid) ch = red_children(u, first, I, J);
+      const double v = child_sum(ch, r);
       cb[C] = v;
-      if (red_next && ((I + J) & 1) == 0) cx[C] = v * cid[C];
+      if (sweep) cx[C] = ((I + J) & 1) == 0 ? v * cid[C] : 0.0;
     }
-  };
-  __syncthreads();
-  if (last == 0) {
-    // the top level is the coarsest: dense solve only
+  }
+  // from level t to the next, both below them
+  __device__ __forceinline__ void low_restrict(int t) {
+    const Lev u = lev_at(t), w = lev_at(t + 1);
+    double *cb = sm + w.b, *cx = sm + w.x;
+    const double *cid = sm + w.a;
+    const bool sweep = t + 1 < last;
+    for (int C = tid; C < w.n; C += kCoarseThreads) {
+      int I, J;
+      cell_ij(C, w.nx, I, J);
+      const int ch = red_children(u, false, I, J), a = ch & 0xffff, b = (unsigned)ch >> 16;
+      double v = 0.0;
+      if (a != kNone) v += low_resid(u, a);
+      if (b != kNone) v += low_resid(u, b);
+      cb[C] = v;
+      if (sweep) cx[C] = ((I + J) & 1) == 0 ? v * cid[C] : 0.0;
+    }
+  }
+  // x = M^{-1} tb on the top level: each thread's own cells (a barrier before others')
+  __device__ __forceinline__ void cycle() {
+    const Lev v0 = lev(0), v1 = lev(1);
+    double *r0 = sm + v0.r;
+    const double *x1 = sm + v1.x;
+    if (last == 0) {
+      // the top level is the coarsest: dense solve only (r in order)
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-        if (own[k][m].ok) r0[own[k][m].c] = own[k][m].b;
-    __syncthreads();
-  } else {
-    // ---- down: top level, red from zero, black, red residuals, restrict.
-    // The black cells start at 0: a missing neighbour reads the cell itself
-    // (times a zero coupling), which must not find what the LDS held before
-    top_half(0, true);
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-      if (own[1][m].ok) x0[own[1][m].c] = 0.0;
-    __syncthreads();
-    top_half(1, false);
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const OwnCell &o = own[0][m];
-      if (o.ok) {
-        double s = o.b;
-        s = fma(o.aE, x0[o.cE], s);
-        s = fma(o.aW, x0[o.cW], s);
-        s = fma(o.aN, x0[o.cN], s);
-        s = fma(o.aS, x0[o.cS], s);
-        r0[o.c] = fma(-o.d, x0[o.c], s);
+      for (int m = 0; m < M; ++m) {
+        const int l = 2 * (tid + m * kCoarseThreads);
+        const bool lbk = to[m] > 0;
+        if (l < v0.n) r0[l] = tb[lbk ? 1 : 0][m];
+        if (l + 1 < v0.n) r0[l + 1] = tb[lbk ? 0 : 1][m];
+        if (has(m)) *at(0, m) = *at(1, m) = 0.0;   // also the place of a missing cell
       }
-      if (own[1][m].ok) r0[own[1][m].c] = 0.0;
-    }
-    __syncthreads();
-    restrict_red(0);
-    __syncthreads();
-    // lower levels: black, then the restriction (with the next level's red)
-    for (int t = 1; t < last; ++t) {
-      low_half(t, 1, false);
       __syncthreads();
-      restrict_red(t);
-      __syncthreads();
-    }
-  }
-  // ---- dense solve on the coarsest level: 16 threads per row
-  {
-    const double *b = last == 0 ? r0 : Bv(last);
-    const int row = tid >> 4, col0 = tid & 15;
-    double v = 0.0;
+    } else {
+      // ---- down: red from zero, black, red residuals, restrict
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = col0 + 16 * q;
-      if (row < nd && col < nd) v += ainv[q] * b[col];
+      for (int m = 0; m < M; ++m) {
+        if (!has(m)) continue;
+        *at(0, m) = tb[0][m] * ti[0][m];
+        *at(1, m) = 0.0;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+        if (has(m)) *at(1, m) = add_top(1, m, tb[1][m]) * ti[1][m];
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+        if (has(m)) r0[tid + m * kCoarseThreads] = add_top(0, m, 0.0);
+      __syncthreads();
+#pragma unroll
+      for (int t = 1; t <= OM; ++t) {
+        if (t > ol) break;
+        const Pair &q = lo[t - 1];
+        const int ch[2] = {lch[0][t - 1], lch[1][t - 1]};
+        double &b0 = lb[0][t - 1], &b1 = lb[1][t - 1];
+        const Lev v = lev(t);
+        double *x = sm + v.x, *r = sm + v.r;
+        restrict_to_own(t == 1 ? r0 : sm + lev(t - 1).r, t, q, ch, b0, b1);
+        __syncthreads();
+        if (q.f & kOk) put(x, q, 1, add_nb(q, 1, x, b1) * q.id[1]);
+        __syncthreads();
+        if (q.f & kOk) r[q.c[0]] = add_nb(q, 0, x, 0.0);
+        __syncthreads();
+      }
+      restrict_to_lds();
+      __syncthreads();
+      for (int t = ol + 1; t < last; ++t) {
+        low_half(t, 1);
+        __syncthreads();
+        low_restrict(t);
+        __syncthreads();
+      }
     }
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 4, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 1, 64);
-    if (col0 == 0 && row < nd) X(last)[row] = v;
-    __syncthreads();
-  }
-  // ---- up: lower levels, then the top level
-  if (last > 0) {
-    for (int t = last - 1; t >= 1; --t) {
+    // ---- dense solve on the coarsest level: 8 threads per row
+    {
+      const double *b = last == 0 ? r0 : sm + end.b;
+      double *xl = sm + end.x;
+      const int row = tid >> 3, col0 = tid & 7;
+      double bv[8], v = 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) bv[q] = b[col0 + 8 * q < nd ? col0 + 8 * q : 0];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v = fma(ainv[q], col0 + 8 * q < nd ? bv[q] : 0.0, v);
+      v += dpp_d<0xB1>(v);     // lane ^ 1, lane ^ 2, the other half of eight
+      v += dpp_d<0x4E>(v);
+      v += dpp_d<0x141>(v);
+      int at = row;
+      if (last == 0) {         // the top level's place
+        int i, j;
+        cell_ij(row, v0.nx, i, j);
+        at = ((i + j) & 1 ? v0.s : 0) + (row >> 1);
+      }
+      if (col0 == 0 && row < nd) xl[at] = v;
+      __syncthreads();
+    }
+    // ---- up
+    if (last == 0) return;
+    for (int t = last - 1; t > ol; --t) {
       low_black_corr(t);
       __syncthreads();
-      low_half(t, 0, false);
+      low_half(t, 0);
       __syncthreads();
     }
-    top_black_corr();
-    __syncthreads();
-    top_half(0, false);
-    __syncthreads();
-  }
-  // ---- out: x of the top level (when the top level is level 0, k_cg_zw
-  // then forms w = A z and the CG's partials)
 #pragma unroll
-  for (int k = 0; k < 2; ++k)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const OwnCell &o = own[k][m];
-      if (o.ok) xout[o.c] = x0[o.c];
+    for (int t = OM; t >= 1; --t) {
+      if (t > ol) continue;
+      const Pair &q = lo[t - 1];
+      const Lev v = lev(t), w = lev(t + 1);
+      double *x = sm + v.x;
+      const double *e = sm + w.x;
+      if (q.f & kOk) put(x, q, 1, add_nb_corr(q, w.nx, x, e, lb[1][t - 1]) * q.id[1]);
+      __syncthreads();
+      if (q.f & kOk) put(x, q, 0, add_nb(q, 0, x, lb[0][t - 1]) * q.id[0]);
+      __syncthreads();
     }
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (has(m)) *at(1, m) = add_top_corr(m, x1, tb[1][m]) * ti[1][m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (has(m)) *at(0, m) = add_top(0, m, tb[0][m]) * ti[0][m];
+  }
+};
+
+template <int M>
+__global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *ds, double omega,
+                                                              int vc, int rr_ext) {
+  extern __shared__ double sm[];
+  __shared__ double red[kCoarseThreads / 64];
+  CoarseWG<M, 2> W(coarse_words(ds), sm, omega);
+  // a problem whose V-cycle starts here or on level 1 makes the r.r test of
+  // the CG step before it here (level 1: the level-0 tile kernel made the
+  // update)
+  const int lc = W.word(kCwLc);
+  const bool fin = lc == 0 || (lc == 1 && !rr_ext);   // rr_ext: k_rr_test made it
+  const RRTest T = W.rr_test(vc == 0, vc > 0 && lc == 1, cdesc(ds, blockIdx.x).state);
+  RRPre q = {0.0, 0.0, 0.0};
+  if (fin) q = rr_prefetch(T);
+  const int32_t f1 = T.state[1], f3 = T.state[3];   // tested after the loads are issued
+  W.begin((gdbl)W.ptr(vc & 1 ? kCwB1 : kCwB0));
+  if (f1 != 0 || f3 != 0) return;
+  if (fin && finish_rr(T, red, q)) return;
+  W.settle();
+  W.cycle();
+  // x of the top level (when that is level 0, k_cg_zw then forms w = A z and
+  // the CG's partials)
+  double *xout = (double *)(__attribute__((address_space(1))) double *)W.ptr(kCwX);
+  const int n = W.lev(0).n;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int c = 2 * ((int)threadIdx.x + m * kCoarseThreads);
+    if (!W.has(m)) continue;
+    const bool lb = W.to[m] > 0;
+    const double u = *W.at(0, m), v = *W.at(1, m), l = lb ? v : u, r = lb ? u : v;
+    if (c + 1 < n) *(dbl2 *)(xout + c) = dbl2{l, r};
+    else xout[c] = l;
+  }
 }
 
 // For a problem whose whole V-cycle ran in the one-workgroup kernel: w = A z
@@ -1301,6 +1736,134 @@ __global__ void k_cg_zw(const SynthDesc *ds, const int2 *bt, int vc) {
 
 
 constexpr double kOmega = 1.7;   // coarse-grid correction scaling (aggregation MG)
+
+// The whole synthetic solve of a problem of at most kCoarseCells cells in one
+// workgroup (launch_synth_solve's iteration, with the same stop test): the
+// CG's vectors stay with the cells' owners in registers, the operators are
+// loaded once, and neither a launch nor the host stands between two
+// iterations. As separate kernels an iteration was four launches of 3 to 7 us
+// and the solve a wait of the host: 32 x 32, two iterations a solve, 45 us of
+// kernels, here 13.4 us. Outer iterations in all, before and here: 40 x 40 88
+// to 54 us, 50 x 50 92 to 82, 64 x 64 121 to 111 (four pairs per thread: the
+// CG's vectors spill).
+// MODE: see k_cg_begin.
+template <int M, int MODE>
+__global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds, int sub,
+                                                             int max_it) {
+  extern __shared__ double sm[];
+  __shared__ double red[2][kCoarseThreads / 64];
+  CDesc &D = cdesc(ds, blockIdx.x);
+  if (D.state[1] != 0) return;
+  CoarseWG<M, M == 4 ? 1 : 2> W(coarse_words(ds), sm, kOmega);
+  W.begin(nullptr);
+  W.settle();
+  const int nx = D.nx;
+  double *xg = D.lev[0].x;
+  const double *X = MODE >= 2 ? xg : D.phi;
+  double x[2][M], p[2][M], s[2][M];
+  double (&r)[2][M] = W.tb;        // the residual is the V-cycle's right-hand side
+  // sums of two values over the workgroup: wave sums, then in wave order
+  auto sum2 = [&](double &u, double &v) {
+    const double a = wave_sum(u), b = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = a; red[1][threadIdx.x >> 6] = b; }
+    __syncthreads();
+    u = v = 0.0;
+    for (int k = 0; k < kCoarseThreads / 64; ++k) { u += red[0][k]; v += red[1][k]; }
+  };
+  // cell of colour k of the thread's m-th pair, and whether it exists
+  auto cell = [&](int k, int m) {
+    return 2 * ((int)threadIdx.x + m * kCoarseThreads) + (W.to[m] > 0 ? 1 - k : k);
+  };
+  auto ok = [&](int k, int m) { return cell(k, m) < D.N; };
+  // A x of an owned cell, x of the grid in LDS
+  auto apply = [&](int k, int m) { return -W.add_top(k, m, -W.td[k][m] * *W.at(k, m)); };
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      x[k][m] = ok(k, m) ? X[cell(k, m)] : 0.0;
+      p[k][m] = s[k][m] = 0.0;
+      if (W.has(m)) *W.at(k, m) = x[k][m];
+    }
+  __syncthreads();
+  double rr = 0.0, bb = 0.0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      r[k][m] = 0.0;
+      if (!ok(k, m)) continue;
+      const int c = cell(k, m);
+      int i, j;
+      cell_ij(c, nx, i, j);
+      double b = MODE != 0 ? rhs_at(D, c, i, j, D.td ? t_sub(D, sub) : nullptr) : D.rhs[c];
+      if (MODE == 2) {
+        const LevelDev A = level(D, 0);
+        const double *WX = D.wx, *WY = D.wy;
+        const double wxc = WX[c], wyc = WY[c], xc = x[k][m];
+        const double hdy = 0.5 * D.dy, hdx = 0.5 * D.dx;
+        double corr = 0.0;
+        if (i + 1 < nx) corr += A.ax[c] * (xc - X[c + 1]) + hdy * (wxc + WX[c + 1]);
+        if (i > 0) corr += A.ax[c - 1] * (xc - X[c - 1]) - hdy * (wxc + WX[c - 1]);
+        if (j + 1 < D.ny) corr += A.ay[c] * (xc - X[c + nx]) + hdx * (wyc + WY[c + nx]);
+        if (j > 0) corr += A.ay[c - nx] * (xc - X[c - nx]) - hdx * (wyc + WY[c - nx]);
+        b += corr;
+      }
+      if (MODE != 0) D.rhs[c] = b;
+      r[k][m] = b - apply(k, m);
+      rr = fma(r[k][m], r[k][m], rr);
+      bb = fma(b, b, bb);
+    }
+  sum2(rr, bb);
+  const double stop = fmax(D.rtol * D.rtol * rr, 1e-28 * bb);
+  bool conv = !(rr > stop);
+  int nit = 0;
+  double ga_prev = 1.0, al_prev = 1.0;
+  while (!conv && nit < max_it) {
+    W.cycle();
+    __syncthreads();
+    double ga = 0.0, de = 0.0, w[2][M];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        w[k][m] = ok(k, m) ? apply(k, m) : 0.0;
+        const double z = ok(k, m) ? *W.at(k, m) : 0.0;
+        ga = fma(r[k][m], z, ga);
+        de = fma(z, w[k][m], de);
+      }
+    sum2(ga, de);
+    const CGCoef q = cg_coef(nit == 0, ga, de, ga_prev, al_prev);
+    rr = 0.0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const double z = ok(k, m) ? *W.at(k, m) : 0.0;
+        p[k][m] = nit > 0 ? fma(q.be, p[k][m], z) : z;
+        s[k][m] = nit > 0 ? fma(q.be, s[k][m], w[k][m]) : w[k][m];
+        x[k][m] = fma(q.al, p[k][m], x[k][m]);
+        r[k][m] = fma(-q.al, s[k][m], r[k][m]);
+        rr = fma(r[k][m], r[k][m], rr);
+      }
+    double none = 0.0;
+    sum2(rr, none);
+    ga_prev = ga;
+    al_prev = q.al;
+    ++nit;
+    conv = !(rr > stop);
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (ok(k, m)) xg[cell(k, m)] = x[k][m];
+  if (threadIdx.x == 0) {
+    D.scal[S_NIT] = nit;
+    D.state[3] = conv ? 1 + nit : 0;
+  }
+}
 
 // ------------------------------------------------------------- update / Err
 // delta = phi' - phi_half (GSIS) or 0 (SI); Err partials; phi = phi_new.
@@ -1551,8 +2114,13 @@ void vcycle(const SynthSet &S, int v, hipStream_t s, int part = 0) {
     hipLaunchKernelGGL(k_mg_down, dim3(S.nb_tile[l]), dim3(kRedBlock), 0, s, ds, S.bt_tile[l], l,
                        v, rr_ext);
   if (part == 1) return;
-  hipLaunchKernelGGL(k_mg_coarse, dim3(S.n), dim3(kCoarseThreads), S.coarse_lds, s, ds, kOmega,
-                     v, rr_ext);
+  const dim3 gw(S.n), bw(kCoarseThreads);
+  if (S.coarse_cells <= 2 * kCoarseThreads)
+    hipLaunchKernelGGL(k_mg_coarse<1>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
+  else if (S.coarse_cells <= 4 * kCoarseThreads)
+    hipLaunchKernelGGL(k_mg_coarse<2>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
+  else
+    hipLaunchKernelGGL(k_mg_coarse<4>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
   for (int l = S.max_lc - 1; l >= 1; --l)
     hipLaunchKernelGGL(k_mg_up, dim3(S.nb_tile[l]), dim3(kRedBlock), 0, s, ds, S.bt_tile[l], l, v,
                        kOmega);
@@ -1569,20 +2137,19 @@ void vcycle(const SynthSet &S, int v, hipStream_t s, int part = 0) {
 
 // ------------------------------------------------------------ host side
 size_t coarse_lds_bytes_from(const PlanDev &P, size_t lc) {
-  size_t n = 0;
-  for (size_t l = lc; l < P.mg.size(); ++l)
-    n += (l == lc ? 2 : 7) * (size_t)P.mg[l].nx * P.mg[l].ny;
+  size_t n = coarse_top_words(P.mg[lc].nx, P.mg[lc].ny, lc + 1 == P.mg.size());
+  for (size_t l = lc + 1; l < P.mg.size(); ++l) n += 7 * (size_t)P.mg[l].nx * P.mg[l].ny;
   return n * sizeof(double);
 }
 
-// First level handled by the single-workgroup kernel: at most kCoarseWG cells
-// and its vectors plus the lower levels' operators within the LDS budget
-// (160 KB per CU, 8 KB of it static in the kernel).
-constexpr size_t kCoarseLdsBudget = 148 * 1024;
+// First level handled by the single-workgroup kernel: at most kCoarseCells
+// cells and its vectors plus the lower levels' operators within the LDS budget
+// (160 KB per CU, some of it static in the kernels).
+constexpr size_t kCoarseLdsBudget = 156 * 1024;
 int coarse_start(const PlanDev &P) {
   int lc = 0;
   while (lc + 1 < (int)P.mg.size() &&
-         (P.mg[lc].nx * P.mg[lc].ny > kCoarseWG || coarse_lds_bytes_from(P, lc) > kCoarseLdsBudget))
+         (P.mg[lc].nx * P.mg[lc].ny > kCoarseCells || coarse_lds_bytes_from(P, lc) > kCoarseLdsBudget))
     ++lc;
   return lc;
 }
@@ -1594,13 +2161,26 @@ int source_tiles_of(int nx, int ny) {
   return ((nx + kSrcT - 1) / kSrcT) * ((ny + kSrcT - 1) / kSrcT);
 }
 
+int coarse_cells(const PlanDev &P) {
+  const MGLevel &L = P.mg[coarse_start(P)];
+  return L.nx * L.ny;
+}
+
 // The attribute is per kernel, not per plan: it is raised to the largest
 // amount any plan may ask for, so that a later plan with a smaller coarse
 // cycle never lowers it under an earlier one.
 void prepare_synth(size_t coarse_lds) {
-  if (coarse_lds > 64 * 1024)
-    (void)hipFuncSetAttribute((const void *)k_mg_coarse, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kCoarseLdsBudget);
+  if (coarse_lds <= 64 * 1024) return;
+  const void *ks[] = {(const void *)&k_mg_coarse<1>,   (const void *)&k_mg_coarse<2>,
+                      (const void *)&k_mg_coarse<4>,   (const void *)&k_cg_small<1, 0>,
+                      (const void *)&k_cg_small<1, 1>, (const void *)&k_cg_small<1, 2>,
+                      (const void *)&k_cg_small<1, 3>, (const void *)&k_cg_small<2, 0>,
+                      (const void *)&k_cg_small<2, 1>, (const void *)&k_cg_small<2, 2>,
+                      (const void *)&k_cg_small<2, 3>, (const void *)&k_cg_small<4, 0>,
+                      (const void *)&k_cg_small<4, 1>, (const void *)&k_cg_small<4, 2>,
+                      (const void *)&k_cg_small<4, 3>};
+  for (const void *k : ks)
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCoarseLdsBudget);
 }
 
 SynthDesc make_synth_desc(const PlanDev &P) {
@@ -1640,28 +2220,32 @@ SynthDesc make_synth_desc(const PlanDev &P) {
   D.ntile0 = tiles_of(P.mg[0].nx, P.mg[0].ny);
   D.ntp = std::max(D.ntile0, nblk(P.N));
   D.coef_sep = lc > 0 && D.ntile0 >= kCoefSepTiles ? 1 : 0;
-  CoarseLevels &CL = D.cl;
-  CL.nlev = D.nlev - lc;
+  // the record of the one-workgroup kernels
+  int32_t *w = D.cl.w;
+  auto ptr = [&](int k, const void *p) { memcpy(w + k, &p, sizeof p); };
+  const int nlev = D.nlev - lc;
+  w[kCwLast] = nlev - 1;
+  w[kCwLc] = lc;
+  w[kCwNb] = nblk(P.N);
+  w[kCwTile] = D.ntile0;
+  w[kCwRrt] = 2 * nblk(P.N) + D.ntp;   // red_rrt
+  ptr(kCwRed, P.red);
+  ptr(kCwScal, P.scal);
+  ptr(kCwB0, lc == 0 ? P.cg_r : P.mg[lc].b);
+  ptr(kCwB1, lc == 0 ? P.cg_r2 : P.mg[lc].b);
+  ptr(kCwX, lc == 0 ? P.cg_z : P.mg[lc].x);
+  ptr(kCwInv, P.coarse_inv);
+  memcpy(w + kCwRtol, &D.rtol, sizeof D.rtol);
   int off = 0;
-  for (int t = 0; t < CL.nlev; ++t) {
+  for (int t = 0; t < nlev; ++t) {
     const MGLevel &L = P.mg[lc + t];
     const int n = L.nx * L.ny;
-    CL.nx[t] = L.nx; CL.ny[t] = L.ny; CL.fx[t] = L.fx; CL.fy[t] = L.fy;
-    CL.dg[t] = L.diag; CL.ax[t] = L.ax; CL.ay[t] = L.ay;
-    CL.xoff[t] = off;
-    off += n;
-    if (t == 0) {
-      CL.boff[t] = 0;           // the top level's b stays in registers
-    } else {
-      CL.boff[t] = off;
-      off += n;
-    }
-    CL.roff[t] = off;
-    off += n;
-    CL.aoff[t] = t == 0 ? 0 : off;
-    if (t > 0) off += 4 * n;
+    int32_t *r = w + kCwLev + 4 * t;
+    r[0] = L.nx | L.ny << 16;
+    r[1] = off | (t + 1 < nlev && L.fx == 2 ? 1 << 20 : 0) | (t + 1 < nlev && L.fy == 2 ? 1 << 21 : 0);
+    ptr(kCwLev + 4 * t + 2, L.diag);   // ax and ay follow
+    off += t == 0 ? coarse_top_words(L.nx, L.ny, nlev == 1) : 7 * n;
   }
-  D.coarse_inv = P.coarse_inv;
   return D;
 }
 
@@ -1703,9 +2287,28 @@ void launch_hot(const SynthSet &S, hipStream_t s, bool combine) {
 // made conditional on convergence) is put into the stream before the host
 // waits; true is returned when the solve has converged at a check, the
 // update then being in the stream.
+// Sets whose every problem starts with the one-workgroup cycle run the whole
+// solve in one kernel (k_cg_small) and never wait.
+namespace {
+template <int M>
+void launch_cg_small(const SynthSet &S, hipStream_t s, int rhs_mode, int sub) {
+  const dim3 g(S.n), b(kCoarseThreads);
+  const int mi = S.synth_max_iter;
+  if (rhs_mode == 1) hipLaunchKernelGGL((k_cg_small<M, 1>), g, b, S.coarse_lds, s, S.desc, sub, mi);
+  else if (rhs_mode == 2) hipLaunchKernelGGL((k_cg_small<M, 2>), g, b, S.coarse_lds, s, S.desc, sub, mi);
+  else if (rhs_mode == 3) hipLaunchKernelGGL((k_cg_small<M, 3>), g, b, S.coarse_lds, s, S.desc, sub, mi);
+  else hipLaunchKernelGGL((k_cg_small<M, 0>), g, b, S.coarse_lds, s, S.desc, sub, mi);
+}
+}  // namespace
 bool launch_synth_solve(const SynthSet &S, hipStream_t s, int32_t *host_flag, int rhs_mode,
                         int sub, hipEvent_t spec) {
   const SynthDesc *ds = S.desc;
+  if (S.max_lc == 0) {
+    if (S.coarse_cells <= 2 * kCoarseThreads) launch_cg_small<1>(S, s, rhs_mode, sub);
+    else if (S.coarse_cells <= 4 * kCoarseThreads) launch_cg_small<2>(S, s, rhs_mode, sub);
+    else launch_cg_small<4>(S, s, rhs_mode, sub);
+    return false;
+  }
   const dim3 gc(S.nb_cell), bk(kRedBlock);
   if (rhs_mode == 1) hipLaunchKernelGGL(k_cg_begin<1>, gc, bk, 0, s, ds, S.bt_cell, sub);
   else if (rhs_mode == 2) hipLaunchKernelGGL(k_cg_begin<2>, gc, bk, 0, s, ds, S.bt_cell, sub);
