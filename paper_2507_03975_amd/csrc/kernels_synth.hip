@@ -71,6 +71,19 @@ __device__ inline double block_sum(double v, double *sh) {
   return r;
 }
 
+// the same for two values; sh needs two entries per wave
+__device__ inline void block_sum2(double &u, double &v, double *sh) {
+  const double a = wave_sum(u), b = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) {
+    sh[2 * (threadIdx.x >> 6)] = a;
+    sh[2 * (threadIdx.x >> 6) + 1] = b;
+  }
+  __syncthreads();
+  u = v = 0.0;
+  for (int k = 0; k < (int)(blockDim.x >> 6); ++k) { u += sh[2 * k]; v += sh[2 * k + 1]; }
+  __syncthreads();
+}
+
 // (i, j) of cell c on a grid nx wide without an integer division: the
 // quotient from the hardware reciprocal is off by at most one for c < 2^28
 // and is corrected.
@@ -256,7 +269,7 @@ __device__ inline int n_rz(CDesc &D) { return D.lc == 0 ? nblk_d(D.N) : D.ntile0
 __device__ inline double first_partial(const double *p, int n) {
   return p[(int)threadIdx.x < n ? threadIdx.x : 0];   // sum_partials drops what is past n
 }
-__device__ inline double sum_partials(const double *p, int n, double *sh, double first) {
+__device__ inline double thread_partials(const double *p, int n, double first) {
   double v = (int)threadIdx.x < n ? first : 0.0;
   // sixteen loads in flight at a time, added in order (terms past n add 0)
   constexpr int U = 16;
@@ -270,7 +283,10 @@ __device__ inline double sum_partials(const double *p, int n, double *sh, double
 #pragma unroll
     for (int u = 0; u < U; ++u) v += w[u];
   }
-  return block_sum(v, sh);
+  return v;
+}
+__device__ inline double sum_partials(const double *p, int n, double *sh, double first) {
+  return block_sum(thread_partials(p, n, first), sh);
 }
 
 // r.r of the iterate just updated (partials per level-0 tile when the tile
@@ -499,8 +515,9 @@ __device__ inline UpdPre upd_prefetch(CDesc &D, int it) {
 // order, and the blocks take the stored beta and alpha.
 __device__ inline CGCoef upd_coef(CDesc &D, const Blk &B, int it, const UpdPre &q, double *sh) {
   if (D.coef_sep) return {q.rz0, q.zw0};
-  const double ga = sum_partials(red_rz(D), n_rz(D), sh, q.rz0);
-  const double de = sum_partials(red_zw(D), n_rz(D), sh, q.zw0);
+  double ga = thread_partials(red_rz(D), n_rz(D), q.rz0);
+  double de = thread_partials(red_zw(D), n_rz(D), q.zw0);
+  block_sum2(ga, de, sh);
   const CGCoef k = cg_coef(it == 0, ga, de, q.ga_prev, q.al_prev);
   if (B.lb == 0 && threadIdx.x == 0) {
     D.scal[rz_slot(it)] = ga;
@@ -527,8 +544,9 @@ __global__ void __launch_bounds__(kRedBlock) k_cg_coef(const SynthDesc *ds, int 
   q.ga_prev = it > 0 ? D.scal[rz_slot(it - 1)] : 1.0;
   q.al_prev = it > 0 ? D.scal[alpha_slot(it - 1)] : 1.0;
   if (cg_off(D.state)) return;
-  const double ga = sum_partials(red_rz(D), n_rz(D), sh, q.rz0);
-  const double de = sum_partials(red_zw(D), n_rz(D), sh, q.zw0);
+  double ga = thread_partials(red_rz(D), n_rz(D), q.rz0);
+  double de = thread_partials(red_zw(D), n_rz(D), q.zw0);
+  block_sum2(ga, de, sh);
   const CGCoef k = cg_coef(it == 0, ga, de, q.ga_prev, q.al_prev);
   if (threadIdx.x == 0) {
     D.scal[rz_slot(it)] = ga;
@@ -541,7 +559,7 @@ __global__ void __launch_bounds__(kRedBlock) k_cg_coef(const SynthDesc *ds, int 
 // CG iteration it on every cell of a problem, with the partial of r.r.
 // With all = 0 only problems whose whole V-cycle runs in the one-workgroup
 // kernel take part: for the others the level-0 tile kernel of the next
-// V-cycle makes the update (cg_update_tile).
+// V-cycle makes the update.
 __global__ void k_cg_update(const SynthDesc *ds, const int2 *bt, int it, int all) {
   __shared__ double sh[kRedBlock];
   const Blk B = blk(bt);
@@ -591,7 +609,7 @@ __device__ inline const double *lev_b(CDesc &D, int l, int v) {
 //        two cells, so the tile and its ring are computed without waiting
 //        for other workgroups. The pre-smoothed x of the tile goes to the
 //        level's spare vector xs, not to x. On level 0 after a CG step it
-//        also makes that step's update (cg_update_tile): b = r_new =
+//        also makes that step's update: b = r_new =
 //        r_old - alpha (w + beta s_old) is formed on the whole region from
 //        r_old, w and s_old, which earlier kernels left complete.
 //  up:   black x = (b + sum a (xs_nb + omega e_parent(nb))) / d with the
@@ -616,133 +634,100 @@ __device__ inline Tile tile_of(const LevelDev &L, int lb) {
   return {L.nx, L.ny, ti * kTW - kHalo, tj * kTH - kHalo};
 }
 
-// b, d and the east / north couplings of the region into LDS (blockDim =
-// kRedBlock); AP: also ap (and ap2 unless NULL) of the region into sap
-// (sap2); XC: also the pre-smoothed
-// x plus the scaled coarse correction, xs + omega e(parent), into sxc. Every
-// load of the thread is issued (at a clamped, valid index) before any is
-// waited for, so the region costs one memory round trip.
-constexpr int kRegionPer = (kRN + kRedBlock - 1) / kRedBlock;
-template <bool AP, bool XC>
-__device__ inline void load_region_t(const LevelDev &L, const double *b, const Tile &T,
-                                     double *sb, double *sd, double *sax, double *say,
-                                     const double *ap, double *sap, const double *xs,
-                                     const double *e, int enx, int sx_, int sy_, double omega,
-                                     double *sxc, const double *ap2 = nullptr,
-                                     double *sap2 = nullptr) {
-  double vb[kRegionPer], vd[kRegionPer], vx[kRegionPer], vy[kRegionPer];
-  double va[kRegionPer], va2[kRegionPer], vs[kRegionPer], ve[kRegionPer];
-  bool in[kRegionPer], hx[kRegionPer], hy[kRegionPer];
+// A thread's cells of a region W x H (with its ring) around a tile: region
+// cell threadIdx.x + k kRedBlock, its place on the grid and its operator row,
+// loaded at a clamped, valid index: every load of a kernel is issued before
+// any is waited for, so the region costs one memory round trip.
+template <int W, int H>
+struct Region {
+  static constexpr int N = W * H, P = (N + kRedBlock - 1) / kRedBlock;
+  int g[P], gi[P], gj[P];      // cell index (0 outside the grid), place
+  bool in[P], red[P];
+  double d[P], ax[P], ay[P];
+  __device__ __forceinline__ void load(const LevelDev &L, int i0, int j0) {
 #pragma unroll
-  for (int k = 0; k < kRegionPer; ++k) {
-    const int r = threadIdx.x + k * kRedBlock;
-    int ri, rj;
-    cell_ij(r, kRW, ri, rj);
-    const int gi = T.i0 + ri, gj = T.j0 + rj;
-    in[k] = r < kRN && gi >= 0 && gi < T.nx && gj >= 0 && gj < T.ny;
-    hx[k] = gi + 1 < T.nx;
-    hy[k] = gj + 1 < T.ny;
-    const int g = in[k] ? gj * T.nx + gi : 0;
-    vb[k] = b[g]; vd[k] = L.dg[g]; vx[k] = L.ax[g]; vy[k] = L.ay[g];
-    if (AP) va[k] = ap[g];
-    if (AP) va2[k] = ap2 ? ap2[g] : 0.0;
-    if (XC) {
-      vs[k] = xs[g];
-      ve[k] = e[in[k] ? (gj >> sy_) * enx + (gi >> sx_) : 0];
+    for (int k = 0; k < P; ++k) {
+      const unsigned r = threadIdx.x + k * kRedBlock;
+      const int rj = r / W, ri = r - rj * W;
+      gi[k] = i0 + ri;
+      gj[k] = j0 + rj;
+      in[k] = (int)r < N && gi[k] >= 0 && gi[k] < L.nx && gj[k] >= 0 && gj[k] < L.ny;
+      red[k] = ((gi[k] + gj[k]) & 1) == 0;
+      g[k] = in[k] ? gj[k] * L.nx + gi[k] : 0;
+      d[k] = L.dg[g[k]]; ax[k] = L.ax[g[k]]; ay[k] = L.ay[g[k]];
     }
   }
+  // the k-th cell lies at least m cells inside the region
+  __device__ __forceinline__ bool inner(int k, int m) const {
+    const unsigned r = threadIdx.x + k * kRedBlock;
+    const int rj = r / W, ri = r - rj * W;
+    return ri >= m && ri < W - m && rj >= m && rj < H - m;
+  }
+  // couplings to the east and north (0 outside the grid and across its edge:
+  // they are stored so) into LDS
+  __device__ __forceinline__ void couplings(double *sax, double *say) const {
 #pragma unroll
-  for (int k = 0; k < kRegionPer; ++k) {
-    const int r = threadIdx.x + k * kRedBlock;
-    if (r >= kRN) continue;
-    sb[r] = in[k] ? vb[k] : 0.0;
-    sd[r] = in[k] ? vd[k] : 1.0;
-    sax[r] = in[k] && hx[k] ? vx[k] : 0.0;
-    say[r] = in[k] && hy[k] ? vy[k] : 0.0;
-    if (AP) sap[r] = in[k] ? va[k] : 0.0;
-    if (AP && sap2) sap2[r] = in[k] ? va2[k] : 0.0;
-    if (XC) {
-      double t = 0.0;
-      if (in[k]) {
-        t = vs[k];
-        t += omega * ve[k];
+    for (int k = 0; k < P; ++k) {
+      const int r = threadIdx.x + k * kRedBlock;
+      if (r < N) {
+        sax[r] = in[k] ? ax[k] : 0.0;
+        say[r] = in[k] ? ay[k] : 0.0;
       }
-      sxc[r] = t;
     }
   }
-}
-__device__ inline void load_region(const LevelDev &L, const double *b, const Tile &T, double *sb,
-                                   double *sd, double *sax, double *say) {
-  load_region_t<false, false>(L, b, T, sb, sd, sax, say, nullptr, nullptr, nullptr, nullptr, 0,
-                              0, 0, 0.0, nullptr);
-}
-
-// The CG update of iteration it = v - 1 folded into the level-0 tile kernel
-// of V-cycle v: beta and alpha from the r.z and z.w partials (every block
-// sums them in the same order), then on the region held in LDS s = w + beta
-// s_old (sw holds w, ss s_old; afterwards ss holds s) and r_v = r_{v-1} -
-// alpha s (sb holds r_{v-1}, afterwards r_v); for the tile's own cells p =
-// z + beta p, x += alpha p, s and r_v to global and a partial of r_v . r_v.
-// zc, pc0, xc: the cell's z, p and x; q: the update's scalars, all loaded
-// early.
-__device__ inline void cg_update_tile(CDesc &D, const Blk &B, const Tile &T, int v, double *sb,
-                                      const double *sw, double *ss, double zc, double pc0,
-                                      double xc, const UpdPre &q, double *sh) {
-  const int it = v - 1;
-  const CGCoef k = upd_coef(D, B, it, q, sh);
-  for (int r = threadIdx.x; r < kRN; r += blockDim.x) {
-    const double sv = it > 0 ? fma(k.be, ss[r], sw[r]) : sw[r];
-    ss[r] = sv;
-    sb[r] = fma(-k.al, sv, sb[r]);
+  // v + the sum of region cell r's couplings times x of its neighbours
+  static __device__ __forceinline__ double add_nb(int r, const double *sax, const double *say,
+                                                  const double *x, double v) {
+    v = fma(sax[r], x[r + 1], v);
+    v = fma(sax[r - 1], x[r - 1], v);
+    v = fma(say[r], x[r + W], v);
+    return fma(say[r - W], x[r - W], v);
   }
-  __syncthreads();
-  const int ti = threadIdx.x % kTW, tj = threadIdx.x / kTW;
-  const int r = (tj + kHalo) * kRW + ti + kHalo;
-  const int gi = T.i0 + kHalo + ti, gj = T.j0 + kHalo + tj;
-  double rr = 0.0;
-  if (gi < T.nx && gj < T.ny) {
-    const int g = gj * T.nx + gi;
-    const double pc = it > 0 ? fma(k.be, pc0, zc) : zc;
-    const double rc = sb[r];
-    D.cg_p[g] = pc;
-    cg_s(D, it)[g] = ss[r];
-    D.lev[0].x[g] = fma(k.al, pc, xc);
-    cg_rv(D, v)[g] = rc;
-    rr = rc * rc;
-  }
-  const double t = block_sum(rr, sh);
-  if (threadIdx.x == 0) red_rrt(D)[B.lb] = t;
-}
+};
 
+// Bound by latency: at 256 x 256 (256 tiles) and below a launch is one round
+// of short phases: one round trip to memory, then 3 half sweeps on the LDS. A
+// thread keeps its region cells' places and operator in registers from the
+// loads to the last half sweep (the CG update of level 0 as well), divides by
+// multiplying with a reciprocal formed once, and takes only the red cells'
+// residuals. 128 x 128: 6.2 to 4.8 us a launch (k_mg_up0 4.6 to 4.0); 512 x
+// 512: 7.7 to 6.6 (8.3 to 6.8); 1024 x 1024: 11.4 to 10.3 (20.8 to 16.8).
 __global__ void __launch_bounds__(kRedBlock) k_mg_down(const SynthDesc *ds, const int2 *bt, int l,
                                                        int v, int rr_ext) {
-  __shared__ double sb[kRN], sd[kRN], sax[kRN], say[kRN], sx[kRN], ss[kRN], sh[kRedBlock];
+  __shared__ double sb[kRN], si[kRN], sax[kRN], say[kRN], sx[kRN], sr[kTW * kTH], sh[kRedBlock];
+  typedef Region<kRW, kRH> Reg;
   const Blk B = blk(bt);
   CDesc &D = cdesc(ds, B.p);
   const int32_t f1 = D.state[1], f3 = D.state[3];   // tested after the region loads
   const LevelDev L = level(D, l), CL = level(D, l + 1);
   const bool upd = l == 0 && v > 0;
+  const int it = v - 1;
   double *xs = L.xs;
   const Tile T = tile_of(L, B.lb);
+  // the thread's tile cell
+  const int ti = threadIdx.x % kTW, tj = threadIdx.x / kTW;
+  const int gi = T.i0 + kHalo + ti, gj = T.j0 + kHalo + tj;
+  const bool in = gi < T.nx && gj < T.ny;
+  const int g = gj * T.nx + gi;
+  Reg R;
+  R.load(L, T.i0, T.j0);
+  double vb[Reg::P], vw[Reg::P], vs[Reg::P];
+  const double *b = upd ? cg_rv(D, it) : lev_b(D, l, v);
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) vb[k] = b[R.g[k]];
   double zc = 0.0, pc0 = 0.0, xc = 0.0;
   UpdPre q = {0.0, 0.0, 1.0, 1.0};
   if (upd) {
-    const int it = v - 1;
+    // r_{v-1} (in vb), w and s_old of the region, z, p and x of the tile
+    // cell; p and s of iteration 0 are not there yet
     q = upd_prefetch(D, it);
-    // r_{v-1}, w and s_old of the region (w into sx, free until the
-    // sweeps), z, p and x of the thread's tile cell
-    load_region_t<true, false>(L, cg_rv(D, it), T, sb, sd, sax, say, D.cg_w, sx, nullptr,
-                               nullptr, 0, 0, 0, 0.0, nullptr, it > 0 ? cg_s(D, it - 1) : nullptr,
-                               ss);
-    const int gi = T.i0 + kHalo + (int)threadIdx.x % kTW, gj = T.j0 + kHalo + (int)threadIdx.x / kTW;
-    if (gi < T.nx && gj < T.ny) {
-      const int g = gj * T.nx + gi;
-      zc = D.cg_z[g];
-      if (it > 0) pc0 = D.cg_p[g];
-      xc = D.lev[0].x[g];
-    }
-  } else {
-    load_region(L, lev_b(D, l, v), T, sb, sd, sax, say);
+    const double *w = D.cg_w, *so = it > 0 ? cg_s(D, it - 1) : w;
+#pragma unroll
+    for (int k = 0; k < Reg::P; ++k) { vw[k] = w[R.g[k]]; vs[k] = so[R.g[k]]; }
+    const int gc = in ? g : 0;
+    zc = D.cg_z[gc];
+    pc0 = it > 0 ? D.cg_p[gc] : 0.0;
+    xc = D.lev[0].x[gc];
   }
   // the r.r test of the CG step before this V-cycle is made by the next
   // kernel of the cycle (level 1 here, block 0; the other blocks go on: if
@@ -752,112 +737,133 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_down(const SynthDesc *ds, cons
   if (fin) qr = rr_prefetch(D, v == 0, v > 0);
   if (f1 != 0 || f3 != 0) return;
   if (fin) (void)finish_rr(D, v == 0, v > 0, sh, qr);
-  __syncthreads();
-  if (upd) cg_update_tile(D, B, T, v, sb, sx, ss, zc, pc0, xc, q, sh);
+  double rr = 0.0;
+  if (upd) {
+    // the CG update: beta and alpha from the r.z and z.w partials (every
+    // block sums them in the same order); s = w + beta s_old, r_v = r_{v-1} -
+    // alpha s on the region; s, r_v, p = z + beta p and x += alpha p of the
+    // tile to global
+    const CGCoef c = upd_coef(D, B, it, q, sh);
+    double *s = cg_s(D, it), *rv = cg_rv(D, v);
+#pragma unroll
+    for (int k = 0; k < Reg::P; ++k) {
+      const double sv = it > 0 ? fma(c.be, vs[k], vw[k]) : vw[k];
+      vb[k] = fma(-c.al, sv, vb[k]);
+      if (R.in[k] && R.inner(k, kHalo)) {
+        s[R.g[k]] = sv;
+        rv[R.g[k]] = vb[k];
+        rr = fma(vb[k], vb[k], rr);
+      }
+    }
+    if (in) {
+      const double pc = it > 0 ? fma(c.be, pc0, zc) : zc;
+      D.cg_p[g] = pc;
+      D.lev[0].x[g] = fma(c.al, pc, xc);
+    }
+  }
   // red half sweep from zero on the whole region
-  for (int r = threadIdx.x; r < kRN; r += blockDim.x) {
-    int ri, rj;
-    cell_ij(r, kRW, ri, rj);
-    sx[r] = (((T.i0 + ri + T.j0 + rj) & 1) == 0) ? sb[r] / sd[r] : 0.0;
+  R.couplings(sax, say);
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (r < kRN) {
+      const double bv = R.in[k] ? vb[k] : 0.0, id = rcp64(R.in[k] ? R.d[k] : 1.0);
+      sb[r] = bv;
+      si[r] = id;
+      sx[r] = R.red[k] ? bv * id : 0.0;
+    }
   }
   __syncthreads();
   // black half sweep on the tile and a ring of one
-  for (int r = threadIdx.x; r < kRN; r += blockDim.x) {
-    int ri, rj;
-    cell_ij(r, kRW, ri, rj);
-    if (ri < 1 || ri > kRW - 2 || rj < 1 || rj > kRH - 2) continue;
-    if (((T.i0 + ri + T.j0 + rj) & 1) != 1) continue;
-    double v = sb[r];
-    v += sax[r] * sx[r + 1];
-    v += sax[r - 1] * sx[r - 1];
-    v += say[r] * sx[r + kRW];
-    v += say[r - kRW] * sx[r - kRW];
-    sx[r] = v / sd[r];
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (!R.red[k] && R.inner(k, 1)) sx[r] = Reg::add_nb(r, sax, say, sx, sb[r]) * si[r];
   }
   __syncthreads();
-  // residual of the tile cell of this thread; x of the tile to global
-  const int ti = threadIdx.x % kTW, tj = threadIdx.x / kTW;
-  const int r = (tj + kHalo) * kRW + ti + kHalo;
-  const int gi = T.i0 + kHalo + ti, gj = T.j0 + kHalo + tj;
-  double y = sd[r] * sx[r];
-  y -= sax[r] * sx[r + 1];
-  y -= sax[r - 1] * sx[r - 1];
-  y -= say[r] * sx[r + kRW];
-  y -= say[r - kRW] * sx[r - kRW];
-  const double res = sb[r] - y;
-  const bool in = gi < T.nx && gj < T.ny;
-  if (in) xs[gj * T.nx + gi] = sx[r];
-  __syncthreads();
-  sb[r] = in ? res : 0.0;   // the tile's residuals (the ring is no longer needed)
-  __syncthreads();
+  // residuals: black ones vanish, a red one is the sum of its couplings times
+  // the black values (what it was from zero, b - d (b / d), is 0); x of the
+  // tile to global
+  {
+    const int r = (tj + kHalo) * kRW + ti + kHalo;
+    sr[threadIdx.x] = in && ((gi + gj) & 1) == 0 ? Reg::add_nb(r, sax, say, sx, 0.0) : 0.0;
+    if (in) xs[g] = sx[r];
+  }
+  if (upd) {
+    const double t = block_sum(rr, sh);   // (its barriers are the restriction's)
+    if (threadIdx.x == 0) red_rrt(D)[B.lb] = t;
+  } else {
+    __syncthreads();
+  }
   // restriction: coarse cells whose children lie in this tile
-  const int fx = L.fx, fy = L.fy, sx_ = fx >> 1, sy_ = fy >> 1;
+  const int sx_ = L.fx >> 1, sy_ = L.fy >> 1;
   const int cw = kTW >> sx_, ch = kTH >> sy_;
   if ((int)threadIdx.x < cw * ch) {
-    const int ci = threadIdx.x % cw, cj = threadIdx.x / cw;
+    const int ci = threadIdx.x & (cw - 1), cj = threadIdx.x >> (5 - sx_);
     const int CI = ((T.i0 + kHalo) >> sx_) + ci, CJ = ((T.j0 + kHalo) >> sy_) + cj;
     if (CI < CL.nx && CJ < CL.ny) {
-      double acc = 0.0;
-      for (int dj = 0; dj < fy; ++dj)
-        for (int di = 0; di < fx; ++di) {
-          const int li = ci * fx + di, lj = cj * fy + dj;
-          if (T.i0 + kHalo + li < T.nx && T.j0 + kHalo + lj < T.ny)
-            acc += sb[(lj + kHalo) * kRW + li + kHalo];
-        }
+      const double *p = sr + (cj << sy_) * kTW + (ci << sx_);
+      double acc = p[0];
+      if (sx_) acc += p[1];
+      if (sy_) acc += p[kTW];
+      if (sx_ && sy_) acc += p[kTW + 1];
       CL.b[CJ * CL.nx + CI] = acc;
     }
   }
 }
+static_assert(kTW == 32, "the restriction's shift");
 
 __global__ void __launch_bounds__(kRedBlock) k_mg_up(const SynthDesc *ds, const int2 *bt, int l,
                                                      int vc, double omega) {
-  __shared__ double sb[kRN], sd[kRN], sax[kRN], say[kRN], sx[kRN];
+  __shared__ double sax[kRN], say[kRN], sx[kRN], sxc[kRN];
+  typedef Region<kRW, kRH> Reg;
   const Blk B = blk(bt);
   CDesc &D = cdesc(ds, B.p);
   const int32_t f1 = D.state[1], f3 = D.state[3];   // tested after the region loads
   const LevelDev L = level(D, l), CL = level(D, l + 1);
-  const double *b = lev_b(D, l, vc);
+  const double *b = lev_b(D, l, vc), *xs = L.xs, *e = CL.x;
   double *x = lev_x(D, l);
-  const double *xs = L.xs;
-  const double *e = CL.x;
   const Tile T = tile_of(L, B.lb);
   const int sx_ = L.fx >> 1, sy_ = L.fy >> 1;
-  // with the pre-smoothed x plus the scaled coarse correction: the black
-  // half sweep sees corrected red neighbours
-  __shared__ double sxc[kRN];
-  load_region_t<false, true>(L, b, T, sb, sd, sax, say, nullptr, nullptr, xs, e, CL.nx, sx_, sy_,
-                             omega, sxc);
+  const int ti = threadIdx.x % kTW, tj = threadIdx.x / kTW;
+  const int gi = T.i0 + kHalo + ti, gj = T.j0 + kHalo + tj;
+  const bool in = gi < T.nx && gj < T.ny;
+  const int g = in ? gj * T.nx + gi : 0;
+  Reg R;
+  R.load(L, T.i0, T.j0);
+  double vb[Reg::P], vs[Reg::P], ve[Reg::P];
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    vb[k] = b[R.g[k]];
+    vs[k] = xs[R.g[k]];
+    ve[k] = e[R.in[k] ? (R.gj[k] >> sy_) * CL.nx + (R.gi[k] >> sx_) : 0];
+  }
+  const double bc = b[g], dc = L.dg[g];
   if (f1 != 0 || f3 != 0) return;
+  // the pre-smoothed x plus the scaled coarse correction: the black half
+  // sweep sees corrected red neighbours
+  R.couplings(sax, say);
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (r < kRN) sxc[r] = R.in[k] ? fma(omega, ve[k], vs[k]) : 0.0;
+    vb[k] = R.in[k] ? vb[k] : 0.0;
+    R.d[k] = rcp64(R.in[k] ? R.d[k] : 1.0);
+  }
+  const double ic = rcp64(dc);
   __syncthreads();
   // black half sweep on the tile and a ring of one, into sx
-  for (int r = threadIdx.x; r < kRN; r += blockDim.x) {
-    int ri, rj;
-    cell_ij(r, kRW, ri, rj);
-    if (ri < 1 || ri > kRW - 2 || rj < 1 || rj > kRH - 2) { sx[r] = 0.0; continue; }
-    if (((T.i0 + ri + T.j0 + rj) & 1) != 1) { sx[r] = 0.0; continue; }
-    double v = sb[r];
-    v += sax[r] * sxc[r + 1];
-    v += sax[r - 1] * sxc[r - 1];
-    v += say[r] * sxc[r + kRW];
-    v += say[r - kRW] * sxc[r - kRW];
-    sx[r] = v / sd[r];
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (!R.red[k] && R.inner(k, 1)) sx[r] = Reg::add_nb(r, sax, say, sxc, vb[k]) * R.d[k];
   }
   __syncthreads();
   // red half sweep on the tile with the new black neighbours
-  const int ti = threadIdx.x % kTW, tj = threadIdx.x / kTW;
-  const int r = (tj + kHalo) * kRW + ti + kHalo;
-  const int gi = T.i0 + kHalo + ti, gj = T.j0 + kHalo + tj;
-  double xv = sx[r];
-  if (((gi + gj) & 1) == 0) {
-    double v = sb[r];
-    v += sax[r] * sx[r + 1];
-    v += sax[r - 1] * sx[r - 1];
-    v += say[r] * sx[r + kRW];
-    v += say[r - kRW] * sx[r - kRW];
-    xv = v / sd[r];
+  if (in) {
+    const int r = (tj + kHalo) * kRW + ti + kHalo;
+    x[g] = ((gi + gj) & 1) == 0 ? Reg::add_nb(r, sax, say, sx, bc) * ic : sx[r];
   }
-  const bool in = gi < T.nx && gj < T.ny;
-  if (in) x[gj * T.nx + gi] = xv;
 }
 
 // Level 0 going up: as k_mg_up, over a ring of three, so that z is final on
@@ -865,10 +871,10 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up(const SynthDesc *ds, const 
 // the tile and a ring of one); then w = A z on the tile, z and w to global,
 // and partials of r.z and z.w for the CG (b = r).
 constexpr int kU0Halo = 3, kU0W = kTW + 2 * kU0Halo, kU0H = kTH + 2 * kU0Halo;
-constexpr int kU0N = kU0W * kU0H, kU0Per = (kU0N + kRedBlock - 1) / kRedBlock;
 __global__ void __launch_bounds__(kRedBlock) k_mg_up0(const SynthDesc *ds, const int2 *bt, int vc,
                                                       double omega) {
-  __shared__ double sb[kU0N], sd[kU0N], sax[kU0N], say[kU0N], sxc[kU0N], sx[kU0N];
+  typedef Region<kU0W, kU0H> Reg;
+  __shared__ double sax[Reg::N], say[Reg::N], sxc[Reg::N], sx[Reg::N];
   __shared__ double sh[kRedBlock];
   const Blk B = blk(bt);
   CDesc &D = cdesc(ds, B.p);
@@ -879,89 +885,55 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up0(const SynthDesc *ds, const
   int ti, tj;
   cell_ij(B.lb, (nx + kTW - 1) / kTW, ti, tj);
   const int i0 = ti * kTW - kU0Halo, j0 = tj * kTH - kU0Halo;
-  {
-    // every load of the thread first (clamped, valid indices), then LDS
-    double vb[kU0Per], vd[kU0Per], vx[kU0Per], vy[kU0Per], vs[kU0Per], ve[kU0Per];
-    bool in[kU0Per], hx[kU0Per], hy[kU0Per];
+  // the thread's tile cell
+  const int ci = threadIdx.x % kTW, cj = threadIdx.x / kTW;
+  const int gi = i0 + kU0Halo + ci, gj = j0 + kU0Halo + cj;
+  const bool in = gi < nx && gj < ny;
+  const int g = in ? gj * nx + gi : 0;
+  Reg R;
+  R.load(L, i0, j0);
+  double vb[Reg::P], vs[Reg::P], ve[Reg::P];
 #pragma unroll
-    for (int k = 0; k < kU0Per; ++k) {
-      const int r = threadIdx.x + k * kRedBlock;
-      int ri, rj;
-      cell_ij(r, kU0W, ri, rj);
-      const int gi = i0 + ri, gj = j0 + rj;
-      in[k] = r < kU0N && gi >= 0 && gi < nx && gj >= 0 && gj < ny;
-      hx[k] = gi + 1 < nx;
-      hy[k] = gj + 1 < ny;
-      const int g = in[k] ? gj * nx + gi : 0;
-      vb[k] = b[g]; vd[k] = L.dg[g]; vx[k] = L.ax[g]; vy[k] = L.ay[g]; vs[k] = L.xs[g];
-      ve[k] = CL.x[in[k] ? (gj >> sy_) * CL.nx + (gi >> sx_) : 0];
-    }
-#pragma unroll
-    for (int k = 0; k < kU0Per; ++k) {
-      const int r = threadIdx.x + k * kRedBlock;
-      if (r >= kU0N) continue;
-      sb[r] = in[k] ? vb[k] : 0.0;
-      sd[r] = in[k] ? vd[k] : 1.0;
-      sax[r] = in[k] && hx[k] ? vx[k] : 0.0;
-      say[r] = in[k] && hy[k] ? vy[k] : 0.0;
-      double t = 0.0;
-      if (in[k]) {
-        t = vs[k];
-        t += omega * ve[k];
-      }
-      sxc[r] = t;
-    }
+  for (int k = 0; k < Reg::P; ++k) {
+    vb[k] = b[R.g[k]];
+    vs[k] = L.xs[R.g[k]];
+    ve[k] = CL.x[R.in[k] ? (R.gj[k] >> sy_) * CL.nx + (R.gi[k] >> sx_) : 0];
   }
+  const double bc = b[g], dc = L.dg[g];
   if (f1 != 0 || f3 != 0) return;
+  R.couplings(sax, say);
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (r < Reg::N) sxc[r] = R.in[k] ? fma(omega, ve[k], vs[k]) : 0.0;
+    vb[k] = R.in[k] ? vb[k] : 0.0;
+    R.d[k] = rcp64(R.in[k] ? R.d[k] : 1.0);
+  }
   __syncthreads();
-  // black on the region less a ring of one, into sx (other cells 0)
-  for (int r = threadIdx.x; r < kU0N; r += blockDim.x) {
-    int ri, rj;
-    cell_ij(r, kU0W, ri, rj);
-    if (ri < 1 || ri > kU0W - 2 || rj < 1 || rj > kU0H - 2 || ((i0 + ri + j0 + rj) & 1) != 1) {
-      sx[r] = 0.0;
-      continue;
-    }
-    double v = sb[r];
-    v += sax[r] * sxc[r + 1];
-    v += sax[r - 1] * sxc[r - 1];
-    v += say[r] * sxc[r + kU0W];
-    v += say[r - kU0W] * sxc[r - kU0W];
-    sx[r] = v / sd[r];
+  // black on the region less a ring of one, into sx
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (!R.red[k] && R.inner(k, 1)) sx[r] = Reg::add_nb(r, sax, say, sxc, vb[k]) * R.d[k];
   }
   __syncthreads();
   // red on the region less a ring of two (reads black cells only)
-  for (int r = threadIdx.x; r < kU0N; r += blockDim.x) {
-    int ri, rj;
-    cell_ij(r, kU0W, ri, rj);
-    if (ri < 2 || ri > kU0W - 3 || rj < 2 || rj > kU0H - 3 || ((i0 + ri + j0 + rj) & 1) != 0)
-      continue;
-    double v = sb[r];
-    v += sax[r] * sx[r + 1];
-    v += sax[r - 1] * sx[r - 1];
-    v += say[r] * sx[r + kU0W];
-    v += say[r - kU0W] * sx[r - kU0W];
-    sx[r] = v / sd[r];
+#pragma unroll
+  for (int k = 0; k < Reg::P; ++k) {
+    const int r = threadIdx.x + k * kRedBlock;
+    if (R.red[k] && R.inner(k, 2)) sx[r] = Reg::add_nb(r, sax, say, sx, vb[k]) * R.d[k];
   }
   __syncthreads();
   // the tile cell of this thread: z, w = A z, partials of r.z and z.w
-  const int ci = threadIdx.x % kTW, cj = threadIdx.x / kTW;
   const int r = (cj + kU0Halo) * kU0W + ci + kU0Halo;
-  const int gi = i0 + kU0Halo + ci, gj = j0 + kU0Halo + cj;
-  const bool in = gi < nx && gj < ny;
-  const double zv = sx[r];
-  double wv = sd[r] * zv;
-  wv -= sax[r] * sx[r + 1];
-  wv -= sax[r - 1] * sx[r - 1];
-  wv -= say[r] * sx[r + kU0W];
-  wv -= say[r - kU0W] * sx[r - kU0W];
+  const double zv = in ? sx[r] : 0.0;
+  const double wv = in ? -Reg::add_nb(r, sax, say, sx, -dc * zv) : 0.0;
   if (in) {
-    const int g = gj * nx + gi;
     D.cg_z[g] = zv;
     D.cg_w[g] = wv;
   }
-  const double trz = block_sum(in ? sb[r] * zv : 0.0, sh);
-  const double tzw = block_sum(in ? zv * wv : 0.0, sh);
+  double trz = bc * zv, tzw = zv * wv;
+  block_sum2(trz, tzw, sh);
   if (threadIdx.x == 0) {
     red_rz(D)[B.lb] = trz;
     red_zw(D)[B.lb] = tzw;
