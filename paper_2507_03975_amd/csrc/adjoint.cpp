@@ -21,7 +21,7 @@ gsis_status adjoint_setup(gsis_plan *pl) {
   const size_t N = P.N, NK = (size_t)P.N * P.K;
   gsis_status st;
   if ((st = dalloc(pl, &B->lam, NK)) || (st = dalloc(pl, &B->rb, NK)) ||
-      (st = dalloc(pl, &B->pl, 12 * N)) || (st = dalloc(pl, &B->s, N)) ||
+      (st = dalloc(pl, &B->pl, 8 * N)) || (st = dalloc(pl, &B->s, N)) ||
       (st = dalloc(pl, &B->s_old, N)) || (st = dalloc(pl, &B->bb, N)) ||
       (st = dalloc(pl, &B->hxb, N)) || (st = dalloc(pl, &B->hyb, N)) ||
       (st = dalloc(pl, &B->phb, N)) || (st = dalloc(pl, &B->Sb, N)) ||

@@ -445,7 +445,7 @@ double *synth_vcycle_total(const PlanDev &P);
 // ---- adjoint (kernels_adjoint.hip)
 struct AdjointBuffers {
   double *lam = nullptr, *rb = nullptr;                          // [K][N]
-  double *pl = nullptr;        // [4][3][N]
+  double2 *pl = nullptr;       // [4][2][N]
   double *s = nullptr, *s_old = nullptr, *bb = nullptr, *hxb = nullptr, *hyb = nullptr;
   double *phb = nullptr, *Sb = nullptr, *bfb = nullptr;
   double *part = nullptr;      // [4][5][N]

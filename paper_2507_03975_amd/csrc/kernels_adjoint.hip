@@ -51,7 +51,7 @@ struct AArgs {
   const double *delta, *phi, *phih;
   const double *gphi, *gFx, *gFy;                             // cotangents or null
   double *lam, *rb;                                           // [K][N] (lam: m, see lam_cell)
-  double *pl;                                                 // [4][3][N], see k_a_planes
+  double2 *pl;                                                // [4][2][N], see k_a_planes
   double *s, *s_old, *bb, *hxb, *hyb, *phb, *Sb, *bfb;
   double *part;                                               // [4][5][N]
   double *dbar;                                               // [4][N]
@@ -244,7 +244,8 @@ __global__ void k_a_phbar(AArgs a, const double *kappa) {
 
 // Ih_bar_k = m_k + w_k P + w_k mu_k X + w_k eta_k Y (m_k: lam_cell): per
 // quadrant and stored cell the three fields that do not depend on the
-// ordinate, pl[q][3][N]. They hold lam_cell's terms and (GSIS) the cotangents
+// ordinate, and the increment's diagonal next to them, (P, X) and (Y,
+// sigma_t + shift) in pl[q][2][N]. They hold lam_cell's terms and (GSIS) the cotangents
 // phb, hbx, hby and the outflow-wall reconstruction transposed, which takes
 // |w_k mu_k| = +-w_k mu_k, one sign per quadrant. The sweep and k_a_out form
 // Ih_bar from them where they need it: as an array of its own it cost a write
@@ -285,10 +286,9 @@ __global__ void __launch_bounds__(kB) k_a_planes(AArgs a) {
       X += (q & 1) ? -vx : vx;
       Y += (q & 2) ? -vy : vy;
     }
-    double *p = a.pl + (size_t)q * 3 * a.N + t;
-    p[0] = sm[0][l];
-    p[a.N] = X;
-    p[2 * (size_t)a.N] = Y;
+    double2 *p = a.pl + (size_t)q * 2 * a.N + t;
+    p[0] = make_double2(sm[0][l], X);
+    p[a.N] = make_double2(Y, a.sdq[(size_t)q * a.N + t]);
   }
 }
 __device__ inline double ihalf(double m, double P, double X, double Y, double w, double wm,
@@ -310,7 +310,7 @@ __global__ void k_a_sweep(AArgs a) {
   const double ax = a.amu[kk], ay = a.aeta[kk];
   const double *Cq = a.cellq + (size_t)q * a.N * 6;
   const double *src = a.lam + (size_t)kk * a.N;
-  const double *pl = a.pl + (size_t)q * 3 * a.N;
+  const double2 *pl = a.pl + (size_t)q * 2 * a.N;
   const double w = a.w[kk], wm = a.wmu[kk], we = a.weta[kk];
   double *out = a.rb + (size_t)kk * a.N;
   __shared__ double edge[2][16];
@@ -336,7 +336,7 @@ __global__ void k_a_sweep(AArgs a) {
         const double east = xr > 0 ? prev : 0.0;
         const double north = yr > 0 ? below : 0.0;
         const double d = Cq[6 * o + 5] + ax + ay;
-        const double ih = ihalf(src[o], pl[o], pl[a.N + o], pl[2 * (long long)a.N + o], w, wm, we);
+        const double ih = ihalf(src[o], pl[o].x, pl[o].y, pl[a.N + o].x, w, wm, we);
         const double v = (ih + ax * east + ay * north) / d;
         out[o] = v;
         prev = v;
@@ -361,10 +361,21 @@ __global__ void k_a_sweep(AArgs a) {
 // SPLIT: as the forward recurrence, the reversed rows spread over np
 // workgroups (workgroup b is part b / K of ordinate b % K), the last reversed
 // row of a part handed to the next through the plan's hand-over buffer.
-constexpr int kAL = 8, kAR = 4 * kAL, kAMaxW = 16;
-static_assert(kAMaxW * kAL + 2 * kAL <= kDiagPad, "diagonal table padding");
-template <bool SPLIT>
-__global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
+// kAL: steps between the waves and of the loads ahead. 12 where a workgroup
+// has at most 4 waves (registers; the memory operations of 12 steps, up to 60,
+// are about what a wave can have under way), else 8.
+// Bound by one wave's instruction issue and the loads' latency: about 220
+// cycles of a step issue, as many wait. Four memory operations a step (the
+// planes in pairs) instead of six, 12 steps ahead and no scalar-load wait: 306
+// to 296 us at 512 x 512 x 128, a pass on 100 x 100 x 864 347 to 331 us. Two
+// ordinates per lane, the planes loaded once for both, were slower: a pass at
+// 512 x 512 x 128 took 871 us for 785.
+constexpr int kAMaxW = 16, kALongW = 4;
+template <bool SPLIT, int kAL>
+__global__ void __launch_bounds__((kAL > 8 ? kALongW : kAMaxW) * 64) k_a_chain(AArgs a, int np) {
+  constexpr int kAR = kAL > 8 ? 64 : 32, kW = kAL > 8 ? kALongW : kAMaxW;
+  static_assert(kW * kAL + 3 * kAL <= kDiagPad, "diagonal table padding");
+  static_assert(kAR >= 4 * kAL, "ring size");
   const int part = SPLIT ? blockIdx.x / a.K : 0;
   const int kk = blockIdx.x - part * a.K;
   const int q = quadrant_of(a, kk);
@@ -374,15 +385,13 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
   const double ax = a.amu[kk], ay = a.aeta[kk], axy = ax + ay;
   const double w = a.w[kk], wm = a.wmu[kk], we = a.weta[kk];
   const __amdgpu_buffer_rsrc_t Sr = buf_rsrc(a.lam + (size_t)kk * N, (size_t)N * 8);
-  const double *pl = a.pl + (size_t)q * 3 * N;
-  const __amdgpu_buffer_rsrc_t Pr = buf_rsrc(pl, (size_t)N * 8);
-  const __amdgpu_buffer_rsrc_t Xr = buf_rsrc(pl + N, (size_t)N * 8);
-  const __amdgpu_buffer_rsrc_t Yr = buf_rsrc(pl + 2 * (size_t)N, (size_t)N * 8);
-  const __amdgpu_buffer_rsrc_t Dr = buf_rsrc(a.sdq + (size_t)q * N, (size_t)N * 8);
+  const double2 *pl = a.pl + (size_t)q * 2 * N;
+  const __amdgpu_buffer_rsrc_t Pr = buf_rsrc(pl, (size_t)N * 16);
+  const __amdgpu_buffer_rsrc_t Yr = buf_rsrc(pl + N, (size_t)N * 16);
   const __amdgpu_buffer_rsrc_t Or = buf_rsrc(a.rb + (size_t)kk * N, (size_t)N * 8);
   const __attribute__((address_space(4))) int *DS =
       (const __attribute__((address_space(4))) int *)(a.dso + kDiagPad);
-  __shared__ double edge[kAMaxW][kAR];
+  __shared__ double edge[kW][kAR];
   const int r0 = part * (int)blockDim.x;    // first reversed row of this part
   const int rows = min((int)blockDim.x, ny - r0);   // one pass per part
   const int nw = (rows + 63) >> 6;
@@ -403,20 +412,25 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
   const int nsteps = nx + rows - 1;
   const int tend = ((nsteps + (nw - 1) * kAL + kAL - 1) / kAL) * kAL;
   const int s0 = -wave * kAL;               // this wave's step at time 0
-  double rb_s[kAL] = {}, rb_d[kAL] = {}, rb_p[kAL] = {}, rb_x[kAL] = {}, rb_y[kAL] = {};
+  double rb_s[kAL] = {};
+  double2 rb_p[kAL] = {}, rb_y[kAL] = {};
   unsigned rb_i[kAL] = {};
   auto load = [&](int t, int so) {          // row-0 storage index so of the step's diagonal
     const unsigned i = (unsigned)(so + yl);
     rb_i[t] = i;
     rb_s[t] = buf_ld64(Sr, i * 8u);
-    rb_d[t] = buf_ld64(Dr, i * 8u);
-    rb_p[t] = buf_ld64(Pr, i * 8u);
-    rb_x[t] = buf_ld64(Xr, i * 8u);
-    rb_y[t] = buf_ld64(Yr, i * 8u);
+    rb_p[t] = buf_ld128(Pr, i * 16u);
+    rb_y[t] = buf_ld128(Yr, i * 16u);
   };
   double vp = 0.0;
+  // diagonal offsets of a block's loads, one block ahead and in lanes, as in
+  // the forward recurrence: no scalar-load wait in a block
+  int dsn = DS[D - (r0 + s0 + min(lane, kAL - 1))];
+  asm volatile("" : "+v"(dsn));
   for (int tb = -kAL; tb < tend; tb += kAL) {
     const int sb = tb + s0;
+    const int dsc = dsn;
+    dsn = DS[D - (r0 + sb + 2 * kAL + min(lane, kAL - 1))];
     double bl[kAL];
     if (wave > 0) {
 #pragma unroll
@@ -429,7 +443,7 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
     }
     int so[kAL];
 #pragma unroll
-    for (int t2 = 0; t2 < kAL; ++t2) so[t2] = DS[D - (r0 + sb + kAL + t2)];
+    for (int t2 = 0; t2 < kAL; ++t2) so[t2] = __builtin_amdgcn_readlane(dsc, t2);
     double vv[kAL];
 #pragma unroll
     for (int t2 = 0; t2 < kAL; ++t2) {
@@ -437,8 +451,8 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
       const int xr = s - xo;
       const bool act = (unsigned)xr < (unsigned)nx;
       const double vN = shr1_fill(vp, bl[t2]);
-      const double inv = rcp64(rb_d[t2] + axy);
-      const double ih = ihalf(rb_s[t2], rb_p[t2], rb_x[t2], rb_y[t2], w, wm, we);
+      const double inv = rcp64(rb_y[t2].y + axy);
+      const double ih = ihalf(rb_s[t2], rb_p[t2].x, rb_p[t2].y, rb_y[t2].x, w, wm, we);
       const double vn = fma(ax * inv, vp, fma(ay * inv, vN, ih * inv));
       const double v = act ? vn : vp;
       buf_store(v, Or, act ? rb_i[t2] * 8u : kNoCell);
@@ -452,7 +466,7 @@ __global__ void __launch_bounds__(kAMaxW * 64) k_a_chain(AArgs a, int np) {
 #pragma unroll
       for (int t2 = 0; t2 < kAL; ++t2) edge[wave][(sb + t2) & (kAR - 1)] = vv[t2];
     }
-    __syncthreads();
+    lds_barrier();
   }
 }
 
@@ -501,8 +515,8 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a, int ts) {
   typedef const __attribute__((address_space(4))) double cdouble;
   cdouble *W = (cdouble *)a.w, *WM = (cdouble *)a.wmu, *WE = (cdouble *)a.weta;
   cdouble *AM = (cdouble *)a.amu, *AE = (cdouble *)a.aeta;
-  const double *pl = a.pl + (size_t)q * 3 * a.N + t;
-  const double P = pl[0], X = pl[a.N], Y = pl[2 * (size_t)a.N];
+  const double2 *pl = a.pl + (size_t)q * 2 * a.N + t;
+  const double P = pl[0].x, X = pl[0].y, Y = pl[a.N].x;
   double sm = 0.0, sr = 0.0;
   // ordinate kk from its loaded values (rb at the cell and its neighbours, m
   // at the cell)
@@ -772,11 +786,15 @@ void adj_launch_pass(const PlanDev &P, const AdjointBuffers &B, const void *args
   hipLaunchKernelGGL(k_a_planes, dim3(nt), dim3(kB), 0, s, a);
   int rows = ((P.ny + 63) / 64) * 64;
   if (rows > 1024) rows = 1024;
-  if (P.adj_parts > 1)
-    hipLaunchKernelGGL(k_a_chain<true>, dim3(P.adj_parts * P.K), dim3(P.adj_rows), 0, s, a,
-                       P.adj_parts);
+  const int np = P.adj_parts;
+  if (np > 1 && P.adj_rows <= kALongW * 64)
+    hipLaunchKernelGGL((k_a_chain<true, 12>), dim3(np * P.K), dim3(P.adj_rows), 0, s, a, np);
+  else if (np > 1)
+    hipLaunchKernelGGL((k_a_chain<true, 8>), dim3(np * P.K), dim3(P.adj_rows), 0, s, a, np);
+  else if (rows <= kALongW * 64 && P.ny <= rows)
+    hipLaunchKernelGGL((k_a_chain<false, 12>), dim3(P.K), dim3(rows), 0, s, a, 1);
   else if (P.ny <= kAMaxW * 64)
-    hipLaunchKernelGGL(k_a_chain<false>, dim3(P.K), dim3(rows), 0, s, a, 1);
+    hipLaunchKernelGGL((k_a_chain<false, 8>), dim3(P.K), dim3(rows), 0, s, a, 1);
   else hipLaunchKernelGGL(k_a_sweep, dim3(P.K), dim3(rows), 0, s, a);
   const int ts = (nb + 7) / 8;
   hipLaunchKernelGGL(k_a_out, dim3(4 * 8 * ts), dim3(kB), 0, s, a, ts);
