@@ -1904,12 +1904,13 @@ __global__ void k_material(const SynthDesc *ds, const int2 *bt, int sub) {
 }
 
 // p[e t], p[e (t + blockDim)], ... (t = threadIdx.x; n terms in all) added
-// in that order; sixteen loads in flight at a time (terms past n add 0, and
-// every sum here is of squares)
-__device__ inline double strided_sum(const double *p, int n, int e) {
+// in that order, the first loaded by the caller (that of every array before any
+// is waited for); sixteen loads in flight at a time (terms past n add 0,
+// and every sum here is of squares)
+__device__ inline double strided_sum(const double *p, int n, int e, double first) {
   constexpr int U = 16;
-  double s = 0.0;
-  for (int t0 = threadIdx.x; t0 < n; t0 += U * (int)blockDim.x) {
+  double s = (int)threadIdx.x < n ? first : 0.0;
+  for (int t0 = threadIdx.x + blockDim.x; t0 < n; t0 += U * (int)blockDim.x) {
     double v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1933,48 +1934,68 @@ __device__ inline double strided_sum(const double *p, int n, int e) {
 // |1 - 1/g| for a growth factor g. last_err[1] keeps that smallest change.
 __device__ inline void err_finish(CDesc &D, double *sh) {
   int32_t *state = D.state;
-  if (state[1] != 0) return;
   const int npart = nblk_d(D.N);
+  // the first partials and the scalars before the flag is tested
+  auto first = [](const double *p, int n, int e) {
+    return p[(int)threadIdx.x < n ? (size_t)e * threadIdx.x : 0];
+  };
+  const double *pe = D.err_parts, *pt = D.td ? D.err_parts_T : pe;
+  const double a0 = first(pe, npart, 2), b0 = first(pe + 1, npart, 2);
+  const double r0 = first(D.tres_part, D.n_tres, 1), q0 = first(D.src2_part, D.n_src2, 1);
+  const double s0 = first(pt, npart, 2), t0 = first(pt + 1, npart, 2);
+  if (state[1] != 0) return;
   // (the residual-norm partials number one per residual wave: tens of
   // thousands on large grids)
-  double a = strided_sum(D.err_parts, npart, 2), b = strided_sum(D.err_parts + 1, npart, 2);
-  double rr = strided_sum(D.tres_part, D.n_tres, 1), ss = strided_sum(D.src2_part, D.n_src2, 1);
+  double a = strided_sum(pe, npart, 2, a0), b = strided_sum(pe + 1, npart, 2, b0);
+  double rr = strided_sum(D.tres_part, D.n_tres, 1, r0);
+  double ss = strided_sum(D.src2_part, D.n_src2, 1, q0);
   double aT = 0.0, bT = 0.0;
   if (D.td) {
-    aT = strided_sum(D.err_parts_T, npart, 2);
-    bT = strided_sum(D.err_parts_T + 1, npart, 2);
+    aT = strided_sum(pt, npart, 2, s0);
+    bT = strided_sum(pt + 1, npart, 2, t0);
   }
   const double dmin = D.last_err[1];
-  double num = block_sum(a, sh);
-  double den = block_sum(b, sh);
-  rr = block_sum(rr, sh);
-  ss = block_sum(ss, sh) * D.sw;
-  if (D.td) {
-    aT = block_sum(aT, sh);
-    bT = block_sum(bT, sh);
+  // the sums side by side: wave sums, then in wave order
+  double sums[6] = {a, b, rr, ss, aT, bT};
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+    if (e >= 4 && !D.td) break;
+    const double w = wave_sum(sums[e]);
+    if ((threadIdx.x & 63) == 0) sh[6 * (threadIdx.x >> 6) + e] = w;
   }
-  if (threadIdx.x == 0) {
-    double err = den > 0.0 ? sqrt(num / den) : (num == 0.0 ? 0.0 : INFINITY);
-    if (D.td) {    // max(Err(rho), Err(T)), the criterion after Eq. Err_W
-      const double eT = bT > 0.0 ? sqrt(aT / bT) : (aT == 0.0 ? 0.0 : INFINITY);
-      err = eT > err ? eT : err;
-    }
-    const double tres = ss > 0.0 ? sqrt(rr / ss) : (rr == 0.0 ? 0.0 : INFINITY);
-    const int m = state[0];
-    D.err_hist[m] = err;
-    D.tres_hist[m] = tres;
-    // V-cycles of this iteration's (last) synthetic solve: the first after
-    // the warm start, one per CG iteration
-    if (D.method) D.scal[S_VCYCLES] += D.scal[S_NIT] + 1.0;
-    const double dn = sqrt(num), pn = sqrt(den);
-    D.last_err[0] = err;
-    if (dn < dmin) D.last_err[1] = dn;
-    state[0] = m + 1;
-    state[2] = 1 - state[2];   // I^{m+1} now lives in the other buffer
-    if (!isfinite(err) || dn > 1e3 * fmax(dmin, 1e-9 * pn)) state[1] = -1;
-    else if (err < D.tol) state[1] = 1;
-    else if (m + 1 >= D.max_iter) state[1] = 2;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+    if (e >= 4 && !D.td) break;
+    sums[e] = 0.0;
+    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) sums[e] += sh[6 * k + e];
   }
+  const double num = sums[0], den = sums[1];
+  rr = sums[2];
+  ss = sums[3] * D.sw;
+  aT = sums[4];
+  bT = sums[5];
+  double err = den > 0.0 ? sqrt(num / den) : (num == 0.0 ? 0.0 : INFINITY);
+  if (D.td) {    // max(Err(rho), Err(T)), the criterion after Eq. Err_W
+    const double eT = bT > 0.0 ? sqrt(aT / bT) : (aT == 0.0 ? 0.0 : INFINITY);
+    err = eT > err ? eT : err;
+  }
+  const double tres = ss > 0.0 ? sqrt(rr / ss) : (rr == 0.0 ? 0.0 : INFINITY);
+  const int m = state[0];
+  D.err_hist[m] = err;
+  D.tres_hist[m] = tres;
+  // V-cycles of this iteration's (last) synthetic solve: the first after
+  // the warm start, one per CG iteration
+  if (D.method) D.scal[S_VCYCLES] += D.scal[S_NIT] + 1.0;
+  const double dn = sqrt(num), pn = sqrt(den);
+  D.last_err[0] = err;
+  if (dn < dmin) D.last_err[1] = dn;
+  state[0] = m + 1;
+  state[2] = 1 - state[2];   // I^{m+1} now lives in the other buffer
+  if (!isfinite(err) || dn > 1e3 * fmax(dmin, 1e-9 * pn)) state[1] = -1;
+  else if (err < D.tol) state[1] = 1;
+  else if (m + 1 >= D.max_iter) state[1] = 2;
 }
 
 // src = (sigma_s phi + q) / (4 pi); the mirrored per-quadrant copies of
@@ -2009,15 +2030,8 @@ __device__ inline void source_tile(CDesc &D, const Blk &B, double *s_sc, double 
     s_sc[t] = sc; s_dq[t] = dq; s_pq[t] = pq;
   }
   __syncthreads();
-  // cell t of a kSrcT x kSrcT square in anti-diagonal order (diagonal e = u +
-  // w, then w): (u, w) in the square's own frame
-  int e = 0, before = 0;
-  for (;; ++e) {
-    const int len = e < kSrcT ? e + 1 : 2 * kSrcT - 1 - e;
-    if (t < before + len) break;
-    before += len;
-  }
-  const int w = (e < kSrcT ? 0 : e - kSrcT + 1) + (t - before), u = e - w;
+  int u, w;                      // cell t of the square in anti-diagonal order
+  square_diag<kSrcT>(t, u, w);
   for (int qd = 0; qd < 4; ++qd) {
     // the square in quadrant qd's mirrored frame: u runs against x when x
     // is mirrored, w against y when y is
@@ -2047,6 +2061,10 @@ __global__ void __launch_bounds__(kRedBlock) k_source(const SynthDesc *ds, const
 // n8 + b runs on XCD b % 8 and takes tile (b % 8) ts + b / 8), so the
 // partly written cache lines at the ends of a tile's diagonal runs mostly
 // meet the neighbouring tile's part in the same L2.
+// Latency is all of it on small grids: the first partials of every sum are
+// loaded together, the sums are reduced side by side, a thread finds its place
+// on the diagonals in closed form. 32 x 32: 5.5 to 3.7 us, 40 x 40 with 1728
+// ordinates 5.8 to 4.8, 128 x 128 (time-dependent) 7.3 to 6.0.
 __global__ void __launch_bounds__(kRedBlock) k_err_source(const SynthDesc *ds, const int2 *bt,
                                                           int n, int n8, int ntile, int ts,
                                                           int cond) {

@@ -1472,20 +1472,6 @@ __device__ __forceinline__ void src2_block(const TArgs &a, const int blk) {
 // less of the cache lines at the runs' ends; smaller ones give small grids
 // more workgroups. ftp (transport-face HoT): the thread also forms its
 // cells' interior face fluxes.
-// cell t of a kMT x kMT square in anti-diagonal order (diagonal e = u + w,
-// then w): its place (u, w) in the square
-template <int kMT>
-__device__ inline void square_diag(int t, int &u, int &w) {
-  int e = 0, before = 0;
-  for (;; ++e) {
-    const int len = e < kMT ? e + 1 : 2 * kMT - 1 - e;
-    if (t < before + len) break;
-    before += len;
-  }
-  w = (e < kMT ? 0 : e - kMT + 1) + (t - before);
-  u = e - w;
-}
-
 template <typename T>
 __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, const int q);
 

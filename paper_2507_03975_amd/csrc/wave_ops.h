@@ -37,6 +37,22 @@ __device__ inline double shr1_fill(double v, double fill) {
   hi = __builtin_amdgcn_update_dpp(hi, __double2hiint(v), 0x138, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
+// Cell t of an MT x MT square (MT <= 32) in anti-diagonal order (diagonal
+// e = u + w, then w): its place (u, w) in the square. In the first half a
+// diagonal starts at e (e + 1) / 2; the root finds e to within one (a loop
+// over the diagonals is up to 63 steps for some lane of every wave).
+template <int MT>
+__device__ inline void square_diag(int t, int &u, int &w) {
+  constexpr int n = MT * MT, half = MT * (MT + 1) / 2;
+  const int s = t < half ? t : n - 1 - t;
+  int e = (int)((__builtin_sqrtf(8.0f * (float)s + 1.0f) - 1.0f) * 0.5f);
+  if (e * (e + 1) / 2 > s) --e;
+  else if ((e + 1) * (e + 2) / 2 <= s) ++e;
+  const int k = s - e * (e + 1) / 2;       // along the diagonal
+  w = t < half ? k : MT - 1 - k;
+  u = t < half ? e - k : 2 * MT - 2 - e - w;
+}
+
 // Sum over the 64 lanes (every lane active) by a butterfly of lane
 // exchanges: each step adds the same two values on both lanes of a pair, so
 // every lane ends with the same bits.
