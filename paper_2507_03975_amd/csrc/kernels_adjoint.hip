@@ -423,11 +423,16 @@ __global__ void __launch_bounds__((kAL > 8 ? kALongW : kAMaxW) * 64) k_a_chain(A
     rb_y[t] = buf_ld128(Yr, i * 16u);
   };
   double vp = 0.0;
+  // as there, a wave outside its rows' steps only meets the barriers
+  const int sfirst = (wave * 64 / kAL - 1) * kAL;
+  const int slast = wave < nw ? nx + wave * 64 + 62 : -tend - kAL;
+  int tb = -kAL;
+  for (; tb < tend && tb + s0 < sfirst; tb += kAL) lds_barrier();
   // diagonal offsets of a block's loads, one block ahead and in lanes, as in
   // the forward recurrence: no scalar-load wait in a block
-  int dsn = DS[D - (r0 + s0 + min(lane, kAL - 1))];
+  int dsn = DS[D - (r0 + sfirst + kAL + min(lane, kAL - 1))];
   asm volatile("" : "+v"(dsn));
-  for (int tb = -kAL; tb < tend; tb += kAL) {
+  for (; tb < tend && tb + s0 <= slast; tb += kAL) {
     const int sb = tb + s0;
     const int dsc = dsn;
     dsn = DS[D - (r0 + sb + 2 * kAL + min(lane, kAL - 1))];
@@ -468,6 +473,7 @@ __global__ void __launch_bounds__((kAL > 8 ? kALongW : kAMaxW) * 64) k_a_chain(A
     }
     lds_barrier();
   }
+  for (; tb < tend; tb += kAL) lds_barrier();
 }
 
 // m' = ihb - sigma_t rb - Div2^T rb, the part of lambda' that belongs to one

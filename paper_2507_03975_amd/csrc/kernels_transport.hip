@@ -997,15 +997,22 @@ __device__ __forceinline__ void chain_ordinate(A &a, const int kk, const int par
     unsigned long long hv = 0;
     bool gave_up = false;                     // a wait timed out: wait no more
     const bool top_lane = SPLIT && tid == rows - 1;   // this part's top row
+    // A wave's rows are active for nx + 63 of the workgroup's steps: before
+    // the block that loads for its first and after its last it only meets
+    // the others at the barriers.
+    const int sfirst = (wave * 64 / LAG - 1) * LAG;
+    const int slast = wave < nw ? nx + wave * 64 + 62 : -tend - LAG;
+    int tb = -LAG;
+    for (; tb < tend && tb + s0 < sfirst; tb += LAG) lds_barrier();
     // diagonal offsets of a block's loads, one block ahead: lane l holds that
     // of the block's load l, read back as a wave-uniform lane value (a vector
     // load, in order with the ring's, so no scalar-load wait in a block)
-    int dsn = DS[y0 - LAG + s0 + PF + (lane & (LAG - 1))];
+    int dsn = DS[y0 + sfirst + PF + (lane & (LAG - 1))];
     // (the first one lands before the loop: still in flight at the loop
     // head, the wait pass would cover it conservatively in every block, with
     // all the ring's loads behind it)
     asm volatile("" : "+v"(dsn));
-    for (int tb = -LAG; tb < tend; tb += LAG) {
+    for (; tb < tend && tb + s0 <= slast; tb += LAG) {
       const int sb = tb + s0;                 // this wave's first step of the block
       const int dsc = dsn;
       dsn = DS[y0 + sb + LAG + PF + (lane & (LAG - 1))];
@@ -1055,6 +1062,7 @@ __device__ __forceinline__ void chain_ordinate(A &a, const int kk, const int par
       }
       lds_barrier();
     }
+    for (; tb < tend; tb += LAG) lds_barrier();
     __syncthreads();   // the pass's row hand-off (rowbuf, global memory)
   }
 }
