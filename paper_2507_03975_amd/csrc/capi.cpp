@@ -500,17 +500,20 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     cus = 0;
   {
     // workgroups per ordinate in the recurrence (GSIS_CHAIN_PARTS=1..4 sets
-    // it): a step costs a wave about the same whatever the rest of the chip
-    // does, but waves sharing a SIMD take turns, so parts of about 256 rows
-    // (one wave per SIMD); more parts while the ordinates fill fewer than
-    // half the CUs; at most 4, each a multiple of 64 rows and at most 1024,
-    // the top part not empty
-    int parts = std::min((ny + 255) / 256, 4);
-    while (parts < 4 && 2 * K * parts < cus) parts *= 2;
-    // the adjoint's sweep loads five values a step where the recurrence loads
-    // two: parts of about 128 rows, two waves (256 rows 85 us in 2 parts
-    // against 112 in 1; 512 rows 307 us in 4 against 349 in 2)
-    int aparts = std::max(parts, std::min((ny + 127) / 128, 4));
+    // it): one up to 384 rows, then parts of about 256 rows; at most 4, each
+    // a multiple of 64 rows and at most 1024, the top part not empty. A wave
+    // outside its rows' steps costs nothing, so one workgroup's waves on one
+    // CU are rarely in each other's way, and a hand-over through memory costs
+    // 10 us or so. An iteration (SI), 1 part and 2: 256 rows, 128 ordinates
+    // 133 and 146 us; 330, 64: 162 and 169; 400, 128: 359 and 355; 512, 128: 546
+    // and 531 (3: 532); 700, 64: 665 and 627 (3: 583); 1000, 16: 1088 and 990
+    // (4: 840). Few ordinates are no reason for more parts: 512 rows, 4
+    // ordinates 280 us in 2, 284 in 4.
+    int parts = ny <= 384 ? 1 : std::min((ny + 255) / 256, 4);
+    // the adjoint's sweep loads twice as much a step: parts of about 128 rows,
+    // two waves (a pass at 512 rows, 128 ordinates 760 us in 4, 779 in 2, 823
+    // in 1; 256 rows 263 in 2, 266 in 1)
+    int aparts = std::min((ny + 127) / 128, 4);
     const char *e = getenv("GSIS_CHAIN_PARTS");
     if (e && e[0] >= '1' && e[0] <= '4' && e[1] == 0) parts = aparts = e[0] - '0';
     auto split = [&](int n, int &np, int &rows) {
