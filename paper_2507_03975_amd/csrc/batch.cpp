@@ -176,6 +176,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
   bool any_sep = false;
   size_t lds = 0;
   int cells = 0;
+  bool whole = true;
   for (int a = 0; a < n; ++a) {
     const PlanDev &P = b->subs[act[a]]->P;
     D[a] = make_synth_desc(P);
@@ -185,6 +186,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
     any_sep = any_sep || D[a].coef_sep != 0;
     lds = std::max(lds, P.S.coarse_lds);
     cells = std::max(cells, P.S.coarse_cells);
+    whole = whole && P.S.whole;
   }
   {
     std::vector<char> dh(sizeof(SynthDesc) * std::max(n, 1));
@@ -198,6 +200,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
   S.min_lc = n ? min_lc : 0;
   S.coarse_lds = lds;
   S.coarse_cells = cells;
+  S.whole = whole;
   S.any_coef_sep = any_sep;
   S.state0 = nullptr;
   auto nb = [](long long m) { return (int)((m + 255) / 256); };

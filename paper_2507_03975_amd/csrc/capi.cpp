@@ -356,6 +356,7 @@ gsis_status make_single_set(gsis_plan *pl) {
   P.lc = D.lc;
   S.coarse_lds = coarse_lds_bytes(P);
   S.coarse_cells = coarse_cells(P);
+  S.whole = P.precision == GSIS_FP64;
   S.synth_max_iter = P.synth_max_iter;
   S.nb_cell = nb(P.N);
   S.bt_cell = nullptr;

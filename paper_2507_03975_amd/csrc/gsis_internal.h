@@ -163,6 +163,7 @@ struct SynthSet {
   int min_lc = 0;                     // shallowest first coarse level
   size_t coarse_lds = 0;              // dynamic LDS of the coarse kernel
   int coarse_cells = 0;               // most cells of a first coarse level
+  bool whole = false;                 // k_cg_small may make the solve
   int synth_max_iter = 50;
   // block tables (nullptr for a single problem) and their block counts
   int2 *bt_cell = nullptr;            // level-0 cells of every problem

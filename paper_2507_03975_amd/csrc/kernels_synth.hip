@@ -683,18 +683,28 @@ struct Region {
     v = fma(say[r], x[r + W], v);
     return fma(say[r - W], x[r - W], v);
   }
+  // d x - the sum of region cell r's couplings times x of its neighbours
+  static __device__ __forceinline__ double apply(int r, double d, const double *sax,
+                                                 const double *say, const double *x) {
+    double y = fma(d, x[r], -(sax[r] * x[r + 1]));
+    y = fma(-sax[r - 1], x[r - 1], y);
+    y = fma(-say[r], x[r + W], y);
+    return fma(-say[r - W], x[r - W], y);
+  }
 };
 
 // Bound by latency: at 256 x 256 (256 tiles) and below a launch is one round
 // of short phases: one round trip to memory, then 3 half sweeps on the LDS. A
 // thread keeps its region cells' places and operator in registers from the
-// loads to the last half sweep (the CG update of level 0 as well), divides by
-// multiplying with a reciprocal formed once, and takes only the red cells'
-// residuals. 128 x 128: 6.2 to 4.8 us a launch (k_mg_up0 4.6 to 4.0); 512 x
-// 512: 7.7 to 6.6 (8.3 to 6.8); 1024 x 1024: 11.4 to 10.3 (20.8 to 16.8).
+// loads to the last half sweep (the CG update of level 0 as well) and forms
+// the reciprocals of its divisions once (div64: the quotients are a division's
+// bits; every operation and its order is that of the plain form, see
+// launch_synth_solve on FP32-mixed plans). 128 x 128: 6.2 to 4.8 us a launch
+// (k_mg_up0 4.6 to 4.0); 512 x 512: 7.7 to 6.6 (8.3 to 6.8); 1024 x 1024: 11.4
+// to 10.3 (20.8 to 16.8).
 __global__ void __launch_bounds__(kRedBlock) k_mg_down(const SynthDesc *ds, const int2 *bt, int l,
                                                        int v, int rr_ext) {
-  __shared__ double sb[kRN], si[kRN], sax[kRN], say[kRN], sx[kRN], sr[kTW * kTH], sh[kRedBlock];
+  __shared__ double sb[kRN], sd[kRN], sax[kRN], say[kRN], sx[kRN], sr[kTW * kTH], sh[kRedBlock];
   typedef Region<kRW, kRH> Reg;
   const Blk B = blk(bt);
   CDesc &D = cdesc(ds, B.p);
@@ -767,10 +777,12 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_down(const SynthDesc *ds, cons
   for (int k = 0; k < Reg::P; ++k) {
     const int r = threadIdx.x + k * kRedBlock;
     if (r < kRN) {
-      const double bv = R.in[k] ? vb[k] : 0.0, id = rcp64(R.in[k] ? R.d[k] : 1.0);
-      sb[r] = bv;
-      si[r] = id;
-      sx[r] = R.red[k] ? bv * id : 0.0;
+      vb[k] = R.in[k] ? vb[k] : 0.0;
+      R.d[k] = R.in[k] ? R.d[k] : 1.0;
+      vw[k] = rcp64(R.d[k]);
+      sb[r] = vb[k];
+      sd[r] = R.d[k];
+      sx[r] = R.red[k] ? div64(vb[k], R.d[k], vw[k]) : 0.0;
     }
   }
   __syncthreads();
@@ -778,15 +790,14 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_down(const SynthDesc *ds, cons
 #pragma unroll
   for (int k = 0; k < Reg::P; ++k) {
     const int r = threadIdx.x + k * kRedBlock;
-    if (!R.red[k] && R.inner(k, 1)) sx[r] = Reg::add_nb(r, sax, say, sx, sb[r]) * si[r];
+    if (!R.red[k] && R.inner(k, 1))
+      sx[r] = div64(Reg::add_nb(r, sax, say, sx, vb[k]), R.d[k], vw[k]);
   }
   __syncthreads();
-  // residuals: black ones vanish, a red one is the sum of its couplings times
-  // the black values (what it was from zero, b - d (b / d), is 0); x of the
-  // tile to global
+  // residuals; x of the tile to global
   {
     const int r = (tj + kHalo) * kRW + ti + kHalo;
-    sr[threadIdx.x] = in && ((gi + gj) & 1) == 0 ? Reg::add_nb(r, sax, say, sx, 0.0) : 0.0;
+    sr[threadIdx.x] = in ? sb[r] - Reg::apply(r, sd[r], sax, say, sx) : 0.0;
     if (in) xs[g] = sx[r];
   }
   if (upd) {
@@ -848,7 +859,8 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up(const SynthDesc *ds, const 
     const int r = threadIdx.x + k * kRedBlock;
     if (r < kRN) sxc[r] = R.in[k] ? fma(omega, ve[k], vs[k]) : 0.0;
     vb[k] = R.in[k] ? vb[k] : 0.0;
-    R.d[k] = rcp64(R.in[k] ? R.d[k] : 1.0);
+    R.d[k] = R.in[k] ? R.d[k] : 1.0;
+    vs[k] = rcp64(R.d[k]);
   }
   const double ic = rcp64(dc);
   __syncthreads();
@@ -856,13 +868,14 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up(const SynthDesc *ds, const 
 #pragma unroll
   for (int k = 0; k < Reg::P; ++k) {
     const int r = threadIdx.x + k * kRedBlock;
-    if (!R.red[k] && R.inner(k, 1)) sx[r] = Reg::add_nb(r, sax, say, sxc, vb[k]) * R.d[k];
+    if (!R.red[k] && R.inner(k, 1))
+      sx[r] = div64(Reg::add_nb(r, sax, say, sxc, vb[k]), R.d[k], vs[k]);
   }
   __syncthreads();
   // red half sweep on the tile with the new black neighbours
   if (in) {
     const int r = (tj + kHalo) * kRW + ti + kHalo;
-    x[g] = ((gi + gj) & 1) == 0 ? Reg::add_nb(r, sax, say, sx, bc) * ic : sx[r];
+    x[g] = ((gi + gj) & 1) == 0 ? div64(Reg::add_nb(r, sax, say, sx, bc), dc, ic) : sx[r];
   }
 }
 
@@ -907,32 +920,36 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up0(const SynthDesc *ds, const
     const int r = threadIdx.x + k * kRedBlock;
     if (r < Reg::N) sxc[r] = R.in[k] ? fma(omega, ve[k], vs[k]) : 0.0;
     vb[k] = R.in[k] ? vb[k] : 0.0;
-    R.d[k] = rcp64(R.in[k] ? R.d[k] : 1.0);
+    R.d[k] = R.in[k] ? R.d[k] : 1.0;
+    vs[k] = rcp64(R.d[k]);
   }
   __syncthreads();
   // black on the region less a ring of one, into sx
 #pragma unroll
   for (int k = 0; k < Reg::P; ++k) {
     const int r = threadIdx.x + k * kRedBlock;
-    if (!R.red[k] && R.inner(k, 1)) sx[r] = Reg::add_nb(r, sax, say, sxc, vb[k]) * R.d[k];
+    if (!R.red[k] && R.inner(k, 1))
+      sx[r] = div64(Reg::add_nb(r, sax, say, sxc, vb[k]), R.d[k], vs[k]);
   }
   __syncthreads();
   // red on the region less a ring of two (reads black cells only)
 #pragma unroll
   for (int k = 0; k < Reg::P; ++k) {
     const int r = threadIdx.x + k * kRedBlock;
-    if (R.red[k] && R.inner(k, 2)) sx[r] = Reg::add_nb(r, sax, say, sx, vb[k]) * R.d[k];
+    if (R.red[k] && R.inner(k, 2))
+      sx[r] = div64(Reg::add_nb(r, sax, say, sx, vb[k]), R.d[k], vs[k]);
   }
   __syncthreads();
   // the tile cell of this thread: z, w = A z, partials of r.z and z.w
   const int r = (cj + kU0Halo) * kU0W + ci + kU0Halo;
   const double zv = in ? sx[r] : 0.0;
-  const double wv = in ? -Reg::add_nb(r, sax, say, sx, -dc * zv) : 0.0;
+  const double wv = in ? Reg::apply(r, dc, sax, say, sx) : 0.0;
   if (in) {
     D.cg_z[g] = zv;
     D.cg_w[g] = wv;
   }
-  double trz = bc * zv, tzw = zv * wv;
+  // (selected, so that no product is fused into the first add of the sums)
+  double trz = in ? bc * zv : 0.0, tzw = in ? zv * wv : 0.0;
   block_sum2(trz, tzw, sh);
   if (threadIdx.x == 0) {
     red_rz(D)[B.lb] = trz;
@@ -964,9 +981,8 @@ __global__ void __launch_bounds__(kRedBlock) k_mg_up0(const SynthDesc *ds, const
 //    to the side and half a row up and down: neighbouring lanes read
 //    neighbouring words, and with zeros around the planes no edge is a case
 //    of its own.
-//  * After the second (black) half sweep from zero the black residuals vanish
-//    and a red one is the sum of its couplings times the black values (what
-//    it was from zero, b - d (b / d), is 0). The black cells start at 0: a
+//  * After the second (black) half sweep from zero the black residuals
+//    vanish, so only red cells form one. The black cells start at 0: a
 //    missing neighbour reads the cell itself, times a zero coupling, which
 //    must not find what the LDS held before.
 //  * Going up, the black half sweep reads its red neighbours with the
@@ -995,21 +1011,19 @@ __device__ inline bool colour_cell(int e, int k, int nx, int ny, int &i, int &j)
 // Two consecutive cells of a level below the top that a thread owns, by
 // colour (0 red, 1 black; in this order of cells colours alternate, also from
 // one row to the next when nx is odd), and the LDS places of them and of their
-// neighbours. The other cell of the pair is the neighbour in the row on one
-// side (not across a row's end: zero coupling), o the one on the other side. A
-// neighbour that does not exist is given the cell's own place, with a zero
-// coupling; so has a last cell without its other one (right-hand side 0).
+// neighbours. A neighbour that does not exist is given the cell's own place,
+// with a zero coupling; so has a last cell without its other one
+// (right-hand side 0).
 struct Pair {
-  int c[2], o[2], n[2], s[2];
+  int c[2], e[2], w[2], n[2], s[2];
   int pc;                      // parent of the black cell on the next level
   int f;                       // flags below
-  double id[2], aP, aO[2], aN[2], aS[2];
+  double d[2], id[2], aE[2], aW[2], aN[2], aS[2];
 };
 // kOk: the pair exists; kLB: its first (left) cell is black; kTwo: the right
 // cell exists. Parents of the black cell's neighbours that differ from its
-// own: kPP the other cell's, kPO the outer one's, kPN, kPS north and south.
-// kWrap: the pair across the first row's end
-enum { kOk = 1, kLB = 2, kTwo = 4, kPP = 8, kPO = 16, kPN = 32, kPS = 64, kWrap = 128 };
+// own: kPE, kPW, kPN, kPS. kWrap: the pair across the first row's end
+enum { kOk = 1, kLB = 2, kTwo = 4, kPE = 8, kPW = 16, kPN = 32, kPS = 64, kWrap = 128 };
 typedef double dbl2 __attribute__((ext_vector_type(2), aligned(8)));
 
 // The problem's record for these kernels (CoarseRec in lane k's word k): read
@@ -1052,12 +1066,12 @@ struct CoarseWG {
   int ol;                      // levels 1 .. ol are owned by threads
   const double omega;
   // the top level's pairs, by colour; places of the neighbours in the other
-  // plane, relative to the pair's: outer at to (red), -to (black), north at tg
-  // (red), th (black), south at -th (red), -tg (black)
-  double ti[2][M], tP[M], tO[2][M], tN[2][M], tS[2][M];   // 1 / diagonal, couplings
+  // plane, relative to the pair's: east at te (red), 1 - te (black), west one
+  // before it, north at tg (red), th (black), south at -th (red), -tg (black)
+  double ti[2][M], tE[2][M], tW[2][M], tN[2][M], tS[2][M];   // 1 / diagonal, couplings
   double tb[2][M];             // right-hand side
   double td[2][M];             // diagonal
-  int to[M], tg[M], th[M];
+  int te[M], tg[M], th[M];
   int tij[M];                  // the left cell's i | j << 16
   Pair lo[OM];
   double lb[2][OM];
@@ -1138,13 +1152,12 @@ struct CoarseWG {
   }
 
   // Pair p of level t > 0, its left cell at (i, j): loads of the operator, by
-  // place (left 0, right 1; the left cell's west coupling in aO[0], the right
-  // cell's east one in aO[1]) until sort() orders them by colour, and the
-  // places meanwhile. Couplings across a grid's edge are stored as zeros (ax
-  // at the end of each row, ay on the last row): those of the west and south
-  // edges are read there. A last cell on its own loads one value past the
-  // level's arrays: they lie one behind the other, and the device pieces they
-  // lie in end on 256 bytes.
+  // place (left 0, right 1) until sort() orders them by colour, and the places
+  // meanwhile. Couplings across a grid's edge are stored as zeros (ax at the
+  // end of each row, ay on the last row): those of the west and south edges
+  // are read there. A last cell on its own loads one value past the level's
+  // arrays: they lie one behind the other, and the device pieces they lie in
+  // end on 256 bytes.
   __device__ __forceinline__ void own(Pair &q, int t, int p, int i, int j) {
     const Lev v = lev(t);
     const int nx = v.nx, ny = v.ny, n = v.n, l = 2 * p;
@@ -1153,20 +1166,21 @@ struct CoarseWG {
     const unsigned o = 8u * l;
     const dbl2 d = ld2(dg, o), x = ld2(ax, o), y = ld2(ay, o);
     const dbl2 u = ld2(ay, o + 8u * (SL ? -nx : n - nx));
-    q.aO[0] = ld1(ax, o + 8u * (W ? -1 : nx - 1));
-    q.id[0] = d.x; q.id[1] = d.y;
-    q.aP = x.x; q.aO[1] = x.y;
+    q.aW[0] = ld1(ax, o + 8u * (W ? -1 : nx - 1));
+    q.d[0] = d.x; q.d[1] = d.y;
+    q.aE[0] = q.aW[1] = x.x; q.aE[1] = x.y;
     q.aN[0] = y.x; q.aN[1] = y.y;
     q.aS[0] = u.x; q.aS[1] = u.y;
     const bool in = i + 1 < nx, two = l + 1 < n;   // in: both in one row
     const int ir = in ? i + 1 : 0, jr = in ? j : j + 1;
-    const bool E = two && ir + 1 < nx, SR = two && jr > 0;
+    const bool ER = two && ir + 1 < nx, EL = two && in, SR = two && jr > 0;
     const bool NL = j + 1 < ny, NR = two && jr + 1 < ny, lbk = (i + j) & 1;
-    const int oL = W ? -1 : 0, oR = E ? 1 : 0;
     const int r = two ? l + 1 : l;
+    const int eL = EL ? 1 : 0, eR = ER ? 1 : 0, wL = W ? 1 : 0;
     const int nL = NL ? nx : 0, nR = NR ? nx : 0, sL = SL ? nx : 0, sR = SR ? nx : 0;
     q.c[0] = lbk ? r : l; q.c[1] = lbk ? l : r;
-    q.o[0] = q.c[0] + (lbk ? oR : oL); q.o[1] = q.c[1] + (lbk ? oL : oR);
+    q.e[0] = q.c[0] + (lbk ? eR : eL); q.e[1] = q.c[1] + (lbk ? eL : eR);
+    q.w[0] = q.c[0] - (lbk ? eL : wL); q.w[1] = q.c[1] - (lbk ? wL : eL);
     q.n[0] = q.c[0] + (lbk ? nR : nL); q.n[1] = q.c[1] + (lbk ? nL : nR);
     q.s[0] = q.c[0] - (lbk ? sR : sL); q.s[1] = q.c[1] - (lbk ? sL : sR);
     q.f = kOk | (lbk ? kLB : 0) | (two ? kTwo : 0) | (!in && !SL ? kWrap : 0);
@@ -1174,25 +1188,28 @@ struct CoarseWG {
     // previous neighbour have another parent; of one, every neighbour
     const int sx = v.sx, sy = v.sy, cnx = lev(t + 1).nx;
     const int ib = lbk ? i : ir, jb = lbk ? j : jr;
-    const bool N = lbk ? NL : NR, S = lbk ? SL : SR;
+    const bool N = lbk ? NL : NR, S = lbk ? SL : SR, E = lbk ? EL : ER, Wb = lbk ? W : EL;
     q.pc = lbk || two ? (jb >> sy) * cnx + (ib >> sx) : 0;
     const bool xo = !sx || (ib & 1), xe = !sx || !(ib & 1);
     const bool yo = !sy || (jb & 1), ye = !sy || !(jb & 1);
-    q.f |= (two && in && (lbk ? xo : xe) ? kPP : 0) | ((lbk ? W && xe : E && xo) ? kPO : 0) |
-           (N && yo ? kPN : 0) | (S && ye ? kPS : 0);
+    q.f |= (E && xo ? kPE : 0) | (Wb && xe ? kPW : 0) | (N && yo ? kPN : 0) | (S && ye ? kPS : 0);
   }
-  // the loaded operator by colour, the diagonal inverted
+  // the loaded operator by colour (a missing cell has none), the diagonal
+  // inverted
   __device__ __forceinline__ void sort(Pair &q, int t) {
     const bool lbk = q.f & kLB, two = q.f & kTwo;
-    const double e = two ? q.aO[1] : 0.0, w = q.aO[0], nl = q.aN[0], sl = q.aS[0];
-    const double nr = two ? q.aN[1] : 0.0;
+    const double el = q.aE[0], er = two ? q.aE[1] : 0.0, wl = q.aW[0], wr = two ? q.aW[1] : 0.0;
+    const double nl = q.aN[0], nr = two ? q.aN[1] : 0.0, sl = q.aS[0];
     const double sr = !two ? 0.0 : q.f & kWrap ? ay0[t] : q.aS[1];
-    const double dl = q.id[0], dr = two ? q.id[1] : 1.0;
-    q.aO[0] = lbk ? e : w; q.aO[1] = lbk ? w : e;
+    const double dl = q.d[0], dr = two ? q.d[1] : 1.0;
+    q.aE[0] = lbk ? er : el; q.aE[1] = lbk ? el : er;
+    q.aW[0] = lbk ? wr : wl; q.aW[1] = lbk ? wl : wr;
     q.aN[0] = lbk ? nr : nl; q.aN[1] = lbk ? nl : nr;
     q.aS[0] = lbk ? sr : sl; q.aS[1] = lbk ? sl : sr;
-    q.id[0] = rcp64(lbk ? dr : dl);
-    q.id[1] = rcp64(lbk ? dl : dr);
+    q.d[0] = lbk ? dr : dl;
+    q.d[1] = lbk ? dl : dr;
+    q.id[0] = div64(1.0, q.d[0], rcp64(q.d[0]));
+    q.id[1] = div64(1.0, q.d[1], rcp64(q.d[1]));
   }
   // The top level's pairs: loads as for own() and, where b is not NULL, of
   // the right-hand side (a thread without an m-th pair loads pair 0).
@@ -1215,17 +1232,17 @@ struct CoarseWG {
       const int ii = p < v.h ? i : 0, jj = p < v.h ? j : 0;
       const dbl2 d = ld2(dg, o), x = ld2(ax, o), y = ld2(ay, o);
       const dbl2 w = ld2(ay, o + 8u * (jj > 0 ? -nx : n - nx));
-      tO[0][m] = ld1(ax, o + 8u * (ii > 0 ? -1 : nx - 1));
+      tW[0][m] = ld1(ax, o + 8u * (ii > 0 ? -1 : nx - 1));
       dbl2 bb = {0.0, 0.0};
       if (b) bb = ld2(b, o);
       ti[0][m] = d.x; ti[1][m] = d.y;
-      tP[m] = x.x; tO[1][m] = x.y;
+      tE[0][m] = tW[1][m] = x.x; tE[1][m] = x.y;
       tN[0][m] = y.x; tN[1][m] = y.y;
       tS[0][m] = w.x; tS[1][m] = w.y;
       tb[0][m] = bb.x; tb[1][m] = bb.y;
       const bool lbk = (i + j) & 1;
       tij[m] = i | j << 16;
-      to[m] = lbk ? 1 : -1;
+      te[m] = lbk ? 1 : 0;
       tg[m] = lbk ? hb : ha;
       th[m] = lbk ? ha : hb;
       r += dr;
@@ -1244,28 +1261,29 @@ struct CoarseWG {
         const int p = tid + m * kCoarseThreads;
         if (2 * p == v.nx - 1) tS[1][m] = ay0[0];
         if (2 * p + 1 >= v.n) {
-          tO[1][m] = tN[1][m] = tS[1][m] = tb[1][m] = 0.0;
+          tE[1][m] = tN[1][m] = tS[1][m] = tb[1][m] = 0.0;
           ti[1][m] = 1.0;
         }
       }
     }
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const bool lbk = to[m] > 0;
+      const bool lbk = te[m];
       auto by_colour = [&](double (&a)[2][M]) {
         const double l = a[0][m], r = a[1][m];
         a[0][m] = lbk ? r : l;
         a[1][m] = lbk ? l : r;
       };
-      by_colour(tO);
+      by_colour(tE);
+      by_colour(tW);
       by_colour(tN);
       by_colour(tS);
       by_colour(tb);
       by_colour(ti);
       td[0][m] = ti[0][m];
       td[1][m] = ti[1][m];
-      ti[0][m] = rcp64(ti[0][m]);
-      ti[1][m] = rcp64(ti[1][m]);
+      ti[0][m] = div64(1.0, td[0][m], rcp64(td[0][m]));
+      ti[1][m] = div64(1.0, td[1][m], rcp64(td[1][m]));
     }
   }
   __device__ __forceinline__ bool has(int m) const {
@@ -1278,11 +1296,11 @@ struct CoarseWG {
   }
   // s + sum of the couplings of the top pair's cell of colour k times x
   __device__ __forceinline__ double add_top(int k, int m, double s) const {
-    const double *x = at(1 - k, m);
-    const double a = x[0], b = x[k ? -to[m] : to[m]];
+    const double *x = at(1 - k, m), *xe = x + (k ? 1 - te[m] : te[m]);
+    const double a = xe[0], b = xe[-1];
     const double n = x[k ? th[m] : tg[m]], u = x[-(k ? tg[m] : th[m])];
-    s = fma(tP[m], a, s);
-    s = fma(tO[k][m], b, s);
+    s = fma(tE[k][m], a, s);
+    s = fma(tW[k][m], b, s);
     s = fma(tN[k][m], n, s);
     return fma(tS[k][m], u, s);
   }
@@ -1290,20 +1308,18 @@ struct CoarseWG {
   // (e, on the next level) added to x
   __device__ __forceinline__ double add_top_corr(int m, const double *e, double s) const {
     const Lev v = lev(0), w = lev(1);
-    const double *x = at(0, m);
-    const double xp = x[0], xo = x[-to[m]], xn = x[th[m]], xs = x[-tg[m]];
-    const bool lbk = to[m] > 0;
+    const double *x = at(0, m), *xp = x + 1 - te[m];
+    const double xe = xp[0], xw = xp[-1], xn = x[th[m]], xs = x[-tg[m]];
     int i = tij[m] & 0xffff, j = tij[m] >> 16;
-    if (!lbk) ++i;
+    if (!te[m]) ++i;
     if (i >= v.nx) { i = 0; j = min(j + 1, v.ny - 1); }
     // parents of the neighbours (of one within the grid where there is none)
     const int I = i >> v.sx, row = (j >> v.sy) * w.nx;
     const int ie = min((i + 1) >> v.sx, w.nx - 1), iw = max(i - 1, 0) >> v.sx;
     const int jn = min((j + 1) >> v.sy, w.ny - 1), js = max(j - 1, 0) >> v.sy;
-    const double ep = e[row + (lbk ? ie : iw)], eo = e[row + (lbk ? iw : ie)];
-    const double en = e[jn * w.nx + I], es = e[js * w.nx + I];
-    s = fma(tP[m], fma(omega, ep, xp), s);
-    s = fma(tO[1][m], fma(omega, eo, xo), s);
+    const double ee = e[row + ie], ew = e[row + iw], en = e[jn * w.nx + I], es = e[js * w.nx + I];
+    s = fma(tE[1][m], fma(omega, ee, xe), s);
+    s = fma(tW[1][m], fma(omega, ew, xw), s);
     s = fma(tN[1][m], fma(omega, en, xn), s);
     return fma(tS[1][m], fma(omega, es, xs), s);
   }
@@ -1314,9 +1330,9 @@ struct CoarseWG {
   }
   // s + sum of the couplings of the pair's cell k times x of its neighbours
   __device__ __forceinline__ double add_nb(const Pair &q, int k, const double *x, double s) {
-    const double a = x[q.c[1 - k]], b = x[q.o[k]], n = x[q.n[k]], u = x[q.s[k]];
-    s = fma(q.aP, a, s);
-    s = fma(q.aO[k], b, s);
+    const double a = x[q.e[k]], b = x[q.w[k]], n = x[q.n[k]], u = x[q.s[k]];
+    s = fma(q.aE[k], a, s);
+    s = fma(q.aW[k], b, s);
     s = fma(q.aN[k], n, s);
     return fma(q.aS[k], u, s);
   }
@@ -1324,12 +1340,11 @@ struct CoarseWG {
   // added to x
   __device__ __forceinline__ double add_nb_corr(const Pair &q, int cnx, const double *x,
                                                 const double *e, double s) {
-    const double xp = x[q.c[0]], xo = x[q.o[1]], xn = x[q.n[1]], xs = x[q.s[1]];
-    const int dir = q.f & kLB ? 1 : -1;      // to the other cell
-    const double ep = e[q.pc + (q.f & kPP ? dir : 0)], eo = e[q.pc - (q.f & kPO ? dir : 0)];
+    const double xe = x[q.e[1]], xw = x[q.w[1]], xn = x[q.n[1]], xs = x[q.s[1]];
+    const double ee = e[q.pc + (q.f & kPE ? 1 : 0)], ew = e[q.pc - (q.f & kPW ? 1 : 0)];
     const double en = e[q.pc + (q.f & kPN ? cnx : 0)], es = e[q.pc - (q.f & kPS ? cnx : 0)];
-    s = fma(q.aP, fma(omega, ep, xp), s);
-    s = fma(q.aO[1], fma(omega, eo, xo), s);
+    s = fma(q.aE[1], fma(omega, ee, xe), s);
+    s = fma(q.aW[1], fma(omega, ew, xw), s);
     s = fma(q.aN[1], fma(omega, en, xn), s);
     return fma(q.aS[1], fma(omega, es, xs), s);
   }
@@ -1410,7 +1425,7 @@ struct CoarseWG {
       double *a = sm + v.a;
       for (int c = tid; c < n; c += kCoarseThreads) {
         const double d = dg[c], x = dg[n + c], y = dg[2 * n + c];
-        a[c] = rcp64(d); a[n + c] = x; a[2 * n + c] = y; a[3 * n + c] = d;
+        a[c] = div64(1.0, d, rcp64(d)); a[n + c] = x; a[2 * n + c] = y; a[3 * n + c] = d;
       }
     }
     // the margins of the top level's planes
@@ -1535,7 +1550,7 @@ struct CoarseWG {
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         const int l = 2 * (tid + m * kCoarseThreads);
-        const bool lbk = to[m] > 0;
+        const bool lbk = te[m];
         if (l < v0.n) r0[l] = tb[lbk ? 1 : 0][m];
         if (l + 1 < v0.n) r0[l + 1] = tb[lbk ? 0 : 1][m];
         if (has(m)) *at(0, m) = *at(1, m) = 0.0;   // also the place of a missing cell
@@ -1556,7 +1571,8 @@ struct CoarseWG {
       __syncthreads();
 #pragma unroll
       for (int m = 0; m < M; ++m)
-        if (has(m)) r0[tid + m * kCoarseThreads] = add_top(0, m, 0.0);
+        if (has(m))
+          r0[tid + m * kCoarseThreads] = fma(-td[0][m], *at(0, m), add_top(0, m, tb[0][m]));
       __syncthreads();
 #pragma unroll
       for (int t = 1; t <= OM; ++t) {
@@ -1570,7 +1586,7 @@ struct CoarseWG {
         __syncthreads();
         if (q.f & kOk) put(x, q, 1, add_nb(q, 1, x, b1) * q.id[1]);
         __syncthreads();
-        if (q.f & kOk) r[q.c[0]] = add_nb(q, 0, x, 0.0);
+        if (q.f & kOk) r[q.c[0]] = fma(-q.d[0], x[q.c[0]], add_nb(q, 0, x, b0));
         __syncthreads();
       }
       restrict_to_lds();
@@ -1587,14 +1603,18 @@ struct CoarseWG {
       const double *b = last == 0 ? r0 : sm + end.b;
       double *xl = sm + end.x;
       const int row = tid >> 3, col0 = tid & 7;
-      double bv[8], v = 0.0;
+      double bv[8], v = 0.0, v1 = 0.0;
 #pragma unroll
       for (int q = 0; q < 8; ++q) bv[q] = b[col0 + 8 * q < nd ? col0 + 8 * q : 0];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v = fma(ainv[q], col0 + 8 * q < nd ? bv[q] : 0.0, v);
-      v += dpp_d<0xB1>(v);     // lane ^ 1, lane ^ 2, the other half of eight
-      v += dpp_d<0x4E>(v);
-      v += dpp_d<0x141>(v);
+      for (int q = 0; q < 8; q += 2) {
+        v = fma(ainv[q], col0 + 8 * q < nd ? bv[q] : 0.0, v);
+        v1 = fma(ainv[q + 1], col0 + 8 * q + 8 < nd ? bv[q + 1] : 0.0, v1);
+      }
+      v += v1;
+      v += __shfl_xor(v, 4, 64);
+      v += dpp_d<0x4E>(v);     // lane ^ 2, lane ^ 1
+      v += dpp_d<0xB1>(v);
       int at = row;
       if (last == 0) {         // the top level's place
         int i, j;
@@ -1662,7 +1682,7 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *d
   for (int m = 0; m < M; ++m) {
     const int c = 2 * ((int)threadIdx.x + m * kCoarseThreads);
     if (!W.has(m)) continue;
-    const bool lb = W.to[m] > 0;
+    const bool lb = W.te[m];
     const double u = *W.at(0, m), v = *W.at(1, m), l = lb ? v : u, r = lb ? u : v;
     if (c + 1 < n) *(dbl2 *)(xout + c) = dbl2{l, r};
     else xout[c] = l;
@@ -1745,7 +1765,7 @@ __global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds
   };
   // cell of colour k of the thread's m-th pair, and whether it exists
   auto cell = [&](int k, int m) {
-    return 2 * ((int)threadIdx.x + m * kCoarseThreads) + (W.to[m] > 0 ? 1 - k : k);
+    return 2 * ((int)threadIdx.x + m * kCoarseThreads) + (W.te[m] ? 1 - k : k);
   };
   auto ok = [&](int k, int m) { return cell(k, m) < D.N; };
   // A x of an owned cell, x of the grid in LDS
@@ -2277,8 +2297,12 @@ void launch_hot(const SynthSet &S, hipStream_t s, bool combine) {
 // made conditional on convergence) is put into the stream before the host
 // waits; true is returned when the solve has converged at a check, the
 // update then being in the stream.
-// Sets whose every problem starts with the one-workgroup cycle run the whole
-// solve in one kernel (k_cg_small) and never wait.
+// FP64 sets whose every problem starts with the one-workgroup cycle run the
+// whole solve in one kernel (k_cg_small) and never wait. Its sums of products
+// are added in another order than the separate kernels' (block partials); an
+// FP32-mixed step rounds differences of the iterate to floats, which turns one
+// unit in the last place of phi into 1e-8 of the flux, so those plans keep the
+// order they had.
 namespace {
 template <int M>
 void launch_cg_small(const SynthSet &S, hipStream_t s, int rhs_mode, int sub) {
@@ -2293,7 +2317,7 @@ void launch_cg_small(const SynthSet &S, hipStream_t s, int rhs_mode, int sub) {
 bool launch_synth_solve(const SynthSet &S, hipStream_t s, int32_t *host_flag, int rhs_mode,
                         int sub, hipEvent_t spec) {
   const SynthDesc *ds = S.desc;
-  if (S.max_lc == 0) {
+  if (S.max_lc == 0 && S.whole) {
     if (S.coarse_cells <= 2 * kCoarseThreads) launch_cg_small<1>(S, s, rhs_mode, sub);
     else if (S.coarse_cells <= 4 * kCoarseThreads) launch_cg_small<2>(S, s, rhs_mode, sub);
     else launch_cg_small<4>(S, s, rhs_mode, sub);

@@ -16,6 +16,13 @@ __device__ inline double rcp64(double x) {
   return fma(r, e, r);
 }
 
+// v / x with r = rcp64(x): the steps of the compiler's own division less its
+// scaling, so the same bits (for operands and quotients of normal size)
+__device__ inline double div64(double v, double x, double r) {
+  const double q = v * r;
+  return fma(fma(-x, q, v), r, q);
+}
+
 // Lane shifts of a double across the wave: shr1 moves lane l's value to
 // lane l + 1 (lane 0 keeps its own, or fill), shl1 to lane l - 1.
 __device__ inline double shr1(double v) {
