@@ -820,7 +820,10 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
     if ((st = record(pl, 1))) return st;
     launch_sweep(P, s);
     if ((st = record(pl, 2))) return st;
-    launch_moments(P, s, P.method == GSIS_GSIS);
+    // source iteration's update takes the moments from their partials itself
+    // (the phase-timed pass keeps the combine with the moments)
+    const bool fused = P.method != GSIS_GSIS && !P.td && P.precision == GSIS_FP64 && !pl->profile;
+    launch_moments(P, s, P.method == GSIS_GSIS, !fused);
     if ((st = record(pl, 3))) return st;
     if (P.method == GSIS_GSIS) {
       launch_hot(P.S, s, P.mom_split == 1);
@@ -854,7 +857,7 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
       updated = launch_synth_solve(P.S, s, host_flag, 1, 0, pl->profile ? nullptr : pl->spec_ev);
     }
     if ((st = record(pl, 5))) return st;
-    if (!updated) launch_update(P.S, s);
+    if (!updated) launch_update(P.S, s, 0, fused ? P.mom_split : 0);
     if ((st = record(pl, 6))) return st;
     HIPCHK(ctx, hipGetLastError());
     if (pl->profile) pl->prof_iters++;

@@ -382,7 +382,8 @@ void launch_boundary_flux_batch(const void *targs, const int2 *bt_face, int nb_f
 // phi, F of the swept intensity; with bflux (GSIS) the boundary faces'
 // F_T . n in the same launch and, for undivided quadrants (mom_split 1), only
 // the per-quadrant partials, which launch_hot(.., true) combines
-void launch_moments(const PlanDev &P, hipStream_t s, bool bflux);
+// combine: also the moments from their partials (else left to launch_update)
+void launch_moments(const PlanDev &P, hipStream_t s, bool bflux, bool combine = true);
 
 // ---- synthetic / update kernels (kernels_synth.hip)
 // Descriptor of plan P's synthetic step (host copy; P's arrays and levels
@@ -434,7 +435,7 @@ bool launch_synth_solve(const SynthSet &S, hipStream_t s, int32_t *host_flag, in
 // iteration, else the last synthetic solution)
 void launch_material(const SynthSet &S, hipStream_t s, int sub);
 // cond: only for problems whose synthetic solve has converged (state[3])
-void launch_update(const SynthSet &S, hipStream_t s, int cond = 0);
+void launch_update(const SynthSet &S, hipStream_t s, int cond = 0, int combine = 0);
 // Time-dependent form, start of a time step: I^n = the current iterate (with
 // its pending correction), rho^n, T^n; the step's counters and flags cleared
 void launch_td_begin(const PlanDev &P, hipStream_t s);

@@ -1900,6 +1900,59 @@ __global__ void k_update(const SynthDesc *ds, const int2 *bt, int cond) {
   }
 }
 
+// SI in FP64, one problem: the moments' combine (f = blockIdx.y: phi, Fx, Fy
+// from ns partials per quadrant, each quadrant's in order, then the quadrants)
+// and, with phi, the update of k_update. As two kernels they were two launches
+// of 5.0 and 4.9 us (40 x 40 x 1728); as one 5.8. (FP32-mixed sums need phi^m,
+// which another block would be replacing.)
+__global__ void k_update_combine(const SynthDesc *ds, int ns) {
+  __shared__ double sh[2 * kRedBlock / 64];
+  CDesc &D = cdesc(ds, 0);
+  const int32_t f1 = D.state[1];   // tested after the loads
+  const int c = blockIdx.x * kRedBlock + threadIdx.x, f = blockIdx.y;
+  const bool in = c < D.N;
+  const size_t N = D.N, cc = in ? c : 0;
+  const double *p = D.mom_part + f * N + cc;
+  const double po = D.phi[cc];
+  double v[4] = {};
+  int z = 0;
+  for (; z + 4 <= ns; z += 4) {
+    double u[4][4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) u[m][q] = p[(12 * (size_t)(z + m) + 3 * q) * N];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += u[m][q];
+  }
+  for (; z < ns; ++z)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] += p[(12 * (size_t)z + 3 * q) * N];
+  if (f1 != 0) return;
+  double s = 0.0;
+  for (int q = 0; q < 4; ++q) s += v[q];
+  if (f > 0) {
+    if (in) (f == 1 ? D.Fx : D.Fy)[c] = s;
+    return;
+  }
+  double num = 0.0, den = 0.0;
+  if (in) {
+    const double d = s - po;
+    num = D.V * d * d;
+    den = D.V * s * s;
+    D.phih[c] = s;
+    D.delta[c] = 0.0;
+    D.phi[c] = s;
+  }
+  block_sum2(num, den, sh);
+  if (threadIdx.x == 0) {
+    D.err_parts[2 * blockIdx.x] = num;
+    D.err_parts[2 * blockIdx.x + 1] = den;
+  }
+}
+
 // Time-dependent form: one step of the material equation per cell (Eqs.
 // MSE_d2, R2_def, MSE_d_mtx2, elem_mtx_M),
 //   T(sub + 1) = T(sub) + R2 / D2,
@@ -2379,8 +2432,11 @@ void launch_material(const SynthSet &S, hipStream_t s, int sub) {
   hipLaunchKernelGGL(k_material, dim3(S.nb_cell), dim3(kRedBlock), 0, s, S.desc, S.bt_cell, sub);
 }
 
-void launch_update(const SynthSet &S, hipStream_t s, int cond) {
-  hipLaunchKernelGGL(k_update, dim3(S.nb_cell), dim3(kRedBlock), 0, s, S.desc, S.bt_cell, cond);
+void launch_update(const SynthSet &S, hipStream_t s, int cond, int combine) {
+  if (combine)
+    hipLaunchKernelGGL(k_update_combine, dim3(S.nb_cell, 3), dim3(kRedBlock), 0, s, S.desc, combine);
+  else
+    hipLaunchKernelGGL(k_update, dim3(S.nb_cell), dim3(kRedBlock), 0, s, S.desc, S.bt_cell, cond);
   const int n8 = (S.n + 7) / 8 * 8, ts = (S.nb_src + 7) / 8;
   const int nb = S.bt_src ? S.nb_src : 8 * ts;
   hipLaunchKernelGGL(k_err_source, dim3(n8 + nb), dim3(kRedBlock), 0, s, S.desc, S.bt_src, S.n,

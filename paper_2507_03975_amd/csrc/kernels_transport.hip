@@ -2144,7 +2144,7 @@ void launch_sweep_batch(const void *targs, const int2 *items, int n_items, int *
 }
 
 template <typename T, int MT>
-void launch_moments_t(const TArgs &a, const PlanDev &P, hipStream_t s, bool bflux) {
+void launch_moments_t(const TArgs &a, const PlanDev &P, hipStream_t s, bool bflux, bool combine) {
   const int ntile = moment_tiles_of(P.nx, P.ny, MT);
   const int ts = (ntile + 7) / 8;   // tiles per XCD
   if (bflux) {   // the combine follows in the HoT kernel (undivided quadrants)
@@ -2157,19 +2157,20 @@ void launch_moments_t(const TArgs &a, const PlanDev &P, hipStream_t s, bool bflu
     hipLaunchKernelGGL((k_moments_q<T, MT>), dim3(8 * ts, 4, P.mom_split), dim3(256), 0, s, a,
                        P.mom_part, ntile, ts);
   }
+  if (!combine) return;
   hipLaunchKernelGGL(k_moments_combine, dim3((P.N + 255) / 256, 3), dim3(256), 0, s, a,
                      (const double *)P.mom_part);
 }
 
-void launch_moments(const PlanDev &P, hipStream_t s, bool bflux) {
+void launch_moments(const PlanDev &P, hipStream_t s, bool bflux, bool combine) {
   const TArgs a = make_args(P);
   const bool big = moment_tile_size(P.nx, P.ny) == 32;
   if (a.fp32) {
-    if (big) launch_moments_t<float, 32>(a, P, s, bflux);
-    else launch_moments_t<float, 16>(a, P, s, bflux);
+    if (big) launch_moments_t<float, 32>(a, P, s, bflux, combine);
+    else launch_moments_t<float, 16>(a, P, s, bflux, combine);
   } else {
-    if (big) launch_moments_t<double, 32>(a, P, s, bflux);
-    else launch_moments_t<double, 16>(a, P, s, bflux);
+    if (big) launch_moments_t<double, 32>(a, P, s, bflux, combine);
+    else launch_moments_t<double, 16>(a, P, s, bflux, combine);
   }
 }
 
