@@ -222,8 +222,10 @@ void gsis_plan_destroy(gsis_plan *plan);
 /* Enqueue n more outer iterations on the plan's stream. Iterations after
  * convergence (Err < tol), divergence or max_iter do no work, so the
  * iterate stops exactly where a synchronous loop would. SI plans return
- * without waiting. GSIS plans wait for the device once per outer iteration:
- * the host reads the synthetic CG's device stop flag (after the CG update
+ * without waiting. FP64 GSIS plans of at most 4096 cells (one kernel makes
+ * their synthetic solve) wait only to stay at most 32 iterations ahead of the
+ * device. Other GSIS plans wait for the device once per outer iteration: the
+ * host reads the synthetic CG's device stop flag (after the CG update
  * of the iteration at which the previous solve stopped, the end of the
  * outer iteration already in the stream behind it) so that it launches no
  * V-cycle past convergence, and stops enqueueing once an iteration has
@@ -233,9 +235,8 @@ gsis_status gsis_plan_iterate(gsis_plan *plan, int32_t n);
  * whether Err < tol was reached (converged = 1) or the iteration diverged
  * (converged = -1, see GSIS_DIVERGED). Returns GSIS_E_DEVICE if the workgroups that share one
  * ordinate's wavefront recurrence (its rows are spread over up to 4 of them
- * when ny > 256 or when the ordinates alone would fill under half the CUs;
- * GSIS_CHAIN_PARTS=1..4 in the environment at plan creation fixes the
- * count) stopped waiting for each other: the iterate is then not
+ * when ny > 384, in the adjoint's sweep when ny > 128; GSIS_CHAIN_PARTS=1..4 in
+ * the environment at plan creation fixes the count) stopped waiting for each other: the iterate is then not
  * valid until gsis_plan_reset. */
 gsis_status gsis_plan_status(gsis_plan *plan, int32_t *n_iter,
                              int32_t *converged, double *last_err);
@@ -354,7 +355,7 @@ typedef struct {
 /* Cotangents g_* and gradients g_sigma_a, g_sigma_s, g_q are [nx*ny] in the
  * caller's cell order, host or device memory as the plan's device_ptrs says;
  * a NULL cotangent is zero, a NULL gradient is not written. The plan keeps
- * three [nx*ny][K] adjoint arrays from the first call on. */
+ * two [nx*ny][K] adjoint arrays from the first call on. */
 gsis_status gsis_plan_adjoint(gsis_plan *plan, const double *g_phi, const double *g_Fx,
                               const double *g_Fy, double tol, int32_t max_iter,
                               double *g_sigma_a, double *g_sigma_s, double *g_q,

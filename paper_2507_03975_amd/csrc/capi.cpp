@@ -813,6 +813,12 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
   PlanDev &P = pl->P;
   hipStream_t s = pl->stream;
   gsis_status st;
+  // GSIS plans whose synthetic solve is one kernel do not wait for it: every
+  // kRunAhead iterations the host looks at the done flag of kRunAhead
+  // iterations before, so it never enqueues more than twice that many past
+  // the end of the solve, and the device never runs dry for the look.
+  const bool ahead = P.method == GSIS_GSIS && synth_in_one_kernel(P.S) && pl->spec_ev;
+  bool pending = false;
   for (int it = 0; it < n; ++it) {
     if (pl->profile && pl->prof_iters >= 100000) pl->profile = 0;
     if ((st = record(pl, 0))) return st;
@@ -864,6 +870,16 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
     // an earlier iteration ended the solve (converged, diverged or at the
     // iteration cap): the remaining ones would only launch kernels that exit
     if (host_flag[0] != 0) break;
+    if (ahead && (it + 1) % kRunAhead == 0) {
+      if (pending) {
+        HIPCHK(ctx, hipEventSynchronize(pl->spec_ev));
+        if (host_flag[kAheadFlag] != 0) break;
+      }
+      HIPCHK(ctx, hipMemcpyAsync(host_flag + kAheadFlag, P.state + 1, sizeof(int32_t),
+                                 hipMemcpyDeviceToHost, s));
+      HIPCHK(ctx, hipEventRecord(pl->spec_ev, s));
+      pending = true;
+    }
   }
   return GSIS_OK;
 }

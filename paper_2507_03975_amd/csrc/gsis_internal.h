@@ -391,6 +391,8 @@ void launch_moments(const PlanDev &P, hipStream_t s, bool bflux, bool combine = 
 SynthDesc make_synth_desc(const PlanDev &P);
 int coarse_start(const PlanDev &P);
 size_t coarse_lds_bytes(const PlanDev &P);
+// a synthetic solve of the set is one launch (and never waits)
+inline bool synth_in_one_kernel(const SynthSet &S) { return S.max_lc == 0 && S.whole; }
 int coarse_cells(const PlanDev &P);   // of the first level of the one-workgroup cycle
 int tiles_of(int nx, int ny);   // multigrid tiles covering an nx x ny level
 int source_tiles_of(int nx, int ny);   // 16 x 16 tiles of the source kernel

@@ -2370,7 +2370,7 @@ void launch_cg_small(const SynthSet &S, hipStream_t s, int rhs_mode, int sub) {
 bool launch_synth_solve(const SynthSet &S, hipStream_t s, int32_t *host_flag, int rhs_mode,
                         int sub, hipEvent_t spec) {
   const SynthDesc *ds = S.desc;
-  if (S.max_lc == 0 && S.whole) {
+  if (synth_in_one_kernel(S)) {
     if (S.coarse_cells <= 2 * kCoarseThreads) launch_cg_small<1>(S, s, rhs_mode, sub);
     else if (S.coarse_cells <= 4 * kCoarseThreads) launch_cg_small<2>(S, s, rhs_mode, sub);
     else launch_cg_small<4>(S, s, rhs_mode, sub);

@@ -21,6 +21,8 @@ struct gsis_ctx {
 };
 
 constexpr int kHostScal = 16, kStatusSlot = 8;   // doubles
+constexpr int kAheadFlag = 28;                   // int32: the done flag of an earlier iteration
+constexpr int kRunAhead = 16;
 
 struct gsis_plan {
   gsis_ctx *ctx = nullptr;
