@@ -63,14 +63,14 @@ SYNTH_RTOL = 0.1
 # so FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0). Valid only for the build whose
 # traffic_key() is recorded; any change to it turns the figures back to null.
 TRAFFIC = {
-    "thick256_fp64": {"sha256": "87b8dd5c5c0bb5a95f7669edeab150399734c57078e5c4d7b3c1cf5eb4da77cf",
-                      "k_resid": 244573448,     # 84267.8 KiB x 2.0 + 70305.6 KiB
-                      "k_chain": 138782520},    # 34856.4 KiB x 2.0 + 65817.0 KiB
-    "block1024_fp64": {"sha256": "87b8dd5c5c0bb5a95f7669edeab150399734c57078e5c4d7b3c1cf5eb4da77cf",
-                       "k_pipe": 3179074724},   # 980894.8 KiB x 2.0 + 1142775.5 KiB
-    "block1024_fp32": {"sha256": "87b8dd5c5c0bb5a95f7669edeab150399734c57078e5c4d7b3c1cf5eb4da77cf",
-                       "k_resid": 2965954644,   # 1153944.9 KiB x 2.0 + 588550.3 KiB
-                       "k_chain": 1283219692},  # 347933.3 KiB x 2.0 + 557277.6 KiB
+    "thick256_fp64": {"sha256": "b00108742c54de27a8d9fa2add5487bf0a2050242a45cc2c6b64f13013ae2eb8",
+                      "k_resid": 244572692,     # 84793.5 KiB x 2.0 + 69253.5 KiB
+                      "k_chain": 138795712},    # 34857.5 KiB x 2.0 + 65827.7 KiB
+    "block1024_fp64": {"sha256": "b00108742c54de27a8d9fa2add5487bf0a2050242a45cc2c6b64f13013ae2eb8",
+                       "k_pipe": 3263603312},    # 1023245.2 KiB x 2.0 + 1140622.2 KiB
+    "block1024_fp32": {"sha256": "b00108742c54de27a8d9fa2add5487bf0a2050242a45cc2c6b64f13013ae2eb8",
+                       "k_resid": 2887818572,     # 1117278.7 KiB x 2.0 + 585577.9 KiB
+                       "k_chain": 1196688008},    # 305596.9 KiB x 2.0 + 557446.8 KiB
 }
 KERNELS = {"k_resid": "k_resid (second-order residual of every cell-ordinate, ALSM gradient "
                       "and BJ limiter, written as the recurrence's right-hand side)",
