@@ -1736,8 +1736,8 @@ constexpr double kOmega = 1.7;   // coarse-grid correction scaling (aggregation 
 // iterations. As separate kernels an iteration was four launches of 3 to 7 us
 // and the solve a wait of the host: 32 x 32, two iterations a solve, 45 us of
 // kernels, here 13.4 us. Outer iterations in all, before and here: 40 x 40 88
-// to 54 us, 50 x 50 92 to 82, 64 x 64 121 to 111 (four pairs per thread: the
-// CG's vectors spill).
+// to 55 us, 50 x 50 92 to 72 (80 with four pairs per thread for its three), 64 x
+// 64 121 to 108 (four pairs: the CG's vectors spill).
 // MODE: see k_cg_begin.
 template <int M, int MODE>
 __global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds, int sub,
@@ -1746,7 +1746,7 @@ __global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds
   __shared__ double red[2][kCoarseThreads / 64];
   CDesc &D = cdesc(ds, blockIdx.x);
   if (D.state[1] != 0) return;
-  CoarseWG<M, M == 4 ? 1 : 2> W(coarse_words(ds), sm, kOmega);
+  CoarseWG<M, M >= 3 ? 1 : 2> W(coarse_words(ds), sm, kOmega);
   W.begin(nullptr);
   W.settle();
   const int nx = D.nx;
@@ -2182,6 +2182,8 @@ void vcycle(const SynthSet &S, int v, hipStream_t s, int part = 0) {
     hipLaunchKernelGGL(k_mg_coarse<1>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
   else if (S.coarse_cells <= 4 * kCoarseThreads)
     hipLaunchKernelGGL(k_mg_coarse<2>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
+  else if (S.coarse_cells <= 6 * kCoarseThreads)
+    hipLaunchKernelGGL(k_mg_coarse<3>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
   else
     hipLaunchKernelGGL(k_mg_coarse<4>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
   for (int l = S.max_lc - 1; l >= 1; --l)
@@ -2235,13 +2237,15 @@ int coarse_cells(const PlanDev &P) {
 void prepare_synth(size_t coarse_lds) {
   if (coarse_lds <= 64 * 1024) return;
   const void *ks[] = {(const void *)&k_mg_coarse<1>,   (const void *)&k_mg_coarse<2>,
-                      (const void *)&k_mg_coarse<4>,   (const void *)&k_cg_small<1, 0>,
-                      (const void *)&k_cg_small<1, 1>, (const void *)&k_cg_small<1, 2>,
-                      (const void *)&k_cg_small<1, 3>, (const void *)&k_cg_small<2, 0>,
-                      (const void *)&k_cg_small<2, 1>, (const void *)&k_cg_small<2, 2>,
-                      (const void *)&k_cg_small<2, 3>, (const void *)&k_cg_small<4, 0>,
-                      (const void *)&k_cg_small<4, 1>, (const void *)&k_cg_small<4, 2>,
-                      (const void *)&k_cg_small<4, 3>};
+                      (const void *)&k_mg_coarse<3>,   (const void *)&k_mg_coarse<4>,
+                      (const void *)&k_cg_small<1, 0>, (const void *)&k_cg_small<1, 1>,
+                      (const void *)&k_cg_small<1, 2>, (const void *)&k_cg_small<1, 3>,
+                      (const void *)&k_cg_small<2, 0>, (const void *)&k_cg_small<2, 1>,
+                      (const void *)&k_cg_small<2, 2>, (const void *)&k_cg_small<2, 3>,
+                      (const void *)&k_cg_small<3, 0>, (const void *)&k_cg_small<3, 1>,
+                      (const void *)&k_cg_small<3, 2>, (const void *)&k_cg_small<3, 3>,
+                      (const void *)&k_cg_small<4, 0>, (const void *)&k_cg_small<4, 1>,
+                      (const void *)&k_cg_small<4, 2>, (const void *)&k_cg_small<4, 3>};
   for (const void *k : ks)
     (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCoarseLdsBudget);
 }
@@ -2373,6 +2377,7 @@ bool launch_synth_solve(const SynthSet &S, hipStream_t s, int32_t *host_flag, in
   if (synth_in_one_kernel(S)) {
     if (S.coarse_cells <= 2 * kCoarseThreads) launch_cg_small<1>(S, s, rhs_mode, sub);
     else if (S.coarse_cells <= 4 * kCoarseThreads) launch_cg_small<2>(S, s, rhs_mode, sub);
+    else if (S.coarse_cells <= 6 * kCoarseThreads) launch_cg_small<3>(S, s, rhs_mode, sub);
     else launch_cg_small<4>(S, s, rhs_mode, sub);
     return false;
   }
