@@ -558,18 +558,47 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a, int ts) {
   auto base = [&](const double *p, int kk) {
     return buf_rsrc(p + (size_t)kk * a.N, (size_t)a.N * 8);
   };
+  // A wave whose 64 cells lie on one diagonal: the next lane's cell is (x - 1,
+  // y + 1), so the north neighbour is the next lane's east one, the south one
+  // the previous lane's west one, the second to the north the second lane's
+  // second to the east. What has no such lane (0 south, 63 north, 62 and 63
+  // second north) comes by one more load (F, through lanes 0, 63, 62, 61). The
+  // address unit is busy four fifths of the time with nine operations per cell
+  // and ordinate; with seven a pass takes 750 us for 764 at 512 x 512 x 128, 299
+  // for 317 at 100 x 100 x 864.
+  const int lane = threadIdx.x & 63;
+  const bool line = __ballot(x + y == __builtin_amdgcn_readfirstlane(x + y)) == ~0ull;
+  unsigned tF = kNoCell;
+  if (line) {
+    const unsigned n2 = (unsigned)__builtin_amdgcn_readlane((int)tN2, 63);
+    tF = lane == 0 ? tS : lane == 63 ? tN : lane == 62 ? tN2 : lane == 61 ? n2 : kNoCell;
+  }
   // U ordinates at a time: every load before any store (the arrays do not
   // overlap, which the compiler cannot see)
-  auto group = [&](auto n, int kk) {
+  auto group = [&](auto n, auto on_line, int kk) {
     constexpr int U = decltype(n)::value;
+    constexpr bool LINE = decltype(on_line)::value;
     double r0[U], rE[U], rE2[U], rW[U], rN[U], rN2[U], rS[U], m[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const __amdgpu_buffer_rsrc_t R = base(a.rb, kk + u);
       r0[u] = buf_ld64(R, t0); rE[u] = buf_ld64(R, tE); rE2[u] = buf_ld64(R, tE2);
-      rW[u] = buf_ld64(R, tW); rN[u] = buf_ld64(R, tN); rN2[u] = buf_ld64(R, tN2);
-      rS[u] = buf_ld64(R, tS);
+      rW[u] = buf_ld64(R, tW);
+      if (LINE) {
+        rN[u] = buf_ld64(R, tF);
+      } else {
+        rN[u] = buf_ld64(R, tN); rN2[u] = buf_ld64(R, tN2); rS[u] = buf_ld64(R, tS);
+      }
       m[u] = buf_ld64(base(a.lam, kk + u), t0);
+    }
+    if (LINE) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const double F = rN[u];
+        rN2[u] = shl1_fill(shl1_fill(rE2[u], rdlane(F, 62)), rdlane(F, 61));
+        rS[u] = shr1_fill(rW[u], F);
+        rN[u] = shl1_fill(rE[u], F);
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -578,8 +607,12 @@ __global__ void __launch_bounds__(kB) k_a_out(AArgs a, int ts) {
   };
   int kk = a.qoff[q];
   const int ke = a.qoff[q + 1];
-  for (; kk + 4 <= ke; kk += 4) group(std::integral_constant<int, 4>(), kk);
-  for (; kk < ke; ++kk) group(std::integral_constant<int, 1>(), kk);
+  auto all = [&](auto on_line) {
+    for (; kk + 4 <= ke; kk += 4) group(std::integral_constant<int, 4>(), on_line, kk);
+    for (; kk < ke; ++kk) group(std::integral_constant<int, 1>(), on_line, kk);
+  };
+  if (line) all(std::true_type());
+  else all(std::false_type());
   a.part[(size_t)q * a.N + t] = sm;
   a.part[(size_t)(4 + q) * a.N + t] = sr;
 }
