@@ -590,7 +590,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       (st = dalloc(pl, &P.tres_hist, o->max_iter)) ||
       (st = dalloc(pl, &P.tres_part, tres_slots(P))) ||
       (st = dalloc(pl, &P.src2_part, (size_t)(N + 255) / 256)) ||
-      (st = dalloc(pl, &P.state, 5)) || (st = dalloc(pl, &P.last_err, 2)) ||
+      (st = dalloc(pl, &P.state, kStateWords)) || (st = dalloc(pl, &P.last_err, 2)) ||
       (st = dalloc(pl, &P.err_parts, 2 * (size_t)((N + 255) / 256) + 2)) ||
       (st = alloc_level(pl, L0)))
     return bail(st);

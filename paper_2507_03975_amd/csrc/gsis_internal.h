@@ -93,6 +93,7 @@ struct MGLevel {
 // step reads its problem from a device array of SynthDesc records, and a
 // block table (problem, block of that problem) spreads one launch over many
 // problems (NULL table: a single problem, block = blockIdx.x).
+constexpr int kStateWords = 6;   // of PlanDev::state
 constexpr int kMaxLevels = 40;
 constexpr int kMaxCoarseLevels = 10;
 // What the one-workgroup kernels need of a problem, one word per lane of a
@@ -271,7 +272,8 @@ struct PlanDev {
   int32_t *state = nullptr;    // [0] iterations done, [1] done flag (1 converged,
                                // -1 diverged, 2 max_iter), [2] current I buffer,
                                // [3] synthetic CG converged, [4] a split
-                               // recurrence's hand-over timed out
+                               // recurrence's hand-over timed out, [5] the
+                               // last k_update ran
   double *last_err = nullptr;  // [2]: Err of the last iteration, smallest ||phi^{m+1} - phi^m||_V
   SynthSet S;                  // launch set of this plan alone
   int lc = 0;                  // first level of the one-workgroup cycle

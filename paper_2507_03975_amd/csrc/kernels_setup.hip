@@ -221,7 +221,7 @@ __global__ void k_plan_reset(ResetArgs a) {
   if (t < (size_t)a.max_iter) { a.err_hist[t] = 0.0; a.tres_hist[t] = 0.0; }
   if (t < a.n_tres) a.tres_part[t] = 0.0;
   if (t < a.n_hand) a.hand[t] = kHandEmpty;
-  if (t < 5) a.state[t] = 0;
+  if (t < kStateWords) a.state[t] = 0;
   if (t == 0) {
     *a.vcycles = 0.0;
     // Err of the last iteration and the smallest ||phi^{m+1} - phi^m||_V so

@@ -1861,7 +1861,9 @@ __global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds
 // delta = phi' - phi_half (GSIS) or 0 (SI); Err partials; phi = phi_new.
 // FP32-mixed mode also records base = phi^m + delta (see the transport file).
 // cond: launched ahead of the host's look at the synthetic solve's flags;
-// runs only if that solve has converged (state[3]), else returns
+// runs only if that solve has converged (state[3]), else returns.
+// state[5] tells the launch that follows (k_err_source) whether it ran: that
+// launch's own end of the iteration changes state[1] while its source tiles run
 __global__ void k_update(const SynthDesc *ds, const int2 *bt, int cond) {
   __shared__ double sh[kRedBlock];
   const Blk B = blk(bt);
@@ -1874,6 +1876,7 @@ __global__ void k_update(const SynthDesc *ds, const int2 *bt, int cond) {
   const double ph = D.phih[cc], po = D.phi[cc];
   // time-dependent form: T^{m+1} = T(sub_iter), against T^m for Err(T)
   const double tn = D.td ? t_sub(D, D.sub_iter)[cc] : 0.0, to = D.td ? D.Tm[cc] : 0.0;
+  if (B.lb == 0 && threadIdx.x == 0) D.state[5] = f1 == 0;
   if (f1 != 0) return;
   double num = 0.0, den = 0.0, numT = 0.0, denT = 0.0;
   if (in) {
@@ -1930,6 +1933,7 @@ __global__ void k_update_combine(const SynthDesc *ds, int ns) {
   for (; z < ns; ++z)
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] += p[(12 * (size_t)z + 3 * q) * N];
+  if (blockIdx.x == 0 && f == 0 && threadIdx.x == 0) D.state[5] = f1 == 0;
   if (f1 != 0) return;
   double s = 0.0;
   for (int q = 0; q < 4; ++q) s += v[q];
@@ -2079,9 +2083,9 @@ __device__ inline void err_finish(CDesc &D, double *sh) {
 // diagonal run over consecutive lanes and consecutive addresses.
 constexpr int kSrcT = 16;
 static_assert(kSrcT * kSrcT == kRedBlock, "one thread per tile cell");
+// run: 0 leaves the source as it is.
 __device__ inline void source_tile(CDesc &D, const Blk &B, double *s_sc, double *s_dq,
-                                   double *s_pq) {
-  const int32_t f1 = D.state[1];   // tested after the operands are loaded
+                                   double *s_pq, const int32_t run) {
   const int nx = D.nx, ny = D.ny, n = D.N;
   int ti, tj;
   cell_ij(B.lb, (nx + kSrcT - 1) / kSrcT, ti, tj);
@@ -2098,7 +2102,7 @@ __device__ inline void source_tile(CDesc &D, const Blk &B, double *s_sc, double 
     }
     const double dq = D.base[c] / kFourPi;
     const double pq = D.phi[c] / kFourPi;
-    if (f1 != 0) return;
+    if (run == 0) return;          // (tested after the operands are loaded)
     if (in) D.src[c] = sc;
     s_sc[t] = sc; s_dq[t] = dq; s_pq[t] = pq;
   }
@@ -2123,13 +2127,16 @@ __device__ inline void source_tile(CDesc &D, const Blk &B, double *s_sc, double 
 __global__ void __launch_bounds__(kRedBlock) k_source(const SynthDesc *ds, const int2 *bt) {
   __shared__ double s_sc[kRedBlock], s_dq[kRedBlock], s_pq[kRedBlock];
   const Blk B = blk(bt);
-  source_tile(cdesc(ds, B.p), B, s_sc, s_dq, s_pq);
+  source_tile(cdesc(ds, B.p), B, s_sc, s_dq, s_pq, 1);
 }
 
 // End of an outer iteration: blocks [0, n) finish Err of problem blockIdx.x,
 // blocks from n8 (n rounded up to a multiple of 8) make source tiles (table
-// bt, or one problem's tiles). The two do not depend on each other; the
-// source is written also on the iteration that ends the solve. One problem:
+// bt, or one problem's tiles). The two do not depend on each other: the
+// source is written also on the iteration that ends the solve (a
+// time-dependent step starts from it), so its tiles go by state[5], which
+// k_update left, not by state[1], which the blocks before them may be setting
+// (from some 2000 tiles on, the last ones start after that). One problem:
 // its ntile tiles (row-major) fall into 8 runs of ts, one per XCD (block
 // n8 + b runs on XCD b % 8 and takes tile (b % 8) ts + b / 8), so the
 // partly written cache lines at the ends of a tile's diagonal runs mostly
@@ -2162,7 +2169,7 @@ __global__ void __launch_bounds__(kRedBlock) k_err_source(const SynthDesc *ds, c
   }
   CDesc &D = cdesc(ds, B.p);
   if (cond && D.state[3] == 0) return;
-  source_tile(D, B, s_sc, s_dq, s_pq);
+  source_tile(D, B, s_sc, s_dq, s_pq, D.state[5]);
 }
 
 // z = M^{-1} r_v (one V(1,1) cycle with scaled coarse corrections) for
