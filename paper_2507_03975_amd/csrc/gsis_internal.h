@@ -15,6 +15,7 @@
 #include <string>
 
 #include "gsis.h"
+#include "wave_steps.h"
 
 namespace gsis {
 
@@ -350,7 +351,6 @@ int residual_pairs(const PlanDev &P);
 // Storage index of row 0 on anti-diagonal d (dg_off(d) - ylo(d)), for d in
 // [-kDiagPad, nx + ny - 1 + kDiagPad); outside the grid's diagonals the value
 // sends every row out of the intensity buffer.
-constexpr int kDiagPad = 256;
 std::vector<int> diag_row0_table(int nx, int ny);
 // Batched sweep: per-problem kernel arguments (fill_targs into a device
 // table of targs_bytes() records), work items (problem, internal ordinate),

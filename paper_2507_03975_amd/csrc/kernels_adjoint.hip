@@ -374,7 +374,7 @@ constexpr int kAMaxW = 16, kALongW = 4;
 template <bool SPLIT, int kAL>
 __global__ void __launch_bounds__((kAL > 8 ? kALongW : kAMaxW) * 64) k_a_chain(AArgs a, int np) {
   constexpr int kAR = kAL > 8 ? 64 : 32, kW = kAL > 8 ? kALongW : kAMaxW;
-  static_assert(kW * kAL + 3 * kAL <= kDiagPad, "diagonal table padding");
+  static_assert(kAL <= kDiagPad && 62 + 3 * kAL <= kDiagPad, "diagonal table padding");
   static_assert(kAR >= 4 * kAL, "ring size");
   const int part = SPLIT ? blockIdx.x / a.K : 0;
   const int kk = blockIdx.x - part * a.K;
@@ -408,7 +408,6 @@ __global__ void __launch_bounds__((kAL > 8 ? kALongW : kAMaxW) * 64) k_a_chain(A
   unsigned long long hv = 0;
   bool gave_up = false;
   const bool last_lane = SPLIT && tid == rows - 1;
-  const int D = nx + ny - 2;
   const int nsteps = nx + rows - 1;
   const int tend = ((nsteps + (nw - 1) * kAL + kAL - 1) / kAL) * kAL;
   const int s0 = -wave * kAL;               // this wave's step at time 0
@@ -424,18 +423,18 @@ __global__ void __launch_bounds__((kAL > 8 ? kALongW : kAMaxW) * 64) k_a_chain(A
   };
   double vp = 0.0;
   // as there, a wave outside its rows' steps only meets the barriers
-  const int sfirst = (wave * 64 / kAL - 1) * kAL;
-  const int slast = wave < nw ? nx + wave * 64 + 62 : -tend - kAL;
+  const int sfirst = wave_first_step(wave, nw, kAL);
+  const int slast = wave_last_step(wave, nw, nx, tend, kAL);
   int tb = -kAL;
   for (; tb < tend && tb + s0 < sfirst; tb += kAL) lds_barrier();
   // diagonal offsets of a block's loads, one block ahead and in lanes, as in
   // the forward recurrence: no scalar-load wait in a block
-  int dsn = DS[D - (r0 + sfirst + kAL + min(lane, kAL - 1))];
+  int dsn = DS[diag_down(nx, ny, r0, sfirst, kAL, min(lane, kAL - 1))];
   asm volatile("" : "+v"(dsn));
   for (; tb < tend && tb + s0 <= slast; tb += kAL) {
     const int sb = tb + s0;
     const int dsc = dsn;
-    dsn = DS[D - (r0 + sb + 2 * kAL + min(lane, kAL - 1))];
+    dsn = DS[diag_down(nx, ny, r0, sb + kAL, kAL, min(lane, kAL - 1))];
     double bl[kAL];
     if (wave > 0) {
 #pragma unroll

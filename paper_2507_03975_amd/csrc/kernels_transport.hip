@@ -927,7 +927,9 @@ __device__ __forceinline__ void chain_ordinate(A &a, const int kk, const int par
   constexpr bool kF32 = sizeof(T) == 4;
   static_assert((R & (R - 1)) == 0 && LAG == PF, "ring sizes");
   static_assert(!(SPLIT && MULTI), "a split recurrence runs one pass per part");
-  static_assert(kCMaxW * kCLag + 2 * kCPF + kCLag <= kDiagPad, "diagonal table padding");
+  // (a wave with rows starts on one of the grid's diagonals or a block before
+  // it and its last load is 62 + 3 LAG steps past its rows' last column)
+  static_assert(LAG <= kDiagPad && 62 + 3 * LAG <= kDiagPad, "diagonal table padding");
   const int q = quadrant_of(a, kk);
   const int nx = a.nx, ny = a.ny, N = a.N;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1004,14 +1006,14 @@ __device__ __forceinline__ void chain_ordinate(A &a, const int kk, const int par
     // x 100 x 1728, 315 for 142 in a batch of 64 to 256 rows (whose workgroups
     // are as large as its largest problem). LAG 6 and 12: 62.3 and 62.2 us at
     // 256 x 256 x 128, 162 and 172 in the batch.
-    const int sfirst = (wave * 64 / LAG - 1) * LAG;
-    const int slast = wave < nw ? nx + wave * 64 + 62 : -tend - LAG;
+    const int sfirst = wave_first_step(wave, nw, LAG);
+    const int slast = wave_last_step(wave, nw, nx, tend, LAG);
     int tb = -LAG;
     for (; tb < tend && tb + s0 < sfirst; tb += LAG) lds_barrier();
     // diagonal offsets of a block's loads, one block ahead: lane l holds that
     // of the block's load l, read back as a wave-uniform lane value (a vector
     // load, in order with the ring's, so no scalar-load wait in a block)
-    int dsn = DS[y0 + sfirst + PF + (lane & (LAG - 1))];
+    int dsn = DS[diag_up(y0, sfirst, LAG, lane & (LAG - 1))];
     // (the first one lands before the loop: still in flight at the loop
     // head, the wait pass would cover it conservatively in every block, with
     // all the ring's loads behind it)
@@ -1019,7 +1021,7 @@ __device__ __forceinline__ void chain_ordinate(A &a, const int kk, const int par
     for (; tb < tend && tb + s0 <= slast; tb += LAG) {
       const int sb = tb + s0;                 // this wave's first step of the block
       const int dsc = dsn;
-      dsn = DS[y0 + sb + LAG + PF + (lane & (LAG - 1))];
+      dsn = DS[diag_up(y0, sb + LAG, LAG, lane & (LAG - 1))];
       // v below lane 0 for the block's steps: the wave below's top lane
       // (written at least one barrier ago), the part below, the previous
       // pass, or 0
