@@ -221,8 +221,8 @@ gsis_status alloc_level(gsis_plan *pl, MGLevel &L) {
   const size_t n = (size_t)L.nx * L.ny;
   gsis_status st;
   if ((st = dalloc(pl, &L.diag, 3 * n))) return st;   // the operator in one piece
-  L.ax = L.diag + n;
-  L.ay = L.diag + 2 * n;
+  L.ax = L.diag + op_ax((int)n);
+  L.ay = L.diag + op_ay((int)n);
   if ((st = dalloc(pl, &L.x, n)) || (st = dalloc(pl, &L.b, n)) || (st = dalloc(pl, &L.r, n)))
     return st;
   return GSIS_OK;
@@ -250,15 +250,16 @@ gsis_status choose_aggregates(gsis_plan *pl, MGLevel &F, double *part) {
     if (!(std::fabs(r - thr) > 1e-9 && std::fabs(-r - thr) > 1e-9)) {
       const size_t n = (size_t)F.nx * F.ny;
       std::vector<double> a(2 * n);
-      HIPCHK(ctx, hipMemcpyAsync(a.data(), F.ax, 2 * n * sizeof(double), hipMemcpyDeviceToHost,
+      static_assert(op_ax(1) == op_ay(1) + 1, "ax behind ay");
+      HIPCHK(ctx, hipMemcpyAsync(a.data(), F.ay, 2 * n * sizeof(double), hipMemcpyDeviceToHost,
                                  pl->stream));
       HIPCHK(ctx, hipStreamSynchronize(pl->stream));
       lx = ly = 0;
       for (int j = 0; j < F.ny; ++j)
         for (int i = 0; i < F.nx; ++i) {
           const size_t c = (size_t)j * F.nx + i;
-          if (i + 1 < F.nx) lx += std::log(a[c]);
-          if (j + 1 < F.ny) ly += std::log(a[n + c]);
+          if (i + 1 < F.nx) lx += std::log(a[n + c]);
+          if (j + 1 < F.ny) ly += std::log(a[c]);
         }
     }
   }
@@ -302,12 +303,12 @@ gsis_status setup_synth(gsis_plan *pl, PlanDev &P) {
       const int c = j * Lc.nx + i;
       dense[(size_t)c * nc + c] = op[c];
       if (i + 1 < Lc.nx) {
-        dense[(size_t)c * nc + c + 1] = -op[nc + c];
-        dense[(size_t)(c + 1) * nc + c] = -op[nc + c];
+        dense[(size_t)c * nc + c + 1] = -op[op_ax(nc) + c];
+        dense[(size_t)(c + 1) * nc + c] = -op[op_ax(nc) + c];
       }
       if (j + 1 < Lc.ny) {
-        dense[(size_t)c * nc + c + Lc.nx] = -op[2 * nc + c];
-        dense[(size_t)(c + Lc.nx) * nc + c] = -op[2 * nc + c];
+        dense[(size_t)c * nc + c + Lc.nx] = -op[op_ay(nc) + c];
+        dense[(size_t)(c + Lc.nx) * nc + c] = -op[op_ay(nc) + c];
       }
     }
   if (!dense_spd_inverse(nc, dense))

@@ -15,6 +15,7 @@
 #include <string>
 
 #include "gsis.h"
+#include "coarse_places.h"
 #include "wave_steps.h"
 
 namespace gsis {
@@ -100,7 +101,7 @@ constexpr int kMaxCoarseLevels = 10;
 // What the one-workgroup kernels need of a problem, one word per lane of a
 // wave: scalars, addresses (two words each), then four words per level from
 // the first coarse one: nx | ny << 16; LDS offset (doubles) of x | log2 of the
-// aggregates in bits 20 (x) and 21 (y); address of the operator (diag, ax, ay
+// aggregates in bits 20 (x) and 21 (y); address of the operator (diag, ay, ax
 // one behind the other). LDS holds x and r of the top level, x, b, r and the
 // operator (4 n) of a lower one, in this order.
 // What a caller puts in place of the plan's own in a SynthDesc (state, rhs,

@@ -1155,18 +1155,16 @@ struct CoarseWG {
   // place (left 0, right 1) until sort() orders them by colour, and the places
   // meanwhile. Couplings across a grid's edge are stored as zeros (ax at the
   // end of each row, ay on the last row): those of the west and south edges
-  // are read there. A last cell on its own loads one value past the level's
-  // arrays: they lie one behind the other, and the device pieces they lie in
-  // end on 256 bytes.
+  // are read there (coarse_places.h: also what loads one value past an array).
   __device__ __forceinline__ void own(Pair &q, int t, int p, int i, int j) {
     const Lev v = lev(t);
     const int nx = v.nx, ny = v.ny, n = v.n, l = 2 * p;
-    const gdbl dg = ldg[t], ax = dg + n, ay = ax + n;
+    const gdbl dg = ldg[t], ax = dg + op_ax(n), ay = dg + op_ay(n);
     const bool W = i > 0, SL = j > 0;
     const unsigned o = 8u * l;
     const dbl2 d = ld2(dg, o), x = ld2(ax, o), y = ld2(ay, o);
-    const dbl2 u = ld2(ay, o + 8u * (SL ? -nx : n - nx));
-    q.aW[0] = ld1(ax, o + 8u * (W ? -1 : nx - 1));
+    const dbl2 u = ld2(ay, o + 8u * south_step(j, nx, n));
+    q.aW[0] = ld1(ax, o + 8u * west_step(i, nx));
     q.d[0] = d.x; q.d[1] = d.y;
     q.aE[0] = q.aW[1] = x.x; q.aE[1] = x.y;
     q.aN[0] = y.x; q.aN[1] = y.y;
@@ -1216,7 +1214,7 @@ struct CoarseWG {
   __device__ __forceinline__ void own_top(gdbl b) {
     const Lev v = lev(0);
     const int nx = v.nx, n = v.n;
-    const gdbl dg = ldg[0], ax = dg + n, ay = ax + n;
+    const gdbl dg = ldg[0], ax = dg + op_ax(n), ay = dg + op_ay(n);
     // the left cell of pair tid, and the step to that of pair tid + 512: in
     // pairs of an even row, in cells of an odd one
     const int odd = nx & 1, u = odd ? nx : nx >> 1, ha = v.ny > 1 ? nx >> 1 : 0;
@@ -1231,8 +1229,8 @@ struct CoarseWG {
       const unsigned o = p < v.h ? 16u * p : 0u;
       const int ii = p < v.h ? i : 0, jj = p < v.h ? j : 0;
       const dbl2 d = ld2(dg, o), x = ld2(ax, o), y = ld2(ay, o);
-      const dbl2 w = ld2(ay, o + 8u * (jj > 0 ? -nx : n - nx));
-      tW[0][m] = ld1(ax, o + 8u * (ii > 0 ? -1 : nx - 1));
+      const dbl2 w = ld2(ay, o + 8u * south_step(jj, nx, n));
+      tW[0][m] = ld1(ax, o + 8u * west_step(ii, nx));
       dbl2 bb = {0.0, 0.0};
       if (b) bb = ld2(b, o);
       ti[0][m] = d.x; ti[1][m] = d.y;
@@ -1383,7 +1381,7 @@ struct CoarseWG {
       const Lev v = lev(t), u = lev(t - 1);
       Pair &q = lo[t - 1];
       q.f = 0;
-      ay0[t] = ld1(ldg[t], 16u * v.n);
+      ay0[t] = ld1(ldg[t], 8u * op_ay(v.n));
       if (2 * tid < v.n) {
         int i, j;
         cell_ij(2 * tid, v.nx, i, j);
@@ -1424,7 +1422,7 @@ struct CoarseWG {
       const gdbl dg = (gdbl)ptr(kCwLev + 4 * t + 2);
       double *a = sm + v.a;
       for (int c = tid; c < n; c += kCoarseThreads) {
-        const double d = dg[c], x = dg[n + c], y = dg[2 * n + c];
+        const double d = dg[c], x = dg[op_ax(n) + c], y = dg[op_ay(n) + c];
         a[c] = div64(1.0, d, rcp64(d)); a[n + c] = x; a[2 * n + c] = y; a[3 * n + c] = d;
       }
     }
@@ -2317,7 +2315,7 @@ SynthDesc make_synth_desc(const PlanDev &P) {
     int32_t *r = w + kCwLev + 4 * t;
     r[0] = L.nx | L.ny << 16;
     r[1] = off | (t + 1 < nlev && L.fx == 2 ? 1 << 20 : 0) | (t + 1 < nlev && L.fy == 2 ? 1 << 21 : 0);
-    ptr(kCwLev + 4 * t + 2, L.diag);   // ax and ay follow
+    ptr(kCwLev + 4 * t + 2, L.diag);   // ay and ax follow
     off += t == 0 ? coarse_top_words(L.nx, L.ny, nlev == 1) : 7 * n;
   }
   return D;

@@ -72,3 +72,40 @@ def test_recurrence_diagonals(tmp_path):
     batch's largest problem, the last pass of a tall grid), reads entries of
     the diagonal table only."""
     _run(tmp_path, "diagonals", DIAGONALS)
+
+
+OPERATOR = r"""
+#include <cstdio>
+#include "coarse_places.h"
+using namespace gsis;
+static long long reads = 0, bad = 0;
+int main() {
+  for (int nx = 1; nx <= 4096; ++nx)
+    for (int ny = 1; nx * ny <= 4096; ++ny) {
+      const int n = nx * ny, piece = (3 * n + kPieceValues - 1) / kPieceValues * kPieceValues;
+      auto load = [&](int at, int values, const char *what) {
+        ++reads;
+        if (at >= 0 && at + values <= piece) return;
+        if (++bad <= 20) printf("%d x %d, %s: values %d..%d of %d\n", nx, ny, what, at,
+                                at + values - 1, piece);
+      };
+      for (int l = 0; l < n; l += 2) {
+        const int i = l % nx, j = l / nx;
+        load(l, 2, "diag");
+        load(op_ax(n) + l, 2, "ax");
+        load(op_ay(n) + l, 2, "ay");
+        load(op_ay(n) + l + south_step(j, nx, n), 2, "ay, south");
+        load(op_ax(n) + l + west_step(i, nx), 1, "ax, west");
+      }
+    }
+  printf("%lld loads, %lld out of range\n", reads, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_coarse_operator_pairs(tmp_path):
+    """The one-workgroup multigrid cycle loads a level's operator two values
+    at a time, up to one past the end of its arrays: never past the piece of
+    memory that holds them, on every grid it can own."""
+    _run(tmp_path, "operator", OPERATOR)
