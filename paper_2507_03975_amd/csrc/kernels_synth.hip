@@ -20,7 +20,8 @@
 // block of that problem), so the problems of a batch advance together while
 // each keeps its own CG scalars, multigrid hierarchy and stop flags.
 // All reductions are two-stage with a fixed order, so results repeat bit for
-// bit, and a problem gets the same numbers alone or in a batch.
+// bit, and a problem gets the same phi and F alone or in a batch (which kernels
+// make its solve depends on the problem only).
 #include "gsis_internal.h"
 #include "wave_ops.h"
 

@@ -1486,10 +1486,13 @@ __device__ __forceinline__ void src2_block(const TArgs &a, const int blk) {
 // less of the cache lines at the runs' ends; smaller ones give small grids
 // more workgroups. ftp (transport-face HoT): the thread also forms its
 // cells' interior face fluxes.
+// A quadrant's ordinates are summed in ns parts (moment_split), which are then
+// added in order: part z alone, for moments_combine to add them, or with SEQ
+// (FP64) all of them one after the other, added here: the same bits.
 template <typename T>
 __device__ void face_flux_q(const TArgs &a, double *ftp, const long long t, const int q);
 
-template <typename T, int kMT>
+template <typename T, int kMT, bool SEQ = false>
 __device__ __forceinline__ void moments_tile(const TArgs &a, double *part, double *ftp,
                                              const int tile, const int q, const int z = 0,
                                              const int ns = 1) {
@@ -1526,7 +1529,12 @@ __device__ __forceinline__ void moments_tile(const TArgs &a, double *part, doubl
                           : ((a.qoff[q + 1] - a.qoff[q] + ns - 1) / ns + 7) / 8 * 8;
   const int kb = min(a.qoff[q] + z * per, a.qoff[q + 1]), ke = min(kb + per, a.qoff[q + 1]);
   part += (size_t)(12 * z) * N;
+  // place of a cell in the tile of the caller's grid
+  auto place = [&](int h) {
+    return ((q & 2) ? kMT - 1 - w[h] : w[h]) * kMT + ((q & 1) ? kMT - 1 - u[h] : u[h]);
+  };
   if constexpr (sizeof(T) == 4) {
+    static_assert(!SEQ, "FP32-mixed sums are not divided");
     // FP32-mixed form: the stored deviations are summed in FP32, each group
     // of eight ordinates as a balanced tree and the groups in order (the
     // rounding of the sum stays near that of the FP32 values themselves);
@@ -1572,39 +1580,56 @@ __device__ __forceinline__ void moments_tile(const TArgs &a, double *part, doubl
       s0[h] = (double)f0[h]; sx[h] = (double)fx[h]; sy[h] = (double)fy[h];
     }
   } else {
+    auto sum = [&](int kk, const int ke) {
 #pragma unroll
-    for (int h = 0; h < kMC; ++h) s0[h] = sx[h] = sy[h] = 0.0;
-    int kk = kb;
-    for (; kk + 8 <= ke; kk += 8) {
-      double v[kMC][8];
+      for (int h = 0; h < kMC; ++h) s0[h] = sx[h] = sy[h] = 0.0;
+      for (; kk + 8 <= ke; kk += 8) {
+        double v[kMC][8];
 #pragma unroll
-      for (int h = 0; h < kMC; ++h)
+        for (int h = 0; h < kMC; ++h)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) v[h][m] = in[h] ? (double)O[(size_t)(kk + m) * N + t[h]] : 0.0;
+          for (int m = 0; m < 8; ++m) v[h][m] = in[h] ? (double)O[(size_t)(kk + m) * N + t[h]] : 0.0;
 #pragma unroll
-      for (int h = 0; h < kMC; ++h)
+        for (int h = 0; h < kMC; ++h)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          s0[h] += W[kk + m] * v[h][m];
-          sx[h] += WM[kk + m] * v[h][m];
-          sy[h] += WE[kk + m] * v[h][m];
+          for (int m = 0; m < 8; ++m) {
+            s0[h] += W[kk + m] * v[h][m];
+            sx[h] += WM[kk + m] * v[h][m];
+            sy[h] += WE[kk + m] * v[h][m];
+          }
+      }
+      for (; kk < ke; ++kk) {
+#pragma unroll
+        for (int h = 0; h < kMC; ++h) {
+          const double v = in[h] ? (double)O[(size_t)kk * N + t[h]] : 0.0;
+          s0[h] += W[kk] * v;
+          sx[h] += WM[kk] * v;
+          sy[h] += WE[kk] * v;
         }
-    }
-    for (; kk < ke; ++kk) {
+      }
+    };
+    sum(kb, ke);
+    if constexpr (SEQ) {
+      // the sums so far in the thread's own places of sm
+      for (int k1 = ke; k1 < a.qoff[q + 1]; k1 += per) {
 #pragma unroll
-      for (int h = 0; h < kMC; ++h) {
-        const double v = in[h] ? (double)O[(size_t)kk * N + t[h]] : 0.0;
-        s0[h] += W[kk] * v;
-        sx[h] += WM[kk] * v;
-        sy[h] += WE[kk] * v;
+        for (int h = 0; h < kMC; ++h) {
+          const int l = place(h);
+          sm[0][l] = s0[h]; sm[1][l] = sx[h]; sm[2][l] = sy[h];
+        }
+        sum(k1, min(k1 + per, a.qoff[q + 1]));
+#pragma unroll
+        for (int h = 0; h < kMC; ++h) {
+          const int l = place(h);
+          s0[h] = sm[0][l] + s0[h]; sx[h] = sm[1][l] + sx[h]; sy[h] = sm[2][l] + sy[h];
+        }
       }
     }
   }
   if (f1 != 0) return;   // the whole block
 #pragma unroll
   for (int h = 0; h < kMC; ++h) {
-    // place in the tile of the caller's grid
-    const int l = ((q & 2) ? kMT - 1 - w[h] : w[h]) * kMT + ((q & 1) ? kMT - 1 - u[h] : u[h]);
+    const int l = place(h);
     sm[0][l] = s0[h];
     sm[1][l] = sx[h];
     sm[2][l] = sy[h];
@@ -1702,7 +1727,8 @@ __global__ void k_moments_q(TArgs a, double *part, int ntile, int ts) {
 
 // Batched launches: bt maps block -> (problem, tile of that problem, or -1:
 // none), each problem's tiles in runs by XCD as above; kBatchMT x kBatchMT
-// tiles.
+// tiles. A batch has blocks enough: the parts of a quadrant's ordinates (as a
+// plan of the problem alone has them) are summed in one block.
 constexpr int kBatchMT = 32;
 template <typename T>
 __global__ void k_moments_q_b(const TArgs *tas, const int2 *bt) {
@@ -1710,7 +1736,7 @@ __global__ void k_moments_q_b(const TArgs *tas, const int2 *bt) {
   if (v.y < 0) return;
   const TArgs &a = tas[v.x];
   if (blockIdx.y == 0) src2_tile<kBatchMT>(a, v.y);
-  moments_tile<T, kBatchMT>(a, a.mom_part, nullptr, v.y, blockIdx.y);
+  moments_tile<T, kBatchMT, sizeof(T) == 8>(a, a.mom_part, nullptr, v.y, blockIdx.y, 0, a.mom_split);
 }
 
 // One of the three moments (f: phi, Fx, Fy) of cell c from its partials: per
