@@ -276,8 +276,8 @@ gsis_status setup_synth(gsis_plan *pl, PlanDev &P) {
   gsis_ctx *ctx = pl->ctx;
   gsis_status st;
   const int kCoarseMax = 64;   // dense inverse of the coarsest level: at most 64 x 64
-  double *part = nullptr;
-  if ((st = dalloc(pl, &part, 2 * (size_t)kLogBlocks))) return st;
+  double *part = P.mom_part;   // (12 N values, not in use yet)
+  static_assert(12 * kCoarseMax >= 2 * kLogBlocks, "partial sums of a level above the coarsest");
   while ((long)P.mg.back().nx * P.mg.back().ny > kCoarseMax &&
          (P.mg.back().nx > 1 || P.mg.back().ny > 1)) {
     if ((st = choose_aggregates(pl, P.mg.back(), part))) return st;
@@ -372,20 +372,24 @@ gsis_status make_single_set(gsis_plan *pl) {
 }
 
 // ------------------------------------------------------------------- plans
-// A plan whose device memory comes from hipMalloc (arena NULL) or is carved
-// from the arena_cap bytes at arena (no device or pinned allocation at all;
-// profiling off).
-// With mt, the time-dependent form (backward-Euler steps of size mt->dt).
-// share: plans that run together (a batch).
 // room for the partial sums of w r^2 of either residual kernel (a batch
 // runs its own on a plan made for the pipelined step)
 static size_t tres_slots(const PlanDev &P) {
   return std::max((size_t)P.n_tres, (size_t)P.n_rtiles * residual_pairs(P));
 }
 
+// A plan whose device memory comes from hipMalloc (arena NULL) or is carved
+// from the arena_cap bytes at arena (no device or pinned allocation at all;
+// profiling off; no adjoint; reset once, here).
+// With mt, the time-dependent form (backward-Euler steps of size mt->dt).
+// share: plans that run together (a batch).
+// lean: the same phi and F from less memory (one moment partial per quadrant,
+// no shorter residual tiles than of 31 diagonals), for a region that the form
+// that runs fastest does not fit. *full: an array did not fit the region.
 static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_options *o,
                                gsis_plan **out, char *arena, size_t arena_cap,
-                               const gsis_material *mt = nullptr, int share = 1) {
+                               const gsis_material *mt = nullptr, int share = 1,
+                               bool lean = false, bool *full = nullptr) {
   if (!ctx) return fail(nullptr, GSIS_E_INVALID_ARG, "ctx is NULL");
   if (!out) return fail(ctx, GSIS_E_INVALID_ARG, "out is NULL");
   *out = nullptr;
@@ -438,6 +442,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     P.dt = mt->dt;
   }
   auto bail = [&](gsis_status s) {
+    if (full) *full = pl->arena_full;
     gsis_plan_destroy(pl);
     return s;
   };
@@ -527,17 +532,20 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       }
       if (np <= 1) rows = 0;
     };
-    split(aparts, P.adj_parts, P.adj_rows);
+    if (!arena) split(aparts, P.adj_parts, P.adj_rows);   // (no adjoint there)
     if (P.sweep_impl == 1 || P.sweep_impl == 2) parts = 1;
     split(parts, P.chain_parts, P.chain_rows);
   }
   P.mom_split = moment_split(P);
+  P.mom_parts = lean ? 1 : P.mom_split;
   // residual tiles (GSIS_RESID_DIAGONALS=31 or 47 sets their length)
   P.resid_rd = residual_tile_diagonals(nx, ny, residual_pairs(P), share, cus);
   {
     const char *e = getenv("GSIS_RESID_DIAGONALS");
     if (e && (!strcmp(e, "31") || !strcmp(e, "47"))) P.resid_rd = atoi(e);
   }
+  if (lean && residual_tiles(nx, ny, 31).size() < residual_tiles(nx, ny, P.resid_rd).size())
+    P.resid_rd = 31;
   const std::vector<int2> rtiles = residual_tiles(nx, ny, P.resid_rd);
   P.n_rtiles = (int)rtiles.size();
   // partial sums of w r^2: one per residual wave
@@ -563,10 +571,13 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     }
     pack.add(&P.w_f, wf);
   }
+  // for the set-up alone; in the caller's region inside arrays not in use yet
   int *perm = nullptr;
   unsigned long long *bad = nullptr;
-  pack.add(&perm, pl->perm);
-  pack.add(&bad, std::vector<unsigned long long>(3, ~0ull));
+  if (!arena) {
+    pack.add(&perm, pl->perm);
+    pack.add(&bad, std::vector<unsigned long long>(3, ~0ull));
+  }
   MGLevel L0;
   L0.nx = nx;
   L0.ny = ny;
@@ -582,7 +593,7 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       (st = dalloc(pl, &P.cN, N)) || (st = dalloc(pl, &P.cS, N)) ||
       (st = dalloc(pl, &P.src, N)) || (st = dalloc(pl, &P.phi, N)) ||
       (st = dalloc(pl, &P.phih, N)) || (st = dalloc(pl, &P.Fx, N)) ||
-      (st = dalloc(pl, &P.mom_part, (size_t)12 * P.mom_split * N)) ||
+      (st = dalloc(pl, &P.mom_part, (size_t)12 * P.mom_parts * N)) ||
       (st = dalloc(pl, &P.Fy, N)) || (st = dalloc(pl, &P.delta, N)) ||
       (st = dalloc(pl, &P.hx, N)) || (st = dalloc(pl, &P.hy, N)) ||
       (st = dalloc(pl, &P.rhs, N)) || (st = dalloc(pl, &P.bnd, nbk)) ||
@@ -624,6 +635,14 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
   if (P.td && ((st = fetch_dev(pl, mt->cv, P.cv, N, "material.cv")) ||
                (st = fetch_dev(pl, mt->T0, P.T0, N, "material.T0"))))
     return bail(st);
+  if (arena) {
+    perm = (int *)P.rowbuf;
+    bad = (unsigned long long *)P.mom_part;
+    if (hipMemcpyAsync(perm, pl->perm.data(), K * sizeof(int), hipMemcpyHostToDevice, s) !=
+            hipSuccess ||
+        hipMemsetAsync(bad, 0xff, 3 * sizeof *bad, s) != hipSuccess)
+      return bail(fail(ctx, GSIS_E_DEVICE, "preparing the checks of the problem failed"));
+  }
   launch_check_cells(N, P.sig_a, P.sig_s, P.q, P.cv, P.T0, P.sig_t, bad, s);
   if (!p->bnd_in) {
     if (hipMemsetAsync(P.bnd, 0, nbk * sizeof(double), s) != hipSuccess)
@@ -715,7 +734,13 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       }
       pl->I0_host.clear();
     }
-    if ((st = upload(pl, &P.phi0, phi0))) return bail(st);
+    if (arena) {   // hx is free until the first iteration, and the only reset is below
+      P.phi0 = P.hx;
+      if (hipMemcpy(P.phi0, phi0.data(), N * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+        return bail(fail(ctx, GSIS_E_DEVICE, "copying the warm start failed"));
+    } else if ((st = upload(pl, &P.phi0, phi0))) {
+      return bail(st);
+    }
   }
   if ((st = setup_synth(pl, P))) return bail(st);
   if ((st = make_single_set(pl))) return bail(st);
@@ -833,7 +858,7 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
     launch_moments(P, s, P.method == GSIS_GSIS, !fused);
     if ((st = record(pl, 3))) return st;
     if (P.method == GSIS_GSIS) {
-      launch_hot(P.S, s, P.mom_split == 1);
+      launch_hot(P.S, s, P.mom_parts == 1);
     }
     if ((st = record(pl, 4))) return st;
     // the synthetic solve copies the device flags to the host once while it
@@ -864,7 +889,7 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
       updated = launch_synth_solve(P.S, s, host_flag, 1, 0, pl->profile ? nullptr : pl->spec_ev);
     }
     if ((st = record(pl, 5))) return st;
-    if (!updated) launch_update(P.S, s, 0, fused ? P.mom_split : 0);
+    if (!updated) launch_update(P.S, s, 0, fused ? P.mom_parts : 0);
     if ((st = record(pl, 6))) return st;
     HIPCHK(ctx, hipGetLastError());
     if (pl->profile) pl->prof_iters++;
@@ -1007,7 +1032,11 @@ static gsis_status solve_with(gsis_ctx *ctx, const gsis_problem *p, const gsis_o
   if (!ctx) return fail(nullptr, GSIS_E_INVALID_ARG, "ctx is NULL");
   if (!r) return fail(ctx, GSIS_E_INVALID_ARG, "result is NULL");
   gsis_plan *pl = nullptr;
-  gsis_status st = plan_create(ctx, p, o, &pl, arena, arena_cap);
+  // a region too small for the form that runs fastest may hold the lean one
+  // (the same fields, fewer partial sums kept)
+  bool full = false;
+  gsis_status st = plan_create(ctx, p, o, &pl, arena, arena_cap, nullptr, 1, false, &full);
+  if (st && full) st = plan_create(ctx, p, o, &pl, arena, arena_cap, nullptr, 1, true);
   if (st) return st;
   int32_t n = 0, conv = 0;
   double le = 0;

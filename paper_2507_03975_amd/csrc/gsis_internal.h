@@ -231,8 +231,10 @@ struct PlanDev {
   double *phi0 = nullptr;      // phi of the warm start (NULL: zero)
   double *T0 = nullptr;        // time-dependent form: initial temperature
   double *phih = nullptr, *Fx = nullptr, *Fy = nullptr;  // moments of I^{m+1/2}
-  double *mom_part = nullptr;  // [mom_split][4][3][N] per-quadrant partial moments
+  double *mom_part = nullptr;  // [mom_parts][4][3][N] per-quadrant partial moments
   int mom_split = 1;           // parts of a quadrant's ordinates (moment_split)
+  int mom_parts = 1;           // of which this many are kept: mom_split, or 1
+                               // (added where they are summed)
   double *ftp = nullptr;       // transport-face HoT: [4][2][N] per-quadrant
                                // sum_k w_k (Omega_k . n) I_f,k on the east / north
                                // face of each cell (reconstructed upwind values)
@@ -383,7 +385,7 @@ void launch_moments_batch(const void *targs, const int2 *bt_cell, int nb_cell,
 void launch_boundary_flux_batch(const void *targs, const int2 *bt_face, int nb_face,
                                 hipStream_t s);
 // phi, F of the swept intensity; with bflux (GSIS) the boundary faces'
-// F_T . n in the same launch and, for undivided quadrants (mom_split 1), only
+// F_T . n in the same launch and, for one partial per quadrant (mom_parts 1), only
 // the per-quadrant partials, which launch_hot(.., true) combines
 // combine: also the moments from their partials (else left to launch_update)
 void launch_moments(const PlanDev &P, hipStream_t s, bool bflux, bool combine = true);

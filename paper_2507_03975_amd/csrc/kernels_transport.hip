@@ -54,7 +54,7 @@ struct TArgs {
   const double *bnd;
   double *phih, *Fx, *Fy, *bflux;
   double *mom_part;
-  int mom_split;     // partials per quadrant (moment_split)
+  int mom_split, mom_parts;   // see PlanDev
   const double *cellq, *dynq;
   double *rowbuf;
   const double *sdq;
@@ -86,6 +86,7 @@ TArgs make_args(const PlanDev &P) {
   a.bnd = P.bnd; a.phih = P.phih; a.Fx = P.Fx; a.Fy = P.Fy; a.bflux = P.bflux;
   a.mom_part = P.mom_part;
   a.mom_split = P.mom_split;
+  a.mom_parts = P.mom_parts;
   a.cellq = P.cellq; a.dynq = P.dynq; a.rowbuf = P.rowbuf;
   a.sdq = P.sdq; a.sdq_f = P.sdq_f; a.w_f = P.w_f; a.rtiles = P.rtiles; a.n_rtiles = P.n_rtiles;
   a.dso = P.dso;
@@ -1717,12 +1718,12 @@ __device__ inline int xcd_tile(int b, int ts) { return (b & 7) * ts + (b >> 3); 
 // Moment partials: block (tile slot, quadrant, part of its ordinates); the
 // first blocks of quadrant 0 also sum src^2 over the tile's blocks of 256
 // cells (src2_tile).
-template <typename T, int MT>
+template <typename T, int MT, bool SEQ>
 __global__ void k_moments_q(TArgs a, double *part, int ntile, int ts) {
   const int tile = xcd_tile(blockIdx.x, ts);
   if (tile >= ntile || (blockIdx.x >> 3) >= ts) return;
   if (blockIdx.y == 0 && blockIdx.z == 0) src2_tile<MT>(a, tile);
-  moments_tile<T, MT>(a, part, nullptr, tile, blockIdx.y, blockIdx.z, a.mom_split);
+  moments_tile<T, MT, SEQ>(a, part, nullptr, tile, blockIdx.y, blockIdx.z, a.mom_split);
 }
 
 // Batched launches: bt maps block -> (problem, tile of that problem, or -1:
@@ -1774,7 +1775,7 @@ __device__ __forceinline__ void moments_combine(const TArgs &a, const double *pa
 }
 
 __global__ void k_moments_combine(TArgs a, const double *part) {
-  moments_combine(a, part, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, a.mom_split);
+  moments_combine(a, part, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, a.mom_parts);
 }
 
 __global__ void k_moments_combine_b(const TArgs *tas, const int2 *bt) {
@@ -1839,7 +1840,7 @@ __device__ __forceinline__ void boundary_flux_wave(const TArgs &a, const int f) 
 // the swept intensity; the four partials are combined by the HoT kernel.
 // With ftp (transport-face HoT) the moment blocks also form the quadrant's
 // interior face fluxes.
-template <typename T, int MT>
+template <typename T, int MT, bool SEQ>
 __global__ void k_moments_q_bflux(TArgs a, double *part, int nbf8, int ntile, int ts,
                                   double *ftp) {
   // nbf8: blocks of four wall faces (one per wave), rounded up to a
@@ -1854,7 +1855,7 @@ __global__ void k_moments_q_bflux(TArgs a, double *part, int nbf8, int ntile, in
   const int tile = xcd_tile(r, ts);
   if (tile >= ntile || (r >> 3) >= ts) return;
   if (qz == 0) src2_tile<MT>(a, tile);
-  moments_tile<T, MT>(a, part, ftp, tile, qz & 3, qz >> 2, a.mom_split);
+  moments_tile<T, MT, SEQ>(a, part, ftp, tile, qz & 3, qz >> 2, a.mom_split);
 }
 
 // Batched wall faces: four (problem, face) entries per workgroup, a wave each.
@@ -2175,18 +2176,18 @@ void launch_sweep_batch(const void *targs, const int2 *items, int n_items, int *
 #undef GSIS_BATCH_LAUNCH
 }
 
-template <typename T, int MT>
+template <typename T, int MT, bool SEQ = false>
 void launch_moments_t(const TArgs &a, const PlanDev &P, hipStream_t s, bool bflux, bool combine) {
   const int ntile = moment_tiles_of(P.nx, P.ny, MT);
   const int ts = (ntile + 7) / 8;   // tiles per XCD
   if (bflux) {   // the combine follows in the HoT kernel (undivided quadrants)
     const int nbf8 = ((P.nbf + 3) / 4 + 7) / 8 * 8;
-    hipLaunchKernelGGL((k_moments_q_bflux<T, MT>), dim3(nbf8 + 4 * 8 * ts * P.mom_split), dim3(256), 0,
-                       s, a,
+    hipLaunchKernelGGL((k_moments_q_bflux<T, MT, SEQ>), dim3(nbf8 + 4 * 8 * ts * P.mom_parts),
+                       dim3(256), 0, s, a,
                        P.mom_part, nbf8, ntile, ts, P.hot_face ? P.ftp : nullptr);
-    if (P.mom_split == 1) return;
+    if (P.mom_parts == 1) return;
   } else {
-    hipLaunchKernelGGL((k_moments_q<T, MT>), dim3(8 * ts, 4, P.mom_split), dim3(256), 0, s, a,
+    hipLaunchKernelGGL((k_moments_q<T, MT, SEQ>), dim3(8 * ts, 4, P.mom_parts), dim3(256), 0, s, a,
                        P.mom_part, ntile, ts);
   }
   if (!combine) return;
@@ -2201,7 +2202,9 @@ void launch_moments(const PlanDev &P, hipStream_t s, bool bflux, bool combine) {
     if (big) launch_moments_t<float, 32>(a, P, s, bflux, combine);
     else launch_moments_t<float, 16>(a, P, s, bflux, combine);
   } else {
-    if (big) launch_moments_t<double, 32>(a, P, s, bflux, combine);
+    // (divided quadrants: fewer than 128 blocks, so 16 x 16 tiles)
+    if (P.mom_parts < P.mom_split) launch_moments_t<double, 16, true>(a, P, s, bflux, combine);
+    else if (big) launch_moments_t<double, 32>(a, P, s, bflux, combine);
     else launch_moments_t<double, 16>(a, P, s, bflux, combine);
   }
 }

@@ -51,6 +51,7 @@ struct gsis_plan {
   // live in host_flag_store instead of pinned memory
   char *arena = nullptr;
   size_t arena_used = 0, arena_cap = 0;
+  bool arena_full = false;        // an array did not fit
   double host_flag_store[kHostScal] = {};
 };
 
@@ -84,11 +85,13 @@ gsis_status dalloc(gsis_plan *pl, T **p, size_t n) {
   if (pl->arena) {
     // 256-byte aligned pieces of the region, in allocation order
     const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~(size_t)255;
-    if (bytes > pl->arena_cap - pl->arena_used)
+    if (bytes > pl->arena_cap - pl->arena_used) {
+      pl->arena_full = true;
       return fail(pl->ctx, GSIS_E_INVALID_ARG,
                   "the problem needs more device memory than the %zu-byte scratch region of "
                   "gsis_solve_noalloc (%zu bytes used when %zu more were asked for)",
                   pl->arena_cap, pl->arena_used, bytes);
+    }
     *p = (T *)(pl->arena + pl->arena_used);
     pl->arena_used += bytes;
     return GSIS_OK;
