@@ -22,7 +22,7 @@ struct gsis_ctx {
 
 constexpr int kHostScal = 16, kStatusSlot = 8;   // doubles
 constexpr int kAheadFlag = 28;                   // int32: the done flag of an earlier iteration
-constexpr int kRunAhead = 16;
+constexpr int kRunAhead = 8;
 
 struct gsis_plan {
   gsis_ctx *ctx = nullptr;
@@ -41,6 +41,11 @@ struct gsis_plan {
                                   // (kStatusSlot) the status read-out
   hipEvent_t spec_ev = nullptr;   // marks the synthetic solve's flag copy (see
                                   // launch_synth_solve); not in the allocation-free solve
+  // plans whose synthetic solve is one kernel (gsis_plan_iterate): iterations
+  // enqueued since the last look at the done flag, a copy of the flag is under
+  // way, the solve was seen to have ended
+  int ahead = 0;
+  bool ahead_pending = false, ended = false;
   // profiling: per iteration GSIS_NUM_PHASES + 1 events bracketing the phases
   std::vector<hipEvent_t> events;
   int prof_iters = 0;
