@@ -538,11 +538,12 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
   }
   P.mom_split = moment_split(P);
   P.mom_parts = lean ? 1 : P.mom_split;
-  // residual tiles (GSIS_RESID_DIAGONALS=31 or 47 sets their length)
+  // residual tiles (GSIS_RESID_DIAGONALS=3, 7, .. 59 sets their length)
   P.resid_rd = residual_tile_diagonals(nx, ny, residual_pairs(P), share, cus);
   {
     const char *e = getenv("GSIS_RESID_DIAGONALS");
-    if (e && (!strcmp(e, "31") || !strcmp(e, "47"))) P.resid_rd = atoi(e);
+    const int rd = e ? atoi(e) : 0;
+    if (rd >= 3 && rd <= kMaxResidDiagonals && rd % 4 == 3 && std::to_string(rd) == e) P.resid_rd = rd;
   }
   if (lean && residual_tiles(nx, ny, 31).size() < residual_tiles(nx, ny, P.resid_rd).size())
     P.resid_rd = 31;

@@ -344,6 +344,8 @@ inline int hand_parts(const PlanDev &P) {
 // 256x256x128: 2048 waves of 43, one round, 49.3 us (31: 2816 waves, 54.6; 39:
 // 2304, 61.6); many rounds, long tiles (512x512x128: 59 230 us, 31 246).
 // share: problems that run together (a batch). From 2^26 cell-ordinates on 47.
+// Lengths are of the form 4 k - 1.
+constexpr int kMaxResidDiagonals = 59;
 int residual_tile_diagonals(int nx, int ny, int pairs, int share, int cus);
 // Tiles of the residual kernel for an nx x ny grid: (first diagonal, first
 // row) of each band of rows x run of rd diagonals that holds a cell.

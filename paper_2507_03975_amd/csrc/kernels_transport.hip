@@ -613,7 +613,7 @@ __device__ __forceinline__ void face_pair(double u, double UE, double UW, double
 // tile (residual_tile_diagonals chooses the length).
 constexpr int kRWaves = 4;           // waves per workgroup, one ordinate each
 constexpr int kRPF = 4;              // steps of loads in flight
-constexpr int kRMaxRD = 59;          // longest tile (its halo in the lanes of one wave)
+constexpr int kRMaxRD = kMaxResidDiagonals;   // longest tile (its halo in the lanes of one wave)
 
 
 template <typename T>
