@@ -507,16 +507,25 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     cus = 0;
   {
     // workgroups per ordinate in the recurrence (GSIS_CHAIN_PARTS=1..4 sets
-    // it): one up to 384 rows, then parts of about 256 rows; at most 4, each
-    // a multiple of 64 rows and at most 1024, the top part not empty. A wave
-    // outside its rows' steps costs nothing, so one workgroup's waves on one
-    // CU are rarely in each other's way, and a hand-over through memory costs
-    // 10 us or so. An iteration (SI), 1 part and 2: 256 rows, 128 ordinates
-    // 133 and 146 us; 330, 64: 162 and 169; 400, 128: 359 and 355; 512, 128: 546
-    // and 531 (3: 532); 700, 64: 665 and 627 (3: 583); 1000, 16: 1088 and 990
-    // (4: 840). Few ordinates are no reason for more parts: 512 rows, 4
-    // ordinates 280 us in 2, 284 in 4.
-    int parts = ny <= 384 ? 1 : std::min((ny + 255) / 256, 4);
+    // it): parts of about 256 rows (one wave per SIMD), at most 4, each a
+    // multiple of 64 rows and at most 1024, the top part not empty. A wave
+    // outside its rows' steps costs nothing, and a hand-over through memory
+    // costs 10 us or so whatever the width, so up to 384 rows stay in one
+    // workgroup where that is less than what five or six waves on four SIMDs
+    // lose: in FP32-mixed form always, in FP64 on grids that are not wide.
+    // An iteration (SI, FP64), 1 part and 2: 256 rows x 128 ordinates 133 and
+    // 146 us; 300 rows, 32 ordinates: 512 wide 182 and 187, 768 wide 245 and
+    // 242, 1536 wide 546 and 496; 384 rows, 64 ordinates: 384 wide 185 and 188,
+    // 512 wide 265 and 246, 1536 wide 731 and 654; 12 ordinates the same way
+    // (384 x 1536 575 and 503, 256 x 256 104 and 117), 256 rows of any width
+    // one part (4096 x 12 972 and 989). FP32-mixed 384 x 1024 x 12 292 and 318.
+    // Above: 400 rows, 128 ordinates 359 and 355; 512, 128: 546 and 531 (3:
+    // 532); 700, 64: 665 and 627 (3: 583); 1000, 16: 1088 and 990 (4: 840). Few
+    // ordinates are no reason for more parts: 512 rows, 4 ordinates 280 us in
+    // 2, 284 in 4.
+    const int waves = (ny + 63) / 64;
+    const bool one = ny <= 384 && (waves <= 4 || f32 || (waves - 4) * nx <= 768);
+    int parts = one ? 1 : std::min((ny + 255) / 256, 4);
     // the adjoint's sweep loads twice as much a step: parts of about 128 rows,
     // two waves (a pass at 512 rows, 128 ordinates 760 us in 4, 779 in 2, 823
     // in 1; 256 rows 263 in 2, 266 in 1)
