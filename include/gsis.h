@@ -236,9 +236,10 @@ gsis_status gsis_plan_iterate(gsis_plan *plan, int32_t n);
  * whether Err < tol was reached (converged = 1) or the iteration diverged
  * (converged = -1, see GSIS_DIVERGED). Returns GSIS_E_DEVICE if the workgroups that share one
  * ordinate's wavefront recurrence (its rows are spread over up to 4 of them
- * when ny > 384, on wide grids when ny > 256, in the adjoint's sweep when ny > 128; GSIS_CHAIN_PARTS=1..4 in
- * the environment at plan creation fixes the count) stopped waiting for each other: the iterate is then not
- * valid until gsis_plan_reset. */
+ * when ny > 384, on wide grids when ny > 256, in the adjoint's sweep when
+ * ny > 128 on grids that are not narrow; GSIS_CHAIN_PARTS=1..4 in the
+ * environment at plan creation fixes the count) stopped waiting for each
+ * other: the iterate is then not valid until gsis_plan_reset. */
 gsis_status gsis_plan_status(gsis_plan *plan, int32_t *n_iter,
                              int32_t *converged, double *last_err);
 /* Wait for the plan's stream and copy phi, F and the history into r (host or

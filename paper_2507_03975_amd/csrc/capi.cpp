@@ -527,9 +527,15 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
     const bool one = ny <= 384 && (waves <= 4 || f32 || (waves - 4) * nx <= 768);
     int parts = one ? 1 : std::min((ny + 255) / 256, 4);
     // the adjoint's sweep loads twice as much a step: parts of about 128 rows,
-    // two waves (a pass at 512 rows, 128 ordinates 760 us in 4, 779 in 2, 823
-    // in 1; 256 rows 263 in 2, 266 in 1)
-    int aparts = std::min((ny + 127) / 128, 4);
+    // two waves, but one part on grids too narrow to earn the hand-overs. A pass
+    // (SI) at 32 ordinates, 1 part and this rule's number otherwise: 192 rows x
+    // 96 columns 73.5 and 81.3 us, x 512 145.7 and 147.5 (2), x 1024 equal;
+    // 256 x 96 84.5 and 90.1 (2), x 256 119.9 and 118.3, x 512 178 and 167; 512 x
+    // 96 120 and 136 (4), x 160 148 and 151, x 256 188 and 175; 1024 x 96 204 and
+    // 228 (4), x 160 258 and 254. 128 ordinates likewise (512 x 96 139 and 157, x
+    // 512 609 and 542).
+    const int narrow = ny <= 192 ? 512 : ny <= 256 ? 224 : ny <= 512 ? 160 : 128;
+    int aparts = nx <= narrow ? 1 : std::min((ny + 127) / 128, 4);
     const char *e = getenv("GSIS_CHAIN_PARTS");
     if (e && e[0] >= '1' && e[0] <= '4' && e[1] == 0) parts = aparts = e[0] - '0';
     auto split = [&](int n, int &np, int &rows) {
