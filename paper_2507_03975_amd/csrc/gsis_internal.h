@@ -409,12 +409,21 @@ int moment_tile_size(int nx, int ny);
 int moment_tile_size_batch();
 // Parts a quadrant's ordinates are summed in. Where the tiles of the four
 // quadrants make fewer than 128 blocks, half the CUs idle while each block
-// walks all of a quadrant's ordinates: parts of at least 24 ordinates then,
-// until about 1024 blocks run (40x40x1728: 36 blocks of 432 ordinates 54 us,
-// 576 of 27 19 us). From 128 blocks on it does not pay (100x100x1728: 196
-// blocks 72 us, 1568 blocks 79 us and a launch to add them). 1 in FP32-mixed
-// form (its sums are rounded in groups of eight ordinates, in order) and with
-// transport-face HoT (its face sums are formed in the same blocks).
+// walks all of a quadrant's ordinates: parts of at least 24 ordinates then (in
+// whole groups of eight), until about 1024 blocks run (40x40x1728: 36 blocks
+// of 432 ordinates 54 us, 16 parts of 32, two of them empty, 19 us).
+// Source iteration: an iteration in parts and whole at 64 blocks 119 and 152
+// us (64x64x1728), 43.1 and 45.5 (64x64x192); at 120 blocks 215 and 233
+// (96x80x1728); beyond the line the gain fades (144: 241 and 255, 196: 347 and
+// 350). GSIS adds the parts in
+// a launch of its own, where else the HoT kernel adds the quadrants, and waits
+// for the wall fluxes in the moments' launch anyway: with many ordinates on few
+// tiles only (32x32x960 87 and 92 us; but 32x32x192 52.0 and 51.9, 16x16x432
+// 53.1 and 51.5, 8x8x192 42 and 37, 80x64x1728 215 and 208, 160x16x1728 245 and
+// 238, 112x112x1728 429 and 406).
+// 1 in FP32-mixed form (its sums are rounded in groups of eight ordinates, in
+// order) and with transport-face HoT (its face sums are formed in the same
+// blocks).
 int moment_split(const PlanDev &P);
 int moment_tiles_of(int nx, int ny, int mt);
 void prepare_synth(size_t coarse_lds);      // kernel attribute for the LDS size

@@ -2033,7 +2033,8 @@ int moment_split(const PlanDev &P) {
   const int mt = moment_tile_size(P.nx, P.ny);
   const long long blocks = 4LL * moment_tiles_of(P.nx, P.ny, mt);
   int ns = 1;
-  if (blocks < 128)
+  const bool divide = P.method == GSIS_GSIS ? blocks <= 32 && P.K >= 800 : blocks < 128;
+  if (divide)
     while (blocks * ns < 1024 && P.K / 4 / (2 * ns) >= 24) ns *= 2;
   return ns;
 }
