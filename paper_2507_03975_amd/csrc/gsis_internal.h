@@ -343,6 +343,9 @@ inline int hand_parts(const PlanDev &P) {
 // tiles (32x32 S4: 3 diagonals 10.2 us, 31 23.1; 64x64x32: 13 against 24);
 // 256x256x128: 2048 waves of 43, one round, 49.3 us (31: 2816 waves, 54.6; 39:
 // 2304, 61.6); many rounds, long tiles (512x512x128: 59 230 us, 31 246).
+// A plan's rounds are those of the XCD with the most ordinates (with 12 of them
+// two XCDs work: 400x450 205 us an iteration in the tiles that 256 CUs would
+// want, 184 in those of 64; 782x5 with 4 109 and 94).
 // share: problems that run together (a batch). From 2^26 cell-ordinates on 47.
 // Lengths are of the form 4 k - 1.
 constexpr int kMaxResidDiagonals = 59;

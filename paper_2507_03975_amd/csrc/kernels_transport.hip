@@ -2044,7 +2044,13 @@ int moment_tiles_of(int nx, int ny, int mt) {
 
 int residual_tile_diagonals(int nx, int ny, int pairs, int share, int cus) {
   if ((long long)nx * ny * pairs * 2 >= (1LL << 26)) return 47;
-  const double slots = 8.0 * std::max(cus, 1);
+  // waves and slots of the XCD with the most work: a plan's groups of kRWaves
+  // pairs are dealt to the eight XCDs (k_resid), so few ordinates leave some
+  // idle; a batch's items go to all of them
+  const int groups = (pairs + kRWaves - 1) / kRWaves;
+  const bool dealt = share == 1;
+  const int load = dealt ? std::min(pairs, kRWaves * ((groups + 7) / 8)) : pairs * share;
+  const double slots = (dealt ? 1.0 : 8.0) * std::max(cus, 1);
   // a step's time in units of a full chip's, with the fraction f of its waves
   // on it: alone, and (measured on the last round) behind full rounds
   auto alone = [](double f) { return f <= 0.5 ? 0.5 + 0.28 * f : 0.64 + 0.36 * std::sqrt(2 * f - 1); };
@@ -2055,7 +2061,7 @@ int residual_tile_diagonals(int nx, int ny, int pairs, int share, int cus) {
     long long tiles = 0;
     for (int y0 = 0; y0 < ny; y0 += 64)
       tiles += (std::min(64, ny - y0) + nx - 1 + rd - 1) / rd;
-    const double w = (double)tiles * pairs * share;
+    const double w = (double)tiles * load;
     const double full = std::floor(w / slots), f = w / slots - full;
     const double t = (rd + 7) * (full + (f == 0 ? 0.0 : full > 0 ? behind(f) : alone(f)));
     if (t < least) { least = t; best = rd; }

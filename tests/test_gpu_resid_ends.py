@@ -82,3 +82,23 @@ def test_batch(ctx, precision, monkeypatch):
         b.close()
         return out
     _each(monkeypatch, "batch precision %d" % precision, run)
+
+
+@pytest.mark.parametrize("shape,quad", [((400, 450), (1, 4)), ((782, 5), (1, 1)), ((60, 70), (2, 8)),
+                                        ((90, 100), (3, 8))])
+def test_few_ordinates(ctx, shape, quad, monkeypatch):
+    """The length chosen where the ordinates go to fewer than eight XCDs, or to
+    some of them twice: the bits of 31 diagonals."""
+    monkeypatch.setenv("GSIS_SWEEP_REFERENCE", "0")
+    p = inputs.random_problem(*shape, quad=inputs.quad_product(*quad), seed=3,
+                              sigma_range=(0.05, 50.0))
+    out = []
+    for rd in (None, "31"):
+        if rd:
+            monkeypatch.setenv("GSIS_RESID_DIAGONALS", rd)
+        else:
+            monkeypatch.delenv("GSIS_RESID_DIAGONALS", raising=False)
+        print("chosen residual length %s %s" % (shape, quad), flush=True)
+        out.append(gsis.gsis_solve(ctx, p, tol=0.0, max_iter=3, method=gsis.GSIS_SI))
+    for k in ("phi", "Fx", "Fy"):
+        assert np.array_equal(_np(out[0][k]), _np(out[1][k])), k
