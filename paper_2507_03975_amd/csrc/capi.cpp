@@ -81,16 +81,19 @@ gsis_status fetch(gsis_ctx *ctx, const double *src, size_t n, int dev, std::vect
   if (n == 0) return GSIS_OK;
   if (dev) {
     hipError_t e = hipMemcpy(dst.data(), src, n * sizeof(double), hipMemcpyDeviceToHost);
-    if (e != hipSuccess)
+    if (e != hipSuccess) {
+      (void)hipGetLastError();   // (not for the next call to find)
       return fail(ctx, GSIS_E_DEVICE, "reading %s: %s", name, hipGetErrorString(e));
+    }
   } else {
     std::memcpy(dst.data(), src, n * sizeof(double));
   }
   return GSIS_OK;
 }
 
-// Everything about the problem but its cell and boundary fields, which are
-// checked on the device (check_fields).
+// Everything about the problem but its cell and boundary fields, which
+// plan_create checks (on the device where they are there, launch_check_cells and
+// launch_setup_bnd).
 gsis_status check_problem(gsis_ctx *ctx, const gsis_problem *p, const gsis_options *o,
                           std::vector<double> &mu, std::vector<double> &eta,
                           std::vector<double> &w) {
@@ -149,8 +152,31 @@ gsis_status check_problem(gsis_ctx *ctx, const gsis_problem *p, const gsis_optio
   return GSIS_OK;
 }
 
+// A kernel on the context's device can read and write p: memory of that
+// device, or host memory that is mapped for it. Memory of another device or
+// pageable host memory passed with device_ptrs is left to the runtime's copies,
+// which take it or return an error.
+bool kernel_reaches(const gsis_ctx *ctx, const void *p) {
+  if (!p) return true;
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (a.type == hipMemoryTypeManaged) return true;
+  if (a.type == hipMemoryTypeHost) return a.devicePointer == p;
+  return a.type == hipMemoryTypeDevice && a.device == ctx->device;
+}
+
 // Copies n doubles of the caller (host or device) to the device on s.
 gsis_status fetch_dev(gsis_plan *pl, const double *src, double *dst, size_t n, const char *name) {
+  if (pl->device_ptrs && !kernel_reaches(pl->ctx, src)) {
+    std::vector<double> h;
+    gsis_status st = fetch(pl->ctx, src, n, 1, h, name);
+    if (st) return st;
+    HIPCHK(pl->ctx, hipMemcpy(dst, h.data(), n * sizeof(double), hipMemcpyHostToDevice));
+    return GSIS_OK;
+  }
   const hipError_t e =
       hipMemcpyAsync(dst, src, n * sizeof(double),
                      pl->device_ptrs ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, pl->stream);
@@ -660,16 +686,23 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
       return bail(fail(ctx, GSIS_E_DEVICE, "preparing the checks of the problem failed"));
   }
   launch_check_cells(N, P.sig_a, P.sig_s, P.q, P.cv, P.T0, P.sig_t, bad, s);
+  const double *bnd_h = nullptr;   // bnd_in where the host checks it
+  std::vector<double> bnd_copy;
   if (!p->bnd_in) {
     if (hipMemsetAsync(P.bnd, 0, nbk * sizeof(double), s) != hipSuccess)
       return bail(fail(ctx, GSIS_E_DEVICE, "hipMemsetAsync failed"));
-  } else if (o->device_ptrs) {
+  } else if (o->device_ptrs && kernel_reaches(ctx, p->bnd_in)) {
     launch_setup_bnd(nbk, K, p->bnd_in, perm, P.bnd, bad, s);
   } else {
     std::vector<double> bnd(nbk);
+    bnd_h = p->bnd_in;
+    if (o->device_ptrs) {
+      if ((st = fetch(ctx, p->bnd_in, nbk, 1, bnd_copy, "bnd_in"))) return bail(st);
+      bnd_h = bnd_copy.data();
+    }
     for (size_t t = 0; t < nbk; ++t) {
       const size_t fc = t / K;
-      bnd[t] = p->bnd_in[fc * K + pl->perm[t - fc * K]];
+      bnd[t] = bnd_h[fc * K + pl->perm[t - fc * K]];
     }
     // (checked below with the caller's index, after the cells)
     if (hipMemcpyAsync(P.bnd, bnd.data(), nbk * sizeof(double), hipMemcpyHostToDevice, s) !=
@@ -683,9 +716,9 @@ static gsis_status plan_create(gsis_ctx *ctx, const gsis_problem *p, const gsis_
         hipStreamSynchronize(s) != hipSuccess)
       return bail(fail(ctx, GSIS_E_DEVICE, "reading the problem's fields: %s",
                        hipGetErrorString(hipGetLastError())));
-    if (p->bnd_in && !o->device_ptrs)
+    if (bnd_h)
       for (size_t t = 0; t < nbk && hb[1] == ~0ull; ++t)
-        if (!std::isfinite(p->bnd_in[t])) hb[1] = t;
+        if (!std::isfinite(bnd_h[t])) hb[1] = t;
     for (int k = 0; k < 3; k += 2) {
       if (hb[k] == ~0ull) continue;
       const size_t c = hb[k] >> 3;
@@ -988,16 +1021,19 @@ extern "C" gsis_status gsis_plan_read(gsis_plan *pl, gsis_result *r) {
   if (st) return st;
   // F of the final iterate: F_half plus the pending correction's flux; for
   // host memory staged in hx, hy, which are free here
-  if (pl->device_ptrs)
+  bool direct = pl->device_ptrs;
+  for (const double *out : {r->phi, r->Fx, r->Fy, r->err_hist, r->tres_hist})
+    direct = direct && kernel_reaches(ctx, out);
+  if (direct)
     launch_plan_read(P, pl->swmu, pl->sweta, r->phi, r->Fx, r->Fy, r->err_hist, r->tres_hist, s);
   else
     launch_plan_read(P, pl->swmu, pl->sweta, nullptr, P.hx, P.hy, nullptr, nullptr, s);
   HIPCHK(ctx, hipGetLastError());
   HIPCHK(ctx, hipStreamSynchronize(s));
   if ((st = status_get(pl, &n_iter, &conv, &le))) return st;
-  if (!pl->device_ptrs) {
+  if (!direct) {
     const size_t bytes = P.N * sizeof(double);
-    const hipMemcpyKind k = hipMemcpyDeviceToHost;
+    const hipMemcpyKind k = pl->device_ptrs ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     HIPCHK(ctx, hipMemcpyAsync(r->phi, P.phi, bytes, k, s));
     HIPCHK(ctx, hipMemcpyAsync(r->Fx, P.hx, bytes, k, s));
     HIPCHK(ctx, hipMemcpyAsync(r->Fy, P.hy, bytes, k, s));
