@@ -158,10 +158,10 @@ def measure_controls(ctx, gsis, pd, opts, N, K, args, phases, nprof, achieved, t
 
 def traffic_key():
     """sha256 of what the transport kernels are built from: their source, the
-    device header it includes and the compile flags (include paths aside)."""
+    device headers it includes and the compile flags (include paths aside)."""
     from paper_2507_03975_amd import build
     h = hashlib.sha256()
-    for name in ("kernels_transport.hip", "wave_ops.h"):
+    for name in ("kernels_transport.hip", "wave_ops.h", "wave_steps.h"):
         with open(os.path.join(ROOT, "paper_2507_03975_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     h.update(" ".join(a for a in build.COMMON if not a.startswith("-I")).encode())

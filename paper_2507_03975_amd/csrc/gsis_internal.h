@@ -95,9 +95,9 @@ struct MGLevel {
 // step reads its problem from a device array of SynthDesc records, and a
 // block table (problem, block of that problem) spreads one launch over many
 // problems (NULL table: a single problem, block = blockIdx.x).
-constexpr int kStateWords = 6;   // of PlanDev::state
 constexpr int kMaxLevels = 40;
 constexpr int kMaxCoarseLevels = 10;
+constexpr int kStateWords = 6;   // of PlanDev::state
 // What the one-workgroup kernels need of a problem, one word per lane of a
 // wave: scalars, addresses (two words each), then four words per level from
 // the first coarse one: nx | ny << 16; LDS offset (doubles) of x | log2 of the

@@ -355,9 +355,11 @@ __global__ void k_a_sweep(AArgs a) {
 // shift), waves run kAL steps apart and meet at a barrier every kAL steps
 // (the top lane's values through an LDS ring), and the operands of a step
 // (m and the fields that make Ih_bar of it, sigma_t + shift) are loaded kAL
-// steps ahead. Out-of-range indices
-// fall outside the buffer resources: their loads read 0, their stores are
-// dropped. rb = ihb / d + (ax / d) rb_east + (ay / d) rb_north.
+// steps ahead. A lane with no cell stores nothing (kNoCell) and does not use
+// what it loads: m's resource returns 0 there, while the 16-byte entries' byte
+// offsets wrap around 32 bits (the table's 2^28 off the grid times 16) and may
+// fall on entries of the field. rb = ihb / d + (ax / d) rb_east + (ay / d)
+// rb_north.
 // SPLIT: as the forward recurrence, the reversed rows spread over np
 // workgroups (workgroup b is part b / K of ordinate b % K), the last reversed
 // row of a part handed to the next through the plan's hand-over buffer.

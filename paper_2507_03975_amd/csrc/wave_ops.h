@@ -16,8 +16,10 @@ __device__ inline double rcp64(double x) {
   return fma(r, e, r);
 }
 
-// v / x with r = rcp64(x): the steps of the compiler's own division less its
-// scaling, so the same bits (for operands and quotients of normal size)
+// v / x with r = rcp64(x): the quotient estimate v r and one correction by its
+// fused remainder (Markstein's division), which gives the correctly rounded
+// quotient, the bits of a plain division, for operands and quotients of normal
+// size
 __device__ inline double div64(double v, double x, double r) {
   const double q = v * r;
   return fma(fma(-x, q, v), r, q);
