@@ -11,12 +11,11 @@
 //     persistent fused launch instead);
 //   * moments, boundary fluxes, HoT, right-hand side, each one launch over
 //     (problem, block) tables;
-//   * the synthetic CG + multigrid solves: those of small problems (FP64, at
-//     most 4096 cells) in one launch, a workgroup per problem, as each would
-//     have it alone; the others in lockstep: each CG or multigrid step is
-//     one launch over the problems that have that level, the coarse cycle one
-//     workgroup per problem, and every problem keeps its own scalars and stop
-//     flag;
+//   * the synthetic CG + multigrid solves of all problems in lockstep: each
+//     CG or multigrid step is one launch over the problems that have that
+//     level, the coarse cycle one workgroup per problem, and every problem
+//     keeps its own scalars and stop flag (FP64 problems of at most 4096 cells
+//     only: one launch makes their whole solves, a workgroup each);
 //   * correction, Err, next source, again one launch each.
 // A problem therefore gets the same phi and F, to the bit, as when solved
 // alone, whatever the other problems are and whichever of them are still
@@ -58,14 +57,9 @@ struct gsis_batch {
   int method = GSIS_GSIS;
   bool fp32 = false;
   std::vector<gsis_plan *> subs;
-  SynthSet S;                      // synthetic step of all problems, but for
-  SynthSet solve[2];               // their solves: those k_cg_small makes, the others
+  SynthSet S;                      // synthetic step of all problems
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  // where both solves have problems, solve[0] runs beside solve[1]: forked
-  // from and joined to stream
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
   // device tables
   void *targs = nullptr;
   int2 *items = nullptr;
@@ -120,17 +114,15 @@ gsis_status bupload(gsis_batch *b, T **p, const std::vector<T> &h) {
   return GSIS_OK;
 }
 
-template <typename T>
-gsis_status tupload(gsis_batch *b, T **p, const std::vector<T> &h) {
+// The tables of a pack go to the device in one allocation and one copy.
+gsis_status tupload(gsis_batch *b, const Pack &t) {
   void *v = nullptr;
-  hipError_t e = hipMalloc(&v, std::max<size_t>(h.size(), 1) * sizeof(T));
+  hipError_t e = hipMalloc(&v, std::max<size_t>(t.h.size(), 1));
   if (e != hipSuccess)
-    return fail(b->ctx, GSIS_E_OOM, "hipMalloc(%zu bytes): %s", h.size() * sizeof(T),
-                hipGetErrorString(e));
+    return fail(b->ctx, GSIS_E_OOM, "hipMalloc(%zu bytes): %s", t.h.size(), hipGetErrorString(e));
   b->tallocs.push_back(v);
-  *p = (T *)v;
-  if (!h.empty())
-    HIPCHK(b->ctx, hipMemcpy(v, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+  if (!t.h.empty()) HIPCHK(b->ctx, hipMemcpy(v, t.h.data(), t.h.size(), hipMemcpyHostToDevice));
+  for (const auto &p : t.at) *p.first = (char *)v + p.second;
   return GSIS_OK;
 }
 
@@ -142,7 +134,7 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
   b->tallocs.clear();
   b->active = act;
   const int n = (int)act.size();
-  gsis_status st;
+  Pack pack;
   // -- kernel arguments and the sweep work items, longest first
   const size_t tb = targs_bytes();
   std::vector<char> th(tb * std::max(n, 1));
@@ -160,12 +152,8 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
   std::vector<int2> items(it.size());
   for (size_t t = 0; t < it.size(); ++t) items[t] = it[t].second;
   b->n_items = (int)items.size();
-  {
-    char *d = nullptr;
-    if ((st = tupload(b, &d, th))) return st;
-    b->targs = d;
-  }
-  if ((st = tupload(b, &b->items, items))) return st;
+  pack.add((char **)&b->targs, th);
+  pack.add(&b->items, items);
   {
     std::vector<int4> ri;
     for (int a = 0; a < n; ++a) {
@@ -177,81 +165,56 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
         for (int g = 0; g < groups; ++g) ri.push_back(make_int4(a, t, g, 0));
     }
     b->n_ritems = (int)ri.size();
-    if ((st = tupload(b, &b->ritems, ri))) return st;
+    pack.add(&b->ritems, ri);
   }
   // -- synthetic step: descriptors and block tables
   SynthSet &S = b->S;
   std::vector<SynthDesc> D(n);
-  // places in act of the problems of either solve
-  std::vector<int> in_solve[2], all;
+  int max_lc = 0, min_lc = 1 << 30;
+  bool any_sep = false, any_zw = false, any_sums = false;
+  size_t lds = 0;
+  int cells = 0;
+  bool whole = true;
   for (int a = 0; a < n; ++a) {
     const PlanDev &P = b->subs[act[a]]->P;
     D[a] = make_synth_desc(P);
     D[a].n_tres = P.n_rtiles * residual_pairs(P);   // the batch's residual kernel's partials
-    in_solve[synth_in_one_kernel(P.S) ? 0 : 1].push_back(a);
-    all.push_back(a);
+    max_lc = std::max(max_lc, D[a].lc);
+    min_lc = std::min(min_lc, D[a].lc);
+    any_sep = any_sep || D[a].coef_sep == kCoefKernel;
+    any_zw = any_zw || needs_zw(D[a]);
+    any_sums = any_sums || D[a].coef_sep == kCoefCoarse;
+    lds = std::max(lds, P.S.coarse_lds);
+    cells = std::max(cells, P.S.coarse_cells);
+    whole = whole && P.S.whole;
   }
-  // descriptors of the problems in set and the table of their cells
+  {
+    std::vector<char> dh(sizeof(SynthDesc) * std::max(n, 1));
+    if (n) memcpy(dh.data(), D.data(), sizeof(SynthDesc) * n);
+    pack.add((char **)&S.desc, dh);
+  }
+  S.n = n;
+  S.max_lc = max_lc;
+  S.min_lc = n ? min_lc : 0;
+  S.coarse_lds = lds;
+  S.coarse_cells = cells;
+  S.whole = whole;
+  S.any_coef_sep = any_sep;
+  S.any_zw = any_zw;
+  S.any_sums = any_sums;
+  S.state0 = nullptr;
   auto nb = [](long long m) { return (int)((m + 255) / 256); };
-  auto describe = [&](const std::vector<int> &set, SynthSet &R) {
-    std::vector<char> dh(sizeof(SynthDesc) * std::max<size_t>(set.size(), 1));
-    std::vector<int2> t;
-    for (size_t e = 0; e < set.size(); ++e) {
-      memcpy(dh.data() + sizeof(SynthDesc) * e, &D[set[e]], sizeof(SynthDesc));
-      for (int lb = 0; lb < nb(D[set[e]].N); ++lb) t.push_back(make_int2((int)e, lb));
-    }
-    char *d = nullptr;
-    gsis_status s = tupload(b, &d, dh);
-    if (s) return s;
-    R.desc = (SynthDesc *)d;
-    R.n = (int)set.size();
-    R.nb_cell = (int)t.size();
-    R.state0 = nullptr;
-    return tupload(b, &R.bt_cell, t);
-  };
-  if ((st = describe(all, S))) return st;
-  for (int k = 0; k < 2; ++k) {
-    const std::vector<int> &set = in_solve[k];
-    SynthSet &R = b->solve[k];
-    R = SynthSet();
-    R.synth_max_iter = S.synth_max_iter;
-    if (set.empty()) continue;
-    if ((int)set.size() == n) {
-      R.desc = S.desc; R.n = n; R.nb_cell = S.nb_cell; R.bt_cell = S.bt_cell;
-    } else if ((st = describe(set, R))) {
-      return st;
-    }
-    R.min_lc = 1 << 30;
-    R.whole = k == 0;
-    for (int a : set) {
-      const PlanDev &P = b->subs[act[a]]->P;
-      R.max_lc = std::max(R.max_lc, D[a].lc);
-      R.min_lc = std::min(R.min_lc, D[a].lc);
-      R.any_coef_sep = R.any_coef_sep || D[a].coef_sep != 0;
-      R.coarse_lds = std::max(R.coarse_lds, P.S.coarse_lds);
-      R.coarse_cells = std::max(R.coarse_cells, P.S.coarse_cells);
-    }
-    R.bt_tile.assign(R.max_lc, nullptr);
-    R.nb_tile.assign(R.max_lc, 0);
-    for (int l = 0; l < R.max_lc; ++l) {
-      std::vector<int2> tt;
-      for (size_t e = 0; e < set.size(); ++e) {
-        const SynthDesc &E = D[set[e]];
-        if (E.lc <= l) continue;
-        for (int lb = 0; lb < tiles_of(E.lev[l].nx, E.lev[l].ny); ++lb)
-          tt.push_back(make_int2((int)e, lb));
-      }
-      R.nb_tile[l] = (int)tt.size();
-      if ((st = tupload(b, &R.bt_tile[l], tt))) return st;
-    }
-    prepare_synth(R.coarse_lds);
-  }
+  std::vector<int2> t;
+  for (int a = 0; a < n; ++a)
+    for (int lb = 0; lb < nb(D[a].N); ++lb) t.push_back(make_int2(a, lb));
+  S.nb_cell = (int)t.size();
+  pack.add(&S.bt_cell, t);
   {
     std::vector<int2> ts;
     for (int a = 0; a < n; ++a)
       for (int lb = 0; lb < source_tiles_of(D[a].nx, D[a].ny); ++lb) ts.push_back(make_int2(a, lb));
     S.nb_src = (int)ts.size();
-    if ((st = tupload(b, &S.bt_src, ts))) return st;
+    pack.add(&S.bt_src, ts);
     // moment tiles: per problem 8 runs of tr = ceil(tiles / 8), entry p of
     // the problem's 8 tr (a multiple of 8, so p % 8 is the XCD) taking tile
     // (p % 8) tr + p / 8, or none
@@ -265,18 +228,27 @@ gsis_status build_tables(gsis_batch *b, const std::vector<int> &act) {
       }
     }
     b->nb_mtile = (int)tm.size();
-    if ((st = tupload(b, &b->bt_mtile, tm))) return st;
+    pack.add(&b->bt_mtile, tm);
+  }
+  S.bt_tile.assign(max_lc, nullptr);
+  S.nb_tile.assign(max_lc, 0);
+  for (int l = 0; l < max_lc; ++l) {
+    std::vector<int2> tt;
+    for (int a = 0; a < n; ++a) {
+      if (D[a].lc <= l) continue;
+      for (int lb = 0; lb < tiles_of(D[a].lev[l].nx, D[a].lev[l].ny); ++lb)
+        tt.push_back(make_int2(a, lb));
+    }
+    S.nb_tile[l] = (int)tt.size();
+    pack.add(&S.bt_tile[l], tt);
   }
   std::vector<int2> tfc;
   for (int a = 0; a < n; ++a)
     for (int f = 0; f < b->subs[act[a]]->P.nbf; ++f) tfc.push_back(make_int2(a, f));
   b->nb_face = (int)tfc.size();
-  return tupload(b, &b->bt_face, tfc);
-}
-
-// CG iterations per synthetic solve from now on.
-void set_cg_iters(gsis_batch *b, int n) {
-  b->S.synth_max_iter = b->solve[0].synth_max_iter = b->solve[1].synth_max_iter = n;
+  pack.add(&b->bt_face, tfc);
+  prepare_synth(lds);
+  return tupload(b, pack);
 }
 
 void enqueue_iteration(gsis_batch *b, bool capture);
@@ -323,7 +295,7 @@ gsis_status compact(gsis_batch *b, const std::vector<int32_t> &st4) {
       most = std::max(most, nit);
     }
     b->cg_iters = std::max(4, std::min(b->synth_cap, (int)most + 2));
-    set_cg_iters(b, b->cg_iters);
+    b->S.synth_max_iter = b->cg_iters;
   }
   gsis_status st = build_tables(b, act);
   if (st) return st;
@@ -353,19 +325,7 @@ void enqueue_iteration(gsis_batch *b, bool capture) {
   if (b->method == GSIS_GSIS) {
     launch_boundary_flux_batch(b->targs, b->bt_face, b->nb_face, s);
     launch_hot(b->S, s, false);
-    // solve[0] is one workgroup per problem for 30 to 100 us, so the two run
-    // side by side: an iteration of 16 problems of 64 to 256 rows, one of them
-    // small, 890 us after one another, 825 so
-    const bool both = b->solve[0].n && b->solve[1].n;
-    hipStream_t s0 = both ? b->side : s;
-    if (both) {
-      (void)hipEventRecord(b->fork, s);
-      (void)hipStreamWaitEvent(s0, b->fork, 0);
-    }
-    if (b->solve[0].n) launch_synth_solve(b->solve[0], s0, nullptr, 1);
-    if (both) (void)hipEventRecord(b->join, s0);
-    if (b->solve[1].n) launch_synth_solve(b->solve[1], s, nullptr, 1);
-    if (both) (void)hipStreamWaitEvent(s, b->join, 0);
+    launch_synth_solve(b->S, s, nullptr, 1);
   }
   launch_update(b->S, s);
 }
@@ -377,7 +337,7 @@ gsis_status reset_all(gsis_batch *b) {
   HIPCHK(b->ctx, hipStreamSynchronize(b->stream));
   if (b->cg_iters0 > 0) {
     b->cg_iters = b->cg_iters0;
-    set_cg_iters(b, b->cg_iters0);
+    b->S.synth_max_iter = b->cg_iters0;
   }
   if ((int)b->active.size() != b->n) {
     HIPCHK(b->ctx, hipStreamSynchronize(b->stream));
@@ -399,9 +359,6 @@ void destroy(gsis_batch *b) {
   for (void *v : b->allocs) (void)hipFree(v);
   for (void *v : b->tallocs) (void)hipFree(v);
   if (b->host_flag) (void)hipHostFree(b->host_flag);
-  if (b->side) (void)hipStreamDestroy(b->side);
-  if (b->fork) (void)hipEventDestroy(b->fork);
-  if (b->join) (void)hipEventDestroy(b->join);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
   delete b;
 }
@@ -460,15 +417,9 @@ gsis_status gsis_batch_create(gsis_ctx *ctx, int32_t n, const gsis_problem *p,
   // -- tables of all problems
   if ((st = balloc(b, &b->counter, 1))) return bail(st);
   b->split = b->subs[0]->P.sweep_impl == 0 || b->subs[0]->P.sweep_impl == 3;
-  set_cg_iters(b, o->synth_max_iter);
+  b->S.synth_max_iter = o->synth_max_iter;
   b->synth_cap = o->synth_max_iter;
   if ((st = build_tables(b, all_problems(n)))) return bail(st);
-  if (b->solve[0].n && b->solve[1].n) {
-    if (hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&b->join, hipEventDisableTiming) != hipSuccess)
-      return bail(fail(ctx, GSIS_E_DEVICE, "creating the batch's second stream failed"));
-  }
   // -- status gather tables
   {
     std::vector<int32_t *> sp(n);
@@ -547,7 +498,7 @@ gsis_status gsis_batch_create(gsis_ctx *ctx, int32_t n, const gsis_problem *p,
       most = std::max(most, nit);
     }
     b->cg_iters = std::max(4, std::min(o->synth_max_iter, (int)most + 2));
-    set_cg_iters(b, b->cg_iters);
+    b->S.synth_max_iter = b->cg_iters;
     b->cg_iters0 = b->cg_iters;
     if ((st = reset_all(b))) return bail(st);
   }

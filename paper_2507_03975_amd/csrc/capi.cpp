@@ -379,7 +379,9 @@ gsis_status make_single_set(gsis_plan *pl) {
   S.n = 1;
   S.max_lc = D.lc;
   S.min_lc = D.lc;
-  S.any_coef_sep = D.coef_sep != 0;
+  S.any_coef_sep = D.coef_sep == kCoefKernel;
+  S.any_zw = needs_zw(D);
+  S.any_sums = D.coef_sep == kCoefCoarse;
   P.lc = D.lc;
   S.coarse_lds = coarse_lds_bytes(P);
   S.coarse_cells = coarse_cells(P);

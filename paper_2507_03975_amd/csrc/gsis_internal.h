@@ -107,7 +107,8 @@ constexpr int kStateWords = 6;   // of PlanDev::state
 // What a caller puts in place of the plan's own in a SynthDesc (state, rhs,
 // phi, level 0's x) is not in it.
 enum { kCwLast, kCwLc, kCwNb, kCwTile, kCwRrt, kCwRed, kCwScal = 7, kCwB0 = 9, kCwB1 = 11,
-       kCwX = 13, kCwInv = 15, kCwRtol = 17, kCwLev = 20 };
+       kCwX = 13, kCwInv = 15, kCwRtol = 17, kCwSums = 19 /* coef_sep is kCoefCoarse */,
+       kCwLev = 20 };
 static_assert(kCwLev + 4 * kMaxCoarseLevels <= 64, "a wave's lanes");
 struct CoarseRec {
   int32_t w[64];
@@ -154,10 +155,16 @@ struct SynthDesc {
   int nlev, lc;                 // levels; first level of the one-workgroup cycle
   int ntile0;                   // multigrid tiles of level 0
   int ntp;                      // slots of each tile-partial region: max(ntile0, cell blocks)
-  int coef_sep;                 // 1: the CG coefficients come from k_cg_coef (many partials)
+  int coef_sep;                 // who forms the CG coefficients (below; 0: every block
+                                // of the update)
   LevelDev lev[kMaxLevels];
   CoarseRec cl;
 };
+// SynthDesc::coef_sep: k_cg_coef (many partials), or the coarse cycle, with all
+// the solve's sums: problems that k_cg_small solves when they are alone, in the
+// same order, so that they get the same bits beside larger ones
+enum { kCoefKernel = 1, kCoefCoarse = 2 };
+inline bool needs_zw(const SynthDesc &D) { return D.lc == 0 && D.coef_sep != kCoefCoarse; }
 // Host-side description of one launch set (a plan, or a batch of plans).
 struct SynthSet {
   int n = 0;                          // problems
@@ -177,6 +184,8 @@ struct SynthSet {
   std::vector<int> nb_tile;
   int32_t *state0 = nullptr;          // single problem: its state (host checks)
   bool any_coef_sep = false;          // some problem's CG coefficients come from k_cg_coef
+  bool any_zw = false;                // some problem needs k_cg_zw
+  bool any_sums = false;              // some problem has kCoefCoarse
 };
 
 struct PlanDev {

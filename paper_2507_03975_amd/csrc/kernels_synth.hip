@@ -20,13 +20,15 @@
 // block of that problem), so the problems of a batch advance together while
 // each keeps its own CG scalars, multigrid hierarchy and stop flags.
 // All reductions are two-stage with a fixed order, so results repeat bit for
-// bit, and a problem gets the same phi and F alone or in a batch (which kernels
-// make its solve depends on the problem only).
+// bit, and a problem gets the same phi and F alone or in a batch (a small one's
+// solve is one kernel alone and several beside larger problems, with the same
+// sums in the same order).
 #include "gsis_internal.h"
 #include "wave_ops.h"
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 namespace gsis {
 namespace {
@@ -538,7 +540,7 @@ constexpr int kCoefSepTiles = 2048;
 __global__ void __launch_bounds__(kRedBlock) k_cg_coef(const SynthDesc *ds, int it) {
   __shared__ double sh[kRedBlock];
   CDesc &D = cdesc(ds, blockIdx.x);
-  if (!D.coef_sep) return;
+  if (D.coef_sep != kCoefKernel) return;
   UpdPre q;
   q.rz0 = first_partial(red_rz(D), n_rz(D));
   q.zw0 = first_partial(red_zw(D), n_rz(D));
@@ -1293,6 +1295,15 @@ struct CoarseWG {
     const Lev v = lev(0);
     return sm + v.x + (k ? v.s : 0) + tid + m * kCoarseThreads;
   }
+  // the pair's cell of colour k, and whether it exists
+  __device__ __forceinline__ int cell(int k, int m) const {
+    return 2 * (tid + m * kCoarseThreads) + (te[m] ? 1 - k : k);
+  }
+  __device__ __forceinline__ bool ok(int k, int m) const { return cell(k, m) < lev(0).n; }
+  // A x of an owned cell, x of the grid in LDS
+  __device__ __forceinline__ double apply(int k, int m) const {
+    return -add_top(k, m, -td[k][m] * *at(k, m));
+  }
   // s + sum of the couplings of the top pair's cell of colour k times x
   __device__ __forceinline__ double add_top(int k, int m, double s) const {
     const double *x = at(1 - k, m), *xe = x + (k ? 1 - te[m] : te[m]);
@@ -1653,17 +1664,94 @@ struct CoarseWG {
   }
 };
 
-template <int M>
+// Sums of two values over the workgroup: wave sums, then in wave order (sh: two
+// entries per wave; barriers before and between).
+__device__ __forceinline__ void coarse_sum2(double &u, double &v, double *sh) {
+  const double a = wave_sum(u), b = wave_sum(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    sh[2 * (threadIdx.x >> 6)] = a;
+    sh[2 * (threadIdx.x >> 6) + 1] = b;
+  }
+  __syncthreads();
+  u = v = 0.0;
+  for (int k = 0; k < kCoarseThreads / 64; ++k) { u += sh[2 * k]; v += sh[2 * k + 1]; }
+}
+// The r.r test (finish_rr) of a problem that k_cg_small solves when it is alone,
+// on the right-hand side in its owners' registers: the sums in k_cg_small's order.
+template <class WG>
+__device__ __forceinline__ bool coarse_rr(const WG &W, CDesc &D, const RRTest &T, double *sh) {
+  constexpr int M = sizeof(W.te) / sizeof(W.te[0]);
+  double rr = 0.0, bb = 0.0, stop = T.scal[S_STOP];
+  const double *rhs = D.rhs;
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      if (!W.ok(k, m)) continue;
+      rr = fma(W.tb[k][m], W.tb[k][m], rr);
+      const double b = T.first ? rhs[W.cell(k, m)] : 0.0;
+      bb = fma(b, b, bb);
+    }
+  coarse_sum2(rr, bb, sh);
+  if (T.first) stop = fmax(T.rtol * T.rtol * rr, 1e-28 * bb);
+  const bool conv = !(rr > stop);
+  if (threadIdx.x == 0) {
+    double *scal = T.scal;
+    scal[S_RR] = rr;
+    if (T.first) {
+      scal[S_BB] = bb;
+      scal[S_STOP] = stop;
+    }
+    const double nit = T.first ? 0.0 : scal[S_NIT] + 1.0;
+    scal[S_NIT] = nit;
+    if (conv) T.state[3] = 1 + (int32_t)nit;
+  }
+  return conv;
+}
+// w = A z of CG iteration it (z: the cycle's result in LDS) and the iteration's
+// coefficients, for k_cg_update, as k_cg_small forms them.
+template <class WG>
+__device__ __forceinline__ void coarse_zw(const WG &W, CDesc &D, int it, double *sh) {
+  constexpr int M = sizeof(W.te) / sizeof(W.te[0]);
+  double ga = 0.0, de = 0.0, *w = D.cg_w;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      if (!W.ok(k, m)) continue;
+      const double wv = W.apply(k, m), z = *W.at(k, m);
+      w[W.cell(k, m)] = wv;
+      ga = fma(W.tb[k][m], z, ga);
+      de = fma(z, wv, de);
+    }
+  coarse_sum2(ga, de, sh);
+  if (threadIdx.x != 0) return;
+  double *scal = D.scal;
+  const CGCoef q = cg_coef(it == 0, ga, de, it > 0 ? scal[rz_slot(it - 1)] : 1.0,
+                           it > 0 ? scal[alpha_slot(it - 1)] : 1.0);
+  scal[rz_slot(it)] = ga;
+  scal[alpha_slot(it)] = q.al;
+  scal[S_BETA] = q.be;
+  scal[S_ZW] = de;
+}
+
+// SUMS: some problem of the set has kCoefCoarse (batches; the code for it takes
+// registers that M = 4 does not have to spare).
+template <int M, bool SUMS>
 __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *ds, double omega,
                                                               int vc, int rr_ext) {
   extern __shared__ double sm[];
-  __shared__ double red[kCoarseThreads / 64];
+  __shared__ double red[2 * kCoarseThreads / 64];
   CoarseWG<M, 2> W(coarse_words(ds), sm, omega);
   // a problem whose V-cycle starts here or on level 1 makes the r.r test of
   // the CG step before it here (level 1: the level-0 tile kernel made the
   // update)
   const int lc = W.word(kCwLc);
-  const bool fin = lc == 0 || (lc == 1 && !rr_ext);   // rr_ext: k_rr_test made it
+  // (a problem that k_cg_small solves alone: below, in its order)
+  const bool sums = SUMS && W.word(kCwSums) != 0;
+  const bool fin = !sums && (lc == 0 || (lc == 1 && !rr_ext));   // rr_ext: k_rr_test made it
   const RRTest T = W.rr_test(vc == 0, vc > 0 && lc == 1, cdesc(ds, blockIdx.x).state);
   RRPre q = {0.0, 0.0, 0.0};
   if (fin) q = rr_prefetch(T);
@@ -1672,7 +1760,11 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const SynthDesc *d
   if (f1 != 0 || f3 != 0) return;
   if (fin && finish_rr(T, red, q)) return;
   W.settle();
+  if constexpr (SUMS)
+    if (sums && coarse_rr(W, cdesc(ds, blockIdx.x), T, red)) return;
   W.cycle();
+  if constexpr (SUMS)
+    if (sums) coarse_zw(W, cdesc(ds, blockIdx.x), vc, red);
   // x of the top level (when that is level 0, k_cg_zw then forms w = A z and
   // the CG's partials)
   double *xout = (double *)(__attribute__((address_space(1))) double *)W.ptr(kCwX);
@@ -1694,7 +1786,7 @@ __global__ void k_cg_zw(const SynthDesc *ds, const int2 *bt, int vc) {
   __shared__ double sh[kRedBlock];
   const Blk B = blk(bt);
   CDesc &D = cdesc(ds, B.p);
-  if (D.lc > 0) return;
+  if (D.lc > 0 || D.coef_sep == kCoefCoarse) return;
   const int32_t f1 = D.state[1], f3 = D.state[3];
   const LevelDev L = level(D, 0);
   const int nx = L.nx, ny = L.ny;
@@ -1742,7 +1834,7 @@ template <int M, int MODE>
 __global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds, int sub,
                                                              int max_it) {
   extern __shared__ double sm[];
-  __shared__ double red[2][kCoarseThreads / 64];
+  __shared__ double red[2 * kCoarseThreads / 64];
   CDesc &D = cdesc(ds, blockIdx.x);
   if (D.state[1] != 0) return;
   CoarseWG<M, M >= 3 ? 1 : 2> W(coarse_words(ds), sm, kOmega);
@@ -1753,22 +1845,10 @@ __global__ void __launch_bounds__(kCoarseThreads) k_cg_small(const SynthDesc *ds
   const double *X = MODE >= 2 ? xg : D.phi;
   double x[2][M], p[2][M], s[2][M];
   double (&r)[2][M] = W.tb;        // the residual is the V-cycle's right-hand side
-  // sums of two values over the workgroup: wave sums, then in wave order
-  auto sum2 = [&](double &u, double &v) {
-    const double a = wave_sum(u), b = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = a; red[1][threadIdx.x >> 6] = b; }
-    __syncthreads();
-    u = v = 0.0;
-    for (int k = 0; k < kCoarseThreads / 64; ++k) { u += red[0][k]; v += red[1][k]; }
-  };
-  // cell of colour k of the thread's m-th pair, and whether it exists
-  auto cell = [&](int k, int m) {
-    return 2 * ((int)threadIdx.x + m * kCoarseThreads) + (W.te[m] ? 1 - k : k);
-  };
+  auto sum2 = [&](double &u, double &v) { coarse_sum2(u, v, red); };
+  auto cell = [&](int k, int m) { return W.cell(k, m); };
   auto ok = [&](int k, int m) { return cell(k, m) < D.N; };
-  // A x of an owned cell, x of the grid in LDS
-  auto apply = [&](int k, int m) { return -W.add_top(k, m, -W.td[k][m] * *W.at(k, m)); };
+  auto apply = [&](int k, int m) { return W.apply(k, m); };
 #pragma unroll
   for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -2184,21 +2264,25 @@ void vcycle(const SynthSet &S, int v, hipStream_t s, int part = 0) {
                        v, rr_ext);
   if (part == 1) return;
   const dim3 gw(S.n), bw(kCoarseThreads);
-  if (S.coarse_cells <= 2 * kCoarseThreads)
-    hipLaunchKernelGGL(k_mg_coarse<1>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
-  else if (S.coarse_cells <= 4 * kCoarseThreads)
-    hipLaunchKernelGGL(k_mg_coarse<2>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
-  else if (S.coarse_cells <= 6 * kCoarseThreads)
-    hipLaunchKernelGGL(k_mg_coarse<3>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
-  else
-    hipLaunchKernelGGL(k_mg_coarse<4>, gw, bw, S.coarse_lds, s, ds, kOmega, v, rr_ext);
+  auto coarse = [&](auto m, auto sums) {
+    hipLaunchKernelGGL((k_mg_coarse<decltype(m)::value, decltype(sums)::value>), gw, bw,
+                       S.coarse_lds, s, ds, kOmega, v, rr_ext);
+  };
+  auto by_cells = [&](auto sums) {
+    if (S.coarse_cells <= 2 * kCoarseThreads) coarse(std::integral_constant<int, 1>(), sums);
+    else if (S.coarse_cells <= 4 * kCoarseThreads) coarse(std::integral_constant<int, 2>(), sums);
+    else if (S.coarse_cells <= 6 * kCoarseThreads) coarse(std::integral_constant<int, 3>(), sums);
+    else coarse(std::integral_constant<int, 4>(), sums);
+  };
+  if (S.any_sums) by_cells(std::true_type());
+  else by_cells(std::false_type());
   for (int l = S.max_lc - 1; l >= 1; --l)
     hipLaunchKernelGGL(k_mg_up, dim3(S.nb_tile[l]), dim3(kRedBlock), 0, s, ds, S.bt_tile[l], l, v,
                        kOmega);
   if (S.max_lc > 0)
     hipLaunchKernelGGL(k_mg_up0, dim3(S.nb_tile[0]), dim3(kRedBlock), 0, s, ds, S.bt_tile[0], v,
                        kOmega);
-  if (S.min_lc == 0)
+  if (S.any_zw)
     hipLaunchKernelGGL(k_cg_zw, dim3(S.nb_cell), dim3(kRedBlock), 0, s, ds, S.bt_cell, v);
   if (S.any_coef_sep)
     hipLaunchKernelGGL(k_cg_coef, dim3(S.n), dim3(kRedBlock), 0, s, ds, v);
@@ -2242,8 +2326,10 @@ int coarse_cells(const PlanDev &P) {
 // cycle never lowers it under an earlier one.
 void prepare_synth(size_t coarse_lds) {
   if (coarse_lds <= 64 * 1024) return;
-  const void *ks[] = {(const void *)&k_mg_coarse<1>,   (const void *)&k_mg_coarse<2>,
-                      (const void *)&k_mg_coarse<3>,   (const void *)&k_mg_coarse<4>,
+  const void *ks[] = {(const void *)&k_mg_coarse<1, false>, (const void *)&k_mg_coarse<2, false>,
+                      (const void *)&k_mg_coarse<3, false>, (const void *)&k_mg_coarse<4, false>,
+                      (const void *)&k_mg_coarse<1, true>,  (const void *)&k_mg_coarse<2, true>,
+                      (const void *)&k_mg_coarse<3, true>,  (const void *)&k_mg_coarse<4, true>,
                       (const void *)&k_cg_small<1, 0>, (const void *)&k_cg_small<1, 1>,
                       (const void *)&k_cg_small<1, 2>, (const void *)&k_cg_small<1, 3>,
                       (const void *)&k_cg_small<2, 0>, (const void *)&k_cg_small<2, 1>,
@@ -2292,7 +2378,8 @@ SynthDesc make_synth_desc(const PlanDev &P) {
   D.lc = lc;
   D.ntile0 = tiles_of(P.mg[0].nx, P.mg[0].ny);
   D.ntp = std::max(D.ntile0, nblk(P.N));
-  D.coef_sep = lc > 0 && D.ntile0 >= kCoefSepTiles ? 1 : 0;
+  D.coef_sep = lc == 0 ? (D.fp32 ? 0 : kCoefCoarse)
+                       : D.ntile0 >= kCoefSepTiles ? kCoefKernel : 0;
   // the record of the one-workgroup kernels
   int32_t *w = D.cl.w;
   auto ptr = [&](int k, const void *p) { memcpy(w + k, &p, sizeof p); };
@@ -2309,6 +2396,7 @@ SynthDesc make_synth_desc(const PlanDev &P) {
   ptr(kCwX, lc == 0 ? P.cg_z : P.mg[lc].x);
   ptr(kCwInv, P.coarse_inv);
   memcpy(w + kCwRtol, &D.rtol, sizeof D.rtol);
+  w[kCwSums] = D.coef_sep == kCoefCoarse ? 1 : 0;
   int off = 0;
   for (int t = 0; t < nlev; ++t) {
     const MGLevel &L = P.mg[lc + t];
@@ -2362,10 +2450,15 @@ void launch_hot(const SynthSet &S, hipStream_t s, bool combine) {
 // update then being in the stream.
 // FP64 sets whose every problem starts with the one-workgroup cycle run the
 // whole solve in one kernel (k_cg_small) and never wait. Its sums of products
-// are added in another order than the separate kernels' (block partials); an
-// FP32-mixed step rounds differences of the iterate to floats, which turns one
-// unit in the last place of phi into 1e-8 of the flux, so those plans keep the
-// order they had.
+// are added by cell owners; beside larger problems the coarse cycle forms them
+// so (kCoefCoarse: the r.r test, w = A z and the CG coefficients), where other
+// problems of that size have k_cg_zw and block partials. An FP32-mixed step
+// rounds differences of the iterate to floats, which turns one unit in the last
+// place of phi into 1e-8 of the flux, so those plans keep the block partials'
+// order. (The small problems' whole solves after or beside the others': 10
+// iterations of 16 problems 5.6 and 5.1 ms, of 6 3.19 and 3.44; with the sums in
+// the coarse cycle 5.1 and 3.0, with block partials, k_cg_zw among the launches,
+// 5.1 and 3.1.)
 namespace {
 template <int M>
 void launch_cg_small(const SynthSet &S, hipStream_t s, int rhs_mode, int sub) {
