@@ -223,8 +223,9 @@ void gsis_plan_destroy(gsis_plan *plan);
  * convergence (Err < tol), divergence or max_iter do no work, so the
  * iterate stops exactly where a synchronous loop would. SI plans return
  * without waiting. FP64 GSIS plans of at most 4096 cells (one kernel makes
- * their synthetic solve) wait only to stay at most 16 iterations ahead of the
- * device, over all calls, and enqueue at most 16 past the end of the solve.
+ * their synthetic solve) wait only to stay at most 24 iterations ahead of the
+ * device, over all calls, and enqueue no more than that past the end of the
+ * solve.
  * Other GSIS plans wait for the device once per outer iteration: the
  * host reads the synthetic CG's device stop flag (after the CG update
  * of the iteration at which the previous solve stopped, the end of the

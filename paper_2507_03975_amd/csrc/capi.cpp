@@ -892,16 +892,33 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
   PlanDev &P = pl->P;
   hipStream_t s = pl->stream;
   gsis_status st;
-  // GSIS plans whose synthetic solve is one kernel do not wait for it: every
-  // kRunAhead iterations, counted over the calls, the host looks at the done
-  // flag of kRunAhead iterations before, so it never is more than twice that
-  // many ahead of the device or past the end of the solve, and the device never
-  // runs dry for the look. 32 x 32, S4, looks every 4, 8 and 16: 44.4, 43.9 and
-  // 43.5 us an iteration, and 1.64, 1.75 and 1.98 ms for a call for 1000 of which
-  // the solve takes 33.
+  // GSIS plans whose synthetic solve is one kernel do not wait for it. The done
+  // flag is copied to the host after 2 kRunAhead iterations, counted over the
+  // calls, and every kRunAhead further ones, and each copy is looked at when the
+  // next is due: the host never is more than three times that many ahead of the
+  // device or past the end of the solve, and the device never runs dry for the
+  // look. 32 x 32, S4, copies every 4, 8 and 16: 44.4, 43.9 and 43.5 us an
+  // iteration, and 1.64, 1.75 and 1.98 ms for a call for 1000 of which the solve
+  // takes 33; the first copy is late because a call for 9 iterations pays 1 % for
+  // it.
   const bool ahead = P.method == GSIS_GSIS && synth_in_one_kernel(P.S) && pl->spec_ev;
   if (ahead && pl->ended) return GSIS_OK;   // the iterations would do no work
   for (int it = 0; it < n; ++it) {
+    int32_t *host_flag = (int32_t *)pl->host_scal;
+    if (ahead && pl->ahead++ == (pl->ahead_pending ? 1 : 2) * kRunAhead) {
+      if (pl->ahead_pending) {
+        HIPCHK(ctx, hipEventSynchronize(pl->spec_ev));
+        if (host_flag[kAheadFlag] != 0) {
+          pl->ended = true;
+          break;
+        }
+      }
+      HIPCHK(ctx, hipMemcpyAsync(host_flag + kAheadFlag, P.state + 1, sizeof(int32_t),
+                                 hipMemcpyDeviceToHost, s));
+      HIPCHK(ctx, hipEventRecord(pl->spec_ev, s));
+      pl->ahead_pending = true;
+      pl->ahead = 1;
+    }
     if (pl->profile && pl->prof_iters >= 100000) pl->profile = 0;
     if ((st = record(pl, 0))) return st;
     launch_residual(P, s);
@@ -920,7 +937,6 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
     // the synthetic solve copies the device flags to the host once while it
     // runs (host_flag[0]: the outer iteration's done flag); cleared first,
     // so a nonzero value below was read during this iteration
-    int32_t *host_flag = (int32_t *)pl->host_scal;
     host_flag[0] = 0;
     bool updated = false;
     if (P.td) {
@@ -952,20 +968,6 @@ extern "C" gsis_status gsis_plan_iterate(gsis_plan *pl, int32_t n) {
     // an earlier iteration ended the solve (converged, diverged or at the
     // iteration cap): the remaining ones would only launch kernels that exit
     if (host_flag[0] != 0) break;
-    if (ahead && ++pl->ahead == kRunAhead) {
-      pl->ahead = 0;
-      if (pl->ahead_pending) {
-        HIPCHK(ctx, hipEventSynchronize(pl->spec_ev));
-        if (host_flag[kAheadFlag] != 0) {
-          pl->ended = true;
-          break;
-        }
-      }
-      HIPCHK(ctx, hipMemcpyAsync(host_flag + kAheadFlag, P.state + 1, sizeof(int32_t),
-                                 hipMemcpyDeviceToHost, s));
-      HIPCHK(ctx, hipEventRecord(pl->spec_ev, s));
-      pl->ahead_pending = true;
-    }
   }
   return GSIS_OK;
 }

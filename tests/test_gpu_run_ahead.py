@@ -1,5 +1,5 @@
 """GPU: plans whose synthetic solve is one kernel enqueue iterations without
-waiting for each, but never more than 16 past the end of the solve, in one call
+waiting for each, but never more than 16 past the end of a solve of eight or more, in one call
 or over many, and start anew after a reset."""
 import sys
 
