@@ -63,14 +63,14 @@ SYNTH_RTOL = 0.1
 # so FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0). Valid only for the build whose
 # traffic_key() is recorded; any change to it turns the figures back to null.
 TRAFFIC = {
-    "thick256_fp64": {"sha256": "b00108742c54de27a8d9fa2add5487bf0a2050242a45cc2c6b64f13013ae2eb8",
-                      "k_resid": 244572692,     # 84793.5 KiB x 2.0 + 69253.5 KiB
-                      "k_chain": 138795712},    # 34857.5 KiB x 2.0 + 65827.7 KiB
-    "block1024_fp64": {"sha256": "b00108742c54de27a8d9fa2add5487bf0a2050242a45cc2c6b64f13013ae2eb8",
-                       "k_pipe": 3263603312},    # 1023245.2 KiB x 2.0 + 1140622.2 KiB
-    "block1024_fp32": {"sha256": "b00108742c54de27a8d9fa2add5487bf0a2050242a45cc2c6b64f13013ae2eb8",
-                       "k_resid": 2887818572,     # 1117278.7 KiB x 2.0 + 585577.9 KiB
-                       "k_chain": 1196688008},    # 305596.9 KiB x 2.0 + 557446.8 KiB
+    "thick256_fp64": {"sha256": "ff40b132463556fe52a113875b544ed88859d16aa30a15bd28975b2470265da4",
+                      "k_resid": 244447564,     # 84711.2 KiB x 2.0 + 69295.8 KiB
+                      "k_chain": 138791092},    # 34855.5 KiB x 2.0 + 65827.2 KiB
+    "block1024_fp64": {"sha256": "ff40b132463556fe52a113875b544ed88859d16aa30a15bd28975b2470265da4",
+                       "k_pipe": 3254681376},    # 1018488.6 KiB x 2.0 + 1141422.5 KiB
+    "block1024_fp32": {"sha256": "ff40b132463556fe52a113875b544ed88859d16aa30a15bd28975b2470265da4",
+                       "k_resid": 2887702500,     # 1117204.8 KiB x 2.0 + 585612.4 KiB
+                       "k_chain": 1200296312},    # 307326.1 KiB x 2.0 + 557512.1 KiB
 }
 KERNELS = {"k_resid": "k_resid (second-order residual of every cell-ordinate, ALSM gradient "
                       "and BJ limiter, written as the recurrence's right-hand side)",
